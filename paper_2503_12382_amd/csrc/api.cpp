@@ -48,7 +48,7 @@ uint32_t bits_range(int lo, int hi) {  // bits lo..hi inclusive
 
 void free_all(Ctx* c) {
   void* ptrs[] = {c->keys_a,  c->keys_b,    c->lv_key,   c->lv_code,  c->lv_parent, c->lv_fc,
-                  c->lv_feat, c->d_count,   c->d_moff,   c->d_err,    c->d_hist,    c->d_ticket,
+                  c->d_count,   c->d_moff,   c->d_err,    c->d_hist,    c->d_ticket,
                   c->d_status, c->d_hash,   c->d_hreg,   c->h_a,      c->h_b,      c->d_nbr,     c->d_lse,
                   c->d_partial, c->d_total, c->w_head,   c->w_hbias,  c->w_head_plain,
                   c->d_lse2,    c->w_emb,   c->d_s1,     c->w_head_t, c->d_perm,
@@ -190,7 +190,6 @@ reno_status reno_create(const reno_params* p, void* hip_stream, reno_ctx** out) 
   A(dalloc(&c->lv_code, lvn, &c->device_bytes));
   A(dalloc(&c->lv_parent, lvn, &c->device_bytes));
   A(dalloc(&c->lv_fc, lvn, &c->device_bytes));
-  A(dalloc(&c->lv_feat, lvn + 8, &c->device_bytes));  // entry lvn stays zero: absent-neighbour input
   A(dalloc(&c->d_count, reno::NLEV, &c->device_bytes));
   A(dalloc(&c->d_moff, reno::NLEV + 1, &c->device_bytes));
   A(dalloc(&c->d_err, 4, &c->device_bytes));
@@ -216,14 +215,13 @@ reno_status reno_create(const reno_params* p, void* hip_stream, reno_ctx** out) 
   A(dalloc(&c->d_s1, (size_t)cap_model, &c->device_bytes));
   A(dalloc(&c->d_partial, (size_t)reno::NLEV * ((c->cap_pts + 63) / 64), &c->device_bytes));
   A(dalloc(&c->d_total, reno::NLEV, &c->device_bytes));
-  int c_in = top ? C : RENO_IN_FEATURES;
   for (int l = 0; l < (top ? 4 : p->layers); ++l) {
-    const int KS = (c_in + 3) / 4, KSP = (KS + 3) & ~3;
-    // fp32: KSP floats per (offset, column block, lane); bf16x3: 8 words
-    A(dalloc(&c->w_conv[l], (size_t)(top ? c->kvol() : 27) * (C / 16) * 64 * std::max(KSP, 8),
-             &c->device_bytes));
+    // first layer of the plain model: its cell table; else per (offset, column
+    // block, lane) fp32 C / 4 floats, bf16x3 8 words
+    const size_t words = !top && l == 0 ? (size_t)8 * 8 * 256 * C
+                                        : (size_t)(top ? c->kvol() : 27) * (C / 16) * 64 * std::max(C / 4, 8);
+    A(dalloc(&c->w_conv[l], words, &c->device_bytes));
     A(dalloc(&c->w_bias[l], (size_t)C, &c->device_bytes));
-    c_in = C;
   }
   A(dalloc(&c->w_head, (size_t)16 * 64 * std::max(C / 4, 8), &c->device_bytes));
   A(dalloc(&c->w_hbias, 256, &c->device_bytes));
@@ -240,8 +238,7 @@ reno_status reno_create(const reno_params* p, void* hip_stream, reno_ctx** out) 
     return fail(nullptr, e == hipErrorOutOfMemory ? RENO_E_NOMEM : RENO_E_HIP, msg);
   }
   // tickets start at zero (every frame clears them again); the reserved zero
-  // row of each feature buffer and the zero input-bit entry are never written
-  // afterwards
+  // row of each feature buffer is never written afterwards
   e = hipMemsetAsync(c->d_ticket, 0, sizeof(uint32_t) * reno::TICKETS, c->stream);
   if (e == hipSuccess)
     e = hipMemsetAsync(c->h_a + (size_t)cap_model * C, 0, sizeof(float) * C, c->stream);
@@ -251,7 +248,6 @@ reno_status reno_create(const reno_params* p, void* hip_stream, reno_ctx** out) 
     e = hipMemsetAsync(c->h_c + (size_t)cap_model * C, 0, sizeof(float) * C, c->stream);
   if (e == hipSuccess && top)
     e = hipMemsetAsync(c->h_d + (size_t)cap_model * C, 0, sizeof(float) * C, c->stream);
-  if (e == hipSuccess) e = hipMemsetAsync(c->lv_feat + lvn, 0, 16, c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess) {
     const std::string msg = std::string("init failed: ") + hipGetErrorString(e);

@@ -66,7 +66,6 @@ struct Ctx {
   uint8_t* lv_code = nullptr;   // O_b
   int32_t* lv_parent = nullptr; // row of the parent in V_{b-1}
   int32_t* lv_fc = nullptr;     // row of the first child in V_{b+1}
-  uint16_t* lv_feat = nullptr;  // delta | O_{b-1}[parent] << 3  (layer-1 input bits)
 
   // device scalars / small arrays
   int32_t* d_count = nullptr;   // [NLEV] N_b
@@ -95,7 +94,7 @@ struct Ctx {
   uint32_t* h_err = nullptr;    // pinned host mirror [1]
 
   // packed weights (operand layouts of the conv/head kernels)
-  float* w_conv[RENO_MAX_LAYERS] = {};
+  float* w_conv[RENO_MAX_LAYERS] = {};  // plain model, layer 0: the cell table [8][8][256][C]
   float* w_bias[RENO_MAX_LAYERS] = {};
   float* w_head = nullptr;
   float* w_hbias = nullptr;

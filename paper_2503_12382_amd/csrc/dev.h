@@ -67,6 +67,14 @@ __device__ __forceinline__ uint32_t wave_or(uint32_t v) {
   return v;
 }
 
+// Orders this wave's LDS accesses around it for the compiler (the hardware
+// runs one wave's LDS operations in order): an exchange between lanes of one
+// wave needs no block barrier.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // ---- agent-scope relaxed atomics on look-back status words ----
 __device__ __forceinline__ uint32_t ld_status(const uint32_t* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -191,8 +199,16 @@ __device__ __forceinline__ uint32_t lookback_wave(uint32_t* status, int tile, ui
   return excl;
 }
 
+// Scales whose voxels are in the coordinate hash of a frame of bit depth B.
+// The neighbour search on a model scale b (b0 < b < B) finds cells of scale
+// b - 1 as children of scale b - 2, so scales up to B - 3 are hashed, and the
+// base scale, which has no stored parents, when there is a model scale.
+__host__ __device__ __forceinline__ bool hashed_scale(int b, int b0, int B) {
+  return b + 2 < B || (b == b0 && b + 1 < B);
+}
+
 // ---- open-addressing coordinate hash in HBM ----
-// Maps a voxel of a parent scale to its occupancy code and the row of its
+// Maps a voxel of a hashed scale to its occupancy code and the row of its
 // first child, so that any cell of the next scale can be resolved from one
 // probe: the child with octant d exists iff bit d of the code is set, and its
 // row is first + popcount(code & ((1 << d) - 1)) (the FCG order).  One table

@@ -126,7 +126,7 @@ __global__ void __launch_bounds__(BASE_ONE_BLOCK) k_clear_set_base(ClearBaseArgs
 
 struct ExpArgs {
   const uint8_t* codes_in;  // caller codes for O_b, or null (already recorded)
-  int b, B;
+  int b, B, b0;
   int fb;                   // frame-id bits above the Morton bits
   int64_t cap_pts;
   int64_t cap_model;
@@ -135,7 +135,6 @@ struct ExpArgs {
   int32_t* fc_b;      // first-child row of each parent (or null)
   uint64_t* key_n;    // scale b+1
   int32_t* parent_n;
-  uint16_t* feat_n;   // layer-1 input word of each child (or null)
   int32_t* count;
   int32_t* moff;
   uint32_t* status;
@@ -246,13 +245,12 @@ __global__ void __launch_bounds__(EXP_THREADS) k_expand(ExpArgs a) {
       }
       a.key_n[q] = kp | d;
       a.parent_n[q] = (int32_t)p;
-      if (a.feat_n) a.feat_n[q] = (uint16_t)(d | (c << 3));
       ++q;
     }
   }
   // the parents (scale b) go into the coordinate hash with their code and
-  // first child when scale b+1 is a model scale
-  if (bn >= a.B) return;
+  // first child when lookups start from their scale
+  if (!hashed_scale(a.b, a.b0, a.B)) return;
 #pragma unroll
   for (int j = 0; j < EXP_KPT; ++j) {
     const int64_t p = base + (int64_t)w * 64 * EXP_KPT + j * 64 + lane;
@@ -335,6 +333,7 @@ hipError_t launch_expand_noalloc(const uint64_t* keys, const uint8_t* codes, int
   ExpArgs a;
   a.codes_in = nullptr;                       // the codes are read, never written
   a.b = 0;                                    // count[0]: parents, count[1]: children
+  a.b0 = 0;
   a.B = 1;                                    // no next model scale: no hash inserts, no row offsets
   a.fb = 0;
   a.cap_pts = cap_children;
@@ -344,7 +343,6 @@ hipError_t launch_expand_noalloc(const uint64_t* keys, const uint8_t* codes, int
   a.fc_b = first_child;
   a.key_n = child_keys;
   a.parent_n = child_parent;
-  a.feat_n = nullptr;
   a.count = reinterpret_cast<int32_t*>(s + NA_COUNT);
   a.moff = nullptr;                           // only touched when b + 1 < B
   a.status = s + NA_HEAD;
@@ -410,6 +408,7 @@ hipError_t launch_expand(Ctx& c, int b, const uint8_t* codes, int B) {
   ExpArgs a;
   a.codes_in = codes;
   a.b = b;
+  a.b0 = c.b0();
   a.B = B;
   a.fb = c.fbits;
   a.cap_pts = c.cap_pts;
@@ -419,7 +418,6 @@ hipError_t launch_expand(Ctx& c, int b, const uint8_t* codes, int B) {
   a.fc_b = c.lv_fc + c.lv(b);
   a.key_n = c.lv_key + c.lv(b + 1);
   a.parent_n = c.lv_parent + c.lv(b + 1);
-  a.feat_n = c.lv_feat + c.lv(b + 1);
   a.count = c.d_count;
   a.moff = c.d_moff;
   const int64_t max_tiles = c.exp_tiles;

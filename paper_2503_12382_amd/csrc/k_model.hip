@@ -2,9 +2,10 @@
 // form: per voxel of a scale, the 11 input bits [delta, parent code] (target
 // embedding, Eqs. 7-8), L submanifold 3x3x3 sparse conv + ReLU layers on the
 // target coordinates (Eq. 9) and a linear head to 256 logits with the softmax
-// normaliser (Eq. 10).
+// normaliser (Eq. 10).  The first layer, whose input is 11 bits, is a sum of
+// table rows (k_first); the others are matrix products (k_conv).
 //
-// Work unit: a wavefront owns a tile of 16 consecutive voxels of one scale (in
+// Work unit of the matrix layers: a wavefront owns a tile of 16 consecutive voxels of one scale (in
 // launches of at most 4 tiles per block, a quad of waves shares it).
 // Each layer is computed transposed, out^T[c_out][16] = sum_k W_k^T in_k^T, on
 // fp32 MFMA 16x16x4: the A operand is the offset's weights (staged once per
@@ -265,14 +266,8 @@ struct ConvArgs {
   const int32_t* count;
   const int32_t* moff;
   int64_t cap_pts, cap_model;
-  const uint64_t* lv_key;
-  const uint16_t* lv_feat;
-  const HashSlot* hash;
-  int hash_lg;
-  const uint64_t* hreg;   // hash region starts of a frame batch (null: one frame)
-  int32_t* nbr;           // [cap_model][NBR_STRIDE], entries 27.. are -1
-  const float* h_in;      // [cap_model + 1][C_in], row cap_model all zero (unused by layer 1)
-  int64_t zero_feat;      // index of a zero entry of lv_feat
+  const int32_t* nbr;     // [cap_model][NBR_STRIDE], entries 27.. are -1
+  const float* h_in;      // [cap_model + 1][C_in], row cap_model all zero
   float* h_out;           // [cap_model][C]
   const float* w;         // packed conv weights
   const float* bias;      // [C]
@@ -286,13 +281,12 @@ struct ConvArgs {
   const uint8_t* s1_code; // codes of the per-scale regions (S1 = O & 15), or NULL: stage 1 only
   float* lse2;            // [cap_model]
   uint8_t* s1_out;        // [cap_model] the S1 stage 2 used
-  const int32_t* perm;    // optional tile order: tile slot -> packed row (layers after the first)
+  const int32_t* perm;    // optional tile order: tile slot -> packed row
   // full predictor
   const float* res;       // residual input added before the ReLU (same rows as h_out), or NULL
   int b_ext;              // scale whose rows live past the zero row (the base scale), or -1
   int64_t ext_off;        // first packed row of that scale (cap_model + 1)
   int64_t cap_rows;       // rows of the feature buffers
-  int fb;                 // frame-id bits above the Morton bits (frame batch), else 0
   // replication + octant embedding fused into the epilogue (Eqs. 7-8): each
   // voxel's result F, plus Emb_D[delta], goes to the rows of its children
   float* xb;              // child rows' input X_B (rows of scale b + 1), or NULL
@@ -380,9 +374,64 @@ struct Staged {
   }
 };
 
+// Where the neighbour search reads: the coordinate hash and the per-scale
+// arrays (scale b at (b - b0) * cap_pts).
+struct CellArgs {
+  const HashSlot* hash;
+  int hash_lg;
+  const uint64_t* hreg;  // hash region starts of a frame batch (null: one frame)
+  int fb;                // frame-id bits above the Morton bits
+  int b0;
+  int64_t cap_pts;
+  const uint8_t* code;
+  const int32_t* fc;
+};
+
+// (first child, code) of N cells of scale s, all of the frame of bits fr (in
+// place above the 3 s Morton bits): code 0 where ok is false or the cell is
+// absent.  The hash maps the cells of scale s - 1, so a cell is found as the
+// child of its own parent cell, and its code and first child are read by row.
+// Neighbouring cells share parents (8 cells around a voxel lie in 3.4 of them
+// on average) and the finest parent scale, the largest, is never inserted, so
+// the probes of absent cells, each a random line of the table, mostly hit
+// lines in use; the hash build, bound by its inserts, halves (10 frames of the
+// 14-bit scan: 111 -> 64 us; 64 frames: 679 -> 414 us).  Probing every cell of
+// a scale below the finest directly instead costs the same at one frame and
+// 1 to 4 % more at 10.  The base scale has no stored parent and is probed
+// directly.
+template <int N>
+__device__ __forceinline__ void find_cells(const CellArgs& a, int s, uint64_t fr, const uint64_t (&cell)[N],
+                                           const bool (&ok)[N], uint2 (&hit)[N]) {
+  const HashReg reg = hash_region(a.hreg, a.hash_lg, frame_part(fr, s));
+  uint64_t tk[N];
+  if (s == a.b0) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) tk[i] = ok[i] ? tag_key(fr | cell[i], s, a.fb) : 0ull;
+    hash_find_n<N>(a.hash, a.hash_lg, reg, tk, hit);
+    return;
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i) tk[i] = ok[i] ? tag_key((fr | cell[i]) >> 3, s - 1, a.fb) : 0ull;
+  hash_find_n<N>(a.hash, a.hash_lg, reg, tk, hit);
+  const uint8_t* code = a.code + (int64_t)(s - a.b0) * a.cap_pts;
+  const int32_t* fc = a.fc + (int64_t)(s - a.b0) * a.cap_pts;
+  uint32_t c[N];
+  int32_t f[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const uint32_t d = (uint32_t)cell[i] & 7u;
+    const bool in = (hit[i].y >> d) & 1u;
+    const uint32_t row = in ? hit[i].x + __popc(hit[i].y & ((1u << d) - 1u)) : 0u;
+    c[i] = in ? code[row] : 0u;
+    f[i] = in ? fc[row] : 0;
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i) hit[i] = make_uint2((uint32_t)f[i], c[i]);
+}
+
 // Neighbour rows of a voxel from the parent scale.  The 27 cells around v lie
 // in at most 8 cells of the parent scale: the parent p and, per axis, the
-// neighbour of p on v's side.  Lane (r, g) probes cells e = 2g and 2g+1
+// neighbour of p on v's side.  Lane (r, g) looks up cells e = 2g and 2g+1
 // (e = ex + 2ey + 4ez) of its voxel r; each hit gives the cell's code and
 // first-child row, from which every neighbour row follows by the FCG order.
 // par is the 8-entry LDS slot of voxel r (shared by the 4 lanes of r); the
@@ -420,30 +469,29 @@ __device__ __forceinline__ uint64_t morton_step(uint64_t k, uint64_t m, bool up,
   return na | rest;
 }
 
-__device__ __forceinline__ void parent_cell_rows(uint64_t kf, int b, int g, const HashSlot* __restrict__ hash,
-                                                 int hash_lg, const uint64_t* __restrict__ hreg, int fb,
-                                                 volatile uint64_t* par, int32_t (&nb)[8]) {
+__device__ __forceinline__ void parent_cell_rows(uint64_t kf, int b, int g, const CellArgs& a,
+                                                 uint64_t* par, int32_t (&nb)[8]) {
   const uint64_t key = morton_part(kf, b), fr = frame_part(kf, b) << (3 * (b - 1));
   const uint32_t oct = (uint32_t)key & 7u;  // v's octant in its parent: the side of each neighbour cell
   const uint64_t pk = key >> 3;
   const uint64_t all = (1ull << (3 * (b - 1))) - 1ull;
   const uint64_t mx = 0x1249249249249249ull & all, my = (mx << 1) & all, mz = (mx << 2) & all;
-  // lane group g probes cells 2g and 2g + 1: the y and z steps of g, then x
+  // lane group g looks up cells 2g and 2g + 1: the y and z steps of g, then x
   bool off_y = false, off_z = false, off_x = false;
   uint64_t c0 = pk;
   if (g & 1) c0 = morton_step(c0, my, (oct & 2u) != 0u, off_y);
   if (g & 2) c0 = morton_step(c0, mz, (oct & 4u) != 0u, off_z);
   const uint64_t c1 = morton_step(c0, mx, (oct & 1u) != 0u, off_x);
-  const bool ok0 = !(off_y || off_z), ok1 = ok0 && !off_x;
-  uint64_t tk[2];
-  tk[0] = ok0 ? tag_key(fr | c0, b - 1, fb) : 0ull;
-  tk[1] = ok1 ? tag_key(fr | c1, b - 1, fb) : 0ull;
+  const bool ok0 = !(off_y || off_z);
+  const uint64_t cells[2] = {c0, c1};
+  const bool ok[2] = {ok0, ok0 && !off_x};
   uint2 hit[2];
-  hash_find_n<2>(hash, hash_lg, hash_region(hreg, hash_lg, frame_part(kf, b)), tk, hit);
-  // cross-lane exchange through LDS (volatile: every read goes to LDS)
+  find_cells<2>(a, b - 1, fr, cells, ok, hit);
+  // cross-lane exchange through LDS within the wave
+  wave_lds_fence();  // earlier reads of the slots are done
   par[2 * g] = ((uint64_t)hit[0].y << 32) | hit[0].x;
   par[2 * g + 1] = ((uint64_t)hit[1].y << 32) | hit[1].x;
-  __builtin_amdgcn_wave_barrier();
+  wave_lds_fence();
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
     const uint32_t c = (offset_moves(j) >> (8 * g)) & 0xFFu;
@@ -610,38 +658,25 @@ __device__ __forceinline__ uint32_t group_offsets(int i) {
   return ((1u << hi) - 1u) & ~((1u << lo) - 1u);
 }
 
-template <int C, bool FIRST, bool LAST, bool TWO, bool BF>
+template <int C, bool LAST, bool TWO, bool BF>
 __global__ void __launch_bounds__(CONV_THREADS) k_conv(ConvArgs a) {
   constexpr int NCB = C / 16;
-  constexpr int KS = FIRST ? 3 : C / 4;
-  constexpr int KSP = (KS + 3) & ~3;
+  constexpr int KS = C / 4;
+  constexpr int KSP = KS;
   constexpr int KT = C / 4;
   // packed weights per (offset, column block, lane): fp32 KSP floats, bf16x3 8 words
   constexpr int WSZ = 27 * NCB * 64 * (BF ? 8 : KSP);
   constexpr int HSZ = LAST ? (TWO ? 2 : 16) * 64 * (BF ? 8 : KT) : 4;
-  // offsets per pipeline stage: the first layer's gathers are 2-byte words behind a
-  // few MFMAs each, and a shallow pipeline measured fastest there
-  constexpr int PCH = FIRST ? 2 : 3;
-  struct Gath {                        // one gathered neighbour slice
-    uint32_t word;                     // first layer: 11 input bits
-    f4 v[FIRST ? 1 : KSP / 4];         // later layers, fp32: KS channels
+  constexpr int PCH = 3;               // offsets per pipeline stage
+  struct Gath {                        // one gathered neighbour slice, fp32: KS channels
+    f4 v[KSP / 4];
   };
-  struct GathB {                       // later layers, bf16x3: channels 8g .. 8g+7
-    uint32_t word;
+  struct GathB {                       // bf16x3: channels 8g .. 8g+7
     uint4 hi, lo;
   };
   using G = typename std::conditional<BF, GathB, Gath>::type;
   __shared__ __attribute__((aligned(16))) float s_w[WSZ];
   __shared__ __attribute__((aligned(16))) float s_h[HSZ];
-  // per wave: parent cells (code<<32|first), rows padded to 9 so that the 16 voxels' cells lie in
-  // different banks
-  __shared__ uint64_t s_par[FIRST ? CONV_WAVES : 1][16][9];
-  // per wave: the tile's neighbour rows, voxel by voxel (32 entries, the last 5 are -1), so that
-  // a lane reads the row of any offset directly (the last layer has no room for them); rows
-  // padded to 36 words, so that the 16 voxels' entries of one offset lie in 16 different banks
-  constexpr bool ROWS = FIRST && !LAST && !BF;
-  constexpr int RW = 36;
-  __shared__ int32_t s_rows[ROWS ? CONV_WAVES : 1][16][RW];
   __shared__ int64_t s_tpre[NLEV + 1];
   __shared__ int64_t s_nv[NLEV];   // N_b of the launch's scales
   __shared__ int64_t s_mo[NLEV];   // first packed row of each scale
@@ -727,32 +762,12 @@ __global__ void __launch_bounds__(CONV_THREADS) k_conv(ConvArgs a) {
     const bool valid = row < nvox;
     // idle lanes read a real row; with a tile order, slot -> row
     const int64_t pos = mo + (valid ? row : nvox - 1);
-    const int64_t prow = (!FIRST && a.perm) ? (int64_t)a.perm[pos] : pos;
+    const int64_t prow = a.perm ? (int64_t)a.perm[pos] : pos;
     const int64_t lvb = (int64_t)(b - a.b0) * a.cap_pts;
 
     // ---- neighbour rows: lane (r, g) holds offsets k = 8g .. 8g+7 of voxel r
-    int4 nlo, nhi;
-    if (FIRST) {
-      int32_t nb[8];
-      parent_cell_rows(a.lv_key[lvb + (prow - mo)], b, g, a.hash, a.hash_lg, a.hreg, a.fb, s_par[w][r], nb);
-      nlo = make_int4(nb[0], nb[1], nb[2], nb[3]);
-      nhi = make_int4(nb[4], nb[5], nb[6], nb[7]);
-      if (valid && grp <= 0) {  // one wave of a quad stores the map rows
-        int4* dst = reinterpret_cast<int4*>(a.nbr + prow * NBR_STRIDE + 8 * g);
-        dst[0] = nlo;
-        dst[1] = nhi;
-      }
-    } else {
-      const int4* src = reinterpret_cast<const int4*>(a.nbr + prow * NBR_STRIDE + 8 * g);
-      nlo = src[0];
-      nhi = src[1];
-    }
-    if constexpr (ROWS) {
-      int4* rr = reinterpret_cast<int4*>(&s_rows[w][r][8 * g]);
-      rr[0] = nlo;
-      rr[1] = nhi;
-      __builtin_amdgcn_wave_barrier();
-    }
+    const int4* src = reinterpret_cast<const int4*>(a.nbr + prow * NBR_STRIDE + 8 * g);
+    const int4 nlo = src[0], nhi = src[1];
     // occupied offsets of the tile: one ballot per entry slot j, lanes of
     // group g covering offsets 8g + j (the 5 padding entries are -1)
     uint32_t offs = 0;
@@ -806,17 +821,13 @@ __global__ void __launch_bounds__(CONV_THREADS) k_conv(ConvArgs a) {
       int32_t nn[PCH];
 #pragma unroll
       for (int c = 0; c < PCH; ++c) {
-        if constexpr (ROWS) nn[c] = s_rows[w][r][ks[c] & 31];
-        else nn[c] = __shfl(pick8(nlo, nhi, ks[c] & 7), r + 16 * ((ks[c] & 31) >> 3));
+        nn[c] = __shfl(pick8(nlo, nhi, ks[c] & 7), r + 16 * ((ks[c] & 31) >> 3));
       }
       __builtin_amdgcn_sched_barrier(0);  // keep the exchanges back to back (one wait for all)
 #pragma unroll
       for (int c = 0; c < PCH; ++c) {
         const int32_t n = (valid && ks[c] >= 0) ? nn[c] : -1;
-        if constexpr (FIRST) {
-          // absent neighbours read the reserved zero entry: no select on loaded data
-          gb[c].word = n >= 0 ? a.lv_feat[lvb + n] : a.lv_feat[a.zero_feat];
-        } else if constexpr (BF) {
+        if constexpr (BF) {
           // rows hold [hi plane: C bf16][lo plane: C bf16]; lanes beyond C/8 feed zeros
           const int64_t srow = n >= 0 ? mo + n : a.cap_model;
           const uint4* src = reinterpret_cast<const uint4*>(a.h_in + srow * C);
@@ -854,31 +865,14 @@ __global__ void __launch_bounds__(CONV_THREADS) k_conv(ConvArgs a) {
           wa[cb][0] = wp[0];
           wa[cb][1] = wp[1];
         }
-        uint4 bh, bl;
-        if constexpr (FIRST) {
-          // 11 input bits: lane group 0 carries bits 0..7, group 1 bits 8..10
-          // (exact in bf16), groups 2-3 zeros; products hi*x + lo*x
-          const uint32_t bits = g < 2 ? (gb[c].word >> (8 * g)) & (g == 0 ? 0xFFu : 0x7u) : 0u;
-          uint32_t wd[4];
+        const uint4 bh = gb[c].hi, bl = gb[c].lo;
+        // the three products, column blocks interleaved
 #pragma unroll
-          for (int pr = 0; pr < 4; ++pr)
-            wd[pr] = (((bits >> (2 * pr)) & 1u) ? 0x3F80u : 0u) | (((bits >> (2 * pr + 1)) & 1u) ? 0x3F800000u : 0u);
-          bh = make_uint4(wd[0], wd[1], wd[2], wd[3]);
+        for (int cb = 0; cb < NCB; ++cb) acc[cb] = mfma_bf(wa[cb][0], bh, acc[cb]);
 #pragma unroll
-          for (int cb = 0; cb < NCB; ++cb) acc[cb] = mfma_bf(wa[cb][0], bh, acc[cb]);
+        for (int cb = 0; cb < NCB; ++cb) acc[cb] = mfma_bf(wa[cb][0], bl, acc[cb]);
 #pragma unroll
-          for (int cb = 0; cb < NCB; ++cb) acc[cb] = mfma_bf(wa[cb][1], bh, acc[cb]);
-        } else {
-          bh = gb[c].hi;
-          bl = gb[c].lo;
-          // the three products, column blocks interleaved
-#pragma unroll
-          for (int cb = 0; cb < NCB; ++cb) acc[cb] = mfma_bf(wa[cb][0], bh, acc[cb]);
-#pragma unroll
-          for (int cb = 0; cb < NCB; ++cb) acc[cb] = mfma_bf(wa[cb][0], bl, acc[cb]);
-#pragma unroll
-          for (int cb = 0; cb < NCB; ++cb) acc[cb] = mfma_bf(wa[cb][1], bh, acc[cb]);
-        }
+        for (int cb = 0; cb < NCB; ++cb) acc[cb] = mfma_bf(wa[cb][1], bh, acc[cb]);
       }
       }
     };
@@ -891,16 +885,10 @@ __global__ void __launch_bounds__(CONV_THREADS) k_conv(ConvArgs a) {
         f4 wv[NCB][KSP / 4];
         load_w(ks[c], wv);
         float bsrc[KSP];
-        if constexpr (FIRST) {
 #pragma unroll
-          for (int s = 0; s < KSP; ++s) bsrc[s] = (float)((gb[c].word >> (g * KS + s)) & 1u);
-          // slot s = KS (padding) meets zero weights
-        } else if constexpr (!BF) {
+        for (int q = 0; q < KSP / 4; ++q)
 #pragma unroll
-          for (int q = 0; q < KSP / 4; ++q)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) bsrc[4 * q + e] = gb[c].v[q][e];
-        }
+          for (int e = 0; e < 4; ++e) bsrc[4 * q + e] = gb[c].v[q][e];
         // column blocks interleaved: NCB independent accumulator chains
 #pragma unroll
         for (int s = 0; s < KS; ++s)
@@ -918,32 +906,15 @@ __global__ void __launch_bounds__(CONV_THREADS) k_conv(ConvArgs a) {
       G gA[PCH], gB[PCH];
       take(ksA);
       gather(ksA, gA);
-      if constexpr (FIRST) {
-        // fully unrolled (at most 27 offsets): straight-line code keeps the
-        // compiler's wait counts exact across the pipeline's stages
-        constexpr int ROUNDS = (27 + 2 * PCH - 1) / (2 * PCH);
-#pragma unroll
-        for (int it = 0; it < ROUNDS; ++it) {
-          take(ksB);
-          gather(ksB, gB);
-          mma(ksA, gA);
-          if (ksB[0] < 0) break;
-          take(ksA);
-          gather(ksA, gA);
-          mma(ksB, gB);
-          if (ksA[0] < 0) break;
-        }
-      } else {
-        while (true) {
-          take(ksB);
-          gather(ksB, gB);
-          mma(ksA, gA);
-          if (ksB[0] < 0) break;
-          take(ksA);
-          gather(ksA, gA);
-          mma(ksB, gB);
-          if (ksA[0] < 0) break;
-        }
+      while (true) {
+        take(ksB);
+        gather(ksB, gB);
+        mma(ksA, gA);
+        if (ksB[0] < 0) break;
+        take(ksA);
+        gather(ksA, gA);
+        mma(ksB, gB);
+        if (ksA[0] < 0) break;
       }
     }
     if (grp < 0) {
@@ -1254,9 +1225,7 @@ template <int C>
 __global__ void __launch_bounds__(256) k_top_prep(int lo, int nsc, int n_embed, int b0, RowMap rm,
                                                   const uint64_t* __restrict__ lv_key,
                                                   const uint8_t* __restrict__ lv_code, int64_t cap_pts,
-                                                  const HashSlot* __restrict__ hash, int hash_lg,
-                                                  const uint64_t* __restrict__ hreg, int fb,
-                                                  const float* __restrict__ emb_o, int32_t* __restrict__ nbr,
+                                                  CellArgs cells, const float* __restrict__ emb_o, int32_t* __restrict__ nbr,
                                                   float* __restrict__ X) {
   constexpr int Q = C / 16;  // f4 per lane of a row
   __shared__ uint64_t s_par[4][16][9];  // rows padded: the 16 voxels' cells in different banks
@@ -1291,7 +1260,7 @@ __global__ void __launch_bounds__(256) k_top_prep(int lo, int nsc, int n_embed, 
     if (b == rm.b_ext)
       base_cell_rows(lv_key[lvb + vr], b, g, lv_key + lvb, n, nb);
     else
-      parent_cell_rows(lv_key[lvb + vr], b, g, hash, hash_lg, hreg, fb, s_par[w][r], nb);
+      parent_cell_rows(lv_key[lvb + vr], b, g, cells, s_par[w][r], nb);
     if (valid) {
       int4* dst = reinterpret_cast<int4*>(nbr + (mo + vr) * NBR_STRIDE + 8 * g);
       dst[0] = make_int4(nb[0], nb[1], nb[2], nb[3]);
@@ -1317,28 +1286,28 @@ __global__ void __launch_bounds__(256) k_top_prep(int lo, int nsc, int n_embed, 
 // voxel r), and the lane ends with the rows of offsets k = 32g .. 32g+31,
 // k = (dx+2) + 5(dy+2) + 25(dz+2) (125 .. 127 padding; -1: absent or
 // off-grid).
-__device__ __forceinline__ void parent_cell_rows5(uint64_t kf, int b, int g, const HashSlot* __restrict__ hash,
-                                                  int hash_lg, const uint64_t* __restrict__ hreg, int fb,
-                                                  volatile uint64_t* par, int32_t (&nb)[32]) {
+__device__ __forceinline__ void parent_cell_rows5(uint64_t kf, int b, int g, const CellArgs& a,
+                                                  uint64_t* par, int32_t (&nb)[32]) {
   const uint64_t key = morton_part(kf, b), fr = frame_part(kf, b) << (3 * (b - 1));
   const int x = (int)compact3(key), y = (int)compact3(key >> 1), z = (int)compact3(key >> 2);
   const int px = x >> 1, py = y >> 1, pz = z >> 1;
   const int plim = 1 << (b - 1);
-  uint64_t tk[7];
+  uint64_t cells[7];
+  bool ok[7];
 #pragma unroll
   for (int i = 0; i < 7; ++i) {
     const int e = g + 4 * i;
     const int cx = px + e % 3 - 1, cy = py + (e / 3) % 3 - 1, cz = pz + e / 9 - 1;
-    tk[i] = (e < 27 && cx >= 0 && cy >= 0 && cz >= 0 && cx < plim && cy < plim && cz < plim)
-                ? tag_key(fr | morton3((uint32_t)cx, (uint32_t)cy, (uint32_t)cz), b - 1, fb)
-                : 0ull;
+    ok[i] = e < 27 && cx >= 0 && cy >= 0 && cz >= 0 && cx < plim && cy < plim && cz < plim;
+    cells[i] = ok[i] ? morton3((uint32_t)cx, (uint32_t)cy, (uint32_t)cz) : 0ull;
   }
   uint2 hit[7];
-  hash_find_n<7>(hash, hash_lg, hash_region(hreg, hash_lg, frame_part(kf, b)), tk, hit);
+  find_cells<7>(a, b - 1, fr, cells, ok, hit);
+  wave_lds_fence();  // earlier reads of the slots are done
 #pragma unroll
   for (int i = 0; i < 7; ++i)
     if (g + 4 * i < 27) par[g + 4 * i] = ((uint64_t)hit[i].y << 32) | hit[i].x;
-  __builtin_amdgcn_wave_barrier();
+  wave_lds_fence();
   const int lim = 1 << b;
 #pragma unroll
   for (int j = 0; j < 32; ++j) {
@@ -1391,9 +1360,7 @@ template <int C>
 __global__ void __launch_bounds__(256) k_top_prep5(int lo, int nsc, int n_embed, int b0, RowMap rm,
                                                    const uint64_t* __restrict__ lv_key,
                                                    const uint8_t* __restrict__ lv_code, int64_t cap_pts,
-                                                   const HashSlot* __restrict__ hash, int hash_lg,
-                                                  const uint64_t* __restrict__ hreg, int fb,
-                                                   const float* __restrict__ emb_o, int32_t* __restrict__ nbr,
+                                                   CellArgs cells, const float* __restrict__ emb_o, int32_t* __restrict__ nbr,
                                                    float* __restrict__ X) {
   constexpr int Q = C / 16;
   __shared__ uint64_t s_par[4][16][27];
@@ -1428,7 +1395,7 @@ __global__ void __launch_bounds__(256) k_top_prep5(int lo, int nsc, int n_embed,
     if (b == rm.b_ext)
       base_cell_rows5(lv_key[lvb + vr], b, g, lv_key + lvb, n, nb);
     else
-      parent_cell_rows5(lv_key[lvb + vr], b, g, hash, hash_lg, hreg, fb, s_par[w][r], nb);
+      parent_cell_rows5(lv_key[lvb + vr], b, g, cells, s_par[w][r], nb);
     if (valid) {
       int4* dst = reinterpret_cast<int4*>(nbr + (mo + vr) * 128 + 32 * g);
 #pragma unroll
@@ -1694,12 +1661,12 @@ __global__ void __launch_bounds__(CW_THREADS) k_convw(ConvArgs a) {
 template <int C, bool TWO>
 constexpr int headw_threads() { return (TWO && C >= 64) ? 256 : 1024; }
 
-template <int C, bool TWO>
+template <int C, bool TWO, bool BF>
 __global__ void __launch_bounds__((headw_threads<C, TWO>())) k_headw(ConvArgs a) {
   constexpr int NCB = C / 16;
   constexpr int HT = headw_threads<C, TWO>();
   constexpr int HWV = HT / 64;
-  constexpr int HQ = (TWO ? 2 : 16) * 64 * (C / 4) / 4;  // 16-byte words of the packed head
+  constexpr int HQ = (TWO ? 2 : 16) * 64 * (BF ? 8 : C / 4) / 4;  // 16-byte words of the packed head
   __shared__ __attribute__((aligned(16))) float s_h[HQ * 4];
   __shared__ int64_t s_tpre[NLEV + 1];
   __shared__ int64_t s_nv[NLEV];
@@ -1737,30 +1704,214 @@ __global__ void __launch_bounds__((headw_threads<C, TWO>())) k_headw(ConvArgs a)
     f4 acc[NCB];
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) acc[cb] = *reinterpret_cast<const f4*>(a.h_in + prow * C + 16 * cb + 4 * g);
-    head_epilogue<C, TWO, false>(a, acc, s_h, lane, g, valid, prow, mo, lvb, s_mo[0]);
+    head_epilogue<C, TWO, BF>(a, acc, s_h, lane, g, valid, prow, mo, lvb, s_mo[0]);
   }
 }
 
-template <int C, bool FIRST, bool LAST, bool TWO, bool BF>
+template <int C, bool BF>
+hipError_t run_headw(Ctx& c, bool two, const ConvArgs& a) {
+  auto go = [&](auto kern, int threads, int most) {
+    const int64_t per = threads / 4;  // voxels of a block's waves: 16 each
+    const int64_t blocks = std::min<int64_t>(most, (c.cap_model + per - 1) / per);
+    if (c.ext_start) {  // timed: the events are the dispatch's own start and end
+      hipExtLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(threads), 0, c.stream, c.ext_start, c.ext_stop, 0u, a);
+      c.ext_start = c.ext_stop = nullptr;
+    } else {
+      hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(threads), 0, c.stream, a);
+    }
+    return hipGetLastError();
+  };
+  return two ? go(k_headw<C, true, BF>, headw_threads<C, true>(), 4096)
+             : go(k_headw<C, false, BF>, headw_threads<C, false>(), 1024);
+}
+
+// ---------------------------------------------------------------------------
+// First conv layer of the plain model, with the neighbour search.
+//
+// Its 11 input bits are the voxel's octant and its parent's code, so what the
+// children of one parent-scale cell add to a voxel's sum depends only on the
+// voxel's octant (8), which of the 8 cells around it the cell is (8) and the
+// cell's code (256): F[oct][e][code] [C] = the sum over the cell's occupied
+// children that touch the voxel of W[k]^T [delta, code].  The table is formed
+// once per weight set, in double, and the layer is the bias plus 8 rows of it,
+// in cell order (code 0, an absent cell, has a zero row).
+//
+// Bound by the probe -> row latency chain and L2 reads (8 C-float rows per
+// voxel; the whole table is 2 MB at C = 32 and stays in each XCD's L2).  One
+// wave per 16 voxels, 4 lanes per voxel: they probe two cells each, exchange
+// the hits through LDS and then sum C / 4 channels each.  Small blocks without
+// staged weights, so that more waves hide the chain than the LDS-resident conv
+// kernel allows.  Against the former layer (27 offsets gathered and issued as
+// fp32 MFMA in the conv kernel): 14-bit scan 56 -> 34 us in the encoder's
+// launch, 131 -> 84 us over the decoder's nine; 10 frames 500 -> 380 us; 16-bit
+// 128-beam scan 159 -> 127 us.  8 unconditional rows per voxel instead of the
+// occupied cells' only took 42 us at 14 bits.
+template <int C>
+__global__ void __launch_bounds__(256) k_first_table(const float* __restrict__ W, float* __restrict__ F) {
+  const int co = threadIdx.x % C;
+  const int row = blockIdx.x * (256 / C) + threadIdx.x / C;  // (oct * 8 + e) * 256 + code
+  const uint32_t code = row & 255u, e = (row >> 8) & 7u, oct = (uint32_t)row >> 11;
+  double acc = 0.0;
+  for (uint32_t d = 0; d < 8; ++d) {
+    if (!((code >> d) & 1u)) continue;
+    // per axis, the child's cell minus the voxel's: in v's parent d - oct; in
+    // the neighbour cell on v's side 1 + d or d - 2, touching when that is +-1
+    int k = 0;
+    bool touch = true;
+    for (int ax = 2; ax >= 0; --ax) {
+      const int o = (oct >> ax) & 1, dd = (d >> ax) & 1;
+      const int step = ((e >> ax) & 1u) ? (o ? 1 + dd : dd - 2) : dd - o;
+      touch = touch && step >= -1 && step <= 1;
+      k = 3 * k + step + 1;
+    }
+    if (!touch) continue;
+    const float* w = W + (size_t)k * RENO_IN_FEATURES * C + co;
+    for (int i = 0; i < 3; ++i)
+      if ((d >> i) & 1u) acc += (double)w[i * C];
+    for (int i = 0; i < 8; ++i)
+      if ((code >> i) & 1u) acc += (double)w[(3 + i) * C];
+  }
+  F[(size_t)row * C + co] = (float)acc;
+}
+
+struct FirstArgs {
+  int b_lo, nsc;
+  RowMap rm;
+  CellArgs cells;
+  const uint64_t* lv_key;
+  const float* table;    // [8][8][256][C]
+  const float* bias;     // [C]
+  int32_t* nbr;          // [rows][NBR_STRIDE]
+  float* out;            // [rows][C]
+};
+
+constexpr int FIRST_WAVES = 4;
+
+template <int C, bool BF>
+__global__ void __launch_bounds__(64 * FIRST_WAVES, 4) k_first(FirstArgs a) {
+  constexpr int Q = C / 16;  // f4 words of a lane's C / 4 channels
+  __shared__ uint64_t s_par[FIRST_WAVES][16][9];  // rows padded: the 16 voxels' cells in different banks
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+  const int r = lane & 15, g = lane >> 4;
+  // lane i holds scale i of the launch: rows, first row, inclusive tile prefix
+  int64_t n_l = 0, mo_l = 0;
+  if (lane < a.nsc) scale_span(a.rm, a.b_lo + lane, mo_l, n_l);
+  int incl = (int)((n_l + 15) / 16);
+  if (a.nsc > 1) {
+#pragma unroll
+    for (int o = 1; o < 32; o <<= 1) {
+      const int y = __shfl_up(incl, o);
+      if (lane >= o) incl += y;
+    }
+  }
+  const int total = __builtin_amdgcn_readlane(incl, a.nsc - 1);
+  // chunks of consecutive tiles are dealt to the XCDs (blockIdx % 8) in turn,
+  // as conv_tile does
+  const int tch = total / 256 < FIRST_WAVES ? FIRST_WAVES : (total / 256 > 256 ? 256 : total / 256);
+  const int xcd = blockIdx.x & 7, step = (int)(gridDim.x >> 3) * FIRST_WAVES;
+  for (int j = (int)(blockIdx.x >> 3) * FIRST_WAVES + w;; j += step) {
+    const int tile = ((j / tch) * 8 + xcd) * tch + j % tch;
+    if (tile >= total) break;
+    const int si = __popcll(__ballot(lane < a.nsc && incl <= tile));
+    const int b = a.b_lo + si;
+    const int n = __builtin_amdgcn_readlane((int)n_l, si);       // voxel and model-row counts stay below 2^30
+    const int64_t mo = __builtin_amdgcn_readlane((int)mo_l, si);
+    const int t0 = si ? __builtin_amdgcn_readlane(incl, si - 1) : 0;
+    const int row = (tile - t0) * 16 + r;
+    const bool valid = row < n;
+    const int vr = valid ? row : n - 1;  // idle lanes search a real voxel
+    const uint64_t key = a.lv_key[(int64_t)(b - a.cells.b0) * a.cells.cap_pts + vr];
+    int32_t nb[8];
+    uint64_t* par = s_par[w][r];
+    parent_cell_rows(key, b, g, a.cells, par, nb);
+    // lane g takes channels 16 q + 4 g .. + 3: the 4 lanes of a voxel read 64
+    // contiguous bytes; absent cells (code 0) load nothing
+    const f4* T = reinterpret_cast<const f4*>(a.table) + (size_t)((uint32_t)key & 7u) * (8 * 256 * C / 4) + g;
+    f4 v[8][Q];
+    uint32_t code[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      code[e] = (uint32_t)(par[e] >> 32);
+#pragma unroll
+      for (int q = 0; q < Q; ++q) v[e][q] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      if (code[e]) {
+        const f4* src = T + (size_t)(e * 256 + (code[e] & 255u)) * (C / 4);
+#pragma unroll
+        for (int q = 0; q < Q; ++q) v[e][q] = src[4 * q];
+      }
+    }
+    f4 acc[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) acc[q] = reinterpret_cast<const f4*>(a.bias)[4 * q + g];
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+#pragma unroll
+      for (int q = 0; q < Q; ++q) acc[q] += v[e][q];
+    if (!valid) continue;
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[q][i] = fmaxf(acc[q][i], 0.0f);
+    const int64_t prow = mo + row;
+    int4* dst = reinterpret_cast<int4*>(a.nbr + prow * NBR_STRIDE + 8 * g);
+    dst[0] = make_int4(nb[0], nb[1], nb[2], nb[3]);
+    dst[1] = make_int4(nb[4], nb[5], nb[6], nb[7]);
+    if constexpr (BF) {  // [hi plane | lo plane] of bf16, the next layer's operand
+      uint16_t* orow = reinterpret_cast<uint16_t*>(a.out + prow * C);
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        uint32_t h0, l0, h1, l1;
+        split2(acc[q][0], acc[q][1], h0, l0);
+        split2(acc[q][2], acc[q][3], h1, l1);
+        *reinterpret_cast<uint2*>(orow + 4 * (4 * q + g)) = make_uint2(h0, h1);
+        *reinterpret_cast<uint2*>(orow + C + 4 * (4 * q + g)) = make_uint2(l0, l1);
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < Q; ++q) reinterpret_cast<f4*>(a.out + prow * C)[4 * q + g] = acc[q];
+    }
+  }
+}
+
+CellArgs cell_args(const Ctx& c) {
+  return CellArgs{c.d_hash, c.hash_lg, c.hreg(), c.fbits, c.b0(), c.cap_pts, c.lv_code, c.lv_fc};
+}
+
+template <int C, bool BF>
+hipError_t run_first(Ctx& c, const FirstArgs& a) {
+  // 8 blocks per CU at most; fewer when the capacity cannot fill them
+  int64_t blocks = ((c.cap_model + 16 * FIRST_WAVES - 1) / (16 * FIRST_WAVES) + 7) & ~int64_t(7);
+  if (blocks > 2048) blocks = 2048;
+  if (c.ext_start) {  // timed: the events are the dispatch's own start and end
+    hipExtLaunchKernelGGL((k_first<C, BF>), dim3((unsigned)blocks), dim3(64 * FIRST_WAVES), 0, c.stream, c.ext_start,
+                          c.ext_stop, 0u, a);
+    c.ext_start = c.ext_stop = nullptr;
+  } else {
+    hipLaunchKernelGGL((k_first<C, BF>), dim3((unsigned)blocks), dim3(64 * FIRST_WAVES), 0, c.stream, a);
+  }
+  return hipGetLastError();
+}
+
+template <int C, bool LAST, bool TWO, bool BF>
 hipError_t run_conv(Ctx& c, const ConvArgs& a) {
   // one block per CU stages the weights once for its 16 waves
   if (c.ext_start) {  // timed: the events are the dispatch's own start and end
-    hipExtLaunchKernelGGL((k_conv<C, FIRST, LAST, TWO, BF>), dim3(256), dim3(CONV_THREADS), 0, c.stream,
+    hipExtLaunchKernelGGL((k_conv<C, LAST, TWO, BF>), dim3(256), dim3(CONV_THREADS), 0, c.stream,
                           c.ext_start, c.ext_stop, 0u, a);
     c.ext_start = c.ext_stop = nullptr;
   } else {
-    hipLaunchKernelGGL((k_conv<C, FIRST, LAST, TWO, BF>), dim3(256), dim3(CONV_THREADS), 0, c.stream, a);
+    hipLaunchKernelGGL((k_conv<C, LAST, TWO, BF>), dim3(256), dim3(CONV_THREADS), 0, c.stream, a);
   }
   return hipGetLastError();
 }
 
 template <int C, bool BF>
-hipError_t run_layer(Ctx& c, bool first, bool last, bool two, const ConvArgs& a) {
-  if (first && last)
-    return two ? run_conv<C, true, true, true, BF>(c, a) : run_conv<C, true, true, false, BF>(c, a);
-  if (first) return run_conv<C, true, false, false, BF>(c, a);
-  if (last) return two ? run_conv<C, false, true, true, BF>(c, a) : run_conv<C, false, true, false, BF>(c, a);
-  return run_conv<C, false, false, false, BF>(c, a);
+hipError_t run_layer(Ctx& c, bool last, bool two, const ConvArgs& a) {
+  if (last) return two ? run_conv<C, true, true, BF>(c, a) : run_conv<C, true, false, BF>(c, a);
+  return run_conv<C, false, false, BF>(c, a);
 }
 
 // Stage 2 of the two-stage head for one scale from the stored features of the
@@ -1820,7 +1971,6 @@ __global__ void __launch_bounds__(256) k_head2(int b, const int32_t* __restrict_
 hipError_t launch_pack_weights(Ctx& c, const reno_weights& w) {
   ProfScope ps_(c, RENO_K_OTHER);
   const int C = c.p.channels;
-  int c_in = RENO_IN_FEATURES;
   const bool bf = c.p.precision == RENO_PREC_BF16X3;
   if (c.p.model_mode == RENO_MODEL_TOP) {  // four C -> C convs (fp32) and the two embeddings
     for (int l = 0; l < 4; ++l) {
@@ -1836,16 +1986,18 @@ hipError_t launch_pack_weights(Ctx& c, const reno_weights& w) {
     hipLaunchKernelGGL(k_copy_f32, dim3(1), dim3(256), 0, c.stream, w.emb_d, c.w_embd, 8 * C);
   }
   for (int l = 0; l < c.p.layers && c.p.model_mode != RENO_MODEL_TOP; ++l) {
-    const int KS = (c_in + 3) / 4;
-    const int KSP = (KS + 3) & ~3;
-    if (bf)
-      hipLaunchKernelGGL(k_pack_conv_bf, dim3(64), dim3(256), 0, c.stream, w.conv_w[l], c_in, C,
+    if (l == 0) {
+      const dim3 grid(8 * 8 * 256 * C / 256);
+      if (C == 32) hipLaunchKernelGGL(k_first_table<32>, grid, dim3(256), 0, c.stream, w.conv_w[0], c.w_conv[0]);
+      else hipLaunchKernelGGL(k_first_table<16>, grid, dim3(256), 0, c.stream, w.conv_w[0], c.w_conv[0]);
+    } else if (bf) {
+      hipLaunchKernelGGL(k_pack_conv_bf, dim3(64), dim3(256), 0, c.stream, w.conv_w[l], C, C,
                          reinterpret_cast<uint32_t*>(c.w_conv[l]));
-    else
-      hipLaunchKernelGGL(k_pack_conv, dim3(64), dim3(256), 0, c.stream, w.conv_w[l], c_in, C, KS, KSP, 27,
+    } else {
+      hipLaunchKernelGGL(k_pack_conv, dim3(64), dim3(256), 0, c.stream, w.conv_w[l], C, C, C / 4, C / 4, 27,
                          c.w_conv[l]);
+    }
     hipLaunchKernelGGL(k_copy_f32, dim3(1), dim3(256), 0, c.stream, w.conv_b[l], c.w_bias[l], C);
-    c_in = C;
   }
   if (c.p.head_mode == RENO_HEAD_TWO_STAGE) {
     // packed blocks [stage 1][stage 2], biases [b1 | b2], plain [C][H1 | H2]
@@ -1901,7 +2053,7 @@ hipError_t launch_top(Ctx& c, int b_lo, int b_hi, float* logits, bool second) {
     const int blocks = (int)std::min<int64_t>(2048, (c.cap_rows() + 63) / 64);
 #define RENO_PREP(CC)                                                                                         \
   hipLaunchKernelGGL(k_top_prep<CC>, dim3(blocks), dim3(256), 0, c.stream, n_lo, b_hi - n_lo + 1, b_hi - n_lo, b0, \
-                     rm, c.lv_key, c.lv_code, (int64_t)c.cap_pts, c.d_hash, c.hash_lg, c.hreg(), c.fbits, c.w_embo, \
+                     rm, c.lv_key, c.lv_code, (int64_t)c.cap_pts, cell_args(c), c.w_embo, \
                      c.d_nbr, c.h_c)
     if (C == 32) RENO_PREP(32); else RENO_PREP(16);
 #undef RENO_PREP
@@ -1912,14 +2064,7 @@ hipError_t launch_top(Ctx& c, int b_lo, int b_hi, float* logits, bool second) {
   a.moff = c.d_moff;
   a.cap_pts = c.cap_pts;
   a.cap_model = c.cap_model;
-  a.lv_key = c.lv_key;
-  a.lv_feat = c.lv_feat;
-  a.hash = c.d_hash;
-  a.hash_lg = c.hash_lg;
-  a.hreg = c.hreg();
-  a.fb = c.fbits;
   a.nbr = c.d_nbr;
-  a.zero_feat = (int64_t)c.nlv * c.cap_pts;
   a.hb = c.w_hbias;
   a.hw = c.w_head;
   a.lse = c.d_lse;
@@ -1956,7 +2101,7 @@ hipError_t launch_top(Ctx& c, int b_lo, int b_hi, float* logits, bool second) {
     a.bias = c.w_bias[wi];
     a.logits = last ? logits : nullptr;
     ProfScope ps_(c, last ? RENO_K_CONV_LAST : RENO_K_CONV_MID);
-    e = (C == 32) ? run_layer<32, false>(c, false, last, two, a) : run_layer<16, false>(c, false, last, two, a);
+    e = (C == 32) ? run_layer<32, false>(c, last, two, a) : run_layer<16, false>(c, last, two, a);
   };
   conv(n_lo, b_hi - 1, 0, c.h_c, c.h_b, nullptr, nullptr, false);
   conv(n_lo, b_hi - 1, 1, c.h_b, nullptr, c.h_c, c.h_d, false);
@@ -1978,11 +2123,11 @@ hipError_t launch_top_wide(Ctx& c, int b_lo, int b_hi, float* logits, bool secon
     const int blocks = (int)std::min<int64_t>(2048, (c.cap_rows() + 63) / 64);
     if (KV == 125)
       hipLaunchKernelGGL(k_top_prep5<C>, dim3(blocks), dim3(256), 0, c.stream, n_lo, b_hi - n_lo + 1, b_hi - n_lo,
-                         b0, rm, c.lv_key, c.lv_code, (int64_t)c.cap_pts, c.d_hash, c.hash_lg, c.hreg(), c.fbits, c.w_embo,
+                         b0, rm, c.lv_key, c.lv_code, (int64_t)c.cap_pts, cell_args(c), c.w_embo,
                          c.d_nbr, c.h_c);
     else
       hipLaunchKernelGGL(k_top_prep<C>, dim3(blocks), dim3(256), 0, c.stream, n_lo, b_hi - n_lo + 1, b_hi - n_lo,
-                         b0, rm, c.lv_key, c.lv_code, (int64_t)c.cap_pts, c.d_hash, c.hash_lg, c.hreg(), c.fbits, c.w_embo,
+                         b0, rm, c.lv_key, c.lv_code, (int64_t)c.cap_pts, cell_args(c), c.w_embo,
                          c.d_nbr, c.h_c);
   }
   ConvArgs a{};
@@ -1991,7 +2136,6 @@ hipError_t launch_top_wide(Ctx& c, int b_lo, int b_hi, float* logits, bool secon
   a.moff = c.d_moff;
   a.cap_pts = c.cap_pts;
   a.cap_model = c.cap_model;
-  a.lv_key = c.lv_key;
   a.nbr = c.d_nbr;
   a.hb = c.w_hbias;
   a.hw = c.w_head;
@@ -2041,16 +2185,9 @@ hipError_t launch_top_wide(Ctx& c, int b_lo, int b_hi, float* logits, bool secon
     a.b_hi = b_hi;
     a.h_in = c.h_a;
     a.logits = logits;
-    if (c.p.head_mode == RENO_HEAD_TWO_STAGE) {
-      constexpr int HT = headw_threads<C, true>();
-      const int blocks = (int)std::min<int64_t>(4096, (c.cap_model + 16 * HT / 64 - 1) / (16 * HT / 64));
-      hipLaunchKernelGGL((k_headw<C, true>), dim3(blocks), dim3(HT), 0, c.stream, a);
-    } else {
-      constexpr int HT = headw_threads<C, false>();
-      const int blocks = (int)std::min<int64_t>(1024, (c.cap_model + 16 * HT / 64 - 1) / (16 * HT / 64));
-      hipLaunchKernelGGL((k_headw<C, false>), dim3(blocks), dim3(HT), 0, c.stream, a);
-    }
+    e = run_headw<C, false>(c, c.p.head_mode == RENO_HEAD_TWO_STAGE, a);
   }
+  if (e != hipSuccess) return e;
   return hipGetLastError();
 }
 
@@ -2079,14 +2216,7 @@ hipError_t launch_model(Ctx& c, int b_lo, int b_hi, float* logits, bool second) 
   a.moff = c.d_moff;
   a.cap_pts = c.cap_pts;
   a.cap_model = c.cap_model;
-  a.lv_key = c.lv_key;
-  a.lv_feat = c.lv_feat;
-  a.hash = c.d_hash;
-  a.hash_lg = c.hash_lg;
-  a.hreg = c.hreg();
-  a.fb = c.fbits;
   a.nbr = c.d_nbr;
-  a.zero_feat = (int64_t)c.nlv * c.cap_pts;
   a.hb = c.w_hbias;
   a.hw = c.w_head;
   a.lse = c.d_lse;
@@ -2105,8 +2235,22 @@ hipError_t launch_model(Ctx& c, int b_lo, int b_hi, float* logits, bool second) 
   a.b_ext = -1;
   a.cap_rows = c.cap_model + 1;
   const RowMap rm{c.d_count, c.d_moff, (int64_t)c.cap_model, -1, 0, (int64_t)c.cap_model + 1};
+  const bool bf = c.p.precision == RENO_PREC_BF16X3, c32 = c.p.channels == 32;
   hipError_t e = hipSuccess;
-  for (int l = 0; l < L && e == hipSuccess; ++l) {
+  {
+    ProfScope ps_(c, RENO_K_CONV_FIRST, true);
+    FirstArgs f{b_lo, b_hi - b_lo + 1, rm, cell_args(c), c.lv_key, c.w_conv[0], c.w_bias[0], c.d_nbr, c.h_a};
+    if (bf && L > 1) e = c32 ? run_first<32, true>(c, f) : run_first<16, true>(c, f);
+    else e = c32 ? run_first<32, false>(c, f) : run_first<16, false>(c, f);
+  }
+  if (L == 1 && e == hipSuccess) {  // the head alone, on the first layer's rows
+    ProfScope ps_(c, RENO_K_CONV_LAST, true);
+    a.h_in = c.h_a;
+    a.logits = logits;
+    if (bf) e = c32 ? run_headw<32, true>(c, two, a) : run_headw<16, true>(c, two, a);
+    else e = c32 ? run_headw<32, false>(c, two, a) : run_headw<16, false>(c, two, a);
+  }
+  for (int l = 1; l < L && e == hipSuccess; ++l) {
     if (l == 1 && order) {
       ProfScope pso_(c, RENO_K_OTHER);
       const int nsc = b_hi - b_lo + 1;
@@ -2116,18 +2260,14 @@ hipError_t launch_model(Ctx& c, int b_lo, int b_hi, float* logits, bool second) 
       a.perm = c.d_perm;
     }
     a.h_in = (l & 1) ? c.h_a : c.h_b;   // layer l reads what layer l-1 wrote
-    a.h_out = (l & 1) ? c.h_b : c.h_a;  // layer 0 writes h_a
+    a.h_out = (l & 1) ? c.h_b : c.h_a;  // layer 0 wrote h_a
     a.w = c.w_conv[l];
     a.bias = c.w_bias[l];
-    a.logits = (l == L - 1) ? logits : nullptr;
-    const bool first = l == 0, last = l == L - 1;
-    ProfScope ps_(c, last ? RENO_K_CONV_LAST : (first ? RENO_K_CONV_FIRST : RENO_K_CONV_MID), true);
-    if (c.p.precision == RENO_PREC_BF16X3)
-      e = (c.p.channels == 32) ? run_layer<32, true>(c, first, last, two, a)
-                               : run_layer<16, true>(c, first, last, two, a);
-    else
-      e = (c.p.channels == 32) ? run_layer<32, false>(c, first, last, two, a)
-                               : run_layer<16, false>(c, first, last, two, a);
+    const bool last = l == L - 1;
+    a.logits = last ? logits : nullptr;
+    ProfScope ps_(c, last ? RENO_K_CONV_LAST : RENO_K_CONV_MID, true);
+    if (bf) e = c32 ? run_layer<32, true>(c, last, two, a) : run_layer<16, true>(c, last, two, a);
+    else e = c32 ? run_layer<32, false>(c, last, two, a) : run_layer<16, false>(c, last, two, a);
   }
   return e;
 }

@@ -383,13 +383,12 @@ __global__ void __launch_bounds__(PYR_THREADS) k_pyramid(PyrArgs a) {
 // ---------------------------------------------------------------------------
 // FOG codes for every scale b0 <= b < B: the children of parent p are the
 // rows [fc[p], fc[p+1]) of V_{b+1}; the code ORs 1 << (child key & 7)
-// (Sec. 3.1: weights 1..128 over the octants).  Also writes each child's
-// layer-1 input bits (delta | code << 3) and inserts every parent of a model
-// scale (b0 <= b <= B-2) into the coordinate hash with its code and first child.
+// (Sec. 3.1: weights 1..128 over the octants).  Also inserts the
+// voxels of the hashed scales into the coordinate hash with their code and
+// first child.
 __global__ void __launch_bounds__(256) k_codes(const uint64_t* __restrict__ key,
                                                const int32_t* __restrict__ fc,
                                                uint8_t* __restrict__ code,
-                                               uint16_t* __restrict__ feat,
                                                const int32_t* __restrict__ count, int b0, int B,
                                                int64_t cap_pts, HashSlot* hash, int hash_lg,
                                                const uint64_t* __restrict__ hreg, int fb, uint32_t* err) {
@@ -430,12 +429,9 @@ __global__ void __launch_bounds__(256) k_codes(const uint64_t* __restrict__ key,
     for (int i = 0; i < 8; ++i)
       if (i < nk) c |= 1u << (uint32_t)(kc[i] & 7ull);
     code[rb + p] = (uint8_t)c;
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-      if (i < nk) feat[rc + lo + i] = (uint16_t)((kc[i] & 7ull) | (c << 3));
-    // parents of model scales go into the coordinate hash with their code
-    // and first child
-    if (b <= B - 2) {
+    // cells that lookups start from (hashed_scale) go into the coordinate hash
+    // with their code and first child
+    if (hashed_scale(b, b0, B)) {
       const uint64_t kp = key[rb + p];
       hash_insert(hash, hash_lg, hash_region(hreg, hash_lg, frame_part(kp, b)), tag_key(kp, b, fb), lo, c, err);
     }
@@ -522,7 +518,7 @@ hipError_t launch_codes(Ctx& c, int B) {
   if (blocks > 2048) blocks = 2048;
   if (blocks < 1) blocks = 1;
   hipLaunchKernelGGL(k_codes, dim3((unsigned)blocks), dim3(256), 0, c.stream, c.lv_key, c.lv_fc,
-                     c.lv_code, c.lv_feat, c.d_count, c.b0(), B, c.cap_pts, c.d_hash, c.hash_lg,
+                     c.lv_code, c.d_count, c.b0(), B, c.cap_pts, c.d_hash, c.hash_lg,
                      c.hreg(), c.fbits, c.d_err);
   return hipGetLastError();
 }
