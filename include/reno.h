@@ -68,10 +68,13 @@ typedef enum {
 #define RENO_MAX_FRAMES 1024
 #define RENO_HEAD_ONE_STAGE 0   /* one 256-way softmax over the code (Eq. 10) */
 #define RENO_HEAD_TWO_STAGE 1   /* bitwise two-stage head (Eqs. 11-13) */
-#define RENO_PREC_FP32 0        /* conv layers and heads on fp32 MFMA */
-#define RENO_PREC_BF16X3 1      /* each fp32 operand split into bf16 hi + lo, products
-                                   hi*hi + hi*lo + lo*hi on bf16 MFMA with fp32
-                                   accumulation (~2^-16 relative per product) */
+#define RENO_PREC_FP32 0        /* results to fp32 rounding: fp32 operands carried as a
+                                   power-of-two factor and fp16 hi + lo (22 bits), on
+                                   fp16 MFMA with fp32 accumulation; fp32 MFMA for the
+                                   wide full predictor */
+#define RENO_PREC_BF16X3 1      /* at least the accuracy of operands split into bf16 hi +
+                                   lo (~2^-16 relative per product); since the fp32 mode
+                                   costs no more, it runs the same kernels */
 #define RENO_MODEL_PLAIN 0      /* 11 input bits [delta, parent code] (Eqs. 7-8), L sparse
                                    conv + ReLU layers (Eq. 9) */
 #define RENO_MODEL_TOP 1        /* full target occupancy predictor (Sec. 3.2, Eqs. 6-9):

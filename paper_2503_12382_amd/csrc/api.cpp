@@ -52,7 +52,8 @@ void free_all(Ctx* c) {
                   c->d_status, c->d_hash,   c->d_hreg,   c->h_a,      c->h_b,      c->d_nbr,     c->d_lse,
                   c->d_partial, c->d_total, c->w_head,   c->w_hbias,  c->w_head_plain,
                   c->d_lse2,    c->w_emb,   c->d_s1,     c->w_head_t, c->d_perm,
-                  c->h_c,       c->h_d,     c->w_embo,   c->w_embd};
+                  c->h_c,       c->h_d,     c->w_embo,   c->w_embd,   c->s_c,     c->s_d,
+                  c->r_a,       c->r_b,     c->r_c,      c->r_d,      c->w_wfac,  c->w_hfac};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   for (int l = 0; l < RENO_MAX_LAYERS; ++l) {
@@ -202,6 +203,17 @@ reno_status reno_create(const reno_params* p, void* hip_stream, reno_ctx** out) 
   const size_t rows = (size_t)c->cap_rows();  // row cap_model stays zero
   A(dalloc(&c->h_a, rows * C, &c->device_bytes));
   A(dalloc(&c->h_b, rows * C, &c->device_bytes));
+  A(dalloc(&c->r_a, rows, &c->device_bytes));
+  A(dalloc(&c->r_b, rows, &c->device_bytes));
+  A(dalloc(&c->w_wfac, (size_t)RENO_MAX_LAYERS * 128, &c->device_bytes));
+  A(dalloc(&c->w_hfac, 2, &c->device_bytes));
+  const bool top_split = top && !c->wide();
+  if (top_split) {
+    A(dalloc(&c->s_c, rows * C, &c->device_bytes));
+    A(dalloc(&c->s_d, rows * C, &c->device_bytes));
+    A(dalloc(&c->r_c, rows, &c->device_bytes));
+    A(dalloc(&c->r_d, rows, &c->device_bytes));
+  }
   if (top) {
     A(dalloc(&c->h_c, rows * C, &c->device_bytes));
     A(dalloc(&c->h_d, rows * C, &c->device_bytes));
@@ -217,13 +229,13 @@ reno_status reno_create(const reno_params* p, void* hip_stream, reno_ctx** out) 
   A(dalloc(&c->d_total, reno::NLEV, &c->device_bytes));
   for (int l = 0; l < (top ? 4 : p->layers); ++l) {
     // first layer of the plain model: its cell table; else per (offset, column
-    // block, lane) fp32 C / 4 floats, bf16x3 8 words
+    // block, lane) the words of C / 4 floats or of the split planes
     const size_t words = !top && l == 0 ? (size_t)8 * 8 * 256 * C
-                                        : (size_t)(top ? c->kvol() : 27) * (C / 16) * 64 * std::max(C / 4, 8);
+                                        : (size_t)(top ? c->kvol() : 27) * (C / 16) * 64 * std::max(C / 4, C == 16 ? 12 : 8);
     A(dalloc(&c->w_conv[l], words, &c->device_bytes));
     A(dalloc(&c->w_bias[l], (size_t)C, &c->device_bytes));
   }
-  A(dalloc(&c->w_head, (size_t)16 * 64 * std::max(C / 4, 8), &c->device_bytes));
+  A(dalloc(&c->w_head, (size_t)16 * 64 * std::max(C / 4, C == 16 ? 12 : 8), &c->device_bytes));
   A(dalloc(&c->w_hbias, 256, &c->device_bytes));
   A(dalloc(&c->w_head_plain, (size_t)C * 256, &c->device_bytes));
   A(dalloc(&c->w_emb, (size_t)16 * C, &c->device_bytes));
@@ -248,6 +260,12 @@ reno_status reno_create(const reno_params* p, void* hip_stream, reno_ctx** out) 
     e = hipMemsetAsync(c->h_c + (size_t)cap_model * C, 0, sizeof(float) * C, c->stream);
   if (e == hipSuccess && top)
     e = hipMemsetAsync(c->h_d + (size_t)cap_model * C, 0, sizeof(float) * C, c->stream);
+  if (e == hipSuccess && top_split)
+    e = hipMemsetAsync(c->s_c + (size_t)cap_model * C, 0, sizeof(float) * C, c->stream);
+  if (e == hipSuccess && top_split)
+    e = hipMemsetAsync(c->s_d + (size_t)cap_model * C, 0, sizeof(float) * C, c->stream);
+  for (float* r : {c->r_a, c->r_b, c->r_c, c->r_d})  // the zero rows' factors
+    if (e == hipSuccess && r) e = hipMemsetAsync(r + cap_model, 0, sizeof(float), c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess) {
     const std::string msg = std::string("init failed: ") + hipGetErrorString(e);

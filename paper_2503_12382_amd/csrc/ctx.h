@@ -78,12 +78,20 @@ struct Ctx {
   uint64_t* d_hreg = nullptr;   // [RENO_MAX_FRAMES + 1] hash region starts of a frame batch
 
   // model buffers (packed model rows: scale b at d_moff[b] ..)
+  // feature rows: fp32, or split into fp16 planes [C hi][C lo] (the same size)
+  // with a factor per row in the r_ array of the same letter
   float* h_a = nullptr;         // [cap_rows][C]
   float* h_b = nullptr;
   float* h_c = nullptr;         // full predictor: X_A = Emb_O[O] of the parent scales (with a zero row)
   float* h_d = nullptr;         // full predictor: X_B of the target scales (with a zero row)
-  int32_t* d_nbr = nullptr;     // [cap_rows][NBR_STRIDE]
-  int32_t* d_perm = nullptr;    // [cap_rows] tile order of the conv layers after the first
+  uint32_t* s_c = nullptr;      // full predictor of k_conv: X_A and X_B as split rows
+  uint32_t* s_d = nullptr;
+  float* r_a = nullptr;         // [cap_rows] each
+  float* r_b = nullptr;
+  float* r_c = nullptr;
+  float* r_d = nullptr;
+  int32_t* d_nbr = nullptr;     // [cap_rows][nbr_stride()]
+  int32_t* d_perm = nullptr;    // [cap_rows] tile order of the streamed-weight conv layers
   float* d_lse = nullptr;       // [cap_model] (two-stage head: stage 1)
   float* d_lse2 = nullptr;      // [cap_model] stage 2 of the two-stage head
   uint8_t* d_s1 = nullptr;      // [cap_model] S1 that stage 2 was evaluated with
@@ -96,6 +104,8 @@ struct Ctx {
   // packed weights (operand layouts of the conv/head kernels)
   float* w_conv[RENO_MAX_LAYERS] = {};  // plain model, layer 0: the cell table [8][8][256][C]
   float* w_bias[RENO_MAX_LAYERS] = {};
+  float* w_wfac = nullptr;      // factors of the split conv weights [layer][128]
+  float* w_hfac = nullptr;      // factors of the split head matrices [2]
   float* w_head = nullptr;
   float* w_hbias = nullptr;
   float* w_head_plain = nullptr;  // [C][256] as given (two-stage: [C][H1 | H2]), for code lengths
@@ -160,6 +170,7 @@ struct Ctx {
   // rows of the feature buffers: the model rows, the zero row cap_model and,
   // for the full predictor, the base scale
   int64_t cap_rows() const { return cap_model + 1 + (top() ? cap_pts : 0); }
+  float* wfac(int l) const { return w_wfac + 128 * l; }
   // buffer that holds the last conv layer's output (h_L), per the ping-pong
   float* hlast() const { return top() ? h_a : ((p.layers & 1) ? h_a : h_b); }
 };

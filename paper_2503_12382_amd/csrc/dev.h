@@ -75,6 +75,15 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_wave_barrier();
 }
 
+// DPP lane moves (CDNA): row_shr:k (0x110 + k) takes the value of lane
+// l - k of the same 16-lane row, row_ror:k (0x120 + k) of lane l - k mod 16
+// of the row, row_bcast:15 (0x142) lane 15 of the previous row, row_bcast:31
+// (0x143) lane 31.  Lanes whose source lies outside are fixed by the callers.
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, false);
+}
+
 // ---- agent-scope relaxed atomics on look-back status words ----
 __device__ __forceinline__ uint32_t ld_status(const uint32_t* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

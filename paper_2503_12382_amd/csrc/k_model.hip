@@ -5,25 +5,22 @@
 // normaliser (Eq. 10).  The first layer, whose input is 11 bits, is a sum of
 // table rows (k_first); the others are matrix products (k_conv).
 //
-// Work unit of the matrix layers: a wavefront owns a tile of 16 consecutive voxels of one scale (in
-// launches of at most 4 tiles per block, a quad of waves shares it).
-// Each layer is computed transposed, out^T[c_out][16] = sum_k W_k^T in_k^T, on
-// fp32 MFMA 16x16x4: the A operand is the offset's weights (staged once per
-// block in LDS, pre-swizzled so each lane reads its operands with 128-bit
-// loads), the B operand is the gathered neighbour rows (each lane loads a
-// contiguous slice of one neighbour row).  Only offsets with at least one
-// occupied neighbour in the tile are issued.  The accumulator layout of the
-// last conv layer is exactly the B operand layout of the head, so the head
-// (16 x 256 logits per tile) runs from registers, followed by a row max / sum
-// of exp over the 64 logits a lane holds and the 4 lanes sharing a voxel.
+// Matrix layers: a wavefront owns 16 or 32 consecutive voxels of one scale (in
+// small launches a quad of waves shares 16).  Each layer is computed
+// transposed, out^T[c_out][16] = sum_k W_k^T in_k^T, on fp16 MFMA 16x16x32
+// with split operands (below): the A operand is the offset's weights (staged
+// once per block in LDS), the B operand the gathered neighbour rows (lane
+// (r, g) loads a contiguous slice of the row of voxel r's neighbour).  Only
+// offsets with at least one occupied neighbour in the tile are issued.  A
+// lane ends with 8 consecutive channels of its voxel, which is exactly the B
+// operand of the head, so the head (16 x 256 logits per tile) runs from
+// registers, followed by a row max / sum of exp over the 64 logits a lane
+// holds and the 4 lanes sharing a voxel.
 // Output-stationary: no atomics, a fixed summation order per voxel (4 offset
-// groups, each chained from zero and folded onto the bias in group order; the
-// softmax normaliser merged per 64-symbol group in group order), so an encoder
-// and a decoder evaluating the same scale get bit-identical results whether a
-// tile is computed by one wave (large launches) or split over a quad of waves
-// by offset group and symbol group (launches of at most 4 tiles per block).
-
-#include <type_traits>
+// groups, each chained from zero and added in group order; the softmax
+// normaliser merged per 64-symbol group in group order), so an encoder and a
+// decoder evaluating the same scale get bit-identical results however a launch
+// shares its tiles among waves.
 
 #include "ctx.h"
 
@@ -31,7 +28,13 @@ namespace reno {
 namespace {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
+typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+
+// fp16 planes of split weights: [hi][lo], and at C = 16, where a gathered row
+// fills one operand, a third one: its sums are so short that the weights' 2^-23
+// would show beside fp32 rounding
+__host__ __device__ constexpr int weight_planes(int C) { return C == 16 ? 3 : 2; }
 
 constexpr int CONV_THREADS = 1024;
 constexpr int CONV_WAVES = CONV_THREADS / 64;
@@ -40,56 +43,129 @@ __device__ __forceinline__ f4 mfma4(float a, float b, f4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-// ---- split-bf16 arithmetic (precision RENO_PREC_BF16X3) ----
-// An fp32 operand x is carried as hi = bf16(x) and lo = bf16(x - hi) (both
-// round to nearest even), so x = hi + lo to about 2^-16 relative; a product
-// is taken as hi*hi + hi*lo + lo*hi (the lo*lo term, ~2^-16 relative, is
-// dropped) on v_mfma_f32_16x16x32_bf16 with fp32 accumulation.  Operands
-// travel as 8 bf16 packed in a uint4 (lane l: row/column l % 16, K slots
-// 8 (l / 16) .. 8 (l / 16) + 7).
-__device__ __forceinline__ f4 mfma_bf(const uint4& a, const uint4& b, f4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8, a), __builtin_bit_cast(bf8, b),
-                                                 c, 0, 0, 0);
+// ---- split-fp16 arithmetic ----
+// A row x of fp32 features is carried as x = f (hi + lo): f the power of two
+// that brings the row's largest entry to [2^14, 2^15), hi = fp16(x / f) and lo
+// = fp16(x / f - hi), both rounded to nearest, 22 bits of every entry within
+// 2^-17 of the row's largest (smaller ones keep an absolute 2^-40 of it).
+// Weights are split the same way, with one factor per output channel (per
+// matrix for a head).  A product is lo*hi + hi*lo + hi*hi on
+// v_mfma_f32_16x16x32_f16 with fp32 accumulation, smallest terms first (lo*lo,
+// 2^-22 of the product, is dropped except at C = 16, where it fits in), 48 cycles per 16 x 16 x 32 block against
+// 256 on fp32 MFMA.  An output sums one fma per offset instead of C / 4
+// chained roundings, so its error against fp64 is about half that of the fp32
+// MFMA chain (one layer of 6 neighbours, C = 32: 0.96e-7 against 1.76e-7
+// relative; a whole 3-layer model's logits: 1.6e-7 against 1.7e-7).
+__device__ __forceinline__ f4 mfma_h(const uint4& a, const uint4& b, f4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, a), __builtin_bit_cast(h8, b), c, 0, 0, 0);
 }
-__device__ __forceinline__ uint32_t bf_bits(__bf16 h) { return __builtin_bit_cast(uint16_t, h); }
-// hi and lo words of two floats (x0 in the low half)
-__device__ __forceinline__ void split2(float x0, float x1, uint32_t& hi, uint32_t& lo) {
-  const __bf16 h0 = (__bf16)x0, h1 = (__bf16)x1;
-  const __bf16 l0 = (__bf16)(x0 - (float)h0), l1 = (__bf16)(x1 - (float)h1);
-  hi = bf_bits(h0) | (bf_bits(h1) << 16);
-  lo = bf_bits(l0) | (bf_bits(l1) << 16);
+__device__ __forceinline__ uint32_t pack_h2(float x0, float x1) {
+  const h2 v = {(_Float16)x0, (_Float16)x1};
+  return __builtin_bit_cast(uint32_t, v);
 }
-// split of 8 floats into packed hi / lo operands
-__device__ __forceinline__ void split8(const float (&x)[8], uint4& hi, uint4& lo) {
-  split2(x[0], x[1], hi.x, lo.x);
-  split2(x[2], x[3], hi.y, lo.y);
-  split2(x[4], x[5], hi.z, lo.z);
-  split2(x[6], x[7], hi.w, lo.w);
+
+// The factor that maps a largest magnitude m to [2^14, 2^15) and its inverse,
+// from the exponent bits (exponents below 14 share the smallest factor).
+__device__ __forceinline__ void split_scale(float m, float& mul, float& fac) {
+  const uint32_t ex = max(__float_as_uint(m) >> 23, 14u);
+  mul = __uint_as_float((268u - ex) << 23);                          // 2^(14 - e)
+  fac = ex > 14u ? __uint_as_float((ex - 14u) << 23) : 0x1p-127f;    // 2^(e - 14)
 }
-// hi*hi + hi*lo + lo*hi accumulated into c
-__device__ __forceinline__ f4 mfma_bf3(const uint4& ah, const uint4& al, const uint4& bh, const uint4& bl, f4 c) {
-  c = mfma_bf(ah, bh, c);
-  c = mfma_bf(ah, bl, c);
-  return mfma_bf(al, bh, c);
+
+// Split of the N entries that a lane holds of a voxel's row, whose other
+// entries are in the lanes STEP and 2 STEP away (16: lanes r + 16 g; 1: lanes 4 r
+// + g): packed words of hi and lo, and the row's factor.  A row with an infinite entry keeps that one at 2^15 against
+// (practically) zero others and gets the factor infinity, so that what it adds
+// to an output is infinite as in fp32.
+template <int N, int STEP = 16>
+__device__ __forceinline__ float row_split(const float (&x)[N], uint32_t (&hi)[N / 2], uint32_t (&lo)[N / 2]) {
+  float m = 0.0f;
+#pragma unroll
+  for (int i = 0; i < N; ++i) m = fmaxf(m, fabsf(x[i]));
+  m = fmaxf(m, __shfl_xor(m, STEP));
+  m = fmaxf(m, __shfl_xor(m, 2 * STEP));
+  float mul, fac;
+  split_scale(m, mul, fac);
+  fac = m == INFINITY ? m : fac;
+#pragma unroll
+  for (int i = 0; i < N; i += 2) {
+    const float v0 = __builtin_amdgcn_fmed3f(x[i] * mul, -32768.0f, 32768.0f);
+    const float v1 = __builtin_amdgcn_fmed3f(x[i + 1] * mul, -32768.0f, 32768.0f);
+    const h2 h = {(_Float16)v0, (_Float16)v1};
+    hi[i / 2] = __builtin_bit_cast(uint32_t, h);
+    lo[i / 2] = pack_h2(v0 - (float)h[0], v1 - (float)h[1]);
+  }
+  return fac;
 }
 
 // ---------------------------------------------------------------------------
-// Weight packing.  Conv layer (C_in -> C): KS = ceil(C_in/4) MFMA k-steps per
-// offset; lane l (g = l/16) feeds input channel ci = g*KS + s at step s and
-// output channel co = 16*cb + l%16.  Packed [27][C/16][64][KSP], KSP = KS
-// rounded up to 4, zero padded (kv offsets: 27, or 125 for a 5x5x5 kernel).
-__global__ void k_pack_conv(const float* __restrict__ W, int c_in, int C, int KS, int KSP, int kv,
-                            float* __restrict__ out) {
-  const int ncb = C / 16;
-  const int total = kv * ncb * 64 * KSP;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += gridDim.x * blockDim.x) {
-    const int s = i % KSP;
-    const int lane = (i / KSP) % 64;
-    const int cb = (i / (KSP * 64)) % ncb;
-    const int k = i / (KSP * 64 * ncb);
-    const int ci = (lane >> 4) * KS + s;
-    const int co = cb * 16 + (lane & 15);
-    out[i] = (s < KS && ci < c_in) ? W[((size_t)k * c_in + ci) * C + co] : 0.0f;
+// Weight packing.
+
+// Largest magnitude over the block's threads (NaN passes through as NaN, so
+// that a broken weight shows in the results instead of vanishing in a maximum).
+__device__ __forceinline__ float block_absmax(float m, bool bad, float* s_m) {
+  for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+  if (__any(bad)) m = NAN;
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) s_m[threadIdx.x >> 6] = m;
+  __syncthreads();
+  float t = 0.0f;
+  bool nan = false;
+  for (unsigned i = 0; i < blockDim.x / 64; ++i) {
+    t = fmaxf(t, s_m[i]);
+    nan = nan || s_m[i] != s_m[i];
+  }
+  return nan ? NAN : t;
+}
+
+// Factors of a weight matrix or channel (split_scale); infinite or NaN weights
+// are kept as they are (factor 1), so they reach the products.
+__device__ __forceinline__ void weight_scale(float m, float& mul, float& fac) {
+  if (m < INFINITY) {
+    split_scale(m, mul, fac);
+  } else {
+    mul = fac = 1.0f;
+  }
+}
+
+// Conv layer W [kv][C][C], one block per output channel co: its factor and the
+// split A operands.  Lane l = (m, g) of column block cb carries output channel
+// co = 8 (m / 4) + 4 cb + m % 4 (C = 32; C = 16: co = m), so that the lane
+// (r, g) that ends with rows 4g .. 4g + 3 of every column block holds
+// consecutive channels of voxel r.  K slot 8g + j: C = 32 input channel 8g +
+// j, planes [hi][lo]; C = 16 the two halves of a gathered row [16 hi][16 lo],
+// planes [W1 | W1], [W2 | W2] and [W3 | W3].  Packed [kv][C/16][plane][64][8] fp16.
+template <int C>
+__global__ void __launch_bounds__(256) k_pack_conv(const float* __restrict__ W, int kv, uint16_t* __restrict__ out,
+                                                   float* __restrict__ fac_out) {
+  constexpr int NCB = C / 16, PL = weight_planes(C);
+  __shared__ float s_m[4];
+  const int co = blockIdx.x, n = kv * C;
+  float m = 0.0f;
+  bool bad = false;
+  for (int i = threadIdx.x; i < n; i += 256) {
+    const float w = W[(size_t)i * C + co];
+    m = fmaxf(m, fabsf(w));
+    bad = bad || w != w;
+  }
+  float mul, fac;
+  weight_scale(block_absmax(m, bad, s_m), mul, fac);
+  if (threadIdx.x == 0) fac_out[co] = fac;
+  const int cb = C == 32 ? (co >> 2) & 1 : 0;
+  const int row = C == 32 ? 4 * (co >> 3) + (co & 3) : co;  // m of the A operand
+  for (int i = threadIdx.x; i < n; i += 256) {
+    const int k = i / C, ci = i % C;
+    const float v = W[(size_t)i * C + co] * mul;
+    uint16_t* o = out + (size_t)(k * NCB + cb) * PL * 64 * 8;
+    const int at = ((ci >> 3) * 16 + row) * 8 + (ci & 7);  // lane (row, ci / 8), slot ci % 8
+    float rest = v;
+#pragma unroll
+    for (int pl = 0; pl < PL; ++pl) {
+      const _Float16 h = (_Float16)rest;
+      rest -= (float)h;
+      o[pl * 64 * 8 + at] = __builtin_bit_cast(uint16_t, h);
+      if (C == 16) o[pl * 64 * 8 + at + 2 * 16 * 8] = __builtin_bit_cast(uint16_t, h);  // groups 2, 3: the row's lo half
+    }
   }
 }
 
@@ -112,70 +188,37 @@ __global__ void k_pack_conv_wide(const float* __restrict__ W, int C, int kv, flo
   }
 }
 
-// Head H [C][NS] (NS = 256, or 16 per stage of the two-stage head): step
-// t = 4*cb + r carries channel c = 16*cb + 4*g + r (the conv accumulator
-// register r of column block cb); lane l carries symbol 16*sb + l%16.
-// Packed [NS/16][64][C/4].
-__global__ void k_pack_head(const float* __restrict__ H, int C, int NS, float* __restrict__ out) {
-  const int KT = C / 4;
-  const int total = NS / 16 * 64 * KT;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += gridDim.x * blockDim.x) {
-    const int t = i % KT;
-    const int lane = (i / KT) % 64;
-    const int sb = i / (KT * 64);
-    const int c = 16 * (t >> 2) + 4 * (lane >> 4) + (t & 3);
-    out[i] = H[(size_t)c * NS + sb * 16 + (lane & 15)];
+// Head H [C][NS] (NS = 256, or 16 per stage of the two-stage head), one block
+// per 16-symbol block sb: the matrix's factor and the split A operands, lane
+// (m, g) carrying symbol 16 sb + m.  C >= 32: K slot 8g + j of chunk ch is
+// channel 32 ch + 8g + j, planes [hi][lo]; C = 16: slots 8g .. 8g + 3 and 8g +
+// 4 .. 8g + 7 both carry channels 4g .. 4g + 3 (a lane's operand is [4 hi][4
+// lo] of them), planes [H1 | H1], [H2 | H2] and [H3 | H3].  Packed
+// [NS/16][max(C/32, 1)][plane][64][8] fp16.
+__global__ void __launch_bounds__(256) k_pack_head(const float* __restrict__ H, int C, int NS,
+                                                   uint16_t* __restrict__ out, float* __restrict__ fac_out) {
+  __shared__ float s_m[4];
+  float m = 0.0f;
+  bool bad = false;
+  for (int i = threadIdx.x; i < C * NS; i += 256) {
+    m = fmaxf(m, fabsf(H[i]));
+    bad = bad || H[i] != H[i];
   }
-}
-
-// bf16x3 conv weights: per (offset k, column block cb, lane (r, g)) the A
-// operand W^T[co = 16cb + r][ci = 8g + j], j = 0..7 (zero for ci >= c_in),
-// as 4 words of hi then 4 words of lo.  Packed [27][C/16][64][8] uint32.
-__global__ void k_pack_conv_bf(const float* __restrict__ W, int c_in, int C, uint32_t* __restrict__ out) {
-  const int ncb = C / 16;
-  const int total = 27 * ncb * 64 * 4;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += gridDim.x * blockDim.x) {
-    const int pr = i % 4;                 // pair of K slots
-    const int lane = (i / 4) % 64;
-    const int cb = (i / 256) % ncb;
-    const int k = i / (256 * ncb);
-    const int co = cb * 16 + (lane & 15);
-    float x[2];
-    for (int h = 0; h < 2; ++h) {
-      const int ci = 8 * (lane >> 4) + 2 * pr + h;
-      x[h] = ci < c_in ? W[((size_t)k * c_in + ci) * C + co] : 0.0f;
+  float mul, fac;
+  weight_scale(block_absmax(m, bad, s_m), mul, fac);
+  if (blockIdx.x == 0 && threadIdx.x == 0) *fac_out = fac;
+  const int nch = C >= 32 ? C / 32 : 1, sb = blockIdx.x, planes = weight_planes(C);
+  for (int i = threadIdx.x; i < nch * 64 * 8; i += 256) {
+    const int j = i & 7, lane = (i >> 3) & 63, ch = i >> 9, g = lane >> 4;
+    const int c = C >= 32 ? 32 * ch + 8 * g + j : 4 * g + (j & 3);
+    const float v = H[(size_t)c * NS + sb * 16 + (lane & 15)] * mul;
+    uint16_t* o = out + (size_t)((sb * nch + ch) * planes) * 64 * 8 + (i & 511);
+    float rest = v;
+    for (int pl = 0; pl < planes; ++pl) {
+      const _Float16 h = (_Float16)rest;
+      rest -= (float)h;
+      o[pl * 64 * 8] = __builtin_bit_cast(uint16_t, h);
     }
-    uint32_t hi, lo;
-    split2(x[0], x[1], hi, lo);
-    uint32_t* o = out + ((size_t)(k * ncb + cb) * 64 + lane) * 8;
-    o[pr] = hi;
-    o[4 + pr] = lo;
-  }
-}
-
-// bf16x3 head H [C][NS]: per symbol block sb and lane (r, g) the A operand
-// H[c(g, j)][16 sb + r] with the K slot -> channel map c(g, j) = 16 (j / 4) +
-// 4g + (j % 4), which is the channel that register j % 4 of accumulator block
-// j / 4 holds in lane (r, g) of the last conv layer (zero beyond C).  Packed
-// [NS/16][64][8] uint32 (hi words, then lo words).
-__global__ void k_pack_head_bf(const float* __restrict__ H, int C, int NS, uint32_t* __restrict__ out) {
-  const int total = NS / 16 * 64 * 4;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += gridDim.x * blockDim.x) {
-    const int pr = i % 4;
-    const int lane = (i / 4) % 64;
-    const int sb = i / 256;
-    const int sym = sb * 16 + (lane & 15);
-    float x[2];
-    for (int h = 0; h < 2; ++h) {
-      const int j = 2 * pr + h;
-      const int c = 16 * (j >> 2) + 4 * (lane >> 4) + (j & 3);
-      x[h] = c < C ? H[(size_t)c * NS + sym] : 0.0f;
-    }
-    uint32_t hi, lo;
-    split2(x[0], x[1], hi, lo);
-    uint32_t* o = out + ((size_t)sb * 64 + lane) * 8;
-    o[pr] = hi;
-    o[4 + pr] = lo;
   }
 }
 
@@ -194,24 +237,65 @@ __global__ void k_put_cols16(const float* __restrict__ H, int C, int col0, float
 }
 
 // ---------------------------------------------------------------------------
-// Two-stage head pieces, shared by the last conv layer (encoder: S1 known)
-// and the decoder's stage-2 kernel, so both produce identical bits.
-//
-// 16 logits of one packed symbol block for a tile: lane (r, g) ends with the
-// logits of symbols 4g .. 4g+3 of voxel r.  h is the tile's feature block in
-// the accumulator layout (lane (r, g), register e of block q: channel
-// 16q + 4g + e of voxel r).
+// Head pieces, shared by the last conv layer, the head on stored features and
+// the decoder's stage-2 kernel, so that all produce identical bits.  A lane
+// (r, g) holds C / 4 features of voxel r: x[8 ch + j] = channel 32 ch + 8g + j
+// (C = 16: x[j] = channel 4g + j).
+
+// B operand of the head from a lane's features.
 template <int C>
-__device__ __forceinline__ f4 head16(const f4* __restrict__ hp, const float* __restrict__ hb, const f4 (&h)[C / 16],
-                                     int g) {
-  f4 zz = *reinterpret_cast<const f4*>(hb + 4 * g);
+struct HeadOp {
+  static constexpr int NCH = C >= 32 ? C / 32 : 1;
+  static constexpr int BLOCK = NCH * weight_planes(C) * 64;  // 16-byte words of one packed 16-symbol block
+  uint4 hi[NCH], lo[C >= 32 ? NCH : 1];
+  float fac;
+  __device__ __forceinline__ void set(const float (&x)[C / 4]) {
+    uint32_t h[C / 8], l[C / 8];
+    fac = row_split<C / 4>(x, h, l);
+    if constexpr (C >= 32) {
 #pragma unroll
-  for (int q = 0; q < C / 16; ++q) {
-    const f4 hv = hp[q];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) zz = mfma4(hv[e], h[q][e], zz);
+      for (int ch = 0; ch < NCH; ++ch) {
+        hi[ch] = make_uint4(h[4 * ch], h[4 * ch + 1], h[4 * ch + 2], h[4 * ch + 3]);
+        lo[ch] = make_uint4(l[4 * ch], l[4 * ch + 1], l[4 * ch + 2], l[4 * ch + 3]);
+      }
+    } else {
+      hi[0] = make_uint4(h[0], h[1], l[0], l[1]);
+    }
   }
-  return zz;
+};
+
+// H^T x of one 16-symbol block in units of the two factors: lane (r, g) ends
+// with symbols 4g .. 4g + 3 of voxel r.  hp: the block's packed operands.
+template <int C>
+__device__ __forceinline__ f4 head_block(const uint4* hp, int lane, const HeadOp<C>& b) {
+  constexpr int NCH = HeadOp<C>::NCH;
+  f4 p = f4{0.0f, 0.0f, 0.0f, 0.0f};
+  if constexpr (C >= 32) {
+#pragma unroll
+    for (int ch = 0; ch < NCH; ++ch) p = mfma_h(hp[(2 * ch + 1) * 64 + lane], b.hi[ch], p);
+#pragma unroll
+    for (int ch = 0; ch < NCH; ++ch) p = mfma_h(hp[2 * ch * 64 + lane], b.lo[ch], p);
+#pragma unroll
+    for (int ch = 0; ch < NCH; ++ch) p = mfma_h(hp[2 * ch * 64 + lane], b.hi[ch], p);
+  } else {
+#pragma unroll
+    for (int pl = weight_planes(C) - 1; pl >= 0; --pl) p = mfma_h(hp[pl * 64 + lane], b.hi[0], p);
+  }
+  return p;
+}
+
+// 16 logits of one stage of the two-stage head.
+template <int C>
+__device__ __forceinline__ f4 head16(const uint4* hp, float hfac, const float* __restrict__ hb,
+                                     const float (&x)[C / 4], int lane, int g) {
+  HeadOp<C> b;
+  b.set(x);
+  const f4 p = head_block<C>(hp, lane, b);
+  const float f = b.fac * hfac;
+  f4 z = *reinterpret_cast<const f4*>(hb + 4 * g);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) z[e] = fmaf(p[e], f, z[e]);
+  return z;
 }
 
 // Natural-log normaliser of the 16 logits spread over lanes r, r+16, r+32, r+48.
@@ -225,34 +309,27 @@ __device__ __forceinline__ float lse16(const f4& z) {
   return m + __logf(s);
 }
 
-// B operand of the bf16x3 head from the accumulator layout (K slot j of lane
-// (r, g) = register j % 4 of block j / 4; zero beyond C).
+// The lane's C / 4 entries of a row of C floats, in the order above.
 template <int C>
-__device__ __forceinline__ void head_operand_bf(const f4 (&h)[C / 16], uint4& hi, uint4& lo) {
-  float x[8];
+__device__ __forceinline__ void load_row(const float* __restrict__ row, int g, float (&x)[C / 4]) {
+  constexpr int Q = C >= 32 ? 2 : 1;  // f4 words per chunk
 #pragma unroll
-  for (int j = 0; j < 8; ++j) x[j] = (j / 4 < C / 16) ? h[j / 4 < C / 16 ? j / 4 : 0][j % 4] : 0.0f;
-  split8(x, hi, lo);
+  for (int ch = 0; ch < (C >= 32 ? C / 32 : 1); ++ch)
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const f4 t = *reinterpret_cast<const f4*>(row + 32 * ch + 4 * Q * g + 4 * q);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[8 * ch + 4 * q + e] = t[e];
+    }
 }
 
-// bf16x3 version of head16: hp points at this lane's packed words of the block.
+// x + the same entries of another row (Emb(S1), Emb_D).
 template <int C>
-__device__ __forceinline__ f4 head16_bf(const uint4* __restrict__ hp, const float* __restrict__ hb,
-                                        const uint4& bh, const uint4& bl, int g) {
-  f4 zz = *reinterpret_cast<const f4*>(hb + 4 * g);
-  return mfma_bf3(hp[0], hp[1], bh, bl, zz);
-}
-
-// h + Emb(S1) in the accumulator layout (emb_row = emb_s1 + S1 * C).
-template <int C>
-__device__ __forceinline__ void add_emb(const f4 (&h)[C / 16], const float* __restrict__ emb_row, int g,
-                                        f4 (&out)[C / 16]) {
+__device__ __forceinline__ void add_row(const float (&x)[C / 4], const float* __restrict__ row, int g,
+                                        float (&out)[C / 4]) {
+  load_row<C>(row, g, out);
 #pragma unroll
-  for (int q = 0; q < C / 16; ++q) {
-    const f4 e = *reinterpret_cast<const f4*>(emb_row + 16 * q + 4 * g);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) out[q][i] = h[q][i] + e[i];
-  }
+  for (int i = 0; i < C / 4; ++i) out[i] = x[i] + out[i];
 }
 
 __global__ void k_copy_f32(const float* __restrict__ src, float* __restrict__ dst, int n) {
@@ -266,12 +343,17 @@ struct ConvArgs {
   const int32_t* count;
   const int32_t* moff;
   int64_t cap_pts, cap_model;
-  const int32_t* nbr;     // [cap_model][NBR_STRIDE], entries 27.. are -1
-  const float* h_in;      // [cap_model + 1][C_in], row cap_model all zero
-  float* h_out;           // [cap_model][C]
+  const int32_t* nbr;     // neighbour map [rows][stride]
+  const float* h_in;      // conv input: split rows (k_conv), fp32 rows (k_convw, k_headw); row cap_model all zero
+  const float* r_in;      // factors of the split rows
+  float* h_out;           // fp32 output rows [rows][C], or NULL
+  uint32_t* s_out;        // split output rows, or NULL
+  float* r_out;           // their factors
   const float* w;         // packed conv weights
+  const float* wfac;      // their factors [C] (k_conv)
   const float* bias;      // [C]
-  const float* hw;        // packed head weights (last layer)
+  const uint4* hw;        // packed head weights (last layer)
+  const float* hfac;      // their factors: one per head matrix
   const float* hb;        // [256]
   float* lse;             // [cap_model]
   float* logits;          // optional [rows][256] (two-stage: [rows][32]), row = packed row - moff[b_lo]
@@ -281,7 +363,7 @@ struct ConvArgs {
   const uint8_t* s1_code; // codes of the per-scale regions (S1 = O & 15), or NULL: stage 1 only
   float* lse2;            // [cap_model]
   uint8_t* s1_out;        // [cap_model] the S1 stage 2 used
-  const int32_t* perm;    // optional tile order: tile slot -> packed row
+  const int32_t* perm;    // k_convw: tile order, tile slot -> packed row
   // full predictor
   const float* res;       // residual input added before the ReLU (same rows as h_out), or NULL
   int b_ext;              // scale whose rows live past the zero row (the base scale), or -1
@@ -290,6 +372,8 @@ struct ConvArgs {
   // replication + octant embedding fused into the epilogue (Eqs. 7-8): each
   // voxel's result F, plus Emb_D[delta], goes to the rows of its children
   float* xb;              // child rows' input X_B (rows of scale b + 1), or NULL
+  uint32_t* xb_s;         // X_B as split rows (k_conv)
+  float* xb_r;            // their factors
   const float* emb_d;     // [8][C]
   const uint8_t* code;    // per-scale regions: O_b
   const int32_t* fc;      // per-scale regions: first child row in V_{b+1}
@@ -316,38 +400,6 @@ __device__ __forceinline__ void scale_span(const RowMap& m, int b, int64_t& mo, 
   } else {
     mo = m.moff[b];
     if (mo + n > m.cap_model) n = 0;
-  }
-}
-
-// Entry j (wave-uniform) of the 8 neighbour rows a lane holds in two int4,
-// as a branch-free select tree.
-__device__ __forceinline__ int32_t pick8(const int4& lo, const int4& hi, int j) {
-  const bool b0 = j & 1, b1 = j & 2, b2 = j & 4;
-  const int32_t l01 = b0 ? lo.y : lo.x, l23 = b0 ? lo.w : lo.z;
-  const int32_t h01 = b0 ? hi.y : hi.x, h23 = b0 ? hi.w : hi.z;
-  const int32_t l = b1 ? l23 : l01, h = b1 ? h23 : h01;
-  return b2 ? h : l;
-}
-
-// Copies n16 16-byte words from global memory to LDS, all loads of a thread
-// issued before its stores.
-template <int N16, int THREADS>
-__device__ __forceinline__ void stage_lds(const f4* __restrict__ src, f4* dst, int tid) {
-  constexpr int PER = (N16 + THREADS - 1) / THREADS;
-  constexpr int BATCH = PER < 12 ? PER : 12;
-#pragma unroll
-  for (int b0 = 0; b0 < PER; b0 += BATCH) {
-    f4 v[BATCH];
-#pragma unroll
-    for (int i = 0; i < BATCH; ++i) {
-      const int idx = (b0 + i) * THREADS + tid;
-      if (b0 + i < PER && idx < N16) v[i] = src[idx];
-    }
-#pragma unroll
-    for (int i = 0; i < BATCH; ++i) {
-      const int idx = (b0 + i) * THREADS + tid;
-      if (b0 + i < PER && idx < N16) dst[idx] = v[i];
-    }
   }
 }
 
@@ -442,6 +494,32 @@ __device__ __forceinline__ void find_cells(const CellArgs& a, int s, uint64_t fr
 // unpacked; a step off the grid leaves the probe empty, and every neighbour
 // in such a cell reads as absent, so the offsets need no bounds of their own.
 
+// OR over each row of 16 lanes.
+__device__ __forceinline__ uint32_t or_row16(uint32_t v) {
+  v |= dpp<0x128>(v);  // row_ror:8, 4, 2, 1
+  v |= dpp<0x124>(v);
+  v |= dpp<0x122>(v);
+  v |= dpp<0x121>(v);
+  return v;
+}
+
+// Stores a voxel's row of the 3x3x3 neighbour map as k_conv reads it: lane 4r + g
+// holds offsets 8g .. 8g + 7 of voxel r; entry MAP_MASK of the row's padding
+// takes the mask of its occupied offsets.
+constexpr int MAP_MASK = 27;
+__device__ __forceinline__ void store_map(int32_t* nbr, int64_t prow, bool valid, int g, const int32_t (&nb)[8]) {
+  uint32_t own = 0;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) own |= (nb[j] >= 0 ? 1u : 0u) << j;
+  own <<= 8 * g;
+  own |= (uint32_t)__shfl_xor((int)own, 1);
+  own |= (uint32_t)__shfl_xor((int)own, 2);
+  if (!valid) return;
+  int4* dst = reinterpret_cast<int4*>(nbr + prow * NBR_STRIDE + 8 * g);
+  dst[0] = make_int4(nb[0], nb[1], nb[2], g == MAP_MASK / 8 ? (int)own : nb[3]);
+  dst[1] = make_int4(nb[4], nb[5], nb[6], nb[7]);
+}
+
 // Per entry slot j of the 8 a lane holds, the four lane groups' offsets
 // k = 8g + j packed one byte each: bit 6 the offset exists (k < 27), bits 3..5
 // the axes it moves up, bits 0..2 the axes it moves at all (k = dx+1 +
@@ -508,50 +586,48 @@ __device__ __forceinline__ void parent_cell_rows(uint64_t kf, int b, int g, cons
 constexpr float LOG2E_F = 1.4426950408889634f;
 
 // One group of 64 symbols of the 256-way head (symbol blocks 4 grp .. 4 grp
-// + 3, 16 symbols each): logits z = H^T h + b on MFMA from the accumulator
-// layout of h, stored when requested, and the group's normaliser terms per
-// lane: gm = the max of the lane's 16 logits, part = the sum of exp(z - gm).
-template <int C, bool BF>
-__device__ __forceinline__ void head_group(const ConvArgs& a, const f4 (&acc)[C / 16], const float* s_h,
-                                           const float* hb, int lane, int g, bool valid, int64_t prow,
-                                           int64_t mo_first, int grp, float& gm, float& part) {
-  constexpr int KT = C / 4;
-  float* lo = (a.logits && valid) ? a.logits + (prow - mo_first) * 256 + 4 * g : nullptr;
-  uint4 bh = make_uint4(0, 0, 0, 0), bl = bh;
-  if constexpr (BF) head_operand_bf<C>(acc, bh, bl);
-  f4 zz[4];
+// + 3, 16 symbols each) for NT tiles: logits z = H^T x + b, stored when
+// requested (lo[t], or NULL), and the group's normaliser terms per lane: gm =
+// the max of the lane's 16 logits, part = the sum of exp(z - gm).
+template <int C, int NT>
+__device__ __forceinline__ void head_group(const uint4* s_h, const float* __restrict__ hb, float hfac,
+                                           const HeadOp<C> (&op)[NT], float* const (&lo)[NT], int lane, int g,
+                                           int grp, float (&gm)[NT], float (&part)[NT]) {
+  f4 zz[NT][4];
 #pragma unroll
   for (int q4 = 0; q4 < 4; ++q4) {
     const int sb = grp * 4 + q4;
-    if constexpr (BF) {
-      zz[q4] = head16_bf<C>(reinterpret_cast<const uint4*>(s_h) + (sb * 64 + lane) * 2, hb + 16 * sb, bh, bl, g);
-    } else {
-      zz[q4] = *reinterpret_cast<const f4*>(hb + 16 * sb + 4 * g);
-      const f4* hp = reinterpret_cast<const f4*>(s_h + (sb * 64 + lane) * KT);
+    const f4 bias = *reinterpret_cast<const f4*>(hb + 16 * sb + 4 * g);
+    const uint4* hp = s_h + (size_t)sb * HeadOp<C>::BLOCK;
 #pragma unroll
-      for (int q = 0; q < KT / 4; ++q) {
-        const f4 hv = hp[q];
+    for (int t = 0; t < NT; ++t) {
+      const f4 p = head_block<C>(hp, lane, op[t]);
+      const float f = op[t].fac * hfac;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) zz[q4] = mfma4(hv[e], acc[q][e], zz[q4]);
-      }
+      for (int e = 0; e < 4; ++e) zz[t][q4][e] = fmaf(p[e], f, bias[e]);
     }
   }
-  gm = zz[0][0];
 #pragma unroll
-  for (int q4 = 0; q4 < 4; ++q4)
+  for (int t = 0; t < NT; ++t) {
+    float mx = zz[t][0][0];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) gm = fmaxf(gm, zz[q4][e]);
-  // exp(z - gm) as 2^(z log2(e) - gm log2(e)): one fused multiply-add per term
-  const float gml = gm * LOG2E_F;
-  part = __builtin_amdgcn_exp2f(fmaf(zz[0][0], LOG2E_F, -gml));
+    for (int q4 = 0; q4 < 4; ++q4)
 #pragma unroll
-  for (int q4 = 0; q4 < 4; ++q4)
+      for (int e = 0; e < 4; ++e) mx = fmaxf(mx, zz[t][q4][e]);
+    // exp(z - gm) as 2^(z log2(e) - gm log2(e)): one fused multiply-add per term
+    const float ml = mx * LOG2E_F;
+    float s = __builtin_amdgcn_exp2f(fmaf(zz[t][0][0], LOG2E_F, -ml));
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (q4 || e) part += __builtin_amdgcn_exp2f(fmaf(zz[q4][e], LOG2E_F, -gml));
-  if (lo) {
+    for (int q4 = 0; q4 < 4; ++q4)
 #pragma unroll
-    for (int q4 = 0; q4 < 4; ++q4) *reinterpret_cast<f4*>(lo + 16 * (grp * 4 + q4)) = zz[q4];
+      for (int e = 0; e < 4; ++e)
+        if (q4 || e) s += __builtin_amdgcn_exp2f(fmaf(zz[t][q4][e], LOG2E_F, -ml));
+    gm[t] = mx;
+    part[t] = s;
+    if (lo[t]) {
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) *reinterpret_cast<f4*>(lo[t] + 16 * (grp * 4 + q4)) = zz[t][q4];
+    }
   }
 }
 
@@ -576,67 +652,68 @@ __device__ __forceinline__ void lse_finish(const ConvArgs& a, float m, float ssu
   if (valid && g == 0) a.lse[prow] = m + __logf(ssum);
 }
 
-// Head of the last conv layer's features h (the conv accumulators of a tile:
-// lane (r, g) holds channels 16 cb + 4 g .. + 3 of voxel r) in registers:
-// the one-stage 256-way head with its softmax normaliser (Eq. 10), or the
-// two-stage head (Eqs. 11-13).  Writes lse (lse2, S1) at row prow and, when
-// requested, the logits at row prow - mo_first.
-template <int C, bool TWO, bool BF>
-__device__ __forceinline__ void head_epilogue(const ConvArgs& a, const f4 (&acc)[C / 16], const float* s_h, int lane,
-                                              int g, bool valid, int64_t prow, int64_t mo, int64_t lvb,
-                                              int64_t mo_first) {
-  constexpr int KT = C / 4;
-  constexpr int NCB = C / 16;
-  if constexpr (TWO) {
-    // ---- two-stage head (Eqs. 11-13): stage 1 over S1; stage 2 over S2
-    // with h + Emb(S1) when the codes of the scale are known
-    const f4* hp = reinterpret_cast<const f4*>(s_h) + lane * (KT / 4);
-    const uint4* hpb = reinterpret_cast<const uint4*>(s_h) + lane * 2;
-    f4 z1;
-    if constexpr (BF) {
-      uint4 bh, bl;
-      head_operand_bf<C>(acc, bh, bl);
-      z1 = head16_bf<C>(hpb, a.hb, bh, bl, g);
-    } else {
-      z1 = head16<C>(hp, a.hb, acc, g);
-    }
-    const float l1 = lse16(z1);
-    if (valid && g == 0) a.lse[prow] = l1;
-    float* lo = (a.logits && valid) ? a.logits + (prow - mo_first) * 32 + 4 * g : nullptr;
-    if (lo) *reinterpret_cast<f4*>(lo) = z1;
-    if (a.s1_code) {
-      const int s1 = a.s1_code[lvb + (prow - mo)] & 15;
-      f4 h2[NCB];
-      add_emb<C>(acc, a.emb + s1 * C, g, h2);
-      f4 z2;
-      if constexpr (BF) {
-        uint4 bh, bl;
-        head_operand_bf<C>(h2, bh, bl);
-        z2 = head16_bf<C>(hpb + 64 * 2, a.hb + 16, bh, bl, g);
-      } else {
-        z2 = head16<C>(hp + 64 * (KT / 4), a.hb + 16, h2, g);
-      }
-      const float l2 = lse16(z2);
-      if (valid && g == 0) {
-        a.lse2[prow] = l2;
-        a.s1_out[prow] = (uint8_t)s1;
-      }
-      if (lo) *reinterpret_cast<f4*>(lo + 16) = z2;
-    }
+// A tile as the epilogue and the head need it (per lane: voxel r).
+struct TileRef {
+  int b;
+  int64_t mo, lvb, prow;
+  bool valid;
+};
+
+// The two-stage head (Eqs. 11-13) on a tile's features: stage 1 over S1; stage
+// 2 over S2 with x + Emb(S1) when the codes of the scale are known.
+template <int C>
+__device__ __forceinline__ void head_two(const ConvArgs& a, const float (&x)[C / 4], const uint4* s_h, int lane, int g,
+                                         const TileRef& tr, int64_t mo_first) {
+  constexpr int BLK = HeadOp<C>::BLOCK;
+  const f4 z1 = head16<C>(s_h, a.hfac[0], a.hb, x, lane, g);
+  const float l1 = lse16(z1);
+  if (tr.valid && g == 0) a.lse[tr.prow] = l1;
+  float* lo = (a.logits && tr.valid) ? a.logits + (tr.prow - mo_first) * 32 + 4 * g : nullptr;
+  if (lo) *reinterpret_cast<f4*>(lo) = z1;
+  if (!a.s1_code) return;
+  const int s1 = a.s1_code[tr.lvb + (tr.prow - tr.mo)] & 15;
+  float x2[C / 4];
+  add_row<C>(x, a.emb + s1 * C, g, x2);
+  const f4 z2 = head16<C>(s_h + BLK, a.hfac[1], a.hb + 16, x2, lane, g);
+  const float l2 = lse16(z2);
+  if (tr.valid && g == 0) {
+    a.lse2[tr.prow] = l2;
+    a.s1_out[tr.prow] = (uint8_t)s1;
   }
-  if constexpr (!TWO) {
-    // ---- head: z^T[256][16] = H^T h^T with the conv accumulators as the B
-    // operand, 64 symbols (4 blocks of 16) per group; the normaliser is
-    // combined group by group in a fixed order (head_group / lse_merge), the
-    // same order a tile split over several waves uses
-    float m = -INFINITY, ssum = 0.0f;
+  if (lo) *reinterpret_cast<f4*>(lo + 16) = z2;
+}
+
+// The head on the features of NT tiles in registers: the one-stage 256-way
+// head with its softmax normaliser (Eq. 10), or the two-stage head.  Writes
+// lse (lse2, S1) at the tiles' rows and, when requested, the logits at row
+// prow - mo_first.  The NT tiles share the reads of the head's weights.
+template <int C, bool TWO, int NT>
+__device__ __forceinline__ void head_epilogue(const ConvArgs& a, const float (&x)[NT][C / 4], const uint4* s_h,
+                                              int lane, int g, const TileRef (&tr)[NT], int64_t mo_first) {
+  if constexpr (TWO) {
+#pragma unroll
+    for (int t = 0; t < NT; ++t) head_two<C>(a, x[t], s_h, lane, g, tr[t], mo_first);
+  } else {
+    HeadOp<C> op[NT];
+    float* lo[NT];
+    float m[NT], ssum[NT];
+    const float hfac = a.hfac[0];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      op[t].set(x[t]);
+      lo[t] = (a.logits && tr[t].valid) ? a.logits + (tr[t].prow - mo_first) * 256 + 4 * g : nullptr;
+      m[t] = -INFINITY;
+      ssum[t] = 0.0f;
+    }
 #pragma unroll 1
     for (int grp = 0; grp < 4; ++grp) {
-      float gm, part;
-      head_group<C, BF>(a, acc, s_h, a.hb, lane, g, valid, prow, mo_first, grp, gm, part);
-      lse_merge(m, ssum, gm, part);
+      float gm[NT], part[NT];
+      head_group<C, NT>(s_h, a.hb, hfac, op, lo, lane, g, grp, gm, part);
+#pragma unroll
+      for (int t = 0; t < NT; ++t) lse_merge(m[t], ssum[t], gm[t], part[t]);
     }
-    lse_finish(a, m, ssum, g, valid, prow);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) lse_finish(a, m[t], ssum[t], g, tr[t].valid, tr[t].prow);
   }
 }
 
@@ -658,402 +735,409 @@ __device__ __forceinline__ uint32_t group_offsets(int i) {
   return ((1u << hi) - 1u) & ~((1u << lo) - 1u);
 }
 
-template <int C, bool LAST, bool TWO, bool BF>
-__global__ void __launch_bounds__(CONV_THREADS) k_conv(ConvArgs a) {
-  constexpr int NCB = C / 16;
-  constexpr int KS = C / 4;
-  constexpr int KSP = KS;
-  constexpr int KT = C / 4;
-  // packed weights per (offset, column block, lane): fp32 KSP floats, bf16x3 8 words
-  constexpr int WSZ = 27 * NCB * 64 * (BF ? 8 : KSP);
-  constexpr int HSZ = LAST ? (TWO ? 2 : 16) * 64 * (BF ? 8 : KT) : 4;
-  constexpr int PCH = 3;               // offsets per pipeline stage
-  struct Gath {                        // one gathered neighbour slice, fp32: KS channels
-    f4 v[KSP / 4];
-  };
-  struct GathB {                       // bf16x3: channels 8g .. 8g+7
-    uint4 hi, lo;
-  };
-  using G = typename std::conditional<BF, GathB, Gath>::type;
-  __shared__ __attribute__((aligned(16))) float s_w[WSZ];
-  __shared__ __attribute__((aligned(16))) float s_h[HSZ];
-  __shared__ int64_t s_tpre[NLEV + 1];
-  __shared__ int64_t s_nv[NLEV];   // N_b of the launch's scales
-  __shared__ int64_t s_mo[NLEV];   // first packed row of each scale
-  __shared__ int s_next;           // next dynamically handed-out tile slot of this block
+// Split row of C channels: [C fp16 hi][C fp16 lo], C 32-bit words.  The slice a
+// lane feeds: C = 32 channels 8g .. 8g + 7 of both planes; C = 16 the 8 halves
+// 8g .. 8g + 7 of the whole row (K slots of k_pack_conv).
+template <int C>
+struct SplitRow {
+  uint4 hi, lo;  // C = 16: hi alone
+  float fac;
+};
 
-  // the wave index through a lane read: the compiler then keeps the tile loop,
+// Stores a lane's entries of a split row and, from lane group 0, its factor.
+template <int C, int STEP = 16>
+__device__ __forceinline__ void store_split(const float (&x)[C / 4], int g, uint32_t* row, float* fac) {
+  uint32_t h[C / 8], l[C / 8];
+  const float f = row_split<C / 4, STEP>(x, h, l);
+  if constexpr (C == 32) {
+    *reinterpret_cast<uint4*>(row + 4 * g) = make_uint4(h[0], h[1], h[2], h[3]);
+    *reinterpret_cast<uint4*>(row + 16 + 4 * g) = make_uint4(l[0], l[1], l[2], l[3]);
+  } else {
+    *reinterpret_cast<uint2*>(row + 2 * g) = make_uint2(h[0], h[1]);
+    *reinterpret_cast<uint2*>(row + 8 + 2 * g) = make_uint2(l[0], l[1]);
+  }
+  if (g == 0) *fac = f;
+}
+
+// Out-of-range byte offset of a buffer load, which then returns zeros without
+// an access; the row's 128-byte (64) and 4-byte offsets derived from it stay
+// out of range of a scale of up to CONV_BUF_ROWS rows and do not wrap.
+constexpr uint32_t NO_ROW = 0xFFFFFF00u;
+constexpr int64_t CONV_BUF_ROWS = (int64_t(1) << 25) - 8;
+
+__device__ __forceinline__ uint4 buf_load16(__amdgpu_buffer_rsrc_t rs, uint32_t off) {
+  return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, 0, 0));
+}
+__device__ __forceinline__ float buf_load4(__amdgpu_buffer_rsrc_t rs, uint32_t off) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)off, 0, 0));
+}
+
+// Conv sums of a tile of 16 voxels (lane (r, g): row row0 + r of a scale of n
+// rows whose first packed row is mo), in units of the weights' factors: all 4
+// offset groups added in group order (grp < 0), or one group's sum alone (a
+// wave of a quad).  The tile's neighbours go to tbl (LDS of this wave,
+// [offset][16], as byte offsets of their rows in the scale), where a lane
+// reads the row of any offset; with a table of 16 offsets only, the second
+// half replaces the first when the walk reaches it.  The tile's occupied
+// offsets are walked in ascending order, PCH at a time, the next PCH gathered
+// before the products of the current ones.  Each offset's products are chained
+// on MFMA from zero and added with the neighbour row's factor by one fma.
+//
+// What bounds it (counters of the 14-bit scan's middle layer): the L1 access
+// rate and the LDS.  In the operand's layout 16 consecutive lanes name 16 rows,
+// so a gather costs one L1 access per lane: with both planes and the factor
+// loaded that way, 28 M accesses, the L1 was busy for most of the launch (57
+// us).  Absent rows (60 % of those named) are therefore out-of-range buffer
+// loads, which return zeros without an access and, unlike skipped loads, keep
+// the compiler's wait counts exact; and the hi plane goes through 4 lane
+// exchanges (LDS) instead.  Exchanging both planes moves the bound to the LDS,
+// none back to the L1: 47 and 50 us against 43.  8 waves with 8 to 16 rows
+// gathered ahead each: 54 us.  Tiles sorted by neighbourhood, which halved the
+// fp32 MFMA work, no longer pay for their pass.
+//
+// BIG: a scale may hold more than CONV_BUF_ROWS rows (4 GB); rows are then
+// read through 64-bit addresses and absent ones from the zero row.
+template <int C, int TBL, bool BIG>
+__device__ __forceinline__ void conv_sum(const ConvArgs& a, const uint4* s_w, uint32_t (*tbl)[16], int lane, int mo,
+                                         int n, int row0, int grp, f4 (&out)[C / 16]) {
+  constexpr int NCB = C / 16, PL = weight_planes(C);
+  constexpr int PCH = 3;
+  constexpr uint32_t ROWB = 4 * C;  // bytes of a split row
+  const int r = lane & 15, g = lane >> 4;
+  const auto rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.h_in) + (int64_t)mo * C, 0,
+                                                      BIG ? 0 : (int)((uint32_t)n * ROWB), 0x00027000);
+  const auto facs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.r_in) + mo, 0, BIG ? 0 : n * 4, 0x00027000);
+  // map row of voxel lane / 4, entries 4p .. 4p + 3 and 16 + 4p .. of its piece p =
+  // lane % 4 (the 4 lanes of a voxel read 64 consecutive bytes)
+  const bool have4 = row0 + (lane >> 2) < n;
+  uint32_t nb[8], offs;
+  {
+    const int4* src =
+        reinterpret_cast<const int4*>(a.nbr + (int64_t)(mo + (have4 ? row0 + (lane >> 2) : 0)) * NBR_STRIDE) + (lane & 3);
+    const int4 lo = src[0], hi = src[4];
+    const int32_t e8[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+    // the union of the 16 voxels' masks (entry 27, the last of piece 2's second half)
+    uint32_t m = have4 && (lane & 3) == 2 ? (uint32_t)hi.w : 0u;
+    m = or_row16(m);
+    offs = (uint32_t)(__builtin_amdgcn_readlane((int)m, 0) | __builtin_amdgcn_readlane((int)m, 16) |
+                      __builtin_amdgcn_readlane((int)m, 32) | __builtin_amdgcn_readlane((int)m, 48));
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const bool has = have4 && e8[j] >= 0;
+      if constexpr (BIG) nb[j] = has ? (uint32_t)(mo + e8[j]) : (uint32_t)a.cap_model;
+      else nb[j] = has ? (uint32_t)e8[j] * ROWB : NO_ROW;
+    }
+  }
+  if (grp >= 0) offs &= group_offsets(grp);
+  auto table = [&](int half) {
+    wave_lds_fence();  // earlier reads of the table are done
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (TBL == 32 || (j >> 2) == half) tbl[(16 * (j >> 2) + 4 * (lane & 3) + (j & 3)) % TBL][lane >> 2] = nb[j];
+    wave_lds_fence();
+  };
+  table(0);
+  int next_half = TBL == 32 ? 32 : 16;  // first offset not in the table
+  f4 acc[NCB];
+#pragma unroll
+  for (int cb = 0; cb < NCB; ++cb) out[cb] = acc[cb] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+  int gcur = grp >= 0 ? grp : 0;  // group whose sum acc holds
+  auto fold = [&]() {
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb) {
+      out[cb] += acc[cb];
+      acc[cb] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+    ++gcur;
+  };
+  // The next PCH offsets (-1 beyond the last) and the gathers of their rows.
+  // The hi plane (C = 16: the row) and the factor are loaded by lane 4v + p,
+  // piece p of voxel v's neighbour: one L1 access per row; the lo plane by lane
+  // (r, g) as the operand has it.
+  auto gather = [&](int (&ks)[PCH], SplitRow<C> (&x)[PCH]) {
+    constexpr uint32_t NONE = NO_ROW;
+    uint32_t at[PCH], at4[PCH];
+#pragma unroll
+    for (int c = 0; c < PCH; ++c) {
+      ks[c] = offs ? __builtin_ctz(offs) : -1;
+      offs &= offs ? offs - 1u : 0u;
+      if (TBL < 32 && ks[c] >= next_half) {  // uniform
+        table(1);
+        next_half = 32;
+      }
+      const uint32_t (*t)[16] = tbl + (ks[c] & 31) % TBL;
+      const uint32_t none = BIG ? (uint32_t)a.cap_model : NONE;
+      at4[c] = ks[c] < 0 ? none : (*t)[lane >> 2];
+      if constexpr (C == 32) at[c] = ks[c] < 0 ? none : (*t)[r];
+    }
+#pragma unroll
+    for (int c = 0; c < PCH; ++c) {
+      if constexpr (BIG) {
+        x[c].hi = reinterpret_cast<const uint4*>(a.h_in + (int64_t)at4[c] * C)[lane & 3];
+        if constexpr (C == 32) x[c].lo = reinterpret_cast<const uint4*>(a.h_in + (int64_t)at[c] * C)[4 + g];
+        x[c].fac = a.r_in[at4[c]];
+      } else {
+        x[c].hi = buf_load16(rows, at4[c] + 16u * (lane & 3));
+        if constexpr (C == 32) x[c].lo = buf_load16(rows, at[c] + 64u + 16u * g);
+        x[c].fac = buf_load4(facs, at4[c] / C);
+      }
+    }
+  };
+  const int from = 4 * (4 * r + g);  // lane 4r + g, for lane (r, g) = r + 16g
+  auto exchange = [&](uint32_t v, int at) { return (uint32_t)__builtin_amdgcn_ds_bpermute(at, (int)v); };
+  auto mma = [&](const int (&ks)[PCH], const SplitRow<C> (&x)[PCH]) {
+#pragma unroll
+    for (int c = 0; c < PCH; ++c) {
+      const int k = ks[c];
+      if (k < 0) break;
+      while (k >= (gcur < 3 ? 7 * (gcur + 1) : 27)) fold();
+      uint4 wv[PL][NCB];
+#pragma unroll
+      for (int pl = 0; pl < PL; ++pl)
+#pragma unroll
+        for (int cb = 0; cb < NCB; ++cb) wv[pl][cb] = s_w[((k * NCB + cb) * PL + pl) * 64 + lane];
+      const uint4 hi = make_uint4(exchange(x[c].hi.x, from), exchange(x[c].hi.y, from), exchange(x[c].hi.z, from),
+                                  exchange(x[c].hi.w, from));
+      const float fac = __uint_as_float(exchange(__float_as_uint(x[c].fac), 16 * r));
+      f4 p[NCB];
+#pragma unroll
+      for (int cb = 0; cb < NCB; ++cb) p[cb] = mfma_h(wv[PL - 1][cb], hi, f4{0.0f, 0.0f, 0.0f, 0.0f});
+#pragma unroll
+      for (int cb = 0; cb < NCB; ++cb) p[cb] = mfma_h(C == 32 ? wv[0][cb] : wv[1][cb], C == 32 ? x[c].lo : hi, p[cb]);
+#pragma unroll
+      for (int cb = 0; cb < NCB; ++cb) p[cb] = mfma_h(wv[0][cb], hi, p[cb]);
+#pragma unroll
+      for (int cb = 0; cb < NCB; ++cb)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[cb][e] = fmaf(p[cb][e], fac, acc[cb][e]);
+    }
+  };
+  int kA[PCH], kB[PCH];
+  SplitRow<C> xA[PCH], xB[PCH];
+  gather(kA, xA);
+  while (true) {
+    gather(kB, xB);
+    mma(kA, xA);
+    if (kB[0] < 0) break;
+    gather(kA, xA);
+    mma(kB, xB);
+    if (kA[0] < 0) break;
+  }
+  if (grp < 0) {
+    while (gcur < 4) fold();  // every group added, also the empty ones
+  } else {
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb) out[cb] = acc[cb];
+  }
+}
+
+// Bias, residual, ReLU, the children's X_B rows (full predictor) and the output
+// rows of a tile from its conv sums: x ends with the lane's features.
+template <int C, bool XB>
+__device__ __forceinline__ void conv_epilogue(const ConvArgs& a, const f4 (&sum)[C / 16], int g, const TileRef& tr,
+                                              float (&x)[C / 4]) {
+  constexpr int N = C / 4;
+  float wf[N], bs[N];
+  load_row<C>(a.wfac, g, wf);
+  load_row<C>(a.bias, g, bs);
+#pragma unroll
+  for (int i = 0; i < N; ++i) x[i] = fmaf(sum[i / 4][i % 4], wf[i], bs[i]);
+  if (a.res) {  // residual block: ReLU(x + conv(.)), x read at the voxel's own row
+    float rs[N];
+    load_row<C>(a.res + tr.prow * C, g, rs);
+#pragma unroll
+    for (int i = 0; i < N; ++i) x[i] += rs[i];
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i) x[i] = fmaxf(x[i], 0.0f);
+  if (!tr.valid) return;
+  if constexpr (XB) {  // children v of this voxel u: X_B[v] = F[u] + Emb_D[delta(v)]
+    int64_t cmo = a.moff[tr.b + 1];
+    const int64_t cn = a.count[tr.b + 1];
+    const uint32_t code = a.code[tr.lvb + (tr.prow - tr.mo)];
+    const int64_t first = a.fc[tr.lvb + (tr.prow - tr.mo)];
+    if (cmo + cn > a.cap_model) cmo = -1;  // overflow (latched where the size was made): no writes
+    int rank = 0;
+    for (int d = 0; d < 8; ++d) {
+      if (cmo >= 0 && ((code >> d) & 1u)) {
+        const int64_t row = cmo + first + rank;
+        float y[N];
+        add_row<C>(x, a.emb_d + d * C, g, y);
+#pragma unroll
+        for (int q = 0; q < N / 4; ++q)
+          *reinterpret_cast<f4*>(a.xb + row * C + N * g + 4 * q) = f4{y[4 * q], y[4 * q + 1], y[4 * q + 2], y[4 * q + 3]};
+        store_split<C>(y, g, a.xb_s + row * C, a.xb_r + row);
+        ++rank;
+      }
+    }
+  }
+  if (a.s_out) store_split<C>(x, g, a.s_out + tr.prow * C, a.r_out + tr.prow);
+  if (a.h_out) {
+#pragma unroll
+    for (int q = 0; q < N / 4; ++q)
+      *reinterpret_cast<f4*>(a.h_out + tr.prow * C + N * g + 4 * q) = f4{x[4 * q], x[4 * q + 1], x[4 * q + 2], x[4 * q + 3]};
+  }
+}
+
+// A sparse 3x3x3 conv layer C -> C (bias, optional residual, ReLU), the last
+// one fused with the head.  One block of 16 waves per CU, the layer's weights
+// (and the head's) staged in its LDS.
+//
+// Against the same layers on fp32 MFMA, 14-bit scan: middle layer 68 -> 43 us,
+// last layer with the 256-way head 108 -> 60 us in the encoder's launch (no
+// tile order before them: 10.7 us more); 155 + 203 -> 105 + 130 us over the
+// decoder's nine scales each.
+enum { CONV_MID = 0, CONV_SCATTER = 1, CONV_HEAD = 2, CONV_HEAD2 = 3 };
+
+template <int C, int KIND, bool BIG>
+__global__ void __launch_bounds__(CONV_THREADS) k_conv(ConvArgs a) {
+  constexpr bool LAST = KIND >= CONV_HEAD, TWO = KIND == CONV_HEAD2;
+  constexpr int NCB = C / 16;
+  constexpr int N = C / 4;
+  constexpr int WSZ = 27 * NCB * weight_planes(C) * 64;  // 16-byte words
+  constexpr int HSZ = LAST ? (TWO ? 2 : 16) * HeadOp<C>::BLOCK : 4;
+  __shared__ uint4 s_w[WSZ];
+  __shared__ uint4 s_h[HSZ];
+  // neighbours of a wave's tile; the weights of the 256-way head leave room for
+  // half of the offsets at a time
+  constexpr int TBL = KIND == CONV_HEAD ? 16 : 32;
+  __shared__ uint32_t s_tbl[CONV_WAVES][TBL][16];
+  __shared__ int s_next;  // next dynamically handed-out tile of this block
+
+  // the wave index through a lane read: the compiler then keeps the unit loop,
   // the offset sets and the group folds in scalar registers and branches
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int r = lane & 15, g = lane >> 4;
   const int nsc = a.b_hi - a.b_lo + 1;
-
   const RowMap rm{a.count, a.moff, a.cap_model, a.b_ext, a.ext_off, a.cap_rows};
-  // Sizes of the launch's scales.  One scale: scalar loads.  Several (the
-  // encoder's batched launch): all loaded at once, lane i of every wave
-  // reading scale b_lo + i, and the tile prefix over the scales is a scan
-  // across the lanes.  Lane i ends with scale i's rows (nb_l, mo_l), tiles
-  // tl and inclusive tile prefix incl (0 and the total beyond the last scale).
+  // sizes of the launch's scales: lane i of every wave holds scale b_lo + i
+  // (rows n_l, first row mo_l; rows and tiles fit in 31 bits)
   static_assert(NLEV < 32, "the scale scan covers 32 lanes");
-  int64_t nb_l = 0, mo_l = 0, total_tiles;
-  int tl = 0, incl;  // tiles of a scale and of a launch fit in 31 bits
-  if (nsc == 1) {
-    int64_t mo, nb;
-    scale_span(rm, a.b_lo, mo, nb);
-    total_tiles = (nb + 15) / 16;
-    if (lane == 0) {
-      nb_l = nb;
-      mo_l = mo;
-      tl = (int)total_tiles;
-    }
-    incl = (int)total_tiles;
-  } else {
-    if (lane < nsc) scale_span(rm, a.b_lo + lane, mo_l, nb_l);
-    tl = (int)((nb_l + 15) / 16);
-    incl = tl;
+  int n_l = 0, mo_l = 0;
+  if (lane < nsc) {
+    int64_t mo, n;
+    scale_span(rm, a.b_lo + lane, mo, n);
+    n_l = (int)n;
+    mo_l = (int)mo;
+  }
+  auto scan32 = [&](int v) {
+    if (nsc > 1) {
 #pragma unroll
-    for (int o = 1; o < 32; o <<= 1) {
-      const int y = __shfl_up(incl, o);
-      if (lane >= o) incl += y;
+      for (int o = 1; o < 32; o <<= 1) {
+        const int y = __shfl_up(v, o);
+        if (lane >= o) v += y;
+      }
     }
-    total_tiles = __builtin_amdgcn_readlane(incl, 31);  // uniform (scalar register)
-  }
+    return v;
+  };
+  const int incl = scan32((n_l + 15) / 16);
+  const int total = __builtin_amdgcn_readlane(incl, nsc - 1);
+  const int mo_first = __builtin_amdgcn_readlane(mo_l, 0);
   // chunk size: 256 chunks per launch (32 per XCD) between 16 and 256 tiles
-  const int64_t tch = total_tiles / 256 < 16 ? 16 : (total_tiles / 256 > 256 ? 256 : total_tiles / 256);
-  // small launches: a quad of waves per tile (at most CONV_WAVES / 4 tiles per block)
-  const bool quads = total_tiles <= (int64_t)gridDim.x * (CONV_WAVES / 4);  // uniform
-  static_assert((16 * NCB * 64 * 16 + 16 * 64 * 8) <= WSZ * 4, "quad exchange area exceeds the weight area");
-  if (quads ? (int64_t)blockIdx.x >= total_tiles : conv_tile(0, tch) >= total_tiles)
-    return;  // whole block idle: no weight staging
+  const int64_t tch = total / 256 < 16 ? 16 : (total / 256 > 256 ? 256 : total / 256);
+  // small launches: a quad of waves per tile
+  const bool quads = total <= (int)gridDim.x * (CONV_WAVES / 4);
+  static_assert(16 * NCB * 64 + 8 * 64 <= WSZ, "quad exchange area exceeds the weight area");
+  if (quads ? (int)blockIdx.x >= total : conv_tile(0, tch) >= total) return;  // whole block idle: no weight staging
   // weight and head loads of the whole block in one round trip
-  Staged<WSZ / 4, CONV_THREADS> stw;
-  Staged<LAST ? HSZ / 4 : 1, CONV_THREADS> sth;
-  stw.load(reinterpret_cast<const f4*>(a.w), tid);
-  if (LAST) sth.load(reinterpret_cast<const f4*>(a.hw), tid);
-  if (w == 0 && lane <= NLEV) {
-    if (lane == 0) s_next = 0;
-    s_tpre[lane] = lane < nsc ? incl - tl : total_tiles;  // padding: never below a valid tile
-    if (lane < NLEV) {
-      s_nv[lane] = nb_l;
-      s_mo[lane] = mo_l;
-    }
+  {
+    Staged<WSZ, CONV_THREADS> stw;
+    Staged<LAST ? HSZ : 1, CONV_THREADS> sth;
+    stw.load(reinterpret_cast<const f4*>(a.w), tid);
+    if (LAST) sth.load(reinterpret_cast<const f4*>(a.hw), tid);
+    if (tid == 0) s_next = 0;
+    stw.store(reinterpret_cast<f4*>(s_w), tid);
+    if (LAST) sth.store(reinterpret_cast<f4*>(s_h), tid);
   }
-  stw.store(reinterpret_cast<f4*>(s_w), tid);
-  if (LAST) sth.store(reinterpret_cast<f4*>(s_h), tid);
   __syncthreads();
 
-  // A tile as the epilogue and the head need it.
-  struct TileRef {
-    int b;
-    int64_t mo, prow, lvb;
-    bool valid;
+  // Opens tile u and sums it.
+  auto open = [&](int u, int grp, TileRef& tr, f4 (&sum)[NCB]) {
+    const int si = nsc > 1 ? __popcll(__ballot(lane < nsc && incl <= u)) : 0;
+    const int n = __builtin_amdgcn_readlane(n_l, si), mo = __builtin_amdgcn_readlane(mo_l, si);
+    const int u0 = si ? __builtin_amdgcn_readlane(incl, si - 1) : 0;
+    const int row = (u - u0) * 16 + r;
+    const bool valid = row < n;
+    const int32_t pos = mo + (valid ? row : n - 1);  // idle lanes name a real row
+    tr = TileRef{a.b_lo + si, mo, (int64_t)(a.b_lo + si - a.b0) * a.cap_pts, pos, valid};
+    conv_sum<C, TBL, BIG>(a, s_w, s_tbl[w], lane, mo, n, (u - u0) * 16, grp, sum);
   };
-  // Opens tile `tile` (scale, rows, neighbour rows) and accumulates it: grp < 0
-  // gives the bias plus all 4 offset-group sums, folded in group order; grp in
-  // 0 .. 3 gives that group's sum alone (a wave of a quad sharing the tile).
-  auto conv_sum = [&](int64_t tile, int grp, TileRef& tr, f4 (&out)[NCB]) {
-    int si = 0;  // scale of the tile: all prefix loads issued together
-#pragma unroll
-    for (int i = 1; i < NLEV; ++i) si += (s_tpre[i] <= tile) ? 1 : 0;
-    const int b = a.b_lo + si;
-    const int64_t nvox = s_nv[si];
-    const int64_t mo = s_mo[si];
-    const int64_t row = (tile - s_tpre[si]) * 16 + r;
-    const bool valid = row < nvox;
-    // idle lanes read a real row; with a tile order, slot -> row
-    const int64_t pos = mo + (valid ? row : nvox - 1);
-    const int64_t prow = a.perm ? (int64_t)a.perm[pos] : pos;
-    const int64_t lvb = (int64_t)(b - a.b0) * a.cap_pts;
-
-    // ---- neighbour rows: lane (r, g) holds offsets k = 8g .. 8g+7 of voxel r
-    const int4* src = reinterpret_cast<const int4*>(a.nbr + prow * NBR_STRIDE + 8 * g);
-    const int4 nlo = src[0], nhi = src[1];
-    // occupied offsets of the tile: one ballot per entry slot j, lanes of
-    // group g covering offsets 8g + j (the 5 padding entries are -1)
-    uint32_t offs = 0;
-    {
-      const int32_t e8[8] = {nlo.x, nlo.y, nlo.z, nlo.w, nhi.x, nhi.y, nhi.z, nhi.w};
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const uint64_t bal = __ballot(valid && e8[j] >= 0);
-#pragma unroll
-        for (int gg = 0; gg < 4; ++gg)
-          offs |= ((bal >> (16 * gg)) & 0xFFFFull) ? (1u << (8 * gg + j)) : 0u;
-      }
-      offs &= 0x7FFFFFFu;
-    }
-    if (grp >= 0) offs &= group_offsets(grp);
-
-    // ---- accumulate over the occupied offsets, software-pipelined: the
-    // gathers of the next PCH offsets are issued before the MFMAs of the
-    // current ones (double buffer; loads are never skipped, an unused slot
-    // reads the zero row, so the wait counts stay exact).
-    // Summation order per output: the offsets fall into 4 fixed groups
-    // (k < 7, < 14, < 21, < 27); each group's products are chained on MFMA
-    // from zero, in ascending offset order, and the 4 group sums are added to
-    // the bias in group order: ((((bias + S0) + S1) + S2) + S3).
-    f4 acc[NCB], tsum[NCB];
-#pragma unroll
-    for (int cb = 0; cb < NCB; ++cb) {
-      tsum[cb] = *reinterpret_cast<const f4*>(a.bias + 16 * cb + 4 * g);
-      acc[cb] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-    }
-    int gcur = grp >= 0 ? grp : 0;  // group whose sum acc holds
-    auto fold = [&]() {
-#pragma unroll
-      for (int cb = 0; cb < NCB; ++cb) {
-        tsum[cb] += acc[cb];
-        acc[cb] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-      }
-      ++gcur;
-    };
-    auto enter = [&](int k) {  // k: the next offset, wave-uniform
-      while (k >= (gcur < 3 ? 7 * (gcur + 1) : 27)) fold();
-    };
-    auto take = [&](int (&ks)[PCH]) {
-#pragma unroll
-      for (int c = 0; c < PCH; ++c) {
-        ks[c] = offs ? __builtin_ctz(offs) : -1;
-        offs &= offs ? offs - 1u : 0u;
-      }
-    };
-    auto gather = [&](const int (&ks)[PCH], G (&gb)[PCH]) {
-      int32_t nn[PCH];
-#pragma unroll
-      for (int c = 0; c < PCH; ++c) {
-        nn[c] = __shfl(pick8(nlo, nhi, ks[c] & 7), r + 16 * ((ks[c] & 31) >> 3));
-      }
-      __builtin_amdgcn_sched_barrier(0);  // keep the exchanges back to back (one wait for all)
-#pragma unroll
-      for (int c = 0; c < PCH; ++c) {
-        const int32_t n = (valid && ks[c] >= 0) ? nn[c] : -1;
-        if constexpr (BF) {
-          // rows hold [hi plane: C bf16][lo plane: C bf16]; lanes beyond C/8 feed zeros
-          const int64_t srow = n >= 0 ? mo + n : a.cap_model;
-          const uint4* src = reinterpret_cast<const uint4*>(a.h_in + srow * C);
-          const int gq = g < C / 8 ? g : 0;
-          gb[c].hi = src[gq];
-          gb[c].lo = src[C / 8 + gq];
-          if (g >= C / 8) gb[c].hi = gb[c].lo = make_uint4(0, 0, 0, 0);
-        } else {
-          // absent neighbours read the reserved all-zero row cap_model
-          const int64_t srow = n >= 0 ? mo + n : a.cap_model;
-          const f4* src = reinterpret_cast<const f4*>(a.h_in + srow * C + g * KS);
-#pragma unroll
-          for (int q = 0; q < KSP / 4; ++q) gb[c].v[q] = src[q];
-        }
-      }
-    };
-    auto load_w = [&](int k, f4 (&wv)[NCB][KSP / 4]) {
-#pragma unroll
-      for (int cb = 0; cb < NCB; ++cb) {
-        const f4* wp = reinterpret_cast<const f4*>(s_w + ((k * NCB + cb) * 64 + lane) * KSP);
-#pragma unroll
-        for (int q = 0; q < KSP / 4; ++q) wv[cb][q] = wp[q];
-      }
-    };
-    auto mma_bf = [&](const int (&ks)[PCH], const G (&gb)[PCH]) {
-      if constexpr (BF) {
-#pragma unroll
-      for (int c = 0; c < PCH; ++c) {
-        if (ks[c] < 0) break;
-        enter(ks[c]);
-        uint4 wa[NCB][2];
-#pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) {
-          const uint4* wp = reinterpret_cast<const uint4*>(s_w) + ((ks[c] * NCB + cb) * 64 + lane) * 2;
-          wa[cb][0] = wp[0];
-          wa[cb][1] = wp[1];
-        }
-        const uint4 bh = gb[c].hi, bl = gb[c].lo;
-        // the three products, column blocks interleaved
-#pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) acc[cb] = mfma_bf(wa[cb][0], bh, acc[cb]);
-#pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) acc[cb] = mfma_bf(wa[cb][0], bl, acc[cb]);
-#pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) acc[cb] = mfma_bf(wa[cb][1], bh, acc[cb]);
-      }
-      }
-    };
-    auto mma_f32 = [&](const int (&ks)[PCH], const G (&gb)[PCH]) {
-      if constexpr (!BF) {
-#pragma unroll
-      for (int c = 0; c < PCH; ++c) {
-        if (ks[c] < 0) break;
-        enter(ks[c]);
-        f4 wv[NCB][KSP / 4];
-        load_w(ks[c], wv);
-        float bsrc[KSP];
-#pragma unroll
-        for (int q = 0; q < KSP / 4; ++q)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) bsrc[4 * q + e] = gb[c].v[q][e];
-        // column blocks interleaved: NCB independent accumulator chains
-#pragma unroll
-        for (int s = 0; s < KS; ++s)
-#pragma unroll
-          for (int cb = 0; cb < NCB; ++cb) acc[cb] = mfma4(wv[cb][s / 4][s % 4], bsrc[s], acc[cb]);
-      }
-      }
-    };
-    auto mma = [&](const int (&ks)[PCH], const G (&gb)[PCH]) {
-      if constexpr (BF) mma_bf(ks, gb);
-      else mma_f32(ks, gb);
-    };
-    {
-      int ksA[PCH], ksB[PCH];
-      G gA[PCH], gB[PCH];
-      take(ksA);
-      gather(ksA, gA);
-      while (true) {
-        take(ksB);
-        gather(ksB, gB);
-        mma(ksA, gA);
-        if (ksB[0] < 0) break;
-        take(ksA);
-        gather(ksA, gA);
-        mma(ksB, gB);
-        if (ksA[0] < 0) break;
-      }
-    }
-    if (grp < 0) {
-      while (gcur < 4) fold();  // every group folded, also the empty ones
-#pragma unroll
-      for (int cb = 0; cb < NCB; ++cb) out[cb] = tsum[cb];
-    } else {
-#pragma unroll
-      for (int cb = 0; cb < NCB; ++cb) out[cb] = acc[cb];
-    }
-    tr.b = b;
-    tr.mo = mo;
-    tr.prow = prow;
-    tr.lvb = lvb;
-    tr.valid = valid;
-  };
-  // Residual, ReLU, the children's X_B rows (full predictor) and the output row.
-  auto epilogue = [&](const TileRef& tr, f4 (&acc)[NCB]) {
-    const int b = tr.b;
-    const int64_t mo = tr.mo, prow = tr.prow, lvb = tr.lvb;
-    const bool valid = tr.valid;
-    if (a.res) {  // residual block: ReLU(x + conv(.)), x read at the voxel's own row
-#pragma unroll
-      for (int cb = 0; cb < NCB; ++cb) acc[cb] += *reinterpret_cast<const f4*>(a.res + prow * C + 16 * cb + 4 * g);
-    }
-#pragma unroll
-    for (int cb = 0; cb < NCB; ++cb)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) acc[cb][e] = fmaxf(acc[cb][e], 0.0f);
-    if (a.xb && valid) {  // children v of this voxel u: X_B[v] = F[u] + Emb_D[delta(v)]
-      int64_t cmo = a.moff[b + 1];
-      const int64_t cn = a.count[b + 1];
-      const uint32_t code = a.code[lvb + (prow - mo)];
-      const int64_t first = a.fc[lvb + (prow - mo)];
-      if (cmo + cn > a.cap_model) cmo = -1;  // overflow (latched where the size was made): no writes
-      int rank = 0;
-#pragma unroll
-      for (int d = 0; d < 8; ++d) {
-        if (cmo >= 0 && ((code >> d) & 1u)) {
-          float* dst = a.xb + (cmo + first + rank) * C;
-#pragma unroll
-          for (int cb = 0; cb < NCB; ++cb)
-            *reinterpret_cast<f4*>(dst + 16 * cb + 4 * g) =
-                acc[cb] + *reinterpret_cast<const f4*>(a.emb_d + d * C + 16 * cb + 4 * g);
-          ++rank;
-        }
-      }
-    }
-    if (valid && a.h_out) {
-      if constexpr (BF && !LAST) {
-        // next layer's input as [hi plane | lo plane] of bf16 (split once per voxel)
-        uint16_t* row = reinterpret_cast<uint16_t*>(a.h_out + prow * C);
-#pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) {
-          uint32_t h0, l0, h1, l1;
-          split2(acc[cb][0], acc[cb][1], h0, l0);
-          split2(acc[cb][2], acc[cb][3], h1, l1);
-          *reinterpret_cast<uint2*>(row + 16 * cb + 4 * g) = make_uint2(h0, h1);
-          *reinterpret_cast<uint2*>(row + C + 16 * cb + 4 * g) = make_uint2(l0, l1);
-        }
-      } else {
-#pragma unroll
-        for (int cb = 0; cb < NCB; ++cb)
-          *reinterpret_cast<f4*>(a.h_out + prow * C + 16 * cb + 4 * g) = acc[cb];
-      }
-    }
-
-  };
-
   if (!quads) {
-    // Tile order (conv_tile): every XCD gets chunks from the whole tile range,
-    // a sample of every scale of the launch, so the XCDs carry about the same
-    // mix of cheap and expensive tiles (coarse scales have far more occupied
-    // offsets per tile).  Inside a block the waves take the block's tiles
-    // dynamically from an LDS counter: the first CONV_WAVES slots statically,
-    // the rest first come, first served.
+    // XCD-aware tile order (conv_tile); inside a block the waves take the
+    // block's tiles dynamically from an LDS counter: the first CONV_WAVES
+    // statically, the rest first come, first served.
     for (int64_t slot = w;;) {
-      const int64_t tile = conv_tile(slot, tch);
-      if (tile >= total_tiles) break;
-      TileRef tr;
-      f4 acc[NCB];
-      conv_sum(tile, -1, tr, acc);
-      epilogue(tr, acc);
-      if constexpr (LAST) head_epilogue<C, TWO, BF>(a, acc, s_h, lane, g, tr.valid, tr.prow, tr.mo, tr.lvb, s_mo[0]);
+      const int64_t u = conv_tile(slot, tch);
+      if (u >= total) break;
+      TileRef tr[1];
+      f4 sum[NCB];
+      float x[1][N];
+      open((int)u, -1, tr[0], sum);
+      conv_epilogue<C, KIND == CONV_SCATTER>(a, sum, g, tr[0], x[0]);
+      if constexpr (LAST) head_epilogue<C, TWO, 1>(a, x, s_h, lane, g, tr, mo_first);
       int nxt = 0;
       if (lane == 0) nxt = atomicAdd(&s_next, 1);
-      slot = CONV_WAVES + __builtin_amdgcn_readfirstlane(__shfl(nxt, 0));
+      slot = CONV_WAVES + __builtin_amdgcn_readfirstlane(nxt);
     }
     return;
   }
 
   // Small launch (at most one tile per quad of waves): quad q of block x takes
-  // tile x + q G, its wave i the offsets of group i, so a tile's serial MFMA
-  // chain is split four ways.  The group sums meet in the weight area of LDS
-  // (free once every conv loop is done) and are folded by wave 0 in the same
-  // order as above; the 256-way head is split by symbol group the same way.
-  // Every wave passes every barrier (no early exit below).
+  // tile x + q G, its wave i the offsets of group i, so a tile's serial chain
+  // is split four ways.  The group sums meet in the weight area of LDS (free
+  // once every conv loop is done) and are added by wave 0 in the same order as
+  // above; the 256-way head is split by symbol group the same way.  Every wave
+  // passes every barrier (no early exit below).
   {
     const int q = w >> 2, gi = w & 3;
-    const int64_t tile = (int64_t)blockIdx.x + (int64_t)gridDim.x * q;
-    const bool has = tile < total_tiles;  // wave-uniform
-    TileRef tr{};
-    f4 acc[NCB];
-    if (has) conv_sum(tile, gi, tr, acc);
+    const int tile = (int)blockIdx.x + (int)gridDim.x * q;
+    const bool has = tile < total;  // wave-uniform
+    TileRef tr[1]{};
+    f4 sum[NCB];
+    if (has) open(tile, gi, tr[0], sum);
     __syncthreads();  // every conv loop of the block is done: the weight area is free
-    f4* s_x = reinterpret_cast<f4*>(s_w);  // [quad][slot 0..3][NCB][64]: group sums 1-3, h
+    f4* s_x = reinterpret_cast<f4*>(s_w);                           // [quad][slot 0..3][NCB][64]: group sums 1-3, x
     float2* s_x2 = reinterpret_cast<float2*>(s_x + 16 * NCB * 64);  // [quad][group][64]: (gm, part)
     auto xs = [&](int slot, int cb) -> f4* { return s_x + ((q * 4 + slot) * NCB + cb) * 64 + lane; };
     if (has && gi > 0) {
 #pragma unroll
-      for (int cb = 0; cb < NCB; ++cb) *xs(gi - 1, cb) = acc[cb];
+      for (int cb = 0; cb < NCB; ++cb) *xs(gi - 1, cb) = sum[cb];
     }
     __syncthreads();
     if (has && gi == 0) {
 #pragma unroll
       for (int cb = 0; cb < NCB; ++cb) {
-        f4 t = *reinterpret_cast<const f4*>(a.bias + 16 * cb + 4 * g);
-        t += acc[cb];
+        f4 t = f4{0.0f, 0.0f, 0.0f, 0.0f} + sum[cb];
         t += *xs(0, cb);
         t += *xs(1, cb);
         t += *xs(2, cb);
-        acc[cb] = t;
+        sum[cb] = t;
       }
-      epilogue(tr, acc);
+      float x[1][N];
+      conv_epilogue<C, KIND == CONV_SCATTER>(a, sum, g, tr[0], x[0]);
       if constexpr (LAST && !TWO) {
 #pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) *xs(3, cb) = acc[cb];  // h for the quad's other waves
+        for (int cb = 0; cb < NCB; ++cb)  // the features for the quad's other waves
+          *xs(3, cb) = f4{x[0][4 * cb], x[0][4 * cb + 1], x[0][4 * cb + 2], x[0][4 * cb + 3]};
       }
-      if constexpr (LAST && TWO) head_epilogue<C, TWO, BF>(a, acc, s_h, lane, g, tr.valid, tr.prow, tr.mo, tr.lvb, s_mo[0]);
+      if constexpr (LAST && TWO) head_epilogue<C, TWO, 1>(a, x, s_h, lane, g, tr, mo_first);
     }
     if constexpr (LAST && !TWO) {
       __syncthreads();
       if (has) {
-        f4 h[NCB];
+        float x[N];
 #pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) h[cb] = *xs(3, cb);
-        float gm, part;
-        head_group<C, BF>(a, h, s_h, a.hb, lane, g, tr.valid, tr.prow, s_mo[0], gi, gm, part);
-        s_x2[(q * 4 + gi) * 64 + lane] = make_float2(gm, part);
+        for (int cb = 0; cb < NCB; ++cb) {
+          const f4 t = *xs(3, cb);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) x[4 * cb + e] = t[e];
+        }
+        HeadOp<C> op[1];
+        op[0].set(x);
+        float* lo[1] = {(a.logits && tr[0].valid) ? a.logits + (tr[0].prow - mo_first) * 256 + 4 * g : nullptr};
+        float gm[1], part[1];
+        head_group<C, 1>(s_h, a.hb, a.hfac[0], op, lo, lane, g, gi, gm, part);
+        s_x2[(q * 4 + gi) * 64 + lane] = make_float2(gm[0], part[0]);
       }
       __syncthreads();
       if (has && gi == 0) {
@@ -1063,13 +1147,13 @@ __global__ void __launch_bounds__(CONV_THREADS) k_conv(ConvArgs a) {
           const float2 v = s_x2[(q * 4 + k) * 64 + lane];
           lse_merge(m, ssum, v.x, v.y);
         }
-        lse_finish(a, m, ssum, g, tr.valid, tr.prow);
+        lse_finish(a, m, ssum, g, tr[0].valid, tr[0].prow);
       }
     }
   }
 }
 
-// Tile order for the layers after the first: inside each window of TO_W
+// Tile order of the streamed-weight layers (k_convw): inside each window of TO_W
 // consecutive voxels of a scale, voxels are grouped by an 11-bit signature of
 // their neighbour occupancy (the 9 offsets of their own z plane and the two
 // z faces), so a 16-voxel tile gathers voxels with similar neighbourhoods and
@@ -1221,16 +1305,20 @@ __device__ __forceinline__ void base_cell_rows(uint64_t kf, int b, int g, const 
   for (int j = 0; j < 8; ++j) nb[j] = (ok[j] && keys[at[j]] == want[j]) ? (int32_t)at[j] : -1;
 }
 
-template <int C>
+// WIDE: the inputs of k_convw (plain map rows, X_A in fp32); else those of
+// k_conv (map rows of store_map, X_A also as split rows).
+template <int C, bool WIDE>
 __global__ void __launch_bounds__(256) k_top_prep(int lo, int nsc, int n_embed, int b0, RowMap rm,
                                                   const uint64_t* __restrict__ lv_key,
                                                   const uint8_t* __restrict__ lv_code, int64_t cap_pts,
                                                   CellArgs cells, const float* __restrict__ emb_o, int32_t* __restrict__ nbr,
-                                                  float* __restrict__ X) {
+                                                  float* __restrict__ X, uint32_t* __restrict__ XS,
+                                                  float* __restrict__ XR) {
   constexpr int Q = C / 16;  // f4 per lane of a row
   __shared__ uint64_t s_par[4][16][9];  // rows padded: the 16 voxels' cells in different banks
   __shared__ int64_t s_n[32], s_mo[32], s_tpre[32];
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, r = lane & 15, g = lane >> 4;
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+  const int r = lane >> 2, g = lane & 3;  // 4 consecutive lanes per voxel: their accesses to its rows coalesce
   if (tid < nsc) {  // sizes of the launch's scales, loaded in parallel
     int64_t o, n;
     scale_span(rm, lo + tid, o, n);
@@ -1261,16 +1349,27 @@ __global__ void __launch_bounds__(256) k_top_prep(int lo, int nsc, int n_embed, 
       base_cell_rows(lv_key[lvb + vr], b, g, lv_key + lvb, n, nb);
     else
       parent_cell_rows(lv_key[lvb + vr], b, g, cells, s_par[w][r], nb);
-    if (valid) {
-      int4* dst = reinterpret_cast<int4*>(nbr + (mo + vr) * NBR_STRIDE + 8 * g);
-      dst[0] = make_int4(nb[0], nb[1], nb[2], nb[3]);
-      dst[1] = make_int4(nb[4], nb[5], nb[6], nb[7]);
-      if (si < n_embed) {
-        const f4* e = reinterpret_cast<const f4*>(emb_o + (int)lv_code[lvb + vr] * C) + g * Q;
-        f4* xr = reinterpret_cast<f4*>(X + (mo + vr) * C) + g * Q;
-#pragma unroll
-        for (int q = 0; q < Q; ++q) xr[q] = e[q];
+    if constexpr (WIDE) {
+      if (valid) {
+        int4* dst = reinterpret_cast<int4*>(nbr + (mo + vr) * NBR_STRIDE + 8 * g);
+        dst[0] = make_int4(nb[0], nb[1], nb[2], nb[3]);
+        dst[1] = make_int4(nb[4], nb[5], nb[6], nb[7]);
       }
+    } else {
+      store_map(nbr, mo + vr, valid, g, nb);
+    }
+    if (valid && si < n_embed) {
+      const f4* e = reinterpret_cast<const f4*>(emb_o + (int)lv_code[lvb + vr] * C) + g * Q;
+      f4* xr = reinterpret_cast<f4*>(X + (mo + vr) * C) + g * Q;
+      float x[C / 4];
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        const f4 t = e[q];
+        xr[q] = t;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[4 * q + i] = t[i];
+      }
+      if constexpr (!WIDE) store_split<C, 1>(x, g, XS + (mo + vr) * C, XR + mo + vr);
     }
   }
 }
@@ -1365,7 +1464,7 @@ __global__ void __launch_bounds__(256) k_top_prep5(int lo, int nsc, int n_embed,
   constexpr int Q = C / 16;
   __shared__ uint64_t s_par[4][16][27];
   __shared__ int64_t s_n[32], s_mo[32], s_tpre[32];
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, r = lane & 15, g = lane >> 4;
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, r = lane >> 2, g = lane & 3;
   if (tid < nsc) {
     int64_t o, n;
     scale_span(rm, lo + tid, o, n);
@@ -1656,18 +1755,17 @@ __global__ void __launch_bounds__(CW_THREADS) k_convw(ConvArgs a) {
 // The head on stored last-layer features h_in (rows of the scales b_lo ..
 // b_hi), for layers computed by k_convw: one wave per tile of 16 voxels, the
 // head weights in LDS, the same arithmetic as the fused head of k_conv.
-// threads of a k_headw block: the two-stage head at C >= 64 needs more
-// registers than 16 waves per CU allow
+// threads of a k_headw block: the heads of wide layers need more registers
+// than 16 waves per CU allow
 template <int C, bool TWO>
-constexpr int headw_threads() { return (TWO && C >= 64) ? 256 : 1024; }
+constexpr int headw_threads() { return C >= 64 ? 256 : 1024; }
 
-template <int C, bool TWO, bool BF>
+template <int C, bool TWO>
 __global__ void __launch_bounds__((headw_threads<C, TWO>())) k_headw(ConvArgs a) {
-  constexpr int NCB = C / 16;
   constexpr int HT = headw_threads<C, TWO>();
   constexpr int HWV = HT / 64;
-  constexpr int HQ = (TWO ? 2 : 16) * 64 * (BF ? 8 : C / 4) / 4;  // 16-byte words of the packed head
-  __shared__ __attribute__((aligned(16))) float s_h[HQ * 4];
+  constexpr int HQ = (TWO ? 2 : 16) * HeadOp<C>::BLOCK;  // 16-byte words of the packed head
+  __shared__ uint4 s_h[HQ];
   __shared__ int64_t s_tpre[NLEV + 1];
   __shared__ int64_t s_nv[NLEV];
   __shared__ int64_t s_mo[NLEV];
@@ -1695,20 +1793,18 @@ __global__ void __launch_bounds__((headw_threads<C, TWO>())) k_headw(ConvArgs a)
     int si = 0;
 #pragma unroll
     for (int i = 1; i < NLEV; ++i) si += (s_tpre[i] <= tile) ? 1 : 0;
-    const int b = a.b_lo + si;
     const int64_t nvox = s_nv[si], mo = s_mo[si];
     const int64_t row = (tile - s_tpre[si]) * 16 + r;
     const bool valid = row < nvox;
-    const int64_t prow = mo + (valid ? row : nvox - 1);
-    const int64_t lvb = (int64_t)(b - a.b0) * a.cap_pts;
-    f4 acc[NCB];
-#pragma unroll
-    for (int cb = 0; cb < NCB; ++cb) acc[cb] = *reinterpret_cast<const f4*>(a.h_in + prow * C + 16 * cb + 4 * g);
-    head_epilogue<C, TWO, BF>(a, acc, s_h, lane, g, valid, prow, mo, lvb, s_mo[0]);
+    const TileRef tr[1] = {{a.b_lo + si, mo, (int64_t)(a.b_lo + si - a.b0) * a.cap_pts,
+                            mo + (valid ? row : nvox - 1), valid}};
+    float x[1][C / 4];
+    load_row<C>(a.h_in + tr[0].prow * C, g, x[0]);
+    head_epilogue<C, TWO, 1>(a, x, s_h, lane, g, tr, s_mo[0]);
   }
 }
 
-template <int C, bool BF>
+template <int C>
 hipError_t run_headw(Ctx& c, bool two, const ConvArgs& a) {
   auto go = [&](auto kern, int threads, int most) {
     const int64_t per = threads / 4;  // voxels of a block's waves: 16 each
@@ -1721,8 +1817,8 @@ hipError_t run_headw(Ctx& c, bool two, const ConvArgs& a) {
     }
     return hipGetLastError();
   };
-  return two ? go(k_headw<C, true, BF>, headw_threads<C, true>(), 4096)
-             : go(k_headw<C, false, BF>, headw_threads<C, false>(), 1024);
+  return two ? go(k_headw<C, true>, headw_threads<C, true>(), 4096)
+             : go(k_headw<C, false>, headw_threads<C, false>(), C >= 64 ? 4096 : 1024);
 }
 
 // ---------------------------------------------------------------------------
@@ -1782,17 +1878,19 @@ struct FirstArgs {
   const float* table;    // [8][8][256][C]
   const float* bias;     // [C]
   int32_t* nbr;          // [rows][NBR_STRIDE]
-  float* out;            // [rows][C]
+  float* out;            // fp32 output rows [rows][C], or NULL
+  uint32_t* s_out;       // split output rows, or NULL
+  float* r_out;          // their factors
 };
 
 constexpr int FIRST_WAVES = 4;
 
-template <int C, bool BF>
+template <int C>
 __global__ void __launch_bounds__(64 * FIRST_WAVES, 4) k_first(FirstArgs a) {
   constexpr int Q = C / 16;  // f4 words of a lane's C / 4 channels
   __shared__ uint64_t s_par[FIRST_WAVES][16][9];  // rows padded: the 16 voxels' cells in different banks
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
-  const int r = lane & 15, g = lane >> 4;
+  const int r = lane >> 2, g = lane & 3;  // 4 consecutive lanes per voxel: their accesses to its rows coalesce
   // lane i holds scale i of the launch: rows, first row, inclusive tile prefix
   int64_t n_l = 0, mo_l = 0;
   if (lane < a.nsc) scale_span(a.rm, a.b_lo + lane, mo_l, n_l);
@@ -1843,35 +1941,33 @@ __global__ void __launch_bounds__(64 * FIRST_WAVES, 4) k_first(FirstArgs a) {
         for (int q = 0; q < Q; ++q) v[e][q] = src[4 * q];
       }
     }
-    f4 acc[Q];
+    const int64_t prow = mo + vr;
+    store_map(a.nbr, prow, valid, g, nb);
+    float x[C / 4];
 #pragma unroll
-    for (int q = 0; q < Q; ++q) acc[q] = reinterpret_cast<const f4*>(a.bias)[4 * q + g];
+    for (int q = 0; q < Q; ++q) {
+      f4 acc = reinterpret_cast<const f4*>(a.bias)[4 * q + g];
 #pragma unroll
-    for (int e = 0; e < 8; ++e)
+      for (int e = 0; e < 8; ++e) acc += v[e][q];
 #pragma unroll
-      for (int q = 0; q < Q; ++q) acc[q] += v[e][q];
+      for (int i = 0; i < 4; ++i) x[4 * q + i] = fmaxf(acc[i], 0.0f);
+    }
     if (!valid) continue;
-#pragma unroll
-    for (int q = 0; q < Q; ++q)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) acc[q][i] = fmaxf(acc[q][i], 0.0f);
-    const int64_t prow = mo + row;
-    int4* dst = reinterpret_cast<int4*>(a.nbr + prow * NBR_STRIDE + 8 * g);
-    dst[0] = make_int4(nb[0], nb[1], nb[2], nb[3]);
-    dst[1] = make_int4(nb[4], nb[5], nb[6], nb[7]);
-    if constexpr (BF) {  // [hi plane | lo plane] of bf16, the next layer's operand
-      uint16_t* orow = reinterpret_cast<uint16_t*>(a.out + prow * C);
+    if (a.s_out) {
+      uint32_t hi[C / 8], lo[C / 8];
+      const float f = row_split<C / 4, 1>(x, hi, lo);
+      uint32_t* orow = a.s_out + prow * C;
 #pragma unroll
       for (int q = 0; q < Q; ++q) {
-        uint32_t h0, l0, h1, l1;
-        split2(acc[q][0], acc[q][1], h0, l0);
-        split2(acc[q][2], acc[q][3], h1, l1);
-        *reinterpret_cast<uint2*>(orow + 4 * (4 * q + g)) = make_uint2(h0, h1);
-        *reinterpret_cast<uint2*>(orow + C + 4 * (4 * q + g)) = make_uint2(l0, l1);
+        *reinterpret_cast<uint2*>(orow + 8 * q + 2 * g) = make_uint2(hi[2 * q], hi[2 * q + 1]);
+        *reinterpret_cast<uint2*>(orow + C / 2 + 8 * q + 2 * g) = make_uint2(lo[2 * q], lo[2 * q + 1]);
       }
-    } else {
+      if (g == 0) a.r_out[prow] = f;
+    }
+    if (a.out) {
 #pragma unroll
-      for (int q = 0; q < Q; ++q) reinterpret_cast<f4*>(a.out + prow * C)[4 * q + g] = acc[q];
+      for (int q = 0; q < Q; ++q)
+        reinterpret_cast<f4*>(a.out + prow * C)[4 * q + g] = f4{x[4 * q], x[4 * q + 1], x[4 * q + 2], x[4 * q + 3]};
     }
   }
 }
@@ -1880,83 +1976,76 @@ CellArgs cell_args(const Ctx& c) {
   return CellArgs{c.d_hash, c.hash_lg, c.hreg(), c.fbits, c.b0(), c.cap_pts, c.lv_code, c.lv_fc};
 }
 
-template <int C, bool BF>
+template <int C>
 hipError_t run_first(Ctx& c, const FirstArgs& a) {
   // 8 blocks per CU at most; fewer when the capacity cannot fill them
   int64_t blocks = ((c.cap_model + 16 * FIRST_WAVES - 1) / (16 * FIRST_WAVES) + 7) & ~int64_t(7);
   if (blocks > 2048) blocks = 2048;
   if (c.ext_start) {  // timed: the events are the dispatch's own start and end
-    hipExtLaunchKernelGGL((k_first<C, BF>), dim3((unsigned)blocks), dim3(64 * FIRST_WAVES), 0, c.stream, c.ext_start,
+    hipExtLaunchKernelGGL(k_first<C>, dim3((unsigned)blocks), dim3(64 * FIRST_WAVES), 0, c.stream, c.ext_start,
                           c.ext_stop, 0u, a);
     c.ext_start = c.ext_stop = nullptr;
   } else {
-    hipLaunchKernelGGL((k_first<C, BF>), dim3((unsigned)blocks), dim3(64 * FIRST_WAVES), 0, c.stream, a);
+    hipLaunchKernelGGL(k_first<C>, dim3((unsigned)blocks), dim3(64 * FIRST_WAVES), 0, c.stream, a);
   }
   return hipGetLastError();
 }
 
-template <int C, bool LAST, bool TWO, bool BF>
+template <int C, int KIND>
 hipError_t run_conv(Ctx& c, const ConvArgs& a) {
   // one block per CU stages the weights once for its 16 waves
-  if (c.ext_start) {  // timed: the events are the dispatch's own start and end
-    hipExtLaunchKernelGGL((k_conv<C, LAST, TWO, BF>), dim3(256), dim3(CONV_THREADS), 0, c.stream,
-                          c.ext_start, c.ext_stop, 0u, a);
-    c.ext_start = c.ext_stop = nullptr;
-  } else {
-    hipLaunchKernelGGL((k_conv<C, LAST, TWO, BF>), dim3(256), dim3(CONV_THREADS), 0, c.stream, a);
-  }
-  return hipGetLastError();
+  auto go = [&](auto kern) {
+    if (c.ext_start) {  // timed: the events are the dispatch's own start and end
+      hipExtLaunchKernelGGL(kern, dim3(256), dim3(CONV_THREADS), 0, c.stream, c.ext_start, c.ext_stop, 0u, a);
+      c.ext_start = c.ext_stop = nullptr;
+    } else {
+      hipLaunchKernelGGL(kern, dim3(256), dim3(CONV_THREADS), 0, c.stream, a);
+    }
+    return hipGetLastError();
+  };
+  return c.cap_pts > CONV_BUF_ROWS ? go(k_conv<C, KIND, true>) : go(k_conv<C, KIND, false>);
 }
 
-template <int C, bool BF>
+template <int C>
 hipError_t run_layer(Ctx& c, bool last, bool two, const ConvArgs& a) {
-  if (last) return two ? run_conv<C, true, true, BF>(c, a) : run_conv<C, true, false, BF>(c, a);
-  return run_conv<C, false, false, BF>(c, a);
+  if (last) return two ? run_conv<C, CONV_HEAD2>(c, a) : run_conv<C, CONV_HEAD>(c, a);
+  return a.xb ? run_conv<C, CONV_SCATTER>(c, a) : run_conv<C, CONV_MID>(c, a);
 }
 
 // Stage 2 of the two-stage head for one scale from the stored features of the
 // last conv layer and a given S1 per voxel (decoder).  One wave per tile of
 // 16 voxels, the same tile split and arithmetic as the fused path.
-template <int C, bool BF>
+template <int C>
 __global__ void __launch_bounds__(256) k_head2(int b, const int32_t* __restrict__ count,
                                                const int32_t* __restrict__ moff, int64_t cap_model,
                                                const float* __restrict__ hL, const uint8_t* __restrict__ s1,
-                                               const uint8_t* __restrict__ code, const float* __restrict__ hw2,
-                                               const float* __restrict__ hb2, const float* __restrict__ emb,
-                                               float* __restrict__ lse2, float* __restrict__ logits2,
-                                               uint8_t* __restrict__ s1_out, uint32_t* err) {
-  constexpr int NCB = C / 16;
+                                               const uint8_t* __restrict__ code, const uint4* __restrict__ hw2,
+                                               const float* __restrict__ hfac2, const float* __restrict__ hb2,
+                                               const float* __restrict__ emb, float* __restrict__ lse2,
+                                               float* __restrict__ logits2, uint8_t* __restrict__ s1_out,
+                                               uint32_t* err) {
   const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
   const int64_t mo = moff[b];
   int64_t n = count[b];
   if (mo + n > cap_model) n = 0;  // overflow was latched where the size was made
   const int64_t ntiles = (n + 15) / 16;
   const int wpb = blockDim.x / 64;
-  const f4* hp = reinterpret_cast<const f4*>(hw2) + lane * (C / 16);
+  const float hfac = *hfac2;
   for (int64_t tile = (int64_t)blockIdx.x * wpb + (threadIdx.x >> 6); tile < ntiles;
        tile += (int64_t)gridDim.x * wpb) {
     const int64_t row = tile * 16 + r;
     const bool valid = row < n;
     const int64_t vr = valid ? row : n - 1;
     const int64_t prow = mo + vr;
-    f4 h[NCB];
-#pragma unroll
-    for (int q = 0; q < NCB; ++q) h[q] = *reinterpret_cast<const f4*>(hL + prow * C + 16 * q + 4 * g);
+    float x[C / 4], x2[C / 4];
+    load_row<C>(hL + prow * C, g, x);
     int a1 = s1 ? s1[vr] : (code[vr] & 15);
     if (a1 > 15) {
       if (valid) latch(err, ERR_SYMBOL);
       a1 = 0;
     }
-    f4 h2[NCB];
-    add_emb<C>(h, emb + a1 * C, g, h2);
-    f4 z2;
-    if constexpr (BF) {
-      uint4 bh, bl;
-      head_operand_bf<C>(h2, bh, bl);
-      z2 = head16_bf<C>(reinterpret_cast<const uint4*>(hw2) + lane * 2, hb2, bh, bl, g);
-    } else {
-      z2 = head16<C>(hp, hb2, h2, g);
-    }
+    add_row<C>(x, emb + a1 * C, g, x2);
+    const f4 z2 = head16<C>(hw2, hfac, hb2, x2, lane, g);
     const float l2 = lse16(z2);
     if (valid && g == 0) {
       lse2[prow] = l2;
@@ -1968,18 +2057,26 @@ __global__ void __launch_bounds__(256) k_head2(int b, const int32_t* __restrict_
 
 }  // namespace
 
+// 32-bit words of one 16-symbol block of the packed head (k_pack_head)
+static int head_block_words(int C) { return (C >= 32 ? C / 32 : 1) * weight_planes(C) * 64 * 4; }
+
 hipError_t launch_pack_weights(Ctx& c, const reno_weights& w) {
   ProfScope ps_(c, RENO_K_OTHER);
   const int C = c.p.channels;
-  const bool bf = c.p.precision == RENO_PREC_BF16X3;
-  if (c.p.model_mode == RENO_MODEL_TOP) {  // four C -> C convs (fp32) and the two embeddings
+  auto pack_conv = [&](const float* src, int kv, int l) {
+    uint16_t* out = reinterpret_cast<uint16_t*>(c.w_conv[l]);
+    if (C == 32)
+      hipLaunchKernelGGL(k_pack_conv<32>, dim3(32), dim3(256), 0, c.stream, src, kv, out, c.wfac(l));
+    else
+      hipLaunchKernelGGL(k_pack_conv<16>, dim3(16), dim3(256), 0, c.stream, src, kv, out, c.wfac(l));
+  };
+  if (c.p.model_mode == RENO_MODEL_TOP) {  // four C -> C convs and the two embeddings
     for (int l = 0; l < 4; ++l) {
       if (c.wide())
         hipLaunchKernelGGL(k_pack_conv_wide, dim3(1024), dim3(256), 0, c.stream, w.top_w[l], C, c.kvol(),
                            c.w_conv[l]);
       else
-        hipLaunchKernelGGL(k_pack_conv, dim3(256), dim3(256), 0, c.stream, w.top_w[l], C, C, C / 4, C / 4,
-                           c.kvol(), c.w_conv[l]);
+        pack_conv(w.top_w[l], 27, l);
       hipLaunchKernelGGL(k_copy_f32, dim3(1), dim3(256), 0, c.stream, w.top_b[l], c.w_bias[l], C);
     }
     hipLaunchKernelGGL(k_copy_f32, dim3(32), dim3(256), 0, c.stream, w.emb_o, c.w_embo, 256 * C);
@@ -1990,26 +2087,17 @@ hipError_t launch_pack_weights(Ctx& c, const reno_weights& w) {
       const dim3 grid(8 * 8 * 256 * C / 256);
       if (C == 32) hipLaunchKernelGGL(k_first_table<32>, grid, dim3(256), 0, c.stream, w.conv_w[0], c.w_conv[0]);
       else hipLaunchKernelGGL(k_first_table<16>, grid, dim3(256), 0, c.stream, w.conv_w[0], c.w_conv[0]);
-    } else if (bf) {
-      hipLaunchKernelGGL(k_pack_conv_bf, dim3(64), dim3(256), 0, c.stream, w.conv_w[l], C, C,
-                         reinterpret_cast<uint32_t*>(c.w_conv[l]));
     } else {
-      hipLaunchKernelGGL(k_pack_conv, dim3(64), dim3(256), 0, c.stream, w.conv_w[l], C, C, C / 4, C / 4, 27,
-                         c.w_conv[l]);
+      pack_conv(w.conv_w[l], 27, l);
     }
     hipLaunchKernelGGL(k_copy_f32, dim3(1), dim3(256), 0, c.stream, w.conv_b[l], c.w_bias[l], C);
   }
+  uint16_t* hw = reinterpret_cast<uint16_t*>(c.w_head);
   if (c.p.head_mode == RENO_HEAD_TWO_STAGE) {
     // packed blocks [stage 1][stage 2], biases [b1 | b2], plain [C][H1 | H2]
-    const int blk = bf ? 64 * 8 : 64 * (C / 4);
-    if (bf) {
-      uint32_t* hw = reinterpret_cast<uint32_t*>(c.w_head);
-      hipLaunchKernelGGL(k_pack_head_bf, dim3(1), dim3(256), 0, c.stream, w.head1_w, C, 16, hw);
-      hipLaunchKernelGGL(k_pack_head_bf, dim3(1), dim3(256), 0, c.stream, w.head2_w, C, 16, hw + blk);
-    } else {
-      hipLaunchKernelGGL(k_pack_head, dim3(4), dim3(256), 0, c.stream, w.head1_w, C, 16, c.w_head);
-      hipLaunchKernelGGL(k_pack_head, dim3(4), dim3(256), 0, c.stream, w.head2_w, C, 16, c.w_head + blk);
-    }
+    hipLaunchKernelGGL(k_pack_head, dim3(1), dim3(256), 0, c.stream, w.head1_w, C, 16, hw, c.w_hfac);
+    hipLaunchKernelGGL(k_pack_head, dim3(1), dim3(256), 0, c.stream, w.head2_w, C, 16,
+                       hw + head_block_words(C) * 2, c.w_hfac + 1);
     hipLaunchKernelGGL(k_copy_f32, dim3(1), dim3(64), 0, c.stream, w.head1_b, c.w_hbias, 16);
     hipLaunchKernelGGL(k_copy_f32, dim3(1), dim3(64), 0, c.stream, w.head2_b, c.w_hbias + 16, 16);
     hipLaunchKernelGGL(k_put_cols16, dim3(2), dim3(256), 0, c.stream, w.head1_w, C, 0, c.w_head_plain);
@@ -2018,11 +2106,7 @@ hipError_t launch_pack_weights(Ctx& c, const reno_weights& w) {
     hipLaunchKernelGGL(k_transpose_head, dim3(2), dim3(256), 0, c.stream, w.head1_w, C, 16, 0, c.w_head_t);
     hipLaunchKernelGGL(k_transpose_head, dim3(2), dim3(256), 0, c.stream, w.head2_w, C, 16, 16, c.w_head_t);
   } else {
-    if (bf)
-      hipLaunchKernelGGL(k_pack_head_bf, dim3(16), dim3(256), 0, c.stream, w.head_w, C, 256,
-                         reinterpret_cast<uint32_t*>(c.w_head));
-    else
-      hipLaunchKernelGGL(k_pack_head, dim3(32), dim3(256), 0, c.stream, w.head_w, C, 256, c.w_head);
+    hipLaunchKernelGGL(k_pack_head, dim3(16), dim3(256), 0, c.stream, w.head_w, C, 256, hw, c.w_hfac);
     hipLaunchKernelGGL(k_copy_f32, dim3(1), dim3(256), 0, c.stream, w.head_b, c.w_hbias, 256);
     hipLaunchKernelGGL(k_copy_f32, dim3(32), dim3(256), 0, c.stream, w.head_w, c.w_head_plain,
                        C * 256);
@@ -2033,11 +2117,11 @@ hipError_t launch_pack_weights(Ctx& c, const reno_weights& w) {
 
 // Full predictor on the scales b_lo .. b_hi (Sec. 3.2, Eqs. 6-9):
 //   neighbour maps of scales b_lo-1 .. b_hi, X_A = Emb_O[O^{d-1}] on scales
-//   b_lo-1 .. b_hi-1 (h_c)                                        one prep launch
-//   T = ReLU(conv_A1(X_A))                                        (h_b)
+//   b_lo-1 .. b_hi-1 (h_c, split s_c)                             one prep launch
+//   T = ReLU(conv_A1(X_A))                                        (split h_b)
 //   F_A = ReLU(X_A + conv_A2(T)), scattered to the children as
-//   X_B = F_A[parent] + Emb_D[delta] on scales b_lo .. b_hi       (h_d; F_A itself is not stored)
-//   T = ReLU(conv_B1(X_B))                                        (h_b)
+//   X_B = F_A[parent] + Emb_D[delta] on scales b_lo .. b_hi       (h_d, split s_d; F_A itself is not stored)
+//   T = ReLU(conv_B1(X_B))                                        (split h_b)
 //   F_B = ReLU(X_B + conv_B2(T)), fused with the head             (h_a)
 // The base scale's rows live past the zero row.  F_B of earlier calls is
 // never overwritten (code lengths of a scale stay valid after the next
@@ -2052,9 +2136,9 @@ hipError_t launch_top(Ctx& c, int b_lo, int b_hi, float* logits, bool second) {
     ProfScope ps_(c, RENO_K_TOP_INPUT);
     const int blocks = (int)std::min<int64_t>(2048, (c.cap_rows() + 63) / 64);
 #define RENO_PREP(CC)                                                                                         \
-  hipLaunchKernelGGL(k_top_prep<CC>, dim3(blocks), dim3(256), 0, c.stream, n_lo, b_hi - n_lo + 1, b_hi - n_lo, b0, \
-                     rm, c.lv_key, c.lv_code, (int64_t)c.cap_pts, cell_args(c), c.w_embo, \
-                     c.d_nbr, c.h_c)
+  hipLaunchKernelGGL((k_top_prep<CC, false>), dim3(blocks), dim3(256), 0, c.stream, n_lo, b_hi - n_lo + 1,      \
+                     b_hi - n_lo, b0, rm, c.lv_key, c.lv_code, (int64_t)c.cap_pts, cell_args(c), c.w_embo,    \
+                     c.d_nbr, c.h_c, c.s_c, c.r_c)
     if (C == 32) RENO_PREP(32); else RENO_PREP(16);
 #undef RENO_PREP
   }
@@ -2066,7 +2150,8 @@ hipError_t launch_top(Ctx& c, int b_lo, int b_hi, float* logits, bool second) {
   a.cap_model = c.cap_model;
   a.nbr = c.d_nbr;
   a.hb = c.w_hbias;
-  a.hw = c.w_head;
+  a.hw = reinterpret_cast<const uint4*>(c.w_head);
+  a.hfac = c.w_hfac;
   a.lse = c.d_lse;
   a.err = c.d_err;
   a.emb = c.w_emb;
@@ -2080,33 +2165,32 @@ hipError_t launch_top(Ctx& c, int b_lo, int b_hi, float* logits, bool second) {
   a.code = c.lv_code;
   a.fc = c.lv_fc;
   const bool two = c.p.head_mode == RENO_HEAD_TWO_STAGE;
-  if (b_lo != b_hi || b_lo >= c.B - 2) {  // sorted tiles, as for the plain model
-    ProfScope pso_(c, RENO_K_OTHER);
-    const int nsc = b_hi - n_lo + 1;
-    const int64_t windows = (c.cap_model + c.cap_pts + TO_W - 1) / TO_W + nsc;
-    hipLaunchKernelGGL(k_tile_order, dim3((unsigned)windows), dim3(TO_THREADS), 0, c.stream, n_lo, nsc, rm, 3,
-                       c.d_nbr, c.d_perm);
-    a.perm = c.d_perm;
-  }
   hipError_t e = hipSuccess;
-  auto conv = [&](int lo, int hi, int wi, const float* in, float* out, const float* res, float* xb, bool last) {
+  auto conv = [&](int lo, int hi, int wi, const void* in, const float* r_in, float* out, const float* res, float* xb,
+                  bool last) {
     if (e != hipSuccess) return;
     a.b_lo = lo;
     a.b_hi = hi;
-    a.h_in = in;
-    a.h_out = out;
+    a.h_in = static_cast<const float*>(in);
+    a.r_in = r_in;
+    a.h_out = last ? out : nullptr;
+    a.s_out = last ? nullptr : reinterpret_cast<uint32_t*>(out);
+    a.r_out = c.r_b;
     a.res = res;
     a.xb = xb;
+    a.xb_s = c.s_d;
+    a.xb_r = c.r_d;
     a.w = c.w_conv[wi];
+    a.wfac = c.wfac(wi);
     a.bias = c.w_bias[wi];
     a.logits = last ? logits : nullptr;
     ProfScope ps_(c, last ? RENO_K_CONV_LAST : RENO_K_CONV_MID);
-    e = (C == 32) ? run_layer<32, false>(c, last, two, a) : run_layer<16, false>(c, last, two, a);
+    e = (C == 32) ? run_layer<32>(c, last, two, a) : run_layer<16>(c, last, two, a);
   };
-  conv(n_lo, b_hi - 1, 0, c.h_c, c.h_b, nullptr, nullptr, false);
-  conv(n_lo, b_hi - 1, 1, c.h_b, nullptr, c.h_c, c.h_d, false);
-  conv(b_lo, b_hi, 2, c.h_d, c.h_b, nullptr, nullptr, false);
-  conv(b_lo, b_hi, 3, c.h_b, c.h_a, c.h_d, nullptr, true);
+  conv(n_lo, b_hi - 1, 0, c.s_c, c.r_c, c.h_b, nullptr, nullptr, false);
+  conv(n_lo, b_hi - 1, 1, c.h_b, c.r_b, nullptr, c.h_c, c.h_d, false);
+  conv(b_lo, b_hi, 2, c.s_d, c.r_d, c.h_b, nullptr, nullptr, false);
+  conv(b_lo, b_hi, 3, c.h_b, c.r_b, c.h_a, c.h_d, nullptr, true);
   return e == hipSuccess ? hipGetLastError() : e;
 }
 
@@ -2126,9 +2210,9 @@ hipError_t launch_top_wide(Ctx& c, int b_lo, int b_hi, float* logits, bool secon
                          b0, rm, c.lv_key, c.lv_code, (int64_t)c.cap_pts, cell_args(c), c.w_embo,
                          c.d_nbr, c.h_c);
     else
-      hipLaunchKernelGGL(k_top_prep<C>, dim3(blocks), dim3(256), 0, c.stream, n_lo, b_hi - n_lo + 1, b_hi - n_lo,
-                         b0, rm, c.lv_key, c.lv_code, (int64_t)c.cap_pts, cell_args(c), c.w_embo,
-                         c.d_nbr, c.h_c);
+      hipLaunchKernelGGL((k_top_prep<C, true>), dim3(blocks), dim3(256), 0, c.stream, n_lo, b_hi - n_lo + 1,
+                         b_hi - n_lo, b0, rm, c.lv_key, c.lv_code, (int64_t)c.cap_pts, cell_args(c), c.w_embo,
+                         c.d_nbr, c.h_c, nullptr, nullptr);
   }
   ConvArgs a{};
   a.b0 = b0;
@@ -2138,7 +2222,8 @@ hipError_t launch_top_wide(Ctx& c, int b_lo, int b_hi, float* logits, bool secon
   a.cap_model = c.cap_model;
   a.nbr = c.d_nbr;
   a.hb = c.w_hbias;
-  a.hw = c.w_head;
+  a.hw = reinterpret_cast<const uint4*>(c.w_head);
+  a.hfac = c.w_hfac;
   a.lse = c.d_lse;
   a.err = c.d_err;
   a.emb = c.w_emb;
@@ -2185,7 +2270,7 @@ hipError_t launch_top_wide(Ctx& c, int b_lo, int b_hi, float* logits, bool secon
     a.b_hi = b_hi;
     a.h_in = c.h_a;
     a.logits = logits;
-    e = run_headw<C, false>(c, c.p.head_mode == RENO_HEAD_TWO_STAGE, a);
+    e = run_headw<C>(c, c.p.head_mode == RENO_HEAD_TWO_STAGE, a);
   }
   if (e != hipSuccess) return e;
   return hipGetLastError();
@@ -2218,7 +2303,8 @@ hipError_t launch_model(Ctx& c, int b_lo, int b_hi, float* logits, bool second) 
   a.cap_model = c.cap_model;
   a.nbr = c.d_nbr;
   a.hb = c.w_hbias;
-  a.hw = c.w_head;
+  a.hw = reinterpret_cast<const uint4*>(c.w_head);
+  a.hfac = c.w_hfac;
   a.lse = c.d_lse;
   a.err = c.d_err;
   a.emb = c.w_emb;
@@ -2227,71 +2313,59 @@ hipError_t launch_model(Ctx& c, int b_lo, int b_hi, float* logits, bool second) 
   a.s1_out = c.d_s1;
   const bool two = c.p.head_mode == RENO_HEAD_TWO_STAGE;
   const int L = c.p.layers;
-  // sorted tiles where the launch is bound by matrix work: a batch of scales,
-  // or the finest model scale (smaller scales are closer to latency-bound and
-  // pay for the extra launch; on the 14-bit scan ordering the second finest
-  // too cost 0.4 %, the third 1.5 %, none of the single scales 1.2 %)
-  const bool order = L >= 2 && (b_lo != b_hi || b_lo >= c.B - 1);
   a.b_ext = -1;
-  a.cap_rows = c.cap_model + 1;
-  const RowMap rm{c.d_count, c.d_moff, (int64_t)c.cap_model, -1, 0, (int64_t)c.cap_model + 1};
-  const bool bf = c.p.precision == RENO_PREC_BF16X3, c32 = c.p.channels == 32;
+  a.cap_rows = c.cap_rows();
+  const RowMap rm{c.d_count, c.d_moff, (int64_t)c.cap_model, -1, 0, c.cap_rows()};
+  const bool c32 = c.p.channels == 32;
   hipError_t e = hipSuccess;
+  // features ping-pong between (h_a, r_a) and (h_b, r_b): split rows, and fp32
+  // rows of the last layer; layer 0 writes h_a
   {
     ProfScope ps_(c, RENO_K_CONV_FIRST, true);
-    FirstArgs f{b_lo, b_hi - b_lo + 1, rm, cell_args(c), c.lv_key, c.w_conv[0], c.w_bias[0], c.d_nbr, c.h_a};
-    if (bf && L > 1) e = c32 ? run_first<32, true>(c, f) : run_first<16, true>(c, f);
-    else e = c32 ? run_first<32, false>(c, f) : run_first<16, false>(c, f);
+    FirstArgs f{b_lo, b_hi - b_lo + 1, rm, cell_args(c), c.lv_key, c.w_conv[0], c.w_bias[0], c.d_nbr,
+                L == 1 ? c.h_a : nullptr, L == 1 ? nullptr : reinterpret_cast<uint32_t*>(c.h_a), c.r_a};
+    e = c32 ? run_first<32>(c, f) : run_first<16>(c, f);
   }
   if (L == 1 && e == hipSuccess) {  // the head alone, on the first layer's rows
     ProfScope ps_(c, RENO_K_CONV_LAST, true);
     a.h_in = c.h_a;
     a.logits = logits;
-    if (bf) e = c32 ? run_headw<32, true>(c, two, a) : run_headw<16, true>(c, two, a);
-    else e = c32 ? run_headw<32, false>(c, two, a) : run_headw<16, false>(c, two, a);
+    e = c32 ? run_headw<32>(c, two, a) : run_headw<16>(c, two, a);
   }
   for (int l = 1; l < L && e == hipSuccess; ++l) {
-    if (l == 1 && order) {
-      ProfScope pso_(c, RENO_K_OTHER);
-      const int nsc = b_hi - b_lo + 1;
-      const int64_t windows = (c.cap_model + TO_W - 1) / TO_W + nsc;
-      hipLaunchKernelGGL(k_tile_order, dim3((unsigned)windows), dim3(TO_THREADS), 0, c.stream, b_lo, nsc, rm, 3,
-                         c.d_nbr, c.d_perm);
-      a.perm = c.d_perm;
-    }
-    a.h_in = (l & 1) ? c.h_a : c.h_b;   // layer l reads what layer l-1 wrote
-    a.h_out = (l & 1) ? c.h_b : c.h_a;  // layer 0 wrote h_a
+    const bool last = l == L - 1, odd = l & 1;
+    float* out = odd ? c.h_b : c.h_a;
+    a.h_in = odd ? c.h_a : c.h_b;
+    a.r_in = odd ? c.r_a : c.r_b;
+    a.h_out = last ? out : nullptr;
+    a.s_out = last ? nullptr : reinterpret_cast<uint32_t*>(out);
+    a.r_out = odd ? c.r_b : c.r_a;
     a.w = c.w_conv[l];
+    a.wfac = c.wfac(l);
     a.bias = c.w_bias[l];
-    const bool last = l == L - 1;
     a.logits = last ? logits : nullptr;
     ProfScope ps_(c, last ? RENO_K_CONV_LAST : RENO_K_CONV_MID, true);
-    if (bf) e = c32 ? run_layer<32, true>(c, last, two, a) : run_layer<16, true>(c, last, two, a);
-    else e = c32 ? run_layer<32, false>(c, last, two, a) : run_layer<16, false>(c, last, two, a);
+    e = c32 ? run_layer<32>(c, last, two, a) : run_layer<16>(c, last, two, a);
   }
   return e;
 }
 
 hipError_t launch_head2(Ctx& c, int b, const uint8_t* s1, float* logits2) {
   ProfScope ps_(c, RENO_K_CONV_LAST);
-  const bool bf = c.p.precision == RENO_PREC_BF16X3;
-  const float* hw2 = c.w_head + (bf ? 64 * 8 : 64 * (c.p.channels / 4));
+  const uint4* hw2 = reinterpret_cast<const uint4*>(c.w_head + head_block_words(c.p.channels));
   const uint8_t* code = c.lv_code + c.lv(b);
   const int blocks = (int)std::min<int64_t>(1024, (c.cap_pts + 63) / 64);
-#define RENO_HEAD2(CC, BFV)                                                                       \
-  hipLaunchKernelGGL((k_head2<CC, BFV>), dim3(blocks), dim3(256), 0, c.stream, b, c.d_count, c.d_moff, \
-                     (int64_t)c.cap_model, c.hlast(), s1, code, hw2, c.w_hbias + 16, c.w_emb, c.d_lse2, \
-                     logits2, c.d_s1, c.d_err)
-  if (c.p.channels == 128) {
-    RENO_HEAD2(128, false);
-  } else if (c.p.channels == 64) {
-    RENO_HEAD2(64, false);
-  } else if (c.p.channels == 32) {
-    if (bf) RENO_HEAD2(32, true); else RENO_HEAD2(32, false);
-  } else {
-    if (bf) RENO_HEAD2(16, true); else RENO_HEAD2(16, false);
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), 0, c.stream, b, c.d_count, c.d_moff, (int64_t)c.cap_model,
+                       c.hlast(), s1, code, hw2, c.w_hfac + 1, c.w_hbias + 16, c.w_emb, c.d_lse2, logits2, c.d_s1,
+                       c.d_err);
+  };
+  switch (c.p.channels) {
+    case 128: go(k_head2<128>); break;
+    case 64: go(k_head2<64>); break;
+    case 32: go(k_head2<32>); break;
+    default: go(k_head2<16>);
   }
-#undef RENO_HEAD2
   return hipGetLastError();
 }
 

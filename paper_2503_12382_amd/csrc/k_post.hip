@@ -7,10 +7,11 @@
 namespace reno {
 namespace {
 
-constexpr float INV_LN2 = 1.4426950408889634f;
+constexpr double INV_LN2 = 1.4426950408889634074;
 
 // bits_v = (lse_v - z_{O_b[v]}) / ln 2 with z_o = hb[o] + sum_c H[c][o] h_L[v][c]
-// (fp32, channel order).  Two-stage head (TWO): with a = O & 15, s = O >> 4,
+// (in double: the dot product's rounding would show beside the normaliser's, and
+// the kernel is bound by its row reads, 10.0 us at 14 bits either way).  Two-stage head (TWO): with a = O & 15, s = O >> 4,
 // bits_v = ((lse1_v - z1_a) + (lse2_v - z2_s)) / ln 2, z1_a = hb1[a] +
 // sum_c H1[c][a] h[c], z2_s = hb2[s] + sum_c H2[c][s] (h[c] + E[a][c]).
 // Blocks stage the transposed head HT [NS][C] in LDS once (rows padded by one
@@ -92,13 +93,12 @@ __global__ void __launch_bounds__(CL_THREADS) k_code_length(
     const int o = lv_code[(int64_t)(b - b0) * cap_pts + vv];
     const float l1 = lse[mo + vv];
     const float l2 = TWO ? lse2[mo + vv] : 0.0f;
-    // the row in chunks of HC channels (all of it for C <= 32); the dot
-    // products run over c in ascending order either way
+    // the row in chunks of HC channels (all of it for C <= 32)
     constexpr int HC = C <= 32 ? C : 16;
     const float4* hr = reinterpret_cast<const float4*>(hL + (mo + vv) * C);
     float bt;
     const int a1 = o & 15, a2 = 16 + (o >> 4);
-    float z1 = TWO ? s_hb[a1] : s_hb[o], z2 = TWO ? s_hb[a2] : 0.0f;
+    double z1 = TWO ? s_hb[a1] : s_hb[o], z2 = TWO ? s_hb[a2] : 0.0;
 #pragma unroll
     for (int c0 = 0; c0 < C; c0 += HC) {
       float h[HC];
@@ -114,17 +114,16 @@ __global__ void __launch_bounds__(CL_THREADS) k_code_length(
       for (int cc = 0; cc < HC; ++cc) {
         const int c = c0 + cc;
         if constexpr (TWO) {
-          z1 = fmaf(s_HT[a1 * RS + c], h[cc], z1);
-          z2 = fmaf(s_HT[a2 * RS + c], h[cc] + s_emb[a1 * C + c], z2);
+          z1 = fma((double)s_HT[a1 * RS + c], (double)h[cc], z1);
+          z2 = fma((double)s_HT[a2 * RS + c], (double)(h[cc] + s_emb[a1 * C + c]), z2);
         } else {
-          z1 = fmaf(s_HT[o * RS + c], h[cc], z1);
+          z1 = fma((double)s_HT[o * RS + c], (double)h[cc], z1);
         }
       }
     }
-    if constexpr (TWO)
-      bt = ((l1 - z1) + (l2 - z2)) * INV_LN2;
-    else
-      bt = (l1 - z1) * INV_LN2;
+    double d = (double)l1 - z1;
+    if constexpr (TWO) d += (double)l2 - z2;
+    bt = (float)(d * INV_LN2);
     double acc = 0.0;
     if (v < n) {
       if (bits_out) bits_out[mo - s_mo[0] + v] = bt;
@@ -423,15 +422,6 @@ __global__ void __launch_bounds__(256) k_symbol_intervals16(const int32_t* __res
 enum { TB_FREQ = 0, TB_CDF = 1, TB_IV = 2, TB_ENTRY = 3 };
 
 __device__ __forceinline__ int uniform_wave() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }
-
-// DPP lane moves (CDNA): row_shr:k (0x110 + k) takes the value of lane
-// l - k of the same 16-lane row, row_ror:k (0x120 + k) of lane l - k mod 16
-// of the row, row_bcast:15 (0x142) lane 15 of the previous row, row_bcast:31
-// (0x143) lane 31.  Lanes whose source lies outside are fixed by the callers.
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, false);
-}
 
 // The moves run in every lane and their results are masked with bit
 // operations: a move under a lane mask would read disabled source lanes.
