@@ -51,9 +51,10 @@ void free_all(Ctx* c) {
                   c->d_count,   c->d_moff,   c->d_err,    c->d_hist,    c->d_ticket,
                   c->d_status, c->d_hash,   c->d_hreg,   c->h_a,      c->h_b,      c->d_nbr,     c->d_lse,
                   c->d_partial, c->d_total, c->w_head,   c->w_hbias,  c->w_head_plain,
-                  c->d_lse2,    c->w_emb,   c->d_s1,     c->w_head_t, c->d_perm,
+                  c->d_lse2,    c->w_emb,   c->d_s1,     c->w_head_t, c->d_perm, c->d_next,
                   c->h_c,       c->h_d,     c->w_embo,   c->w_embd,   c->s_c,     c->s_d,
-                  c->r_a,       c->r_b,     c->r_c,      c->r_d,      c->w_wfac,  c->w_hfac};
+                  c->r_a,       c->r_b,     c->r_c,      c->r_d,      c->w_wfac,  c->w_hfac,
+                  c->w_part};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   for (int l = 0; l < RENO_MAX_LAYERS; ++l) {
@@ -207,8 +208,8 @@ reno_status reno_create(const reno_params* p, void* hip_stream, reno_ctx** out) 
   A(dalloc(&c->r_b, rows, &c->device_bytes));
   A(dalloc(&c->w_wfac, (size_t)RENO_MAX_LAYERS * 128, &c->device_bytes));
   A(dalloc(&c->w_hfac, 2, &c->device_bytes));
-  const bool top_split = top && !c->wide();
-  if (top_split) {
+  A(dalloc(&c->w_part, (size_t)64 * 128, &c->device_bytes));
+  if (top) {
     A(dalloc(&c->s_c, rows * C, &c->device_bytes));
     A(dalloc(&c->s_d, rows * C, &c->device_bytes));
     A(dalloc(&c->r_c, rows, &c->device_bytes));
@@ -224,6 +225,7 @@ reno_status reno_create(const reno_params* p, void* hip_stream, reno_ctx** out) 
   A(dalloc(&c->d_lse, (size_t)cap_model, &c->device_bytes));
   A(dalloc(&c->d_lse2, (size_t)cap_model, &c->device_bytes));
   A(dalloc(&c->d_perm, rows, &c->device_bytes));
+  A(dalloc(&c->d_next, 32, &c->device_bytes));
   A(dalloc(&c->d_s1, (size_t)cap_model, &c->device_bytes));
   A(dalloc(&c->d_partial, (size_t)reno::NLEV * ((c->cap_pts + 63) / 64), &c->device_bytes));
   A(dalloc(&c->d_total, reno::NLEV, &c->device_bytes));
@@ -260,9 +262,9 @@ reno_status reno_create(const reno_params* p, void* hip_stream, reno_ctx** out) 
     e = hipMemsetAsync(c->h_c + (size_t)cap_model * C, 0, sizeof(float) * C, c->stream);
   if (e == hipSuccess && top)
     e = hipMemsetAsync(c->h_d + (size_t)cap_model * C, 0, sizeof(float) * C, c->stream);
-  if (e == hipSuccess && top_split)
+  if (e == hipSuccess && top)
     e = hipMemsetAsync(c->s_c + (size_t)cap_model * C, 0, sizeof(float) * C, c->stream);
-  if (e == hipSuccess && top_split)
+  if (e == hipSuccess && top)
     e = hipMemsetAsync(c->s_d + (size_t)cap_model * C, 0, sizeof(float) * C, c->stream);
   for (float* r : {c->r_a, c->r_b, c->r_c, c->r_d})  // the zero rows' factors
     if (e == hipSuccess && r) e = hipMemsetAsync(r + cap_model, 0, sizeof(float), c->stream);

@@ -84,7 +84,7 @@ struct Ctx {
   float* h_b = nullptr;
   float* h_c = nullptr;         // full predictor: X_A = Emb_O[O] of the parent scales (with a zero row)
   float* h_d = nullptr;         // full predictor: X_B of the target scales (with a zero row)
-  uint32_t* s_c = nullptr;      // full predictor of k_conv: X_A and X_B as split rows
+  uint32_t* s_c = nullptr;      // full predictor: X_A and X_B as split rows
   uint32_t* s_d = nullptr;
   float* r_a = nullptr;         // [cap_rows] each
   float* r_b = nullptr;
@@ -92,6 +92,7 @@ struct Ctx {
   float* r_d = nullptr;
   int32_t* d_nbr = nullptr;     // [cap_rows][nbr_stride()]
   int32_t* d_perm = nullptr;    // [cap_rows] tile order of the streamed-weight conv layers
+  uint32_t* d_next = nullptr;   // their work counters [layer][XCD]
   float* d_lse = nullptr;       // [cap_model] (two-stage head: stage 1)
   float* d_lse2 = nullptr;      // [cap_model] stage 2 of the two-stage head
   uint8_t* d_s1 = nullptr;      // [cap_model] S1 that stage 2 was evaluated with
@@ -106,6 +107,7 @@ struct Ctx {
   float* w_bias[RENO_MAX_LAYERS] = {};
   float* w_wfac = nullptr;      // factors of the split conv weights [layer][128]
   float* w_hfac = nullptr;      // factors of the split head matrices [2]
+  float* w_part = nullptr;      // partial maxima of a conv layer's channels while its weights are packed [64][128]
   float* w_head = nullptr;
   float* w_hbias = nullptr;
   float* w_head_plain = nullptr;  // [C][256] as given (two-stage: [C][H1 | H2]), for code lengths

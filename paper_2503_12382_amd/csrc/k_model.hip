@@ -39,10 +39,6 @@ __host__ __device__ constexpr int weight_planes(int C) { return C == 16 ? 3 : 2;
 constexpr int CONV_THREADS = 1024;
 constexpr int CONV_WAVES = CONV_THREADS / 64;
 
-__device__ __forceinline__ f4 mfma4(float a, float b, f4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
 // ---- split-fp16 arithmetic ----
 // A row x of fp32 features is carried as x = f (hi + lo): f the power of two
 // that brings the row's largest entry to [2^14, 2^15), hi = fp16(x / f) and lo
@@ -103,19 +99,16 @@ __device__ __forceinline__ float row_split(const float (&x)[N], uint32_t (&hi)[N
 
 // Largest magnitude over the block's threads (NaN passes through as NaN, so
 // that a broken weight shows in the results instead of vanishing in a maximum).
-__device__ __forceinline__ float block_absmax(float m, bool bad, float* s_m) {
-  for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-  if (__any(bad)) m = NAN;
+__device__ __forceinline__ float absmax(float m, float w) { return w != w || m != m ? NAN : fmaxf(m, fabsf(w)); }
+
+__device__ __forceinline__ float block_absmax(float m, float* s_m) {
+  for (int o = 32; o > 0; o >>= 1) m = absmax(m, __shfl_xor(m, o));
   __syncthreads();
   if ((threadIdx.x & 63) == 0) s_m[threadIdx.x >> 6] = m;
   __syncthreads();
   float t = 0.0f;
-  bool nan = false;
-  for (unsigned i = 0; i < blockDim.x / 64; ++i) {
-    t = fmaxf(t, s_m[i]);
-    nan = nan || s_m[i] != s_m[i];
-  }
-  return nan ? NAN : t;
+  for (unsigned i = 0; i < blockDim.x / 64; ++i) t = absmax(t, s_m[i]);
+  return t;
 }
 
 // Factors of a weight matrix or channel (split_scale); infinite or NaN weights
@@ -128,37 +121,49 @@ __device__ __forceinline__ void weight_scale(float m, float& mul, float& fac) {
   }
 }
 
-// Conv layer W [kv][C][C], one block per output channel co: its factor and the
-// split A operands.  Lane l = (m, g) of column block cb carries output channel
-// co = 8 (m / 4) + 4 cb + m % 4 (C = 32; C = 16: co = m), so that the lane
-// (r, g) that ends with rows 4g .. 4g + 3 of every column block holds
-// consecutive channels of voxel r.  K slot 8g + j: C = 32 input channel 8g +
-// j, planes [hi][lo]; C = 16 the two halves of a gathered row [16 hi][16 lo],
-// planes [W1 | W1], [W2 | W2] and [W3 | W3].  Packed [kv][C/16][plane][64][8] fp16.
-template <int C>
-__global__ void __launch_bounds__(256) k_pack_conv(const float* __restrict__ W, int kv, uint16_t* __restrict__ out,
-                                                   float* __restrict__ fac_out) {
-  constexpr int NCB = C / 16, PL = weight_planes(C);
-  __shared__ float s_m[4];
-  const int co = blockIdx.x, n = kv * C;
+// Largest magnitude of every output channel of W [n][C] over each block's share
+// of the n rows: part [gridDim.x][C].
+constexpr int WMAX_BLOCKS = 64;
+__global__ void __launch_bounds__(256) k_weight_max(const float* __restrict__ W, int n, int C, float* __restrict__ part) {
+  __shared__ float s_m[256];
+  const int co = threadIdx.x % C, per = 256 / C;
   float m = 0.0f;
-  bool bad = false;
-  for (int i = threadIdx.x; i < n; i += 256) {
-    const float w = W[(size_t)i * C + co];
-    m = fmaxf(m, fabsf(w));
-    bad = bad || w != w;
+  for (int i = blockIdx.x * per + threadIdx.x / C; i < n; i += gridDim.x * per) m = absmax(m, W[(size_t)i * C + co]);
+  s_m[threadIdx.x] = m;
+  __syncthreads();
+  if ((int)threadIdx.x >= C) return;
+  for (int j = 1; j < per; ++j) m = absmax(m, s_m[j * C + co]);
+  part[(size_t)blockIdx.x * C + co] = m;
+}
+
+// Conv layer W [kv][C][C]: the output channels' factors (from k_weight_max) and
+// the split A operands.  Lane l = (m, g) of column block cb carries an output
+// channel such that the lane (r, g) that ends with rows 4g .. 4g + 3 of the
+// column blocks holds channels 32 ch + 8g .. + 7 of voxel r (C = 16: channel m).
+// K slot 8g + j: C >= 32 input channel 32 ch + 8g + j of piece ch, planes
+// [hi][lo]; C = 16 the two halves of a gathered row [16 hi][16 lo], planes
+// [W1 | W1], [W2 | W2] and [W3 | W3].  Packed [kv][C/16][ch][plane][64][8] fp16.
+template <int C>
+__global__ void __launch_bounds__(256) k_pack_conv(const float* __restrict__ W, int kv, const float* __restrict__ part,
+                                                   uint16_t* __restrict__ out, float* __restrict__ fac_out) {
+  constexpr int NCB = C / 16, NCH = C >= 32 ? C / 32 : 1, PL = weight_planes(C);
+  __shared__ float s_mul[C];
+  if ((int)threadIdx.x < C) {
+    float m = 0.0f, mul, fac;
+    for (int i = 0; i < WMAX_BLOCKS; ++i) m = absmax(m, part[i * C + threadIdx.x]);
+    weight_scale(m, mul, fac);
+    s_mul[threadIdx.x] = mul;
+    if (blockIdx.x == 0) fac_out[threadIdx.x] = fac;
   }
-  float mul, fac;
-  weight_scale(block_absmax(m, bad, s_m), mul, fac);
-  if (threadIdx.x == 0) fac_out[co] = fac;
-  const int cb = C == 32 ? (co >> 2) & 1 : 0;
-  const int row = C == 32 ? 4 * (co >> 3) + (co & 3) : co;  // m of the A operand
-  for (int i = threadIdx.x; i < n; i += 256) {
-    const int k = i / C, ci = i % C;
-    const float v = W[(size_t)i * C + co] * mul;
-    uint16_t* o = out + (size_t)(k * NCB + cb) * PL * 64 * 8;
-    const int at = ((ci >> 3) * 16 + row) * 8 + (ci & 7);  // lane (row, ci / 8), slot ci % 8
-    float rest = v;
+  __syncthreads();
+  const int64_t n = (int64_t)kv * C * C;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+    const int co = (int)(i % C), ci = (int)(i / C % C), k = (int)(i / (C * C));
+    const int cb = C >= 32 ? 2 * (co >> 5) + ((co >> 2) & 1) : 0;
+    const int row = C >= 32 ? 4 * ((co & 31) >> 3) + (co & 3) : co;  // m of the A operand
+    uint16_t* o = out + ((size_t)(k * NCB + cb) * NCH + (C >= 32 ? ci >> 5 : 0)) * PL * 64 * 8;
+    const int at = (((ci & 31) >> 3) * 16 + row) * 8 + (ci & 7);  // lane (row, group of ci), slot ci % 8
+    float rest = W[i] * s_mul[co];
 #pragma unroll
     for (int pl = 0; pl < PL; ++pl) {
       const _Float16 h = (_Float16)rest;
@@ -166,25 +171,6 @@ __global__ void __launch_bounds__(256) k_pack_conv(const float* __restrict__ W, 
       o[pl * 64 * 8 + at] = __builtin_bit_cast(uint16_t, h);
       if (C == 16) o[pl * 64 * 8 + at + 2 * 16 * 8] = __builtin_bit_cast(uint16_t, h);  // groups 2, 3: the row's lo half
     }
-  }
-}
-
-// Conv weights W [kv][C][C] for the streamed-weight kernel: the operands of
-// k_pack_conv (lane (r, g), step s = 4q + e: W[ci = g*KS + s][co = 16cb + r],
-// KS = C/4), stored lane-fastest as 16-byte words [kv][C/16][KS/4][64], so a
-// wave's LDS reads of one (cb, q) are 64 consecutive words (no bank conflicts).
-__global__ void k_pack_conv_wide(const float* __restrict__ W, int C, int kv, float* __restrict__ out) {
-  const int ncb = C / 16, KS = C / 4, nq = KS / 4;
-  const int total = kv * C * C;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += gridDim.x * blockDim.x) {
-    const int e = i % 4;
-    const int lane = (i / 4) % 64;
-    const int q = (i / 256) % nq;
-    const int cb = (i / (256 * nq)) % ncb;
-    const int k = i / (256 * nq * ncb);
-    const int ci = (lane >> 4) * KS + 4 * q + e;
-    const int co = cb * 16 + (lane & 15);
-    out[i] = W[((size_t)k * C + ci) * C + co];
   }
 }
 
@@ -199,13 +185,9 @@ __global__ void __launch_bounds__(256) k_pack_head(const float* __restrict__ H, 
                                                    uint16_t* __restrict__ out, float* __restrict__ fac_out) {
   __shared__ float s_m[4];
   float m = 0.0f;
-  bool bad = false;
-  for (int i = threadIdx.x; i < C * NS; i += 256) {
-    m = fmaxf(m, fabsf(H[i]));
-    bad = bad || H[i] != H[i];
-  }
+  for (int i = threadIdx.x; i < C * NS; i += 256) m = absmax(m, H[i]);
   float mul, fac;
-  weight_scale(block_absmax(m, bad, s_m), mul, fac);
+  weight_scale(block_absmax(m, s_m), mul, fac);
   if (blockIdx.x == 0 && threadIdx.x == 0) *fac_out = fac;
   const int nch = C >= 32 ? C / 32 : 1, sb = blockIdx.x, planes = weight_planes(C);
   for (int i = threadIdx.x; i < nch * 64 * 8; i += 256) {
@@ -323,6 +305,19 @@ __device__ __forceinline__ void load_row(const float* __restrict__ row, int g, f
     }
 }
 
+// Stores a lane's entries of a row of C floats.
+template <int C>
+__device__ __forceinline__ void store_row(const float (&x)[C / 4], int g, float* __restrict__ row) {
+  constexpr int Q = C >= 32 ? 2 : 1;
+#pragma unroll
+  for (int ch = 0; ch < (C >= 32 ? C / 32 : 1); ++ch)
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int i = 8 * ch + 4 * q;
+      *reinterpret_cast<f4*>(row + 32 * ch + 4 * Q * g + 4 * q) = f4{x[i], x[i + 1], x[i + 2], x[i + 3]};
+    }
+}
+
 // x + the same entries of another row (Emb(S1), Emb_D).
 template <int C>
 __device__ __forceinline__ void add_row(const float (&x)[C / 4], const float* __restrict__ row, int g,
@@ -344,13 +339,14 @@ struct ConvArgs {
   const int32_t* moff;
   int64_t cap_pts, cap_model;
   const int32_t* nbr;     // neighbour map [rows][stride]
-  const float* h_in;      // conv input: split rows (k_conv), fp32 rows (k_convw, k_headw); row cap_model all zero
+  const float* h_in;      // conv input: split rows (k_headw: fp32 rows); row cap_model all zero
   const float* r_in;      // factors of the split rows
   float* h_out;           // fp32 output rows [rows][C], or NULL
   uint32_t* s_out;        // split output rows, or NULL
   float* r_out;           // their factors
+  uint32_t* next;         // groups taken of each XCD's share [8], zero at launch (k_convw)
   const float* w;         // packed conv weights
-  const float* wfac;      // their factors [C] (k_conv)
+  const float* wfac;      // their factors [C]
   const float* bias;      // [C]
   const uint4* hw;        // packed head weights (last layer)
   const float* hfac;      // their factors: one per head matrix
@@ -372,7 +368,7 @@ struct ConvArgs {
   // replication + octant embedding fused into the epilogue (Eqs. 7-8): each
   // voxel's result F, plus Emb_D[delta], goes to the rows of its children
   float* xb;              // child rows' input X_B (rows of scale b + 1), or NULL
-  uint32_t* xb_s;         // X_B as split rows (k_conv)
+  uint32_t* xb_s;         // X_B as split rows
   float* xb_r;            // their factors
   const float* emb_d;     // [8][C]
   const uint8_t* code;    // per-scale regions: O_b
@@ -717,15 +713,18 @@ __device__ __forceinline__ void head_epilogue(const ConvArgs& a, const float (&x
   }
 }
 
+// The k-th tile of an XCD's share.
+__device__ __forceinline__ int64_t xcd_tile(int xcd, int64_t k, int64_t tch) {
+  return ((k / tch) * 8 + xcd) * tch + k % tch;
+}
+
 // Tile of a block's slot, XCD-aware: workgroups are dealt round-robin to the
 // 8 XCDs (block b runs on XCD b % 8), so chunks of tch consecutive tiles are
 // dealt to the XCDs in turn and the blocks of one XCD sweep that XCD's chunks
 // together: tiles that gather the same neighbour rows run on one L2 at about
 // the same time.  Increasing in the slot for a fixed block.
 __device__ __forceinline__ int64_t conv_tile(int64_t slot, int64_t tch) {
-  const int64_t xcd = blockIdx.x & 7, j = blockIdx.x >> 3, nb = gridDim.x >> 3;
-  const int64_t k = j + nb * slot;  // the XCD's k-th tile
-  return ((k / tch) * 8 + xcd) * tch + k % tch;
+  return xcd_tile(blockIdx.x & 7, (blockIdx.x >> 3) + (int64_t)(gridDim.x >> 3) * slot, tch);
 }
 
 // Offsets of group i of the conv's fixed summation order: k in [7i, 7i + 7),
@@ -736,8 +735,8 @@ __device__ __forceinline__ uint32_t group_offsets(int i) {
 }
 
 // Split row of C channels: [C fp16 hi][C fp16 lo], C 32-bit words.  The slice a
-// lane feeds: C = 32 channels 8g .. 8g + 7 of both planes; C = 16 the 8 halves
-// 8g .. 8g + 7 of the whole row (K slots of k_pack_conv).
+// lane of k_conv feeds: C = 32 channels 8g .. 8g + 7 of both planes; C = 16 the 8
+// halves 8g .. 8g + 7 of the whole row (K slots of k_pack_conv).
 template <int C>
 struct SplitRow {
   uint4 hi, lo;  // C = 16: hi alone
@@ -749,9 +748,13 @@ template <int C, int STEP = 16>
 __device__ __forceinline__ void store_split(const float (&x)[C / 4], int g, uint32_t* row, float* fac) {
   uint32_t h[C / 8], l[C / 8];
   const float f = row_split<C / 4, STEP>(x, h, l);
-  if constexpr (C == 32) {
-    *reinterpret_cast<uint4*>(row + 4 * g) = make_uint4(h[0], h[1], h[2], h[3]);
-    *reinterpret_cast<uint4*>(row + 16 + 4 * g) = make_uint4(l[0], l[1], l[2], l[3]);
+  if constexpr (C >= 32) {
+#pragma unroll
+    for (int ch = 0; ch < C / 32; ++ch) {
+      *reinterpret_cast<uint4*>(row + 16 * ch + 4 * g) = make_uint4(h[4 * ch], h[4 * ch + 1], h[4 * ch + 2], h[4 * ch + 3]);
+      *reinterpret_cast<uint4*>(row + C / 2 + 16 * ch + 4 * g) =
+          make_uint4(l[4 * ch], l[4 * ch + 1], l[4 * ch + 2], l[4 * ch + 3]);
+    }
   } else {
     *reinterpret_cast<uint2*>(row + 2 * g) = make_uint2(h[0], h[1]);
     *reinterpret_cast<uint2*>(row + 8 + 2 * g) = make_uint2(l[0], l[1]);
@@ -963,20 +966,14 @@ __device__ __forceinline__ void conv_epilogue(const ConvArgs& a, const f4 (&sum)
         const int64_t row = cmo + first + rank;
         float y[N];
         add_row<C>(x, a.emb_d + d * C, g, y);
-#pragma unroll
-        for (int q = 0; q < N / 4; ++q)
-          *reinterpret_cast<f4*>(a.xb + row * C + N * g + 4 * q) = f4{y[4 * q], y[4 * q + 1], y[4 * q + 2], y[4 * q + 3]};
+        store_row<C>(y, g, a.xb + row * C);
         store_split<C>(y, g, a.xb_s + row * C, a.xb_r + row);
         ++rank;
       }
     }
   }
   if (a.s_out) store_split<C>(x, g, a.s_out + tr.prow * C, a.r_out + tr.prow);
-  if (a.h_out) {
-#pragma unroll
-    for (int q = 0; q < N / 4; ++q)
-      *reinterpret_cast<f4*>(a.h_out + tr.prow * C + N * g + 4 * q) = f4{x[4 * q], x[4 * q + 1], x[4 * q + 2], x[4 * q + 3]};
-  }
+  if (a.h_out) store_row<C>(x, g, a.h_out + tr.prow * C);
 }
 
 // A sparse 3x3x3 conv layer C -> C (bias, optional residual, ReLU), the last
@@ -1161,18 +1158,22 @@ __global__ void __launch_bounds__(CONV_THREADS) k_conv(ConvArgs a) {
 // 2.4x -> 1.6x the occupied pairs).  A voxel's result does not depend on which
 // voxels share its tile (absent offsets add exact zeros), so any order, even
 // the arrival order inside a group, gives the same outputs.  One block per
-// window: counting sort in LDS.
+// window: counting sort in LDS.  The first block also clears the work counters
+// of the launches that follow.
 constexpr int TO_W = 2048;
 constexpr int TO_THREADS = 1024;
 constexpr int TO_KEYS = 2048;
+constexpr int CW_LAYERS = 4;  // launches of k_convw that follow
 
 __global__ void __launch_bounds__(TO_THREADS) k_tile_order(int b_lo, int nsc, RowMap rm, int ks,
-                                                           const int32_t* __restrict__ nbr, int32_t* __restrict__ perm) {
+                                                           const int32_t* __restrict__ nbr, int32_t* __restrict__ perm,
+                                                           uint32_t* __restrict__ next) {
   __shared__ uint32_t s_cnt[TO_KEYS];
   __shared__ uint32_t s_wsum[TO_THREADS / 64];
   __shared__ int64_t s_n[NLEV], s_mo[NLEV];
   __shared__ int64_t s_w0, s_wmo, s_wn;
   const int tid = threadIdx.x;
+  if (blockIdx.x == 0 && tid < CW_LAYERS * 8) next[tid] = 0u;
   if (tid < nsc) {  // sizes of the launch's scales, loaded in parallel
     int64_t mo, n;
     scale_span(rm, b_lo + tid, mo, n);
@@ -1305,8 +1306,18 @@ __device__ __forceinline__ void base_cell_rows(uint64_t kf, int b, int g, const 
   for (int j = 0; j < 8; ++j) nb[j] = (ok[j] && keys[at[j]] == want[j]) ? (int32_t)at[j] : -1;
 }
 
-// WIDE: the inputs of k_convw (plain map rows, X_A in fp32); else those of
-// k_conv (map rows of store_map, X_A also as split rows).
+// X_A = Emb_O[code] at a row, in fp32 (the residual) and split (the conv's
+// input); lanes 4r + g.
+template <int C>
+__device__ __forceinline__ void embed_row(const float* __restrict__ emb, int g, int64_t row, float* __restrict__ X,
+                                          uint32_t* __restrict__ XS, float* __restrict__ XR) {
+  float x[C / 4];
+  load_row<C>(emb, g, x);
+  store_row<C>(x, g, X + row * C);
+  store_split<C, 1>(x, g, XS + row * C, XR + row);
+}
+
+// WIDE: plain map rows, as k_convw reads them; else those of store_map (k_conv).
 template <int C, bool WIDE>
 __global__ void __launch_bounds__(256) k_top_prep(int lo, int nsc, int n_embed, int b0, RowMap rm,
                                                   const uint64_t* __restrict__ lv_key,
@@ -1314,7 +1325,6 @@ __global__ void __launch_bounds__(256) k_top_prep(int lo, int nsc, int n_embed, 
                                                   CellArgs cells, const float* __restrict__ emb_o, int32_t* __restrict__ nbr,
                                                   float* __restrict__ X, uint32_t* __restrict__ XS,
                                                   float* __restrict__ XR) {
-  constexpr int Q = C / 16;  // f4 per lane of a row
   __shared__ uint64_t s_par[4][16][9];  // rows padded: the 16 voxels' cells in different banks
   __shared__ int64_t s_n[32], s_mo[32], s_tpre[32];
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
@@ -1358,19 +1368,7 @@ __global__ void __launch_bounds__(256) k_top_prep(int lo, int nsc, int n_embed, 
     } else {
       store_map(nbr, mo + vr, valid, g, nb);
     }
-    if (valid && si < n_embed) {
-      const f4* e = reinterpret_cast<const f4*>(emb_o + (int)lv_code[lvb + vr] * C) + g * Q;
-      f4* xr = reinterpret_cast<f4*>(X + (mo + vr) * C) + g * Q;
-      float x[C / 4];
-#pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        const f4 t = e[q];
-        xr[q] = t;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) x[4 * q + i] = t[i];
-      }
-      if constexpr (!WIDE) store_split<C, 1>(x, g, XS + (mo + vr) * C, XR + mo + vr);
-    }
+    if (valid && si < n_embed) embed_row<C>(emb_o + (int)lv_code[lvb + vr] * C, g, mo + vr, X, XS, XR);
   }
 }
 
@@ -1460,8 +1458,8 @@ __global__ void __launch_bounds__(256) k_top_prep5(int lo, int nsc, int n_embed,
                                                    const uint64_t* __restrict__ lv_key,
                                                    const uint8_t* __restrict__ lv_code, int64_t cap_pts,
                                                    CellArgs cells, const float* __restrict__ emb_o, int32_t* __restrict__ nbr,
-                                                   float* __restrict__ X) {
-  constexpr int Q = C / 16;
+                                                   float* __restrict__ X, uint32_t* __restrict__ XS,
+                                                   float* __restrict__ XR) {
   __shared__ uint64_t s_par[4][16][27];
   __shared__ int64_t s_n[32], s_mo[32], s_tpre[32];
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, r = lane >> 2, g = lane & 3;
@@ -1499,12 +1497,7 @@ __global__ void __launch_bounds__(256) k_top_prep5(int lo, int nsc, int n_embed,
       int4* dst = reinterpret_cast<int4*>(nbr + (mo + vr) * 128 + 32 * g);
 #pragma unroll
       for (int q = 0; q < 8; ++q) dst[q] = make_int4(nb[4 * q], nb[4 * q + 1], nb[4 * q + 2], nb[4 * q + 3]);
-      if (si < n_embed) {
-        const f4* e = reinterpret_cast<const f4*>(emb_o + (int)lv_code[lvb + vr] * C) + g * Q;
-        f4* xr = reinterpret_cast<f4*>(X + (mo + vr) * C) + g * Q;
-#pragma unroll
-        for (int q = 0; q < Q; ++q) xr[q] = e[q];
-      }
+      if (si < n_embed) embed_row<C>(emb_o + (int)lv_code[lvb + vr] * C, g, mo + vr, X, XS, XR);
     }
   }
 }
@@ -1532,34 +1525,137 @@ struct OffMask {
   }
 };
 
-constexpr int CW_THREADS = 512;
+constexpr int cw_waves(int C) { return C == 128 ? 16 : 8; }         // waves (tiles of a group) of a block
+constexpr unsigned cw_blocks(int C) { return C == 128 ? 256 : 512; }  // 16 waves of 128 registers on each CU
 constexpr int CW_SPLIT_ROUNDS = 2;  // column split while a block has at most this many tile sets
-constexpr int CW_WAVES = CW_THREADS / 64;
+
+// The rows of one offset's neighbours as a lane's operands (k_conv's layout,
+// one piece per 32 input channels).
+template <int C>
+struct WideRows {
+  static constexpr int NCH = C >= 32 ? C / 32 : 1;
+  uint4 hi[NCH], lo[C >= 32 ? NCH : 1];
+  float fac = 0.0f;
+  __device__ __forceinline__ void clear() {
+#pragma unroll
+    for (int ch = 0; ch < NCH; ++ch) hi[ch] = make_uint4(0u, 0u, 0u, 0u);
+    if constexpr (C >= 32) {
+#pragma unroll
+      for (int ch = 0; ch < NCH; ++ch) lo[ch] = make_uint4(0u, 0u, 0u, 0u);
+    }
+  }
+  // row < 0: absent, nothing is loaded; the (finite) rows held stay, against the factor 0
+  __device__ __forceinline__ void load(const ConvArgs& a, int64_t row, int g) {
+    fac = 0.0f;
+    if (row < 0) return;
+    const uint4* src = reinterpret_cast<const uint4*>(a.h_in + row * C) + g;
+#pragma unroll
+    for (int ch = 0; ch < NCH; ++ch) {
+      hi[ch] = src[4 * ch];
+      if constexpr (C >= 32) lo[ch] = src[C / 8 + 4 * ch];
+    }
+    fac = a.r_in[row];
+  }
+};
+
+// acc += fac W_k^T rows for N column blocks, wb their packed operands of the
+// offset ([block][32-channel piece][plane][64]); a piece's smallest products first.
+template <int C, int N>
+__device__ __forceinline__ void wide_mma(const uint4* wb, int lane, const WideRows<C>& x, f4* acc) {
+  constexpr int NCH = WideRows<C>::NCH, PL = weight_planes(C);
+  f4 p[N];
+#pragma unroll
+  for (int q = 0; q < N; ++q) p[q] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+  auto w = [&](int q, int ch, int pl) { return wb[((q * NCH + ch) * PL + pl) * 64 + lane]; };
+  if constexpr (C >= 32) {
+#pragma unroll
+    for (int ch = 0; ch < NCH; ++ch) {
+      uint4 wh[N];
+#pragma unroll
+      for (int q = 0; q < N; ++q) p[q] = mfma_h(w(q, ch, 1), x.hi[ch], p[q]);
+#pragma unroll
+      for (int q = 0; q < N; ++q) {
+        wh[q] = w(q, ch, 0);
+        p[q] = mfma_h(wh[q], x.lo[ch], p[q]);
+      }
+#pragma unroll
+      for (int q = 0; q < N; ++q) p[q] = mfma_h(wh[q], x.hi[ch], p[q]);
+    }
+  } else {
+#pragma unroll
+    for (int pl = PL - 1; pl >= 0; --pl)
+#pragma unroll
+      for (int q = 0; q < N; ++q) p[q] = mfma_h(w(q, 0, pl), x.hi[0], p[q]);
+  }
+#pragma unroll
+  for (int q = 0; q < N; ++q)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[q][e] = fmaf(p[q][e], x.fac, acc[q][e]);
+}
+
+// The same for one column block whose operands are in registers.
+template <int C>
+__device__ __forceinline__ void wide_mma_regs(const uint4* wv, const WideRows<C>& x, f4& acc) {
+  constexpr int NCH = WideRows<C>::NCH, PL = weight_planes(C);
+  f4 p = f4{0.0f, 0.0f, 0.0f, 0.0f};
+  if constexpr (C >= 32) {
+#pragma unroll
+    for (int ch = 0; ch < NCH; ++ch) {
+      p = mfma_h(wv[ch * PL + 1], x.hi[ch], p);
+      p = mfma_h(wv[ch * PL], x.lo[ch], p);
+      p = mfma_h(wv[ch * PL], x.hi[ch], p);
+    }
+  } else {
+#pragma unroll
+    for (int pl = PL - 1; pl >= 0; --pl) p = mfma_h(wv[pl], x.hi[0], p);
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) acc[e] = fmaf(p[e], x.fac, acc[e]);
+}
 
 // Sparse conv C -> C (ReLU, optional residual input, child scatter and row
-// store as in k_conv) with the weights streamed through LDS, for layers whose
-// weights do not fit in it (a 5x5x5 kernel at C = 128 holds 8 MB).  A block
-// takes groups of CW_WAVES tiles, one per wave.  For each offset in the union
-// of the group's occupied offsets, in ascending order, the block stages that
-// offset's C x C weights in LDS (double buffered: the next offset's loads are
-// issued before the current MFMAs), and each wave whose tile has the offset
-// accumulates its gathered neighbour rows on fp32 MFMA 16x16x4 in the layout
-// of k_conv; the wave's next gather is issued before its MFMAs.  A voxel sums
-// its offsets in ascending order whatever its group, so results do not depend
-// on the grouping.
-template <int C, int KV>
-__global__ void __launch_bounds__(CW_THREADS) k_convw(ConvArgs a) {
+// store as in k_conv) with the weights streamed, for layers whose weights do
+// not fit in LDS (a 5x5x5 kernel at C = 128 holds 8 MB).  A block takes groups
+// of tiles, one per wave.  For each offset in the union of the group's occupied
+// offsets, in ascending order, the block stages that offset's weights in LDS
+// (one offset ahead there, the one after in flight), and each wave whose tile
+// has the offset adds its gathered neighbour rows on split fp16 MFMA as k_conv
+// does and gathers its next rows into the same registers.  Launches with few
+// tiles split each tile's column blocks over waves instead, every wave reading
+// its own slice of the weights from memory into registers, without LDS or
+// barriers.  A voxel adds its offsets in ascending order, each chained from
+// zero, whatever its group, so results do not depend on the grouping.
+//
+// A 5x5x5 layer at C = 128 is bound by the weights' way from memory (8 MB do
+// not stay in a 4 MB L2: half of the lines miss), so its groups are as large as
+// the registers of a CU allow, 16 tiles on 16 waves; with 8 waves of twice the
+// registers and the rows gathered ahead into a second set it took 2.0 ms
+// instead of 1.55 (64-beam scan at 14 bits, mean of the layers; 4.2 ms on fp32
+// MFMA).  Groups differ in their offsets (27 to 125), so blocks take them first
+// come, first served, their own XCD's share before the others' (2.33 -> 2.0 ms
+// in the 8-wave form).  C = 64, 3x3x3: a chain of 27 rows and barriers at one or
+// two groups a block, 170 us on fp32 MFMA, 103 now.
+// Column split up to two sets a block: at four the 3x3x3 layers at C = 64 take
+// 112 us instead of 103, at sixteen the 5x5x5 layers at C = 128 5.0 ms.
+template <int C, int KV, bool XB>
+__global__ void __launch_bounds__(64 * cw_waves(C), 4) k_convw(ConvArgs a) {
+  constexpr int CW_WAVES = cw_waves(C), CW_THREADS = 64 * CW_WAVES;
   constexpr int NCB = C / 16;
-  constexpr int KS = C / 4;  // input channels of a lane group (one contiguous slice of a row)
+  constexpr int NCH = WideRows<C>::NCH;
   constexpr int NBS = KV > 27 ? 128 : NBR_STRIDE;
-  constexpr int EPL = NBS / 4;  // map entries per lane
-  constexpr int WQ = C * C / 4;  // 16-byte words of one offset's packed weights
-  __shared__ __attribute__((aligned(16))) float s_w[2][C * C];
+  constexpr int EPL = NBS / 4;                             // map entries per lane
+  constexpr int CBW = NCH * weight_planes(C) * 64;         // 16-byte words of a column block's weights of an offset
+  constexpr int WQ = NCB * CBW;                            // of all of them
+  constexpr int TPB = CW_WAVES / NCB;                      // tiles of a block in a column-split launch
+  __shared__ uint4 s_w[2][WQ];
   __shared__ uint64_t s_mask[CW_WAVES][2];
   __shared__ int64_t s_tpre[NLEV + 1];
   __shared__ int64_t s_nv[NLEV];
   __shared__ int64_t s_mo[NLEV];
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, r = lane & 15, g = lane >> 4;
+  __shared__ int64_t s_next[2];
+  static_assert(NCB == 1 || 2 * WQ >= CW_WAVES * 64, "the column blocks' sums meet in the weight area");
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int r = lane & 15, g = lane >> 4;
   const int nsc = a.b_hi - a.b_lo + 1;
   const RowMap rm{a.count, a.moff, a.cap_model, a.b_ext, a.ext_off, a.cap_rows};
   int64_t total_tiles = 0;
@@ -1570,12 +1666,6 @@ __global__ void __launch_bounds__(CW_THREADS) k_convw(ConvArgs a) {
   }
   const int64_t groups = (total_tiles + CW_WAVES - 1) / CW_WAVES;
   const int64_t tch = groups / 64 < 4 ? 4 : (groups / 64 > 64 ? 64 : groups / 64);
-  // Column split for launches with few tiles: a block takes TPB tiles and
-  // wave w computes column block w % NCB of tile w / NCB, so a tile's serial
-  // walk over its offsets is spread over NCB waves (each output channel's
-  // MFMA chain is the same as with one wave per tile) and the block walks the
-  // union of TPB tiles instead of CW_WAVES.
-  constexpr int TPB = CW_WAVES / NCB;
   const int64_t sets = (total_tiles + TPB - 1) / TPB;
   const bool split = NCB > 1 && sets <= (int64_t)gridDim.x * CW_SPLIT_ROUNDS;  // uniform
   const int64_t nwork = split ? sets : groups;
@@ -1592,29 +1682,39 @@ __global__ void __launch_bounds__(CW_THREADS) k_convw(ConvArgs a) {
     }
     for (int i = nsc; i <= NLEV; ++i) s_tpre[i] = acc;
   }
-  const f4* wsrc = reinterpret_cast<const f4*>(a.w);
-  const int cb0 = split ? w % NCB : 0;  // the wave's (first) column block
+  const uint4* wsrc = reinterpret_cast<const uint4*>(a.w);
+  WideRows<C> xa;
+  xa.clear();
+  int vic = blockIdx.x & 7;  // thread 0: the XCD whose share the block takes groups of
   for (int64_t gs = 0;; ++gs) {
-    const int64_t grp = split ? (int64_t)blockIdx.x + gs * (int64_t)gridDim.x : conv_tile(gs, tch);  // block-uniform
+    __syncthreads();  // prefix and s_next visible; the previous group is done with s_mask and s_w
+    const int64_t grp = split ? (int64_t)blockIdx.x + gs * (int64_t)gridDim.x
+                              : (gs == 0 ? conv_tile(0, tch) : s_next[gs & 1]);  // block-uniform
     if (grp >= nwork) break;
-    __syncthreads();  // prefix visible; the previous group is done with s_mask and s_w
+    if (!split && tid == 0) {  // the next group, read after the next turn's barrier
+      int64_t ng = groups;
+      for (int t = 0; t < 8; ++t) {
+        ng = xcd_tile(vic, (gridDim.x >> 3) + (int64_t)atomicAdd(a.next + vic, 1u), tch);
+        if (ng < groups) break;
+        vic = (vic + 1) & 7;
+      }
+      s_next[(gs + 1) & 1] = ng;
+    }
     const int64_t tile = split ? grp * TPB + w / NCB : grp * CW_WAVES + w;
     const bool have = tile < total_tiles;
-    int b = a.b_lo;
-    int64_t mo = 0, prow = 0, lvb = 0;
-    bool valid = false;
+    TileRef tr{a.b_lo, 0, 0, 0, false};
     if (have) {
       int si = 0;
 #pragma unroll
       for (int i = 1; i < NLEV; ++i) si += (s_tpre[i] <= tile) ? 1 : 0;
-      b = a.b_lo + si;
       const int64_t nvox = s_nv[si];
-      mo = s_mo[si];
       const int64_t row = (tile - s_tpre[si]) * 16 + r;
-      valid = row < nvox;
-      const int64_t pos = mo + (valid ? row : nvox - 1);  // idle lanes read a real row
-      prow = a.perm ? (int64_t)a.perm[pos] : pos;          // with a tile order, slot -> row
-      lvb = (int64_t)(b - a.b0) * a.cap_pts;
+      tr.b = a.b_lo + si;
+      tr.mo = s_mo[si];
+      tr.lvb = (int64_t)(tr.b - a.b0) * a.cap_pts;
+      tr.valid = row < nvox;
+      const int64_t pos = tr.mo + (tr.valid ? row : nvox - 1);  // idle lanes read a real row
+      tr.prow = a.perm ? (int64_t)a.perm[pos] : pos;            // with a tile order, slot -> row
     }
     // occupied offsets of the wave's tile (wave-uniform), from the map rows
     OffMask own;
@@ -1623,7 +1723,7 @@ __global__ void __launch_bounds__(CW_THREADS) k_convw(ConvArgs a) {
 #pragma unroll
       for (int q = 0; q < EPL / 4; ++q) {
         int4 t = make_int4(-1, -1, -1, -1);
-        if (have) t = reinterpret_cast<const int4*>(a.nbr + prow * NBS + EPL * g)[q];
+        if (have) t = reinterpret_cast<const int4*>(a.nbr + tr.prow * NBS + EPL * g)[q];
         nbv[4 * q] = t.x;
         nbv[4 * q + 1] = t.y;
         nbv[4 * q + 2] = t.z;
@@ -1631,124 +1731,99 @@ __global__ void __launch_bounds__(CW_THREADS) k_convw(ConvArgs a) {
       }
 #pragma unroll
       for (int j = 0; j < EPL; ++j) {
-        const uint64_t bal = __ballot(valid && nbv[j] >= 0);
+        const uint64_t bal = __ballot(tr.valid && nbv[j] >= 0);
 #pragma unroll
         for (int gg = 0; gg < 4; ++gg)
           if ((bal >> (16 * gg)) & 0xFFFFull) own.set(gg * EPL + j);
       }
     }
+    // each lane reads its own voxel's map entry of an offset one of the wave's
+    // offsets ahead of the gather, which follows the products of the offset
+    // before into the same registers
+    const int32_t* maprow = a.nbr + tr.prow * NBS;
+    auto entry = [&](int k) -> int32_t { return (k >= 0 && have) ? maprow[k] : -1; };
+    auto gather = [&](int32_t nn) { xa.load(a, tr.valid && nn >= 0 ? tr.mo + nn : -1, g); };
+    f4 acc[NCB];
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb) acc[cb] = f4{0.0f, 0.0f, 0.0f, 0.0f};
     if (lane == 0) {
       s_mask[w][0] = own.lo;
       s_mask[w][1] = own.hi;
     }
-    __syncthreads();
-    OffMask uni;
-    for (int ww = 0; ww < CW_WAVES; ++ww) {
-      uni.lo |= s_mask[ww][0];
-      uni.hi |= s_mask[ww][1];
-    }
-    // each lane reads its own voxel's map entry of an offset two of the
-    // wave's offsets ahead of its use, and gathers one offset ahead
-    const int32_t* maprow = a.nbr + prow * NBS;
-    auto entry = [&](int k) -> int32_t { return (k >= 0 && have) ? maprow[k] : -1; };
-    auto gather = [&](int32_t nn, f4 (&x)[KS / 4]) {
-      const int64_t srow = (valid && nn >= 0) ? mo + nn : a.cap_model;  // absent: the zero row
-      const f4* src = reinterpret_cast<const f4*>(a.h_in + srow * C + g * KS);
-#pragma unroll
-      for (int q = 0; q < KS / 4; ++q) x[q] = src[q];
-    };
-    // acc[j] holds column block cb0 + j (split: j = 0 only)
-    f4 acc[NCB];
-#pragma unroll
-    for (int cb = 0; cb < NCB; ++cb) acc[cb] = *reinterpret_cast<const f4*>(a.bias + 16 * (cb0 + (split ? 0 : cb)) + 4 * g);
-    f4 xa[KS / 4], xb[KS / 4];
     int ko = own.pop();
     const int32_t eo = entry(ko);
     int kq = own.pop();
     int32_t eq = entry(kq);
-    if (ko >= 0) gather(eo, xa);
-    int kc = uni.pop();
-    Staged<WQ, CW_THREADS> stw;
-    if (kc >= 0) {  // always: wave 0 has a valid voxel, whose own centre is occupied
-      stw.load(wsrc + (int64_t)kc * WQ, tid);
+    if (ko >= 0) gather(eo);
+    if (split) {
+      const int cb = w % NCB;
+      uint4 wv[CBW / 64];
+      auto weights = [&](int k) {
+#pragma unroll
+        for (int i = 0; i < CBW / 64; ++i) wv[i] = wsrc[(int64_t)k * WQ + cb * CBW + i * 64 + lane];
+      };
+      if (ko >= 0) weights(ko);
+      while (ko >= 0) {  // wave-uniform
+        wide_mma_regs<C>(wv, xa, acc[0]);
+        ko = kq;
+        if (ko >= 0) {
+          weights(ko);
+          gather(eq);
+        }
+        kq = own.pop();
+        eq = entry(kq);
+      }
+      // the column blocks of a tile meet in LDS; the wave of block 0 goes on
+      f4* s_x = reinterpret_cast<f4*>(s_w[0]);  // [wave][64]
+      s_x[w * 64 + lane] = acc[0];
+      __syncthreads();
+      if (!have || cb != 0) continue;
+#pragma unroll
+      for (int j = 0; j < NCB; ++j) acc[j] = s_x[(w + j) * 64 + lane];
+    } else {
+      __syncthreads();
+      OffMask uni;
+      for (int ww = 0; ww < CW_WAVES; ++ww) {
+        uni.lo |= s_mask[ww][0];
+        uni.hi |= s_mask[ww][1];
+      }
+      int kc = uni.pop(), kn = uni.pop();
+      Staged<WQ, CW_THREADS> stw;
+      auto weights = [&](int k) { stw.load(reinterpret_cast<const f4*>(wsrc + (int64_t)k * WQ), tid); };
+      weights(kc);  // a group has an offset: its wave 0 a valid voxel, whose own centre is occupied
       stw.store(reinterpret_cast<f4*>(s_w[0]), tid);
-    }
-    __syncthreads();
-    int buf = 0;
-    while (kc >= 0) {  // block-uniform
-      const int kn = uni.pop();
-      if (kn >= 0) stw.load(wsrc + (int64_t)kn * WQ, tid);
-      if (kc == ko) {
-        const int kr = own.pop();
-        const int32_t er = entry(kr);
-        if (kq >= 0) gather(eq, xb);
-        const float* wb = s_w[buf];
-        if (split) {
+      if (kn >= 0) weights(kn);
+      __syncthreads();
+      int buf = 0;
+      while (kc >= 0) {  // block-uniform
+        const bool mine = kc == ko;
+        if (mine) {
+          constexpr int NB = NCB == 2 || NCB == 4 ? 2 : 1;
 #pragma unroll
-          for (int q = 0; q < KS / 4; ++q) {
-            const f4 wv = reinterpret_cast<const f4*>(wb)[(cb0 * (KS / 4) + q) * 64 + lane];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc[0] = mfma4(wv[e], xa[q][e], acc[0]);
-          }
-        } else {
-#pragma unroll
-          for (int q = 0; q < KS / 4; ++q) {
-            f4 wv[NCB];
-#pragma unroll
-            for (int cb = 0; cb < NCB; ++cb) wv[cb] = reinterpret_cast<const f4*>(wb)[(cb * (KS / 4) + q) * 64 + lane];
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-#pragma unroll
-              for (int cb = 0; cb < NCB; ++cb) acc[cb] = mfma4(wv[cb][e], xa[q][e], acc[cb]);
+          for (int cb = 0; cb < NCB; cb += NB) {
+            wide_mma<C, NB>(s_w[buf] + cb * CBW, lane, xa, acc + cb);
+            __builtin_amdgcn_sched_barrier(0);  // operands of all blocks at once would not fit the registers
           }
         }
-#pragma unroll
-        for (int q = 0; q < KS / 4; ++q) xa[q] = xb[q];
-        ko = kq;
-        kq = kr;
-        eq = er;
+        kc = kn;
+        if (kn >= 0) {  // weights one offset ahead in LDS, two ahead in flight
+          stw.store(reinterpret_cast<f4*>(s_w[buf ^ 1]), tid);
+          kn = uni.pop();
+          if (kn >= 0) weights(kn);
+        }
+        if (mine) {
+          ko = kq;
+          if (ko >= 0) gather(eq);
+          kq = own.pop();
+          eq = entry(kq);
+        }
+        __syncthreads();
+        buf ^= 1;
       }
-    if (kn >= 0) stw.store(reinterpret_cast<f4*>(s_w[buf ^ 1]), tid);
-      __syncthreads();
-      buf ^= 1;
-      kc = kn;
     }
     if (!have) continue;
-    const int ncw = split ? 1 : NCB;  // column blocks this wave holds: cb0 .. cb0 + ncw - 1
-    if (a.res) {  // residual block: ReLU(x + conv(.)), x read at the voxel's own row
-#pragma unroll
-      for (int j = 0; j < NCB; ++j)
-        if (j < ncw) acc[j] += *reinterpret_cast<const f4*>(a.res + prow * C + 16 * (cb0 + j) + 4 * g);
-    }
-#pragma unroll
-    for (int cb = 0; cb < NCB; ++cb)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) acc[cb][e] = fmaxf(acc[cb][e], 0.0f);
-    if (a.xb && valid) {  // children v of this voxel u: X_B[v] = F[u] + Emb_D[delta(v)]
-      int64_t cmo = a.moff[b + 1];
-      const int64_t cn = a.count[b + 1];
-      const uint32_t code = a.code[lvb + (prow - mo)];
-      const int64_t first = a.fc[lvb + (prow - mo)];
-      if (cmo + cn > a.cap_model) cmo = -1;  // overflow (latched where the size was made): no writes
-      int rank = 0;
-#pragma unroll
-      for (int d = 0; d < 8; ++d) {
-        if (cmo >= 0 && ((code >> d) & 1u)) {
-          float* dst = a.xb + (cmo + first + rank) * C;
-#pragma unroll
-          for (int j = 0; j < NCB; ++j)
-            if (j < ncw)
-              *reinterpret_cast<f4*>(dst + 16 * (cb0 + j) + 4 * g) =
-                  acc[j] + *reinterpret_cast<const f4*>(a.emb_d + d * C + 16 * (cb0 + j) + 4 * g);
-          ++rank;
-        }
-      }
-    }
-    if (valid && a.h_out) {
-#pragma unroll
-      for (int j = 0; j < NCB; ++j)
-        if (j < ncw) *reinterpret_cast<f4*>(a.h_out + prow * C + 16 * (cb0 + j) + 4 * g) = acc[j];
-    }
+    float x[C / 4];
+    conv_epilogue<C, XB>(a, acc, g, tr, x);
   }
 }
 
@@ -2065,18 +2140,19 @@ hipError_t launch_pack_weights(Ctx& c, const reno_weights& w) {
   const int C = c.p.channels;
   auto pack_conv = [&](const float* src, int kv, int l) {
     uint16_t* out = reinterpret_cast<uint16_t*>(c.w_conv[l]);
-    if (C == 32)
-      hipLaunchKernelGGL(k_pack_conv<32>, dim3(32), dim3(256), 0, c.stream, src, kv, out, c.wfac(l));
-    else
-      hipLaunchKernelGGL(k_pack_conv<16>, dim3(16), dim3(256), 0, c.stream, src, kv, out, c.wfac(l));
+    hipLaunchKernelGGL(k_weight_max, dim3(WMAX_BLOCKS), dim3(256), 0, c.stream, src, kv * C, C, c.w_part);
+    const dim3 grid((unsigned)std::min<int64_t>(1024, ((int64_t)kv * C * C + 255) / 256));
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(256), 0, c.stream, src, kv, c.w_part, out, c.wfac(l)); };
+    switch (C) {
+      case 128: go(k_pack_conv<128>); break;
+      case 64: go(k_pack_conv<64>); break;
+      case 32: go(k_pack_conv<32>); break;
+      default: go(k_pack_conv<16>);
+    }
   };
   if (c.p.model_mode == RENO_MODEL_TOP) {  // four C -> C convs and the two embeddings
     for (int l = 0; l < 4; ++l) {
-      if (c.wide())
-        hipLaunchKernelGGL(k_pack_conv_wide, dim3(1024), dim3(256), 0, c.stream, w.top_w[l], C, c.kvol(),
-                           c.w_conv[l]);
-      else
-        pack_conv(w.top_w[l], 27, l);
+      pack_conv(w.top_w[l], c.kvol(), l);
       hipLaunchKernelGGL(k_copy_f32, dim3(1), dim3(256), 0, c.stream, w.top_b[l], c.w_bias[l], C);
     }
     hipLaunchKernelGGL(k_copy_f32, dim3(32), dim3(256), 0, c.stream, w.emb_o, c.w_embo, 256 * C);
@@ -2208,11 +2284,11 @@ hipError_t launch_top_wide(Ctx& c, int b_lo, int b_hi, float* logits, bool secon
     if (KV == 125)
       hipLaunchKernelGGL(k_top_prep5<C>, dim3(blocks), dim3(256), 0, c.stream, n_lo, b_hi - n_lo + 1, b_hi - n_lo,
                          b0, rm, c.lv_key, c.lv_code, (int64_t)c.cap_pts, cell_args(c), c.w_embo,
-                         c.d_nbr, c.h_c);
+                         c.d_nbr, c.h_c, c.s_c, c.r_c);
     else
       hipLaunchKernelGGL((k_top_prep<C, true>), dim3(blocks), dim3(256), 0, c.stream, n_lo, b_hi - n_lo + 1,
                          b_hi - n_lo, b0, rm, c.lv_key, c.lv_code, (int64_t)c.cap_pts, cell_args(c), c.w_embo,
-                         c.d_nbr, c.h_c, nullptr, nullptr);
+                         c.d_nbr, c.h_c, c.s_c, c.r_c);
   }
   ConvArgs a{};
   a.b0 = b0;
@@ -2241,28 +2317,39 @@ hipError_t launch_top_wide(Ctx& c, int b_lo, int b_hi, float* logits, bool secon
     const int nsc = b_hi - n_lo + 1;
     const int64_t windows = (c.cap_model + c.cap_pts + TO_W - 1) / TO_W + nsc;
     hipLaunchKernelGGL(k_tile_order, dim3((unsigned)windows), dim3(TO_THREADS), 0, c.stream, n_lo, nsc, rm,
-                       KV == 125 ? 5 : 3, c.d_nbr, c.d_perm);
+                       KV == 125 ? 5 : 3, c.d_nbr, c.d_perm, c.d_next);
     a.perm = c.d_perm;
   }
   hipError_t e = hipSuccess;
-  auto conv = [&](int lo, int hi, int wi, const float* in, float* out, const float* res, float* xb) {
+  auto conv = [&](int lo, int hi, int wi, const void* in, const float* r_in, float* out, const float* res, float* xb,
+                  bool last) {
     if (e != hipSuccess) return;
     a.b_lo = lo;
     a.b_hi = hi;
-    a.h_in = in;
-    a.h_out = out;
+    a.h_in = static_cast<const float*>(in);
+    a.r_in = r_in;
+    a.h_out = last ? out : nullptr;
+    a.s_out = last ? nullptr : reinterpret_cast<uint32_t*>(out);
+    a.r_out = c.r_b;
     a.res = res;
     a.xb = xb;
+    a.xb_s = c.s_d;
+    a.xb_r = c.r_d;
     a.w = c.w_conv[wi];
+    a.wfac = c.wfac(wi);
     a.bias = c.w_bias[wi];
+    a.next = c.d_next + 8 * wi;
     ProfScope ps_(c, RENO_K_CONV_MID);
-    hipLaunchKernelGGL((k_convw<C, KV>), dim3(256), dim3(CW_THREADS), 0, c.stream, a);
+    if (xb)
+      hipLaunchKernelGGL((k_convw<C, KV, true>), dim3(cw_blocks(C)), dim3(64 * cw_waves(C)), 0, c.stream, a);
+    else
+      hipLaunchKernelGGL((k_convw<C, KV, false>), dim3(cw_blocks(C)), dim3(64 * cw_waves(C)), 0, c.stream, a);
     e = hipGetLastError();
   };
-  conv(n_lo, b_hi - 1, 0, c.h_c, c.h_b, nullptr, nullptr);
-  conv(n_lo, b_hi - 1, 1, c.h_b, nullptr, c.h_c, c.h_d);
-  conv(b_lo, b_hi, 2, c.h_d, c.h_b, nullptr, nullptr);
-  conv(b_lo, b_hi, 3, c.h_b, c.h_a, c.h_d, nullptr);
+  conv(n_lo, b_hi - 1, 0, c.s_c, c.r_c, c.h_b, nullptr, nullptr, false);
+  conv(n_lo, b_hi - 1, 1, c.h_b, c.r_b, nullptr, c.h_c, c.h_d, false);
+  conv(b_lo, b_hi, 2, c.s_d, c.r_d, c.h_b, nullptr, nullptr, false);
+  conv(b_lo, b_hi, 3, c.h_b, c.r_b, c.h_a, c.h_d, nullptr, true);
   if (e != hipSuccess) return e;
   {
     ProfScope ps_(c, RENO_K_CONV_LAST);

@@ -107,3 +107,29 @@ def test_context_beyond_32_bit_row_offsets(C, two):
     large = _run(pts, B, b0, R, C, 3, w, two, max_points=(1 << 25) + 1, rows=40000)
     np.testing.assert_array_equal(large, small)
     _check(large, pts, B, b0, R, w, two)
+
+
+@pytest.mark.parametrize("C,ks,n", [(128, 3, 12000), (64, 3, 24000), (32, 5, 48000), (16, 5, 3000)])
+def test_streamed_layers_staged_and_column_split(C, ks, n):
+    """All scales at once stage the weights for groups of tiles, one scale at a time splits
+    each tile's columns over waves (C = 16 has one column block and never splits): the same
+    bits, and the smaller scales against the oracle."""
+    B, b0, R = 9, 3, 10.0
+    rs = np.random.default_rng(C + ks)
+    cells = np.unique(rs.integers(0, 1 << (B - 2), size=(n, 3)) + (1 << (B - 3)), axis=0)
+    pts = (-10.0 + (cells + 0.5) * (20.0 / (1 << B))).astype(np.float32)
+    say("streamed layers C", C, "k", ks, "points", len(pts))
+    w = gen_weights(C, 2, seed=C, bias_std=0.1, two_stage=True, top=True, kernel_size=ks)
+    ctx = reno.Context(len(pts), B, b0, R, C, 2, two_stage=True, top=True, kernel_size=ks)
+    ctx.set_weights(reno.weights_to_device(w))
+    ctx.build_pyramid(to_dev(pts), B)
+    lg = ctx.predict_probs(reno.RENO_ALL_SCALES, logits=True).cpu().numpy()
+    one = [ctx.predict_probs(b, logits=True).cpu().numpy() for b in range(b0 + 1, B)]
+    rows = sum(ctx.num_voxels(b) for b in range(b0 + 1, B))
+    ctx.close()
+    assert C == 16 or rows > 16 * 1024 * 128 // C >= n  # staged all together, split one by one
+    np.testing.assert_array_equal(np.concatenate(one), lg)
+    P = oracle.Pyramid.from_points(pts, B, b0, R)
+    for b, got in zip((b0 + 1, b0 + 2), one):
+        ref = np.concatenate(P.model2(b, w)[:2], 1)
+        assert np.abs(got - ref).max() <= 4e-6 * np.abs(ref).max(), b
