@@ -21,6 +21,9 @@
 #include "ctx.h"
 #include "dev.h"
 
+// v_writelane_b32, which has no builtin of its own: old with lane `at` (uniform) set to v
+extern "C" __device__ int llvm_writelane(int v, int at, int old) __asm("llvm.amdgcn.writelane.i32");
+
 namespace reno {
 namespace {
 
@@ -338,79 +341,89 @@ __device__ __forceinline__ int64_t wave_sum(int64_t v) {
 
 
 // The decoder's table of one voxel: entries start_s | f_s << 16 (start_0 =
-// 0, ascending, f_s >= 1).  K = 256: four entries per lane (symbols 4l ..
-// 4l + 3); K = 16: one entry in each of lanes 0 .. 15.
+// 0, ascending, f_s >= 1), the last ones in the lowest lanes.  K = 256: lane l
+// holds symbols 4 (63 - l) .. 4 (63 - l) + 3; K = 16: lanes l = 0 .. 15 (repeated
+// by the others) symbol 15 - l.  `turn` is the lane's group or symbol.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 template <int K>
 struct Table {
   uint32_t e[K == 256 ? 4 : 1];
 };
 
 template <int K>
-__device__ __forceinline__ Table<K> load_table(const uint32_t* tab, int64_t i, int lane) {
+__device__ __forceinline__ int table_turn(int lane) {
+  return K == 256 ? 63 - lane : 15 - (lane & 15);
+}
+
+// through the uniform address of the table
+template <int K>
+__device__ __forceinline__ Table<K> load_table(uint64_t at, int turn) {
   Table<K> r;
   if constexpr (K == 256) {
-    const uint4 v = reinterpret_cast<const uint4*>(tab + i * 256)[lane];
+    const u32x4 v = reinterpret_cast<const __attribute__((address_space(1))) u32x4*>(at)[turn];
     r.e[0] = v.x;
     r.e[1] = v.y;
     r.e[2] = v.z;
     r.e[3] = v.w;
   } else {
-    r.e[0] = tab[i * 16 + (lane & 15)];
+    r.e[0] = reinterpret_cast<const __attribute__((address_space(1))) uint32_t*>(at)[turn];
   }
   return r;
 }
 
-// The symbol s with start_s <= slot < start_s + f_s and its interval.  Every
-// lane picks, among its own entries, the last one starting at or below slot
-// (vector work that runs beside the scalar part), a ballot of "my first entry
-// <= slot" names the lane holding s (starts ascend across the lanes), and
-// two lane reads bring that lane's pick out.
+// One step of the coder: the symbol s with start_s <= slot < start_s + f_s and
+// the state f_s (x >> 16) + slot - start_s.  Every lane picks, among its own
+// entries, the last one starting at or below slot and computes the state that
+// this entry gives; the first lane of a ballot of "my first entry <= slot" holds
+// s (starts descend across the lanes; lane 63, K = 16: 15, always votes, its
+// first entry is 0), and lane reads bring that lane's state and symbol out.
+// K = 16: the symbol comes out as 15 - s.
 template <int K>
-__device__ __forceinline__ void find_symbol(const Table<K>& tb, uint32_t slot, uint32_t* sym, uint32_t* lo_s,
-                                            uint32_t* f_s) {
+__device__ __forceinline__ u32x2 step_state(const Table<K>& tb, u32x2 x, uint32_t turn4, uint32_t* sym) {
+  const uint16_t slot = (uint16_t)x[0];  // 16-bit compares take the low halves as they are
+  uint32_t pick = tb.e[0], k = turn4;
   if constexpr (K == 256) {
-    const bool c1 = (tb.e[1] & 0xFFFFu) <= slot, c2 = (tb.e[2] & 0xFFFFu) <= slot,
-               c3 = (tb.e[3] & 0xFFFFu) <= slot;
-    const uint32_t pick = c3 ? tb.e[3] : c2 ? tb.e[2] : c1 ? tb.e[1] : tb.e[0];
-    const uint32_t k = c3 ? 3u : c2 ? 2u : c1 ? 1u : 0u;
-    const uint64_t ball = __ballot((tb.e[0] & 0xFFFFu) <= slot);  // lane 0 always (its first entry is 0)
-    const int ls = 63 - __clzll((long long)ball);
-    const uint32_t a = rdl(pick, ls);
-    *sym = 4u * (uint32_t)ls + rdl(k, ls);
-    *lo_s = a & 0xFFFFu;
-    *f_s = a >> 16;
-  } else {
-    const uint64_t ball = __ballot((tb.e[0] & 0xFFFFu) <= slot) & 0xFFFFull;
-    const int ls = 63 - __clzll((long long)ball);
-    const uint32_t a = rdl(tb.e[0], ls);
-    *sym = (uint32_t)ls;
-    *lo_s = a & 0xFFFFu;
-    *f_s = a >> 16;
+    const bool c1 = (uint16_t)tb.e[1] <= slot, c2 = (uint16_t)tb.e[2] <= slot, c3 = (uint16_t)tb.e[3] <= slot;
+    const uint32_t p01 = c1 ? tb.e[1] : tb.e[0], p23 = c3 ? tb.e[3] : tb.e[2];
+    pick = c2 ? p23 : p01;
+    k = turn4 + (uint32_t)c1 + (uint32_t)c2 + (uint32_t)c3;
   }
+  const int at = __builtin_ctzll(__ballot((uint16_t)tb.e[0] <= slot));
+  const uint32_t f = pick >> 16;
+  const uint32_t y = (uint32_t)(__builtin_bit_cast(uint64_t, x) >> kProb);
+  const uint64_t t = (uint64_t)f * y + ((uint32_t)slot - (pick & 0xFFFFu));
+  const uint32_t hi = __umul24(f, x[1] >> kProb) + (uint32_t)(t >> 32);
+  *sym = K == 256 ? rdl(k, at) : (uint32_t)at;
+  return u32x2{rdl((uint32_t)t, at), rdl(hi, at)};
 }
 
-// One wavefront per stream, in trips of 64 symbols.  A wavefront issues
-// about one instruction per four cycles, so a stream's time is its symbol
-// count times the instructions of one step: the step is kept short.  The
-// coder state lives in scalar registers; a step reads its table from
-// registers loaded kRing steps before (unconditional, clamped loads, so the
-// compiler's wait names exactly that load), its renormalisation word from a
-// register window of the stream (a lane read), and stores its symbol to LDS;
-// the trip's symbols are written out together at its end (with the trip's S1
-// values for stage 2).  Full trips run without per-step bounds; the last,
-// partial trip checks them.  The window moves between trips only: a trip
-// reads at most 64 words, from the two registers win0 and win1 (128 words),
-// while the third, win2, is loaded a whole trip ahead (unconditionally, at
-// a fixed point), so that no step waits on a window load issued after its
-// own table loads.  A stream that runs past its end reads its last word
-// again and is caught by the final check of its length and state.
+// One wavefront per stream, in trips of 64 symbols.  A stream's time is its
+// symbol count times one step, and a step is a chain: state, compare, ballot,
+// find first, lane read, test of the state.  The step is kept to that chain and
+// little beside it, 32 instructions for 256 symbols and 19 for 16; with index
+// arithmetic for every load, the state formed after the lane read, in scalar
+// registers, and the symbols stored through LDS it was 52 and 42.  Streams of
+// 1024 symbols: 137 -> 110 us and 92 -> 72 us.
+// The coder state lives in scalar registers; a step reads its table from
+// registers loaded kRing steps before (unconditional loads through a running
+// address, so the compiler's wait names exactly that load), the rare
+// renormalisation word from a register window of the stream (a lane read, out
+// of the straight line), and leaves its symbol in its lane of a register; the
+// trip's symbols are written out together at its end (with the trip's S1
+// values for stage 2).  Trips whose loads all lie inside the stream run without
+// bounds; the last ones clamp the loads and check the steps.  The window moves
+// between trips only: a trip reads at most 64 words, from the two registers
+// win0 and win1 (128 words), while the third, win2, is loaded a whole trip
+// ahead (unconditionally, at a fixed point), so that no step waits on a window
+// load issued after its own table loads.  A stream that runs past its end reads
+// its last word again and is caught by the final check of its length and state.
 template <int K, bool S1>
 __global__ void __launch_bounds__(64 * kDecWaves) k_rans_decode(DecArgs a, const uint32_t* __restrict__ words,
                                                                 const uint32_t* __restrict__ tab,
                                                                 const uint8_t* __restrict__ s1,
                                                                 uint8_t* __restrict__ out) {
   static_assert(64 % kRing == 0, "a trip holds whole turns of the table ring");
-  __shared__ uint8_t s_sym[kDecWaves][64];
   const int lane = threadIdx.x & 63;
   // the wavefront index read through a lane read: the compiler then knows
   // that everything per stream is uniform and keeps it in scalar registers
@@ -457,7 +470,7 @@ __global__ void __launch_bounds__(64 * kDecWaves) k_rans_decode(DecArgs a, const
   const int ns = (int)n, Ss = (int)S, ws = (int)wave, lens = (int)len;
   const int m = ns > ws ? (ns - ws + Ss - 1) / Ss : 0;
   const int i_last = m > 0 ? ws + (m - 1) * Ss : 0;
-  uint64_t x = ((uint64_t)in[0] << 32) | in[1];
+  u32x2 x = {in[1], in[0]};  // low and high word: tested and shifted by words
   int p = 2;
   // renormalisation words: lane l of win0 holds word wb + l, win1 and win2
   // the next 64 each (the last word repeated past the stream's end, so that
@@ -469,43 +482,52 @@ __global__ void __launch_bounds__(64 * kDecWaves) k_rans_decode(DecArgs a, const
   // then never wait behind the table loads in flight
   __builtin_amdgcn_s_waitcnt(0);
   uint32_t win2 = word_at(wb + 128 + lane);
+  const int turn = table_turn<K>(lane);
+  auto tab_at = [&](int i) { return (uint64_t)(uintptr_t)(tab + (int64_t)i * K); };
   Table<K> ring[kRing];
 #pragma unroll
-  for (int u = 0; u < kRing; ++u) ring[u] = load_table<K>(tab, min(ws + u * Ss, i_last), lane);
-  int nidx = ws + kRing * Ss;  // the symbol whose table the next load fetches
-  uint8_t* ssymb = s_sym[rfl(threadIdx.x >> 6)];
-  // one trip; GUARD: the trip may hold fewer than 64 symbols (the last one)
+  for (int u = 0; u < kRing; ++u) ring[u] = load_table<K>(tab_at(min(ws + u * Ss, i_last)), turn);
+  const uint32_t turn4 = 4u * (uint32_t)turn;
+  // one trip; GUARD: the trip's loads may reach past the stream's last symbol,
+  // the trip may hold fewer than 64 symbols
   auto trip = [&](int k0, auto guard) {
     constexpr bool GUARD = decltype(guard)::value;
     const int i_mine = ws + (k0 + lane) * Ss;  // the symbol whose result lane `lane` writes
     const uint32_t s1v = S1 ? (uint32_t)s1[min(i_mine, i_last)] : 0u;
+    int nidx = ws + (k0 + kRing) * Ss;  // the symbol whose table the next load fetches
+    uint64_t at = tab_at(nidx);
+    const uint64_t at_step = (uint64_t)Ss * K * sizeof(uint32_t);
+    uint32_t symv = 0;
 #pragma unroll
     for (int u = 0; u < 64; ++u) {
       // every step issues its load, so the count of loads in flight is the
       // same on every path and the wait for this step's table is exact
       const Table<K> cur = ring[u % kRing];
-      ring[u % kRing] = load_table<K>(tab, min(nidx, i_last), lane);
-      // advanced through a lane read, which the compiler cannot see through:
-      // otherwise it keeps one address per unrolled step in scalar registers
-      nidx = (int)rfl((uint32_t)(nidx + Ss));
+      // the running address passes through a register that the compiler cannot
+      // see through: otherwise it keeps one address per unrolled step
+      if constexpr (GUARD) {
+        ring[u % kRing] = load_table<K>(tab_at(min(nidx, i_last)), turn);
+        nidx = (int)rfl((uint32_t)(nidx + Ss));
+      } else {
+        asm("" : "+s"(at));
+        ring[u % kRing] = load_table<K>(at, turn);
+        at += at_step;
+      }
       if (!GUARD || k0 + u < m) {
-        const uint32_t slot = (uint32_t)x & ((1u << kProb) - 1u);
-        uint32_t sym, lo_s, f_s;
-        find_symbol<K>(cur, slot, &sym, &lo_s, &f_s);
-        x = (uint64_t)f_s * (x >> kProb) + slot - lo_s;
-        if ((uint32_t)(x >> 31) == 0) {  // x < 2^31 (x < 2^63 always)
-          const int q = p - wb;          // below 128 inside a trip
-          const uint32_t w0 = rdl(win0, q & 63), w1 = rdl(win1, q & 63);
-          x = (x << 32) | (q < 64 ? w0 : w1);
-          ++p;
+        uint32_t sym;
+        x = step_state<K>(cur, x, turn4, &sym);
+        if (__builtin_expect(x[1] == 0, 0)) {
+          if (x[0] >> 31 == 0) {   // the state is below 2^31 (below 2^63 always)
+            const int q = p - wb;  // below 128 inside a trip
+            const uint32_t w0 = rdl(win0, q & 63), w1 = rdl(win1, q & 63);
+            x = u32x2{q < 64 ? w0 : w1, x[0]};
+            ++p;
+          }
         }
-        // every lane stores the same byte: no lane mask to set up
-        ssymb[u] = (uint8_t)sym;
+        symv = (uint32_t)llvm_writelane((int)sym, u, (int)symv);
       }
     }
-    // LDS operations of one wavefront complete in order: the stores above
-    // are visible here
-    const uint32_t symv = ssymb[lane];
+    if (K == 16) symv = 15u - symv;
     if (!GUARD || k0 + lane < m) out[i_mine] = (uint8_t)(S1 ? (s1v | (symv << 4)) : symv);
     // the window moves on once its first 64 words are used up; win2 is
     // reloaded either way (the same words when the window did not move)
@@ -515,10 +537,10 @@ __global__ void __launch_bounds__(64 * kDecWaves) k_rans_decode(DecArgs a, const
     wb = shift ? wb + 64 : wb;
     win2 = word_at(wb + 128 + lane);
   };
-  const int full = m & ~63;
-  for (int k0 = 0; k0 < full; k0 += 64) trip(k0, std::false_type{});
-  if (full < m) trip(full, std::true_type{});
-  if (lane == 0 && (p != lens || x != kLow)) latch(a.err, ERR_STREAM);
+  int k0 = 0;
+  for (; k0 + 64 + kRing <= m; k0 += 64) trip(k0, std::false_type{});
+  for (; k0 < m; k0 += 64) trip(k0, std::true_type{});
+  if (lane == 0 && (p != lens || __builtin_bit_cast(uint64_t, x) != kLow)) latch(a.err, ERR_STREAM);
 }
 
 }  // namespace
