@@ -216,6 +216,23 @@ __host__ __device__ __forceinline__ bool hashed_scale(int b, int b0, int B) {
   return b + 2 < B || (b == b0 && b + 1 < B);
 }
 
+// The children of a code that are kept when they start at row `first` of a scale
+// of `cap` rows: the lowest ones that fit.  A parent whose children a full scale
+// cuts off is stored with what is left of its code, so that every row that
+// follows from a stored (code, first child) is a row of the scale also in a
+// frame that has overflowed: later launches of the frame run before the host
+// learns of it, and they read codes and features at such rows.
+__host__ __device__ __forceinline__ uint32_t kept_children(uint32_t code, int64_t first, int64_t cap) {
+  if (first + 8 <= cap) return code;
+  uint32_t kept = 0;
+  for (uint32_t d = 0; d < 8; ++d)
+    if (((code >> d) & 1u) && first < cap) {
+      kept |= 1u << d;
+      ++first;
+    }
+  return kept;
+}
+
 // ---- open-addressing coordinate hash in HBM ----
 // Maps a voxel of a hashed scale to its occupancy code and the row of its
 // first child, so that any cell of the next scale can be resolved from one

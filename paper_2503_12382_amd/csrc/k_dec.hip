@@ -233,16 +233,18 @@ __global__ void __launch_bounds__(EXP_THREADS) k_expand(ExpArgs a) {
   for (int j = 0; j < EXP_KPT; ++j) {
     const int64_t p = base + (int64_t)w * 64 * EXP_KPT + j * 64 + lane;
     if (p >= np) continue;
-    const uint32_t c = code[j];
-    int64_t q = wbase + incl[j] - (uint32_t)__popc(c);
+    int64_t q = wbase + incl[j] - (uint32_t)__popc(code[j]);
+    incl[j] = (uint32_t)(q - wbase);  // from here on: the first child's place
+    const uint32_t c = kept_children(code[j], q, a.cap_pts);
+    if (c != code[j]) {
+      latch(a.err, ERR_CAPACITY);
+      code[j] = c;
+      if (a.moff) a.code_b[p] = (uint8_t)c;  // without a context the codes are the caller's, and only read
+    }
     if (a.fc_b) a.fc_b[p] = (int32_t)q;
     const uint64_t kp = key[j] << 3;
     for (uint32_t d = 0; d < 8; ++d) {
       if (!((c >> d) & 1u)) continue;
-      if (q >= a.cap_pts) {
-        latch(a.err, ERR_CAPACITY);
-        break;
-      }
       a.key_n[q] = kp | d;
       a.parent_n[q] = (int32_t)p;
       ++q;
@@ -255,9 +257,8 @@ __global__ void __launch_bounds__(EXP_THREADS) k_expand(ExpArgs a) {
   for (int j = 0; j < EXP_KPT; ++j) {
     const int64_t p = base + (int64_t)w * 64 * EXP_KPT + j * 64 + lane;
     if (p >= np) continue;
-    const int64_t q = wbase + incl[j] - (uint32_t)__popc(code[j]);
     hash_insert(a.hash, a.hash_lg, hash_region(a.hreg, a.hash_lg, frame_part(key[j], a.b)),
-                tag_key(key[j], a.b, a.fb), (int32_t)q, code[j], a.err);
+                tag_key(key[j], a.b, a.fb), (int32_t)(wbase + incl[j]), code[j], a.err);
   }
 }
 
