@@ -1790,8 +1790,12 @@ __global__ void __launch_bounds__(64 * cw_waves(C), 4) k_convw(ConvArgs a) {
       int kc = uni.pop(), kn = uni.pop();
       Staged<WQ, CW_THREADS> stw;
       auto weights = [&](int k) { stw.load(reinterpret_cast<const f4*>(wsrc + (int64_t)k * WQ), tid); };
-      weights(kc);  // a group has an offset: its wave 0 a valid voxel, whose own centre is occupied
-      stw.store(reinterpret_cast<f4*>(s_w[0]), tid);
+      // a group can have no offset at all: base voxels that are not in order (an
+      // error that the host learns of later) are not even found as their own neighbours
+      if (kc >= 0) {
+        weights(kc);
+        stw.store(reinterpret_cast<f4*>(s_w[0]), tid);
+      }
       if (kn >= 0) weights(kn);
       __syncthreads();
       int buf = 0;
