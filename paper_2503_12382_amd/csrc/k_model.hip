@@ -22,6 +22,8 @@
 // decoder evaluating the same scale get bit-identical results however a launch
 // shares its tiles among waves.
 
+#include <type_traits>
+
 #include "ctx.h"
 
 namespace reno {
@@ -68,29 +70,42 @@ __device__ __forceinline__ void split_scale(float m, float& mul, float& fac) {
   fac = ex > 14u ? __uint_as_float((ex - 14u) << 23) : 0x1p-127f;    // 2^(e - 14)
 }
 
-// Split of the N entries that a lane holds of a voxel's row, whose other
-// entries are in the lanes STEP and 2 STEP away (16: lanes r + 16 g; 1: lanes 4 r
-// + g): packed words of hi and lo, and the row's factor.  A row with an infinite entry keeps that one at 2^15 against
-// (practically) zero others and gets the factor infinity, so that what it adds
-// to an output is infinite as in fp32.
-template <int N, int STEP = 16>
-__device__ __forceinline__ float row_split(const float (&x)[N], uint32_t (&hi)[N / 2], uint32_t (&lo)[N / 2]) {
-  float m = 0.0f;
+template <int N>
+__device__ __forceinline__ float abs_max(const float (&x)[N], float m = 0.0f) {
 #pragma unroll
   for (int i = 0; i < N; ++i) m = fmaxf(m, fabsf(x[i]));
+  return m;
+}
+
+// Factors of a row from a lane's largest magnitude, whose other entries are in
+// the lanes STEP and 2 STEP away (16: lanes r + 16 g; 1: lanes 4 r + g).  A row
+// with an infinite entry keeps that one at 2^15 against (practically) zero others
+// and gets the factor infinity, so that what it adds to an output is infinite as
+// in fp32.
+template <int STEP = 16>
+__device__ __forceinline__ void row_scale(float m, float& mul, float& fac) {
   m = fmaxf(m, __shfl_xor(m, STEP));
   m = fmaxf(m, __shfl_xor(m, 2 * STEP));
-  float mul, fac;
   split_scale(m, mul, fac);
   fac = m == INFINITY ? m : fac;
+}
+
+// Packed words of hi and lo of entries x0, x1 of a row.
+__device__ __forceinline__ void split_words(float x0, float x1, float mul, uint32_t& hi, uint32_t& lo) {
+  const float v0 = __builtin_amdgcn_fmed3f(x0 * mul, -32768.0f, 32768.0f);
+  const float v1 = __builtin_amdgcn_fmed3f(x1 * mul, -32768.0f, 32768.0f);
+  const h2 h = {(_Float16)v0, (_Float16)v1};
+  hi = __builtin_bit_cast(uint32_t, h);
+  lo = pack_h2(v0 - (float)h[0], v1 - (float)h[1]);
+}
+
+// A whole row: packed words of hi and lo, and the row's factor.
+template <int N, int STEP = 16>
+__device__ __forceinline__ float row_split(const float (&x)[N], uint32_t (&hi)[N / 2], uint32_t (&lo)[N / 2]) {
+  float mul, fac;
+  row_scale<STEP>(abs_max(x), mul, fac);
 #pragma unroll
-  for (int i = 0; i < N; i += 2) {
-    const float v0 = __builtin_amdgcn_fmed3f(x[i] * mul, -32768.0f, 32768.0f);
-    const float v1 = __builtin_amdgcn_fmed3f(x[i + 1] * mul, -32768.0f, 32768.0f);
-    const h2 h = {(_Float16)v0, (_Float16)v1};
-    hi[i / 2] = __builtin_bit_cast(uint32_t, h);
-    lo[i / 2] = pack_h2(v0 - (float)h[0], v1 - (float)h[1]);
-  }
+  for (int i = 0; i < N; i += 2) split_words(x[i], x[i + 1], mul, hi[i / 2], lo[i / 2]);
   return fac;
 }
 
@@ -743,21 +758,38 @@ struct SplitRow {
   float fac;
 };
 
-// Stores a lane's entries of a split row and, from lane group 0, its factor.
-template <int C, int STEP = 16>
-__device__ __forceinline__ void store_split(const float (&x)[C / 4], int g, uint32_t* row, float* fac) {
-  uint32_t h[C / 8], l[C / 8];
-  const float f = row_split<C / 4, STEP>(x, h, l);
-  if constexpr (C >= 32) {
+// Stores piece ch of a lane's entries (32 channels of the row, all of it at C =
+// 16) as split words.
+template <int C>
+__device__ __forceinline__ void store_split_piece(const float* x, float mul, int ch, int g, uint32_t* row) {
+  constexpr int W = C >= 32 ? 4 : 2;  // words of a lane's piece in each plane
+  uint32_t h[W], l[W];
 #pragma unroll
-    for (int ch = 0; ch < C / 32; ++ch) {
-      *reinterpret_cast<uint4*>(row + 16 * ch + 4 * g) = make_uint4(h[4 * ch], h[4 * ch + 1], h[4 * ch + 2], h[4 * ch + 3]);
-      *reinterpret_cast<uint4*>(row + C / 2 + 16 * ch + 4 * g) =
-          make_uint4(l[4 * ch], l[4 * ch + 1], l[4 * ch + 2], l[4 * ch + 3]);
-    }
+  for (int i = 0; i < W; ++i) split_words(x[2 * i], x[2 * i + 1], mul, h[i], l[i]);
+  if constexpr (C >= 32) {
+    *reinterpret_cast<uint4*>(row + 16 * ch + 4 * g) = make_uint4(h[0], h[1], h[2], h[3]);
+    *reinterpret_cast<uint4*>(row + C / 2 + 16 * ch + 4 * g) = make_uint4(l[0], l[1], l[2], l[3]);
   } else {
     *reinterpret_cast<uint2*>(row + 2 * g) = make_uint2(h[0], h[1]);
     *reinterpret_cast<uint2*>(row + 8 + 2 * g) = make_uint2(l[0], l[1]);
+  }
+}
+
+// A piece's work ends here where the registers do not hold that of all pieces.
+template <int C>
+__device__ __forceinline__ void piece_end() {
+  if constexpr (C > 32) __builtin_amdgcn_sched_barrier(0);
+}
+
+// Stores a lane's entries of a split row and, from lane group 0, its factor.
+template <int C, int STEP = 16>
+__device__ __forceinline__ void store_split(const float (&x)[C / 4], int g, uint32_t* row, float* fac) {
+  float mul, f;
+  row_scale<STEP>(abs_max(x), mul, f);
+#pragma unroll
+  for (int ch = 0; ch < (C >= 32 ? C / 32 : 1); ++ch) {
+    store_split_piece<C>(x + 8 * ch, mul, ch, g, row);
+    piece_end<C>();
   }
   if (g == 0) *fac = f;
 }
@@ -939,17 +971,21 @@ __device__ __forceinline__ void conv_sum(const ConvArgs& a, const uint4* s_w, ui
 template <int C, bool XB>
 __device__ __forceinline__ void conv_epilogue(const ConvArgs& a, const f4 (&sum)[C / 16], int g, const TileRef& tr,
                                               float (&x)[C / 4]) {
-  constexpr int N = C / 4;
-  float wf[N], bs[N];
-  load_row<C>(a.wfac, g, wf);
-  load_row<C>(a.bias, g, bs);
+  constexpr int N = C / 4, NC = N < 8 ? N : 8;
 #pragma unroll
-  for (int i = 0; i < N; ++i) x[i] = fmaf(sum[i / 4][i % 4], wf[i], bs[i]);
-  if (a.res) {  // residual block: ReLU(x + conv(.)), x read at the voxel's own row
-    float rs[N];
-    load_row<C>(a.res + tr.prow * C, g, rs);
+  for (int c0 = 0; c0 < N; c0 += NC) {  // one 32-channel piece at a time
+    float wf[NC], bs[NC];
+    load_row<4 * NC>(a.wfac + 4 * c0, g, wf);
+    load_row<4 * NC>(a.bias + 4 * c0, g, bs);
 #pragma unroll
-    for (int i = 0; i < N; ++i) x[i] += rs[i];
+    for (int i = 0; i < NC; ++i) x[c0 + i] = fmaf(sum[(c0 + i) / 4][i % 4], wf[i], bs[i]);
+    if (a.res) {  // residual block: ReLU(x + conv(.)), x read at the voxel's own row
+      float rs[NC];
+      load_row<4 * NC>(a.res + tr.prow * C + 4 * c0, g, rs);
+#pragma unroll
+      for (int i = 0; i < NC; ++i) x[c0 + i] += rs[i];
+    }
+    piece_end<C>();
   }
 #pragma unroll
   for (int i = 0; i < N; ++i) x[i] = fmaxf(x[i], 0.0f);
@@ -960,14 +996,31 @@ __device__ __forceinline__ void conv_epilogue(const ConvArgs& a, const f4 (&sum)
     const uint32_t code = a.code[tr.lvb + (tr.prow - tr.mo)];
     const int64_t first = a.fc[tr.lvb + (tr.prow - tr.mo)];
     if (cmo + cn > a.cap_model) cmo = -1;  // overflow (latched where the size was made): no writes
+    auto child = [&](int c0, int d, float (&y)[NC]) {
+      load_row<4 * NC>(a.emb_d + d * C + 4 * c0, g, y);
+#pragma unroll
+      for (int i = 0; i < NC; ++i) y[i] = x[c0 + i] + y[i];
+    };
     int rank = 0;
     for (int d = 0; d < 8; ++d) {
       if (cmo >= 0 && ((code >> d) & 1u)) {
         const int64_t row = cmo + first + rank;
-        float y[N];
-        add_row<C>(x, a.emb_d + d * C, g, y);
-        store_row<C>(y, g, a.xb + row * C);
-        store_split<C>(y, g, a.xb_s + row * C, a.xb_r + row);
+        float m = 0.0f, mul, f, y[NC];
+#pragma unroll
+        for (int c0 = 0; c0 < N; c0 += NC) {
+          child(c0, d, y);
+          store_row<4 * NC>(y, g, a.xb + row * C + 4 * c0);
+          m = abs_max(y, m);
+          piece_end<C>();
+        }
+        row_scale(m, mul, f);
+#pragma unroll
+        for (int c0 = 0; c0 < N; c0 += NC) {
+          if constexpr (N > NC) child(c0, d, y);  // formed again: all pieces would not fit the registers
+          store_split_piece<C>(y, mul, c0 / NC, g, a.xb_s + row * C);
+          piece_end<C>();
+        }
+        if (g == 0) a.xb_r[row] = f;
         ++rank;
       }
     }
@@ -1509,6 +1562,7 @@ struct OffMask {
     if (o < 64) lo |= 1ull << o;
     else hi |= 1ull << (o - 64);
   }
+  __device__ __forceinline__ bool has(int o) const { return o < 64 ? (lo >> o) & 1ull : (hi >> (o - 64)) & 1ull; }
   // lowest offset, removed from the set (-1 when empty)
   __device__ __forceinline__ int pop() {
     if (lo) {
@@ -1525,9 +1579,9 @@ struct OffMask {
   }
 };
 
-constexpr int cw_waves(int C) { return C == 128 ? 16 : 8; }         // waves (tiles of a group) of a block
+constexpr int cw_waves(int C) { return C == 128 ? 16 : 8; }         // waves of a block
 constexpr unsigned cw_blocks(int C) { return C == 128 ? 256 : 512; }  // 16 waves of 128 registers on each CU
-constexpr int CW_SPLIT_ROUNDS = 2;  // column split while a block has at most this many tile sets
+constexpr int64_t CW_SPLIT_TILES = 2048;  // column split up to this many tiles a launch
 
 // The rows of one offset's neighbours as a lane's operands (k_conv's layout,
 // one piece per 32 input channels).
@@ -1593,67 +1647,281 @@ __device__ __forceinline__ void wide_mma(const uint4* wb, int lane, const WideRo
     for (int e = 0; e < 4; ++e) acc[q][e] = fmaf(p[q][e], x.fac, acc[q][e]);
 }
 
-// The same for one column block whose operands are in registers.
-template <int C>
-__device__ __forceinline__ void wide_mma_regs(const uint4* wv, const WideRows<C>& x, f4& acc) {
-  constexpr int NCH = WideRows<C>::NCH, PL = weight_planes(C);
-  f4 p = f4{0.0f, 0.0f, 0.0f, 0.0f};
-  if constexpr (C >= 32) {
+// A block's view of the scales of a launch (in LDS).
+struct WideScales {
+  int64_t tpre[NLEV + 1];  // first tile of each scale
+  int64_t nv[NLEV], mo[NLEV];
+};
+
+// Tile `tile` as lane (r, .) sees it; idle lanes name a real row.
+__device__ __forceinline__ TileRef wide_tile(const ConvArgs& a, const WideScales& sc, int64_t tile, int r) {
+  int si = 0;
 #pragma unroll
-    for (int ch = 0; ch < NCH; ++ch) {
-      p = mfma_h(wv[ch * PL + 1], x.hi[ch], p);
-      p = mfma_h(wv[ch * PL], x.lo[ch], p);
-      p = mfma_h(wv[ch * PL], x.hi[ch], p);
-    }
-  } else {
+  for (int i = 1; i < NLEV; ++i) si += (sc.tpre[i] <= tile) ? 1 : 0;
+  const int64_t nvox = sc.nv[si];
+  const int64_t row = (tile - sc.tpre[si]) * 16 + r;
+  TileRef tr;
+  tr.b = a.b_lo + si;
+  tr.mo = sc.mo[si];
+  tr.lvb = (int64_t)(tr.b - a.b0) * a.cap_pts;
+  tr.valid = row < nvox;
+  const int64_t pos = tr.mo + (tr.valid ? row : nvox - 1);
+  tr.prow = a.perm ? (int64_t)a.perm[pos] : pos;  // with a tile order, slot -> row
+  return tr;
+}
+
+// A lane's share of a tile's map rows (lane (r, g): entries EPL g .. of voxel r;
+// -1 where `have` is false or the voxel is not valid) and the tile's occupied offsets.
+template <int EPL>
+__device__ __forceinline__ OffMask wide_map(const ConvArgs& a, const TileRef& tr, bool have, int g, int32_t (&nbv)[EPL]) {
 #pragma unroll
-    for (int pl = PL - 1; pl >= 0; --pl) p = mfma_h(wv[pl], x.hi[0], p);
+  for (int q = 0; q < EPL / 4; ++q) {
+    int4 t = make_int4(-1, -1, -1, -1);
+    if (have && tr.valid) t = reinterpret_cast<const int4*>(a.nbr + tr.prow * (4 * EPL) + EPL * g)[q];
+    nbv[4 * q] = t.x;
+    nbv[4 * q + 1] = t.y;
+    nbv[4 * q + 2] = t.z;
+    nbv[4 * q + 3] = t.w;
   }
+  uint32_t mine = 0;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) acc[e] = fmaf(p[e], x.fac, acc[e]);
+  for (int j = 0; j < EPL; ++j) mine |= (nbv[j] >= 0 ? 1u : 0u) << j;
+  mine = or_row16(mine);
+  uint64_t q[4];
+#pragma unroll
+  for (int gg = 0; gg < 4; ++gg) q[gg] = (uint32_t)__builtin_amdgcn_readlane((int)mine, 16 * gg);
+  OffMask own;
+  if constexpr (EPL == 32) {
+    own.lo = q[0] | (q[1] << 32);
+    own.hi = q[2] | (q[3] << 32);
+  } else {
+    own.lo = q[0] | (q[1] << EPL) | (q[2] << 2 * EPL) | (q[3] << 3 * EPL);
+  }
+  return own;
+}
+
+// v, as a value that the compiler knows nothing of: addresses formed from it stay
+// where they are used instead of in registers across the walk over the offsets.
+__device__ __forceinline__ int opaque(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
+__device__ __forceinline__ uint64_t uniform64(uint64_t v) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
+  return ((uint64_t)hi << 32) | lo;
+}
+
+// Shapes of k_convw.  Staged form: one tile per wave.  Column-split form: half
+// of the waves multiply, one column block each (SG tile subgroups of NCB waves),
+// the others fetch the rows of their subgroup's tiles, one of the NCB slices
+// (32-channel piece, plane) of a row each; SLOTS tiles per subgroup.
+template <int C, int KV>
+struct WideShape {
+  static constexpr int WAVES = cw_waves(C), THREADS = 64 * WAVES;
+  static constexpr int NCB = C / 16, NCH = WideRows<C>::NCH, PL = weight_planes(C);
+  static constexpr int NBS = KV > 27 ? 128 : NBR_STRIDE, EPL = NBS / 4;  // map row, entries per lane
+  static constexpr int CBW = NCH * PL * 64;  // 16-byte words of a column block's weights of an offset
+  static constexpr int WQ = NCB * CBW;       // of all of them
+  static constexpr bool SPLITS = NCB > 1;
+  static constexpr int SG = SPLITS ? WAVES / 2 / NCB : 1, SLOTS = SPLITS ? 4 / SG : 0, TILES = SG * SLOTS;
+  static constexpr int ROWS = 2 * TILES * NCB * 64;  // 16-byte words: rows of two offsets,
+  static constexpr int MAP = TILES * NBS * 16 / 4;   // the tiles' maps [offset][voxel],
+  static constexpr int FAC = 2 * TILES * 16 / 4;     // the rows' factors
+  static constexpr int LDS = 2 * WQ > ROWS + MAP + FAC ? 2 * WQ : ROWS + MAP + FAC;
+};
+
+// Column-split form of k_convw, for launches whose tiles would leave most CUs
+// idle at one tile per wave.  A block takes up to TILES tiles and walks the union
+// of their occupied offsets; at each, a multiplying wave holds its column block's
+// weights in registers and reads the tiles' rows from LDS, so that the tiles
+// share one read of the weights, which bounds these launches (64 KB an offset and
+// block at C = 128).  Both weights (two sets of registers) and rows (two LDS
+// buffers, the gathers of one more in registers) are fetched one offset ahead.
+// With one tile's column block per wave, its weights and rows loaded after the
+// products of the offset before, a decoder's launches at C = 128 took 447 to 690
+// us with 5x5x5 kernels and 96 to 147 us with 3x3x3 ones; now 96 to 420 and 34 to
+// 48 (16 to 64 beams, 11 and 12 bits).
+template <int C, int KV, bool XB>
+__device__ __forceinline__ void convw_split(const ConvArgs& a, const WideScales& sc, uint4* s_buf,
+                                            uint64_t (*s_mask)[2], int64_t total_tiles, int tps, int w, int lane0) {
+  using S = WideShape<C, KV>;
+  constexpr int NCB = S::NCB, NCH = S::NCH, SLOTS = S::SLOTS, TILES = S::TILES, WR = S::CBW / 64;
+  static_assert(NCB >= SLOTS && NCB == 2 * NCH, "a fetching wave per row slice, one of them per tile's factors");
+  uint4* s_rows = s_buf;                                            // [2][TILES][NCB][64]
+  int32_t* s_map = reinterpret_cast<int32_t*>(s_buf + S::ROWS);     // [TILES][NBS][16]
+  float* s_fac = reinterpret_cast<float*>(s_buf + S::ROWS + S::MAP);  // [2][TILES][16]
+  const bool mult = w < S::WAVES / 2;  // multiplying wave
+  const int sg = (w % (S::WAVES / 2)) / NCB, cb = w % NCB;
+  for (int64_t set = blockIdx.x; set * tps < total_tiles; set += gridDim.x) {
+    __syncthreads();  // prefix visible; the previous set is done with the LDS
+    const int lane = opaque(lane0), r = lane & 15, g = lane >> 4;
+    const uint4* wsrc = reinterpret_cast<const uint4*>(a.w) + cb * S::CBW + lane;
+    // wave w opens tile w
+    const int64_t tile = set * tps + w;
+    const bool have = w < tps && tile < total_tiles;
+    TileRef tr{a.b_lo, 0, 0, 0, false};
+    if (w < TILES) {
+      if (have) tr = wide_tile(a, sc, tile, r);
+      int32_t nbv[S::EPL];
+      const OffMask own = wide_map<S::EPL>(a, tr, have, g, nbv);
+#pragma unroll
+      for (int j = 0; j < S::EPL; ++j)
+        s_map[(w * S::NBS + S::EPL * g + j) * 16 + r] = nbv[j] >= 0 ? (int32_t)tr.mo + nbv[j] : -1;
+      if (lane == 0) {
+        s_mask[w][0] = own.lo;
+        s_mask[w][1] = own.hi;
+      }
+    }
+    __syncthreads();
+    OffMask uni, m[SLOTS];  // of the set, and of the subgroup's tiles
+#pragma unroll
+    for (int t = 0; t < TILES; ++t) {
+      uni.lo |= uniform64(s_mask[t][0]);
+      uni.hi |= uniform64(s_mask[t][1]);
+    }
+#pragma unroll
+    for (int j = 0; j < SLOTS; ++j) {
+      m[j].lo = uniform64(s_mask[j * S::SG + sg][0]);
+      m[j].hi = uniform64(s_mask[j * S::SG + sg][1]);
+    }
+    // a multiplying wave's sums, a fetching wave's rows in flight
+    f4 st[SLOTS];
+#pragma unroll
+    for (int j = 0; j < SLOTS; ++j) st[j] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+    float vf = 0.0f;  // fetching wave of slice j < SLOTS: slot j's factors in flight
+    uint4 wv[2][WR];
+    auto weights = [&](int k, uint4 (&v)[WR]) {
+#pragma unroll
+      for (int i = 0; i < WR; ++i) v[i] = wsrc[(int64_t)k * S::WQ + i * 64];
+    };
+    auto fetch = [&](int k) {
+#pragma unroll
+      for (int j = 0; j < SLOTS; ++j) {
+        if (!m[j].has(k)) continue;
+        const int32_t row = s_map[((j * S::SG + sg) * S::NBS + k) * 16 + r];
+        if (row >= 0)
+          st[j] = reinterpret_cast<const f4*>(a.h_in + (int64_t)row * C)[(cb & 1) * (C / 8) + 4 * (cb >> 1) + g];
+        if (cb == j) vf = row >= 0 ? a.r_in[row] : 0.0f;
+      }
+    };
+    auto put = [&](int k, int buf) {
+#pragma unroll
+      for (int j = 0; j < SLOTS; ++j) {
+        if (!m[j].has(k)) continue;
+        const int t = buf * TILES + j * S::SG + sg;
+        s_rows[(t * NCB + cb) * 64 + lane] = __builtin_bit_cast(uint4, st[j]);
+        if (cb == j && g == 0) s_fac[t * 16 + r] = vf;
+      }
+    };
+    auto mma = [&](int k, const uint4 (&v)[WR], int buf) {
+#pragma unroll
+      for (int j = 0; j < SLOTS; ++j) {
+        if (!m[j].has(k)) continue;
+        const int t = buf * TILES + j * S::SG + sg;
+        const uint4* x = s_rows + t * NCB * 64 + lane;
+        const float fac = s_fac[t * 16 + r];
+        f4 p = f4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int ch = 0; ch < NCH; ++ch) {  // the chain of wide_mma
+          const uint4 hi = x[2 * ch * 64], lo = x[(2 * ch + 1) * 64];
+          p = mfma_h(v[2 * ch + 1], hi, p);
+          p = mfma_h(v[2 * ch], lo, p);
+          p = mfma_h(v[2 * ch], hi, p);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) st[j][e] = fmaf(p[e], fac, st[j][e]);
+      }
+    };
+    int kc = uni.pop(), kn = uni.pop();
+    if (kc >= 0) {  // block-uniform
+      if (mult) {
+        weights(kc, wv[0]);
+        weights(kn >= 0 ? kn : kc, wv[1]);
+      } else {
+        fetch(kc);
+        put(kc, 0);
+        if (kn >= 0) fetch(kn);
+      }
+      __syncthreads();
+      // one offset: products of kc from set BUF, rows of kn to the other buffer,
+      // the loads of the offset after
+      auto step = [&](auto which) {
+        constexpr int BUF = decltype(which)::value;
+        const int kf = uni.pop();
+        if (mult) {
+          mma(kc, wv[BUF], BUF);
+          weights(kf >= 0 ? kf : kc, wv[BUF]);  // unconditional: exact waits
+        } else {
+          if (kn >= 0) put(kn, BUF ^ 1);
+          if (kf >= 0) fetch(kf);
+        }
+        __syncthreads();
+        kc = kn;
+        kn = kf;
+        return kc >= 0;
+      };
+      while (step(std::integral_constant<int, 0>{}) && step(std::integral_constant<int, 1>{})) {
+      }
+    }
+    // the column blocks of a tile meet in LDS; wave t goes on with tile t
+    f4* s_x = reinterpret_cast<f4*>(s_rows);  // [TILES][NCB][64]
+    if (mult) {
+#pragma unroll
+      for (int j = 0; j < SLOTS; ++j) s_x[((j * S::SG + sg) * NCB + cb) * 64 + lane] = st[j];
+    }
+    __syncthreads();
+    if (!have) continue;
+    f4 acc[NCB];
+#pragma unroll
+    for (int q = 0; q < NCB; ++q) acc[q] = s_x[(w * NCB + q) * 64 + lane];
+    float x[C / 4];
+    const int l2 = opaque(lane);  // the tile is opened again: held across the walk it would cost registers there
+    conv_epilogue<C, XB>(a, acc, l2 >> 4, wide_tile(a, sc, tile, l2 & 15), x);
+  }
 }
 
 // Sparse conv C -> C (ReLU, optional residual input, child scatter and row
 // store as in k_conv) with the weights streamed, for layers whose weights do
-// not fit in LDS (a 5x5x5 kernel at C = 128 holds 8 MB).  A block takes groups
-// of tiles, one per wave.  For each offset in the union of the group's occupied
-// offsets, in ascending order, the block stages that offset's weights in LDS
-// (one offset ahead there, the one after in flight), and each wave whose tile
-// has the offset adds its gathered neighbour rows on split fp16 MFMA as k_conv
-// does and gathers its next rows into the same registers.  Launches with few
-// tiles split each tile's column blocks over waves instead, every wave reading
-// its own slice of the weights from memory into registers, without LDS or
-// barriers.  A voxel adds its offsets in ascending order, each chained from
-// zero, whatever its group, so results do not depend on the grouping.
+// not fit in LDS (a 5x5x5 kernel at C = 128 holds 8 MB).  Staged form: a block
+// takes groups of tiles, one per wave.  For each offset in the union of the
+// group's occupied offsets, in ascending order, the block stages that offset's
+// weights in LDS (one offset ahead there, the one after in flight), and each wave
+// whose tile has the offset adds its gathered neighbour rows on split fp16 MFMA as
+// k_conv does and gathers its next rows into the same registers.  Launches with
+// few tiles take the column-split form above.  A voxel adds its offsets in
+// ascending order, each chained from zero, whatever its group or form, so results
+// do not depend on the grouping.
 //
 // A 5x5x5 layer at C = 128 is bound by the weights' way from memory (8 MB do
-// not stay in a 4 MB L2: half of the lines miss), so its groups are as large as
-// the registers of a CU allow, 16 tiles on 16 waves; with 8 waves of twice the
-// registers and the rows gathered ahead into a second set it took 2.0 ms
-// instead of 1.55 (64-beam scan at 14 bits, mean of the layers; 4.2 ms on fp32
-// MFMA).  Groups differ in their offsets (27 to 125), so blocks take them first
-// come, first served, their own XCD's share before the others' (2.33 -> 2.0 ms
-// in the 8-wave form).  C = 64, 3x3x3: a chain of 27 rows and barriers at one or
-// two groups a block, 170 us on fp32 MFMA, 103 now.
-// Column split up to two sets a block: at four the 3x3x3 layers at C = 64 take
-// 112 us instead of 103, at sixteen the 5x5x5 layers at C = 128 5.0 ms.
+// not stay in a 4 MB L2), so its groups are as large as the waves of a CU allow,
+// 16 tiles on 16 waves; with 8 waves of twice the registers and the rows gathered
+// ahead into a second set it took 2.0 ms instead of 1.55 (64-beam scan at 14 bits,
+// mean of the layers; 4.2 ms on fp32 MFMA).  128 registers a wave hold a tile's
+// sums and rows at C = 128 with little to spare: a few values of the opening and
+// the epilogue go through scratch (52 to 80 bytes a lane; none at C <= 64).
+// Groups differ in their offsets (27 to 125), so blocks take them first come,
+// first served, their own XCD's share before the others' (2.33 -> 2.0 ms in the
+// 8-wave form).
+//
+// Staged against column-split form, us a launch by tiles (one scale of LiDAR
+// scans per call, mean of the four layers):
+//   tiles        137   294   555   974  1227  2027  2320  4220  6699
+//   C 128 k 5  496/157 537/190 525/228 526/262 528/350 545/418 561/573 678/801 981/1152
+//   C 128 k 3  147/44  156/50  160/59  159/68  163/80  169/104 176/141 219/211 296/305
+//   C  64 k 5  158/71  162/72  157/87  156/100 165/117 179/139 192/196 262/268 331/371
+//   C  64 k 3   49/26   50/28   52/32   55/37   59/42   67/48   73/63  103/89  119/120
+//   C  32 k 5   91/61   94/68   95/64   95/66  104/79  114/84  123/123 166/161 201/217
+// so launches of up to CW_SPLIT_TILES = 2048 tiles split.
 template <int C, int KV, bool XB>
 __global__ void __launch_bounds__(64 * cw_waves(C), 4) k_convw(ConvArgs a) {
-  constexpr int CW_WAVES = cw_waves(C), CW_THREADS = 64 * CW_WAVES;
-  constexpr int NCB = C / 16;
-  constexpr int NCH = WideRows<C>::NCH;
-  constexpr int NBS = KV > 27 ? 128 : NBR_STRIDE;
-  constexpr int EPL = NBS / 4;                             // map entries per lane
-  constexpr int CBW = NCH * weight_planes(C) * 64;         // 16-byte words of a column block's weights of an offset
-  constexpr int WQ = NCB * CBW;                            // of all of them
-  constexpr int TPB = CW_WAVES / NCB;                      // tiles of a block in a column-split launch
-  __shared__ uint4 s_w[2][WQ];
+  using S = WideShape<C, KV>;
+  constexpr int CW_WAVES = S::WAVES, CW_THREADS = S::THREADS, NCB = S::NCB, CBW = S::CBW, WQ = S::WQ;
+  __shared__ uint4 s_buf[S::LDS];  // staged form: the weights of two offsets
   __shared__ uint64_t s_mask[CW_WAVES][2];
-  __shared__ int64_t s_tpre[NLEV + 1];
-  __shared__ int64_t s_nv[NLEV];
-  __shared__ int64_t s_mo[NLEV];
+  __shared__ WideScales s_sc;
   __shared__ int64_t s_next[2];
-  static_assert(NCB == 1 || 2 * WQ >= CW_WAVES * 64, "the column blocks' sums meet in the weight area");
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int r = lane & 15, g = lane >> 4;
   const int nsc = a.b_hi - a.b_lo + 1;
@@ -1666,32 +1934,38 @@ __global__ void __launch_bounds__(64 * cw_waves(C), 4) k_convw(ConvArgs a) {
   }
   const int64_t groups = (total_tiles + CW_WAVES - 1) / CW_WAVES;
   const int64_t tch = groups / 64 < 4 ? 4 : (groups / 64 > 64 ? 64 : groups / 64);
-  const int64_t sets = (total_tiles + TPB - 1) / TPB;
-  const bool split = NCB > 1 && sets <= (int64_t)gridDim.x * CW_SPLIT_ROUNDS;  // uniform
-  const int64_t nwork = split ? sets : groups;
-  if (split ? (int64_t)blockIdx.x >= sets : conv_tile(0, tch) >= groups) return;  // whole block idle
+  const bool split = S::SPLITS && total_tiles <= CW_SPLIT_TILES;  // uniform
+  // tiles of a column-split block: as few per subgroup as give every block one set
+  const int64_t per = (total_tiles + (int64_t)gridDim.x * S::SG - 1) / ((int64_t)gridDim.x * S::SG);
+  const int tps = S::SG * (int)(per < 1 ? 1 : (per > S::SLOTS ? S::SLOTS : per));
+  if (split ? (int64_t)blockIdx.x * tps >= total_tiles : conv_tile(0, tch) >= groups) return;  // whole block idle
   if (tid == 0) {
     int64_t acc = 0;
     for (int i = 0; i < nsc; ++i) {
       int64_t mo, nb;
       scale_span(rm, a.b_lo + i, mo, nb);
-      s_tpre[i] = acc;
-      s_nv[i] = nb;
-      s_mo[i] = mo;
+      s_sc.tpre[i] = acc;
+      s_sc.nv[i] = nb;
+      s_sc.mo[i] = mo;
       acc += (nb + 15) / 16;
     }
-    for (int i = nsc; i <= NLEV; ++i) s_tpre[i] = acc;
+    for (int i = nsc; i <= NLEV; ++i) s_sc.tpre[i] = acc;
+  }
+  if constexpr (S::SPLITS) {
+    if (split) {
+      convw_split<C, KV, XB>(a, s_sc, s_buf, s_mask, total_tiles, tps, w, lane);
+      return;
+    }
   }
   const uint4* wsrc = reinterpret_cast<const uint4*>(a.w);
   WideRows<C> xa;
   xa.clear();
   int vic = blockIdx.x & 7;  // thread 0: the XCD whose share the block takes groups of
   for (int64_t gs = 0;; ++gs) {
-    __syncthreads();  // prefix and s_next visible; the previous group is done with s_mask and s_w
-    const int64_t grp = split ? (int64_t)blockIdx.x + gs * (int64_t)gridDim.x
-                              : (gs == 0 ? conv_tile(0, tch) : s_next[gs & 1]);  // block-uniform
-    if (grp >= nwork) break;
-    if (!split && tid == 0) {  // the next group, read after the next turn's barrier
+    __syncthreads();  // prefix and s_next visible; the previous group is done with s_mask and s_buf
+    const int64_t grp = gs == 0 ? conv_tile(0, tch) : s_next[gs & 1];  // block-uniform
+    if (grp >= groups) break;
+    if (tid == 0) {  // the next group, read after the next turn's barrier
       int64_t ng = groups;
       for (int t = 0; t < 8; ++t) {
         ng = xcd_tile(vic, (gridDim.x >> 3) + (int64_t)atomicAdd(a.next + vic, 1u), tch);
@@ -1700,47 +1974,19 @@ __global__ void __launch_bounds__(64 * cw_waves(C), 4) k_convw(ConvArgs a) {
       }
       s_next[(gs + 1) & 1] = ng;
     }
-    const int64_t tile = split ? grp * TPB + w / NCB : grp * CW_WAVES + w;
+    const int64_t tile = grp * CW_WAVES + w;
     const bool have = tile < total_tiles;
     TileRef tr{a.b_lo, 0, 0, 0, false};
-    if (have) {
-      int si = 0;
-#pragma unroll
-      for (int i = 1; i < NLEV; ++i) si += (s_tpre[i] <= tile) ? 1 : 0;
-      const int64_t nvox = s_nv[si];
-      const int64_t row = (tile - s_tpre[si]) * 16 + r;
-      tr.b = a.b_lo + si;
-      tr.mo = s_mo[si];
-      tr.lvb = (int64_t)(tr.b - a.b0) * a.cap_pts;
-      tr.valid = row < nvox;
-      const int64_t pos = tr.mo + (tr.valid ? row : nvox - 1);  // idle lanes read a real row
-      tr.prow = a.perm ? (int64_t)a.perm[pos] : pos;            // with a tile order, slot -> row
-    }
-    // occupied offsets of the wave's tile (wave-uniform), from the map rows
+    if (have) tr = wide_tile(a, s_sc, tile, r);
     OffMask own;
     {
-      int32_t nbv[EPL];
-#pragma unroll
-      for (int q = 0; q < EPL / 4; ++q) {
-        int4 t = make_int4(-1, -1, -1, -1);
-        if (have) t = reinterpret_cast<const int4*>(a.nbr + tr.prow * NBS + EPL * g)[q];
-        nbv[4 * q] = t.x;
-        nbv[4 * q + 1] = t.y;
-        nbv[4 * q + 2] = t.z;
-        nbv[4 * q + 3] = t.w;
-      }
-#pragma unroll
-      for (int j = 0; j < EPL; ++j) {
-        const uint64_t bal = __ballot(tr.valid && nbv[j] >= 0);
-#pragma unroll
-        for (int gg = 0; gg < 4; ++gg)
-          if ((bal >> (16 * gg)) & 0xFFFFull) own.set(gg * EPL + j);
-      }
+      int32_t nbv[S::EPL];
+      own = wide_map<S::EPL>(a, tr, have, g, nbv);
     }
     // each lane reads its own voxel's map entry of an offset one of the wave's
     // offsets ahead of the gather, which follows the products of the offset
     // before into the same registers
-    const int32_t* maprow = a.nbr + tr.prow * NBS;
+    const int32_t* maprow = a.nbr + tr.prow * S::NBS;
     auto entry = [&](int k) -> int32_t { return (k >= 0 && have) ? maprow[k] : -1; };
     auto gather = [&](int32_t nn) { xa.load(a, tr.valid && nn >= 0 ? tr.mo + nn : -1, g); };
     f4 acc[NCB];
@@ -1755,79 +2001,53 @@ __global__ void __launch_bounds__(64 * cw_waves(C), 4) k_convw(ConvArgs a) {
     int kq = own.pop();
     int32_t eq = entry(kq);
     if (ko >= 0) gather(eo);
-    if (split) {
-      const int cb = w % NCB;
-      uint4 wv[CBW / 64];
-      auto weights = [&](int k) {
+    __syncthreads();
+    OffMask uni;
+    for (int ww = 0; ww < CW_WAVES; ++ww) {
+      uni.lo |= s_mask[ww][0];
+      uni.hi |= s_mask[ww][1];
+    }
+    int kc = uni.pop(), kn = uni.pop();
+    Staged<WQ, CW_THREADS> stw;
+    auto weights = [&](int k) { stw.load(reinterpret_cast<const f4*>(wsrc + (int64_t)k * WQ), tid); };
+    // a group can have no offset at all: base voxels that are not in order (an
+    // error that the host learns of later) are not even found as their own neighbours
+    if (kc >= 0) {
+      weights(kc);
+      stw.store(reinterpret_cast<f4*>(s_buf), tid);
+    }
+    if (kn >= 0) weights(kn);
+    __syncthreads();
+    int buf = 0;
+    while (kc >= 0) {  // block-uniform
+      const bool mine = kc == ko;
+      if (mine) {
+        constexpr int NB = NCB == 2 || NCB == 4 ? 2 : 1;
 #pragma unroll
-        for (int i = 0; i < CBW / 64; ++i) wv[i] = wsrc[(int64_t)k * WQ + cb * CBW + i * 64 + lane];
-      };
-      if (ko >= 0) weights(ko);
-      while (ko >= 0) {  // wave-uniform
-        wide_mma_regs<C>(wv, xa, acc[0]);
-        ko = kq;
-        if (ko >= 0) {
-          weights(ko);
-          gather(eq);
+        for (int cb = 0; cb < NCB; cb += NB) {
+          wide_mma<C, NB>(s_buf + buf * WQ + cb * CBW, lane, xa, acc + cb);
+          __builtin_amdgcn_sched_barrier(0);  // operands of all blocks at once would not fit the registers
         }
+      }
+      kc = kn;
+      if (kn >= 0) {  // weights one offset ahead in LDS, two ahead in flight
+        stw.store(reinterpret_cast<f4*>(s_buf + (buf ^ 1) * WQ), tid);
+        kn = uni.pop();
+        if (kn >= 0) weights(kn);
+      }
+      if (mine) {
+        ko = kq;
+        if (ko >= 0) gather(eq);
         kq = own.pop();
         eq = entry(kq);
       }
-      // the column blocks of a tile meet in LDS; the wave of block 0 goes on
-      f4* s_x = reinterpret_cast<f4*>(s_w[0]);  // [wave][64]
-      s_x[w * 64 + lane] = acc[0];
       __syncthreads();
-      if (!have || cb != 0) continue;
-#pragma unroll
-      for (int j = 0; j < NCB; ++j) acc[j] = s_x[(w + j) * 64 + lane];
-    } else {
-      __syncthreads();
-      OffMask uni;
-      for (int ww = 0; ww < CW_WAVES; ++ww) {
-        uni.lo |= s_mask[ww][0];
-        uni.hi |= s_mask[ww][1];
-      }
-      int kc = uni.pop(), kn = uni.pop();
-      Staged<WQ, CW_THREADS> stw;
-      auto weights = [&](int k) { stw.load(reinterpret_cast<const f4*>(wsrc + (int64_t)k * WQ), tid); };
-      // a group can have no offset at all: base voxels that are not in order (an
-      // error that the host learns of later) are not even found as their own neighbours
-      if (kc >= 0) {
-        weights(kc);
-        stw.store(reinterpret_cast<f4*>(s_w[0]), tid);
-      }
-      if (kn >= 0) weights(kn);
-      __syncthreads();
-      int buf = 0;
-      while (kc >= 0) {  // block-uniform
-        const bool mine = kc == ko;
-        if (mine) {
-          constexpr int NB = NCB == 2 || NCB == 4 ? 2 : 1;
-#pragma unroll
-          for (int cb = 0; cb < NCB; cb += NB) {
-            wide_mma<C, NB>(s_w[buf] + cb * CBW, lane, xa, acc + cb);
-            __builtin_amdgcn_sched_barrier(0);  // operands of all blocks at once would not fit the registers
-          }
-        }
-        kc = kn;
-        if (kn >= 0) {  // weights one offset ahead in LDS, two ahead in flight
-          stw.store(reinterpret_cast<f4*>(s_w[buf ^ 1]), tid);
-          kn = uni.pop();
-          if (kn >= 0) weights(kn);
-        }
-        if (mine) {
-          ko = kq;
-          if (ko >= 0) gather(eq);
-          kq = own.pop();
-          eq = entry(kq);
-        }
-        __syncthreads();
-        buf ^= 1;
-      }
+      buf ^= 1;
     }
     if (!have) continue;
     float x[C / 4];
-    conv_epilogue<C, XB>(a, acc, g, tr, x);
+    const int l2 = opaque(lane);  // opened again, as in the column-split form
+    conv_epilogue<C, XB>(a, acc, l2 >> 4, wide_tile(a, s_sc, tile, l2 & 15), x);
   }
 }
 

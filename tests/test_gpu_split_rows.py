@@ -109,11 +109,11 @@ def test_context_beyond_32_bit_row_offsets(C, two):
     _check(large, pts, B, b0, R, w, two)
 
 
-@pytest.mark.parametrize("C,ks,n", [(128, 3, 12000), (64, 3, 24000), (32, 5, 48000), (16, 5, 3000)])
+@pytest.mark.parametrize("C,ks,n", [(128, 3, 24000), (64, 3, 24000), (32, 5, 24000), (16, 5, 3000)])
 def test_streamed_layers_staged_and_column_split(C, ks, n):
-    """All scales at once stage the weights for groups of tiles, one scale at a time splits
-    each tile's columns over waves (C = 16 has one column block and never splits): the same
-    bits, and the smaller scales against the oracle."""
+    """All scales at once stage the weights for groups of tiles (above 2048 tiles), one scale
+    at a time splits each tile's columns over waves (C = 16 has one column block and never
+    splits): the same bits, and the smaller scales against the oracle."""
     B, b0, R = 9, 3, 10.0
     rs = np.random.default_rng(C + ks)
     cells = np.unique(rs.integers(0, 1 << (B - 2), size=(n, 3)) + (1 << (B - 3)), axis=0)
@@ -127,9 +127,44 @@ def test_streamed_layers_staged_and_column_split(C, ks, n):
     one = [ctx.predict_probs(b, logits=True).cpu().numpy() for b in range(b0 + 1, B)]
     rows = sum(ctx.num_voxels(b) for b in range(b0 + 1, B))
     ctx.close()
-    assert C == 16 or rows > 16 * 1024 * 128 // C >= n  # staged all together, split one by one
+    assert C == 16 or rows > 16 * (2048 + B) and n <= 16 * 2048  # staged all together, split one by one
     np.testing.assert_array_equal(np.concatenate(one), lg)
     P = oracle.Pyramid.from_points(pts, B, b0, R)
     for b, got in zip((b0 + 1, b0 + 2), one):
         ref = np.concatenate(P.model2(b, w)[:2], 1)
         assert np.abs(got - ref).max() <= 4e-6 * np.abs(ref).max(), b
+
+
+def _unmorton(k):
+    xyz = np.zeros((len(k), 3), np.int64)
+    for i in range(10):
+        for ax in range(3):
+            xyz[:, ax] |= ((k >> (3 * i + ax)) & 1) << i
+    return xyz
+
+
+@pytest.mark.parametrize("C,ks,tiles", [(128, 3, 256), (128, 3, 257), (128, 5, 1024), (128, 3, 1025), (128, 3, 2048),
+                                        (128, 3, 2049), (64, 3, 512), (64, 5, 513), (64, 3, 1537), (64, 3, 2048),
+                                        (32, 5, 1024), (32, 5, 1025), (32, 5, 2048)])
+def test_column_split_at_the_edges_of_its_sets(C, ks, tiles):
+    """A scale of exactly `tiles` tiles, alone (one to four tiles a block, one or two rounds, the last tile count
+    that splits and the first that does not) and beside a full finer scale eight times its size (staged): the same
+    bits.  The finer scale's rows take no part in the coarser one's sums."""
+    b, b0, R = 8, 6, 10.0
+    n = 16 * tiles - 5
+    cells = _unmorton(np.arange(8 * n))  # every child of the first n cells of scale b
+    B = b + 2
+    pts = (-R + (2 * cells + 0.5) * (2 * R / (1 << B))).astype(np.float32)
+    say("column split at", tiles, "tiles, C", C, "k", ks)
+    w = gen_weights(C, 2, seed=tiles, bias_std=0.1, two_stage=True, top=True, kernel_size=ks)
+    ctx = reno.Context(len(pts), B, b0, R, C, 2, two_stage=True, top=True, kernel_size=ks,
+                       max_model_voxels=len(pts) * 5 // 4 + 4096)
+    ctx.set_weights(reno.weights_to_device(w))
+    ctx.build_pyramid(to_dev(pts), B)
+    assert ctx.num_voxels(b) == n
+    one = ctx.predict_probs(b, logits=True).cpu().numpy()
+    lg = ctx.predict_probs(reno.RENO_ALL_SCALES, logits=True).cpu().numpy()
+    first = ctx.num_voxels(b - 1)
+    ctx.close()
+    assert np.isfinite(one).all()
+    np.testing.assert_array_equal(lg[first:first + n], one)
