@@ -2051,14 +2051,24 @@ __global__ void __launch_bounds__(64 * cw_waves(C), 4) k_convw(ConvArgs a) {
   }
 }
 
+// Threads and blocks of a k_headw launch.  C >= 64 needs more registers than 16
+// waves per CU allow (112 to 190 a wave), and there the blocks are no more than
+// are resident at once: the grid has to cover the largest scale of the context,
+// every further block would stage the head for a tile or two, or for none.  One
+// stage, C = 128 (128 KB staged, one block a CU): 8 waves, 11 us at 16 beams 11
+// bits, 18 at 64 beams 14 bits (decoder), 76 us in the encoder's launch; 4 waves
+// 11, 20, 106; 16 waves, with scratch, 18, 24, 70 (4 waves and up to 4096 blocks,
+// idle ones staging too: 11, 50, 150).  C = 64 with 4 waves 7, 11, 46, with 8 waves
+// 8, 11, 44 (before: 7, 21, 66).  Two stages, C = 128: 512 blocks 8 us (decoder, 64
+// beams) and 47 (encoder), 1024 8 and 49, 4096 9 and 69 (idle ones staging: 14, 62).
+template <int C, bool TWO>
+constexpr int headw_threads() { return C < 64 ? 1024 : (C == 128 && !TWO ? 512 : 256); }
+template <int C, bool TWO>
+constexpr int headw_blocks() { return C >= 64 ? (C == 128 && !TWO ? 256 : 512) : (TWO ? 4096 : 1024); }
+
 // The head on stored last-layer features h_in (rows of the scales b_lo ..
 // b_hi), for layers computed by k_convw: one wave per tile of 16 voxels, the
 // head weights in LDS, the same arithmetic as the fused head of k_conv.
-// threads of a k_headw block: the heads of wide layers need more registers
-// than 16 waves per CU allow
-template <int C, bool TWO>
-constexpr int headw_threads() { return C >= 64 ? 256 : 1024; }
-
 template <int C, bool TWO>
 __global__ void __launch_bounds__((headw_threads<C, TWO>())) k_headw(ConvArgs a) {
   constexpr int HT = headw_threads<C, TWO>();
@@ -2071,6 +2081,13 @@ __global__ void __launch_bounds__((headw_threads<C, TWO>())) k_headw(ConvArgs a)
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, r = lane & 15, g = lane >> 4;
   const int nsc = a.b_hi - a.b_lo + 1;
   const RowMap rm{a.count, a.moff, a.cap_model, -1, 0, a.cap_model + 1};
+  int64_t total = 0;
+  for (int i = 0; i < nsc; ++i) {
+    int64_t mo, nb;
+    scale_span(rm, a.b_lo + i, mo, nb);
+    total += (nb + 15) / 16;
+  }
+  if ((int64_t)blockIdx.x * HWV >= total) return;  // whole block idle: no staging
   Staged<HQ, HT> sth;
   sth.load(reinterpret_cast<const f4*>(a.hw), tid);
   if (tid == 0) {
@@ -2087,7 +2104,6 @@ __global__ void __launch_bounds__((headw_threads<C, TWO>())) k_headw(ConvArgs a)
   }
   sth.store(reinterpret_cast<f4*>(s_h), tid);
   __syncthreads();
-  const int64_t total = s_tpre[NLEV];
   for (int64_t tile = (int64_t)blockIdx.x * HWV + w; tile < total; tile += (int64_t)gridDim.x * HWV) {
     int si = 0;
 #pragma unroll
@@ -2116,8 +2132,8 @@ hipError_t run_headw(Ctx& c, bool two, const ConvArgs& a) {
     }
     return hipGetLastError();
   };
-  return two ? go(k_headw<C, true>, headw_threads<C, true>(), 4096)
-             : go(k_headw<C, false>, headw_threads<C, false>(), C >= 64 ? 4096 : 1024);
+  return two ? go(k_headw<C, true>, headw_threads<C, true>(), headw_blocks<C, true>())
+             : go(k_headw<C, false>, headw_threads<C, false>(), headw_blocks<C, false>());
 }
 
 // ---------------------------------------------------------------------------

@@ -148,23 +148,23 @@ def _unmorton(k):
                                         (32, 5, 1024), (32, 5, 1025), (32, 5, 2048)])
 def test_column_split_at_the_edges_of_its_sets(C, ks, tiles):
     """A scale of exactly `tiles` tiles, alone (one to four tiles a block, one or two rounds, the last tile count
-    that splits and the first that does not) and beside a full finer scale eight times its size (staged): the same
-    bits.  The finer scale's rows take no part in the coarser one's sums."""
-    b, b0, R = 8, 6, 10.0
+    that splits and the first that does not) and beside a full finer scale eight times its size (staged; the head's
+    waves take several tiles each): the same bits.  The finer scale's rows take no part in the coarser one's sums.
+    Odd counts run the one-stage head, even ones the two-stage head."""
+    b, b0, R, two = 8, 6, 10.0, tiles % 2 == 0
     n = 16 * tiles - 5
     cells = _unmorton(np.arange(8 * n))  # every child of the first n cells of scale b
     B = b + 2
     pts = (-R + (2 * cells + 0.5) * (2 * R / (1 << B))).astype(np.float32)
     say("column split at", tiles, "tiles, C", C, "k", ks)
-    w = gen_weights(C, 2, seed=tiles, bias_std=0.1, two_stage=True, top=True, kernel_size=ks)
-    ctx = reno.Context(len(pts), B, b0, R, C, 2, two_stage=True, top=True, kernel_size=ks,
+    w = gen_weights(C, 2, seed=tiles, bias_std=0.1, two_stage=two, top=True, kernel_size=ks)
+    ctx = reno.Context(len(pts), B, b0, R, C, 2, two_stage=two, top=True, kernel_size=ks,
                        max_model_voxels=len(pts) * 5 // 4 + 4096)
     ctx.set_weights(reno.weights_to_device(w))
     ctx.build_pyramid(to_dev(pts), B)
     assert ctx.num_voxels(b) == n
-    one = ctx.predict_probs(b, logits=True).cpu().numpy()
-    lg = ctx.predict_probs(reno.RENO_ALL_SCALES, logits=True).cpu().numpy()
+    one = ctx.predict_probs(b, logits=True)
+    lg = ctx.predict_probs(reno.RENO_ALL_SCALES, logits=True)
     first = ctx.num_voxels(b - 1)
+    assert bool(torch.isfinite(one).all()) and torch.equal(lg[first:first + n], one)
     ctx.close()
-    assert np.isfinite(one).all()
-    np.testing.assert_array_equal(lg[first:first + n], one)
