@@ -68,13 +68,22 @@ typedef enum {
 #define RENO_MAX_FRAMES 1024
 #define RENO_HEAD_ONE_STAGE 0   /* one 256-way softmax over the code (Eq. 10) */
 #define RENO_HEAD_TWO_STAGE 1   /* bitwise two-stage head (Eqs. 11-13) */
-#define RENO_PREC_FP32 0        /* results to fp32 rounding: fp32 operands carried as a
-                                   power-of-two factor and fp16 hi + lo (22 bits), on
-                                   fp16 MFMA with fp32 accumulation; fp32 MFMA for the
-                                   wide full predictor */
-#define RENO_PREC_BF16X3 1      /* at least the accuracy of operands split into bf16 hi +
-                                   lo (~2^-16 relative per product); since the fp32 mode
-                                   costs no more, it runs the same kernels */
+#define RENO_PREC_FP32 0        /* fp32 weights and features; products of the conv layers
+                                   and heads on fp16 MFMA with fp32 accumulation, from
+                                   operands carried as a power-of-two factor (a feature
+                                   row's, an output channel's or symbol's) and fp16 hi +
+                                   lo, after each input channel c is divided by b_c, the
+                                   power of two of its largest weight, and its features
+                                   multiplied by it.  A product x_c w_co is kept to
+                                   2^-21 of itself, or to about 2^-39 of the row's
+                                   largest |x_c| b_c times the output's largest
+                                   |w_co| / b_c where that is more; beside the rounding
+                                   of the sums, fp32 accuracy unless the products of a
+                                   row differ by more than 2^15.  Weights must be finite
+                                   (an infinite one gives NaN) */
+#define RENO_PREC_BF16X3 1      /* asks for no more than products of operands split into
+                                   bf16 hi + lo; runs what RENO_PREC_FP32 runs, which
+                                   costs no more */
 #define RENO_MODEL_PLAIN 0      /* 11 input bits [delta, parent code] (Eqs. 7-8), L sparse
                                    conv + ReLU layers (Eq. 9) */
 #define RENO_MODEL_TOP 1        /* full target occupancy predictor (Sec. 3.2, Eqs. 6-9):
@@ -93,7 +102,7 @@ typedef struct {
   int min_bit_depth;         /* b0, the coarsest scale, 0 <= b0 < B */
   double range_m;            /* R: the grid covers [-R, R) on each axis */
   int in_features;           /* must be RENO_IN_FEATURES */
-  int channels;              /* C: 16 or 32 */
+  int channels;              /* C: 16 or 32 (full predictor: also 64 or 128) */
   int layers;                /* L: 1 .. RENO_MAX_LAYERS sparse conv layers */
   int head_mode;             /* RENO_HEAD_ONE_STAGE (0) or RENO_HEAD_TWO_STAGE */
   int precision;             /* RENO_PREC_FP32 (0) or RENO_PREC_BF16X3 */
@@ -403,8 +412,8 @@ typedef enum {
   RENO_K_ZERO = 0,      /* per-frame clear of counters, look-back state and hash */
   RENO_K_QUANTIZE,      /* quantisation, Morton keys, digit histograms */
   RENO_K_SORT,          /* one radix-sort pass */
-  RENO_K_PYRAMID,       /* all scales, parents, first children, hash inserts */
-  RENO_K_CODES,         /* FOG codes and layer-1 input bits */
+  RENO_K_PYRAMID,       /* all scales, parents, first children */
+  RENO_K_CODES,         /* FOG codes, hash inserts */
   RENO_K_SET_BASE,      /* decoder initial state */
   RENO_K_EXPAND,        /* FCG expansion of one scale */
   RENO_K_CONV_FIRST,    /* first conv layer with the hash probes */

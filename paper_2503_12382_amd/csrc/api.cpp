@@ -54,7 +54,8 @@ void free_all(Ctx* c) {
                   c->d_lse2,    c->w_emb,   c->d_s1,     c->w_head_t, c->d_perm, c->d_next,
                   c->h_c,       c->h_d,     c->w_embo,   c->w_embd,   c->s_c,     c->s_d,
                   c->r_a,       c->r_b,     c->r_c,      c->r_d,      c->w_wfac,  c->w_hfac,
-                  c->w_part};
+                  c->w_part,    c->w_bal,   c->w_hbal,    c->w_hrat,  c->w_xrat,    c->w_embs,
+                  c->w_embr};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   for (int l = 0; l < RENO_MAX_LAYERS; ++l) {
@@ -207,7 +208,11 @@ reno_status reno_create(const reno_params* p, void* hip_stream, reno_ctx** out) 
   A(dalloc(&c->r_a, rows, &c->device_bytes));
   A(dalloc(&c->r_b, rows, &c->device_bytes));
   A(dalloc(&c->w_wfac, (size_t)RENO_MAX_LAYERS * 128, &c->device_bytes));
-  A(dalloc(&c->w_hfac, 2, &c->device_bytes));
+  A(dalloc(&c->w_bal, (size_t)RENO_MAX_LAYERS * 128, &c->device_bytes));
+  A(dalloc(&c->w_hfac, 257, &c->device_bytes));
+  A(dalloc(&c->w_hbal, 256, &c->device_bytes));
+  A(dalloc(&c->w_hrat, 128, &c->device_bytes));
+  A(dalloc(&c->w_xrat, 128, &c->device_bytes));
   A(dalloc(&c->w_part, (size_t)64 * 128, &c->device_bytes));
   if (top) {
     A(dalloc(&c->s_c, rows * C, &c->device_bytes));
@@ -219,6 +224,8 @@ reno_status reno_create(const reno_params* p, void* hip_stream, reno_ctx** out) 
     A(dalloc(&c->h_c, rows * C, &c->device_bytes));
     A(dalloc(&c->h_d, rows * C, &c->device_bytes));
     A(dalloc(&c->w_embo, (size_t)256 * C, &c->device_bytes));
+    A(dalloc(&c->w_embs, (size_t)256 * C, &c->device_bytes));
+    A(dalloc(&c->w_embr, 256, &c->device_bytes));
     A(dalloc(&c->w_embd, (size_t)8 * C, &c->device_bytes));
   }
   A(dalloc(&c->d_nbr, rows * c->nbr_stride(), &c->device_bytes));

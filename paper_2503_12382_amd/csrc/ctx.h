@@ -106,15 +106,22 @@ struct Ctx {
   float* w_conv[RENO_MAX_LAYERS] = {};  // plain model, layer 0: the cell table [8][8][256][C]
   float* w_bias[RENO_MAX_LAYERS] = {};
   float* w_wfac = nullptr;      // factors of the split conv weights [layer][128]
-  float* w_hfac = nullptr;      // factors of the split head matrices [2]
+  float* w_bal = nullptr;       // balance of their input channels [layer][128]
+  float* w_hfac = nullptr;      // factors of the head's symbols [256] (two-stage: [16 | 16]), [256]: the one they share, or 0
+  float* w_hbal = nullptr;      // balance of the features (the first head matrix's) and of stage 2's inputs [2][128]
+  float* w_hrat = nullptr;      // two-stage: what takes the features' balance to stage 2's [128]
+  float* w_xrat = nullptr;      // full predictor: and to that of the conv that reads X_B [128]
   float* w_part = nullptr;      // partial maxima of a conv layer's channels while its weights are packed [64][128]
   float* w_head = nullptr;
   float* w_hbias = nullptr;
-  float* w_head_plain = nullptr;  // [C][256] as given (two-stage: [C][H1 | H2]), for code lengths
+  // for the stored features, which carry the balance w_hbal
+  float* w_head_plain = nullptr;  // [C][256] (two-stage: [C][H1 | H2]) of the symbol tables
   float* w_emb = nullptr;         // [16][C] Emb(S1) of the two-stage head
   float* w_head_t = nullptr;      // head transposed, one row per symbol: [256][C] (two-stage: [H1^T; H2^T])
-  float* w_embo = nullptr;        // [256][C] Emb_O of the full predictor
-  float* w_embd = nullptr;        // [8][C]   Emb_D of the full predictor
+  float* w_embo = nullptr;        // [256][C] Emb_O of the full predictor, with the features' balance
+  uint32_t* w_embs = nullptr;     // [256][C] Emb_O as split rows, with the balance of the conv that reads them
+  float* w_embr = nullptr;        // [256]    their factors
+  float* w_embd = nullptr;        // [8][C]   Emb_D of the full predictor, with the features' balance
   bool have_weights = false;
 
   // frame state
@@ -173,6 +180,7 @@ struct Ctx {
   // for the full predictor, the base scale
   int64_t cap_rows() const { return cap_model + 1 + (top() ? cap_pts : 0); }
   float* wfac(int l) const { return w_wfac + 128 * l; }
+  float* wbal(int l) const { return w_bal + 128 * l; }
   // buffer that holds the last conv layer's output (h_L), per the ping-pong
   float* hlast() const { return top() ? h_a : ((p.layers & 1) ? h_a : h_b); }
 };

@@ -46,14 +46,25 @@ constexpr int CONV_WAVES = CONV_THREADS / 64;
 // that brings the row's largest entry to [2^14, 2^15), hi = fp16(x / f) and lo
 // = fp16(x / f - hi), both rounded to nearest, 22 bits of every entry within
 // 2^-17 of the row's largest (smaller ones keep an absolute 2^-40 of it).
-// Weights are split the same way, with one factor per output channel (per
-// matrix for a head).  A product is lo*hi + hi*lo + hi*hi on
-// v_mfma_f32_16x16x32_f16 with fp32 accumulation, smallest terms first (lo*lo,
-// 2^-22 of the product, is dropped except at C = 16, where it fits in), 48 cycles per 16 x 16 x 32 block against
+// Weights are split the same way, with one factor per output channel or symbol.
+// A product is lo*hi + hi*lo + hi*hi on v_mfma_f32_16x16x32_f16 with fp32
+// accumulation, smallest terms first (lo*lo, 2^-22 of the product, is dropped
+// except at C = 16, where it fits in), 48 cycles per 16 x 16 x 32 block against
 // 256 on fp32 MFMA.  An output sums one fma per offset instead of C / 4
 // chained roundings, so its error against fp64 is about half that of the fp32
 // MFMA chain (one layer of 6 neighbours, C = 32: 0.96e-7 against 1.76e-7
 // relative; a whole 3-layer model's logits: 1.6e-7 against 1.7e-7).
+// In fp32 a channel's magnitude is arbitrary: scaled by 2^k, and the weights that
+// read it by 2^-k, every product is the same.  A shared factor would lose bits to
+// that once channels lie 2^17 apart, so the matrices are balanced as they are
+// packed: input channel c is divided by b_c, the power of two at or below its
+// largest weight (0 where all are 0), and the rows split for that matrix carry
+// channel c times b_c, exactly.  Entries and weights are then small beside others
+// only where their products are.  The balance of a layer's output is part of its
+// own weights' factors and bias (of the first layer's table, of the embeddings);
+// where two matrices read a row, it carries the balance of one and is multiplied
+// by the ratio (k_feature_balance) for the other.  With every row multiplied as it
+// is split, the 14-bit scan's calls were 2 to 5 % slower.
 __device__ __forceinline__ f4 mfma_h(const uint4& a, const uint4& b, f4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, a), __builtin_bit_cast(h8, b), c, 0, 0, 0);
 }
@@ -62,18 +73,24 @@ __device__ __forceinline__ uint32_t pack_h2(float x0, float x1) {
   return __builtin_bit_cast(uint32_t, v);
 }
 
-// The factor that maps a largest magnitude m to [2^14, 2^15) and its inverse,
-// from the exponent bits (exponents below 14 share the smallest factor).
+// The larger of two magnitudes; NaN if one is (a maximum would lose it, and the
+// entry with it).
+__device__ __forceinline__ float max_nan(float a, float b) { return __builtin_elementwise_maximum(a, b); }
+
+// What maps a largest magnitude m to [2^14, 2^15), and a row's factor in units of
+// 2^-14: the weights' factors are kept in units of 2^14, so that sums stay near
+// the magnitude of their terms and overflow where those do.  From the exponent
+// bits (exponents below 14 share the smallest factor; a denormal factor is exact).
 __device__ __forceinline__ void split_scale(float m, float& mul, float& fac) {
   const uint32_t ex = max(__float_as_uint(m) >> 23, 14u);
-  mul = __uint_as_float((268u - ex) << 23);                          // 2^(14 - e)
-  fac = ex > 14u ? __uint_as_float((ex - 14u) << 23) : 0x1p-127f;    // 2^(e - 14)
+  mul = __uint_as_float((268u - ex) << 23);                                       // 2^(14 - e)
+  fac = __uint_as_float(ex > 28u ? (ex - 28u) << 23 : 1u << (ex - 6u));           // 2^(e - 28)
 }
 
 template <int N>
 __device__ __forceinline__ float abs_max(const float (&x)[N], float m = 0.0f) {
 #pragma unroll
-  for (int i = 0; i < N; ++i) m = fmaxf(m, fabsf(x[i]));
+  for (int i = 0; i < N; ++i) m = max_nan(m, fabsf(x[i]));
   return m;
 }
 
@@ -81,13 +98,13 @@ __device__ __forceinline__ float abs_max(const float (&x)[N], float m = 0.0f) {
 // the lanes STEP and 2 STEP away (16: lanes r + 16 g; 1: lanes 4 r + g).  A row
 // with an infinite entry keeps that one at 2^15 against (practically) zero others
 // and gets the factor infinity, so that what it adds to an output is infinite as
-// in fp32.
+// in fp32; a row with a NaN gets the factor NaN.
 template <int STEP = 16>
 __device__ __forceinline__ void row_scale(float m, float& mul, float& fac) {
-  m = fmaxf(m, __shfl_xor(m, STEP));
-  m = fmaxf(m, __shfl_xor(m, 2 * STEP));
+  m = max_nan(m, __shfl_xor(m, STEP));
+  m = max_nan(m, __shfl_xor(m, 2 * STEP));
   split_scale(m, mul, fac);
-  fac = m == INFINITY ? m : fac;
+  fac = m < INFINITY ? fac : m;
 }
 
 // Packed words of hi and lo of entries x0, x1 of a row.
@@ -112,47 +129,83 @@ __device__ __forceinline__ float row_split(const float (&x)[N], uint32_t (&hi)[N
 // ---------------------------------------------------------------------------
 // Weight packing.
 
-// Largest magnitude over the block's threads (NaN passes through as NaN, so
-// that a broken weight shows in the results instead of vanishing in a maximum).
-__device__ __forceinline__ float absmax(float m, float w) { return w != w || m != m ? NAN : fmaxf(m, fabsf(w)); }
-
-__device__ __forceinline__ float block_absmax(float m, float* s_m) {
-  for (int o = 32; o > 0; o >>= 1) m = absmax(m, __shfl_xor(m, o));
+// The balance b_c of C input channels (above) from their largest magnitudes over
+// W [kv][C][NS] (a head: kv = 1), one block per channel.  Infinite or NaN
+// weights leave their channel as it is.
+__global__ void __launch_bounds__(256) k_balance(const float* __restrict__ W, int kv, int C, int NS,
+                                                 float* __restrict__ bal) {
+  __shared__ float s_m[256];
+  const int c = blockIdx.x;
+  float m = 0.0f;
+  for (int i = threadIdx.x; i < kv * NS; i += 256) m = max_nan(m, fabsf(W[((size_t)(i / NS) * C + c) * NS + i % NS]));
+  s_m[threadIdx.x] = m;
   __syncthreads();
-  if ((threadIdx.x & 63) == 0) s_m[threadIdx.x >> 6] = m;
-  __syncthreads();
-  float t = 0.0f;
-  for (unsigned i = 0; i < blockDim.x / 64; ++i) t = absmax(t, s_m[i]);
-  return t;
+  if (threadIdx.x != 0) return;
+  for (int i = 1; i < 256; ++i) m = max_nan(m, s_m[i]);
+  const uint32_t ex = max(__float_as_uint(m) >> 23, 1u);
+  bal[c] = m == 0.0f ? 0.0f : m < INFINITY ? __uint_as_float(ex << 23) : 1.0f;
 }
 
-// Factors of a weight matrix or channel (split_scale); infinite or NaN weights
-// are kept as they are (factor 1), so they reach the products.
-__device__ __forceinline__ void weight_scale(float m, float& mul, float& fac) {
-  if (m < INFINITY) {
-    split_scale(m, mul, fac);
-  } else {
-    mul = fac = 1.0f;
+// 1 / b_c (b_c = 0: no weight is scaled by it)
+__device__ __forceinline__ float unbalance(float b) { return b > 0.0f ? 1.0f / b : 0.0f; }
+
+// The features' balance, which the last layer's rows carry (hbal; with the full
+// predictor also its child rows X_B): the first head matrix's, for channels that
+// this one does not read the second's (hbal + C ..., two-stage), then that of the
+// conv that reads X_B (b1; full predictor).  Those two become the features'
+// balance times a ratio (hrat, xrat), a power of two inside fp32.
+__device__ __forceinline__ float ratio(float a, float b) {
+  if (!(a > 0.0f) || !(b > 0.0f)) return 0.0f;
+  const int e = (int)(__float_as_uint(a) >> 23) - (int)(__float_as_uint(b) >> 23);
+  return __uint_as_float((uint32_t)(min(max(e, -126), 126) + 127) << 23);
+}
+__global__ void __launch_bounds__(128) k_feature_balance(int C, float* __restrict__ hbal, float* __restrict__ hbal2,
+                                                         float* __restrict__ hrat, float* __restrict__ b1,
+                                                         float* __restrict__ xrat) {
+  const int c = threadIdx.x;
+  if (c >= C) return;
+  float f = hbal[c];
+  if (hbal2 && f == 0.0f) f = hbal2[c];
+  if (b1 && f == 0.0f) f = b1[c];
+  hbal[c] = f;
+  if (hbal2) {
+    hrat[c] = ratio(hbal2[c], f);
+    hbal2[c] = f * hrat[c];
+  }
+  if (b1) {
+    xrat[c] = ratio(b1[c], f);
+    b1[c] = f * xrat[c];
   }
 }
 
-// Largest magnitude of every output channel of W [n][C] over each block's share
-// of the n rows: part [gridDim.x][C].
+// What brings an output channel's (or symbol's) balanced weights to fp16 and the
+// factor that takes it back, in units of 2^14 (split_scale); infinite or NaN
+// weights are kept as they are, so they reach the products.
+__device__ __forceinline__ void weight_scale(float m, float& mul, float& fac) {
+  const uint32_t ex = min(max(__float_as_uint(m) >> 23, 15u), 254u);
+  mul = m < INFINITY ? __uint_as_float((268u - ex) << 23) : 1.0f;   // 2^(14 - e)
+  fac = m < INFINITY ? __uint_as_float(ex << 23) : 0x1p14f;         // 2^e
+}
+
+// Largest balanced magnitude of every output channel of W [n][C] (row i of input
+// channel i % C) over each block's share of the n rows: part [gridDim.x][C].
 constexpr int WMAX_BLOCKS = 64;
-__global__ void __launch_bounds__(256) k_weight_max(const float* __restrict__ W, int n, int C, float* __restrict__ part) {
+__global__ void __launch_bounds__(256) k_weight_max(const float* __restrict__ W, int n, int C,
+                                                    const float* __restrict__ bal, float* __restrict__ part) {
   __shared__ float s_m[256];
   const int co = threadIdx.x % C, per = 256 / C;
   float m = 0.0f;
-  for (int i = blockIdx.x * per + threadIdx.x / C; i < n; i += gridDim.x * per) m = absmax(m, W[(size_t)i * C + co]);
+  for (int i = blockIdx.x * per + threadIdx.x / C; i < n; i += gridDim.x * per)
+    m = max_nan(m, fabsf(W[(size_t)i * C + co] * unbalance(bal[i % C])));
   s_m[threadIdx.x] = m;
   __syncthreads();
   if ((int)threadIdx.x >= C) return;
-  for (int j = 1; j < per; ++j) m = absmax(m, s_m[j * C + co]);
+  for (int j = 1; j < per; ++j) m = max_nan(m, s_m[j * C + co]);
   part[(size_t)blockIdx.x * C + co] = m;
 }
 
-// Conv layer W [kv][C][C]: the output channels' factors (from k_weight_max) and
-// the split A operands.  Lane l = (m, g) of column block cb carries an output
+// Conv layer W [kv][C][C]: the output channels' factors (from k_weight_max; times
+// the output's balance obal) and the split A operands.  Lane l = (m, g) of column block cb carries an output
 // channel such that the lane (r, g) that ends with rows 4g .. 4g + 3 of the
 // column blocks holds channels 32 ch + 8g .. + 7 of voxel r (C = 16: channel m).
 // K slot 8g + j: C >= 32 input channel 32 ch + 8g + j of piece ch, planes
@@ -160,15 +213,16 @@ __global__ void __launch_bounds__(256) k_weight_max(const float* __restrict__ W,
 // [W1 | W1], [W2 | W2] and [W3 | W3].  Packed [kv][C/16][ch][plane][64][8] fp16.
 template <int C>
 __global__ void __launch_bounds__(256) k_pack_conv(const float* __restrict__ W, int kv, const float* __restrict__ part,
+                                                   const float* __restrict__ bal, const float* __restrict__ obal,
                                                    uint16_t* __restrict__ out, float* __restrict__ fac_out) {
   constexpr int NCB = C / 16, NCH = C >= 32 ? C / 32 : 1, PL = weight_planes(C);
   __shared__ float s_mul[C];
   if ((int)threadIdx.x < C) {
     float m = 0.0f, mul, fac;
-    for (int i = 0; i < WMAX_BLOCKS; ++i) m = absmax(m, part[i * C + threadIdx.x]);
+    for (int i = 0; i < WMAX_BLOCKS; ++i) m = max_nan(m, part[i * C + threadIdx.x]);
     weight_scale(m, mul, fac);
     s_mul[threadIdx.x] = mul;
-    if (blockIdx.x == 0) fac_out[threadIdx.x] = fac;
+    if (blockIdx.x == 0) fac_out[threadIdx.x] = fac * obal[threadIdx.x];
   }
   __syncthreads();
   const int64_t n = (int64_t)kv * C * C;
@@ -178,7 +232,7 @@ __global__ void __launch_bounds__(256) k_pack_conv(const float* __restrict__ W, 
     const int row = C >= 32 ? 4 * ((co & 31) >> 3) + (co & 3) : co;  // m of the A operand
     uint16_t* o = out + ((size_t)(k * NCB + cb) * NCH + (C >= 32 ? ci >> 5 : 0)) * PL * 64 * 8;
     const int at = (((ci & 31) >> 3) * 16 + row) * 8 + (ci & 7);  // lane (row, group of ci), slot ci % 8
-    float rest = W[i] * s_mul[co];
+    float rest = W[i] * unbalance(bal[ci]) * s_mul[co];
 #pragma unroll
     for (int pl = 0; pl < PL; ++pl) {
       const _Float16 h = (_Float16)rest;
@@ -189,28 +243,56 @@ __global__ void __launch_bounds__(256) k_pack_conv(const float* __restrict__ W, 
   }
 }
 
+// Largest balanced magnitude of every symbol of a head H [C][NS].
+__global__ void __launch_bounds__(64) k_head_max(const float* __restrict__ H, int C, int NS, const float* __restrict__ bal,
+                                                 float* __restrict__ smax) {
+  const int sym = blockIdx.x * 64 + threadIdx.x;
+  if (sym >= NS) return;
+  float m = 0.0f;
+  for (int c = 0; c < C; ++c) m = max_nan(m, fabsf(H[(size_t)c * NS + sym] * unbalance(bal[c])));
+  smax[sym] = m;
+}
+
 // Head H [C][NS] (NS = 256, or 16 per stage of the two-stage head), one block
-// per 16-symbol block sb: the matrix's factor and the split A operands, lane
+// per 16-symbol block sb: the symbols' factors and the split A operands, lane
 // (m, g) carrying symbol 16 sb + m.  C >= 32: K slot 8g + j of chunk ch is
 // channel 32 ch + 8g + j, planes [hi][lo]; C = 16: slots 8g .. 8g + 3 and 8g +
 // 4 .. 8g + 7 both carry channels 4g .. 4g + 3 (a lane's operand is [4 hi][4
 // lo] of them), planes [H1 | H1], [H2 | H2] and [H3 | H3].  Packed
 // [NS/16][max(C/32, 1)][plane][64][8] fp16.
+// 256 symbols whose largest weights lie within 2^8 of each other share the factor
+// of the largest: a symbol's entries down to 2^-9 of its own largest keep their 22
+// bits, and a logit's smaller terms an absolute 2^-32 of the largest one.  Where
+// they do, fac_out[256] is that factor, else 0: one factor instead of a load and
+// four products per block takes the 256-way head's launch from 65 to 62 us.
 __global__ void __launch_bounds__(256) k_pack_head(const float* __restrict__ H, int C, int NS,
+                                                   const float* __restrict__ bal, const float* __restrict__ smax,
                                                    uint16_t* __restrict__ out, float* __restrict__ fac_out) {
-  __shared__ float s_m[4];
-  float m = 0.0f;
-  for (int i = threadIdx.x; i < C * NS; i += 256) m = absmax(m, H[i]);
-  float mul, fac;
-  weight_scale(block_absmax(m, s_m), mul, fac);
-  if (blockIdx.x == 0 && threadIdx.x == 0) *fac_out = fac;
+  __shared__ float s_mul[16];
   const int nch = C >= 32 ? C / 32 : 1, sb = blockIdx.x, planes = weight_planes(C);
+  if (threadIdx.x < 16) {
+    float m = smax[sb * 16 + threadIdx.x], mul, fac;
+    bool shared = NS == 256;
+    if (shared) {
+      float hi = 0.0f, lo = INFINITY;
+      for (int i = 0; i < NS; ++i) {
+        hi = max_nan(hi, smax[i]);
+        lo = fminf(lo, smax[i]);
+      }
+      shared = hi < INFINITY && lo >= hi * 0x1p-8f;
+      if (shared) m = hi;
+    }
+    weight_scale(m, mul, fac);
+    s_mul[threadIdx.x] = mul;
+    fac_out[sb * 16 + threadIdx.x] = fac;
+    if (NS == 256 && sb == 0 && threadIdx.x == 0) fac_out[256] = shared ? fac : 0.0f;
+  }
+  __syncthreads();
   for (int i = threadIdx.x; i < nch * 64 * 8; i += 256) {
     const int j = i & 7, lane = (i >> 3) & 63, ch = i >> 9, g = lane >> 4;
     const int c = C >= 32 ? 32 * ch + 8 * g + j : 4 * g + (j & 3);
-    const float v = H[(size_t)c * NS + sb * 16 + (lane & 15)] * mul;
     uint16_t* o = out + (size_t)((sb * nch + ch) * planes) * 64 * 8 + (i & 511);
-    float rest = v;
+    float rest = H[(size_t)c * NS + sb * 16 + (lane & 15)] * unbalance(bal[c]) * s_mul[lane & 15];
     for (int pl = 0; pl < planes; ++pl) {
       const _Float16 h = (_Float16)rest;
       rest -= (float)h;
@@ -220,17 +302,27 @@ __global__ void __launch_bounds__(256) k_pack_head(const float* __restrict__ H, 
 }
 
 // Transposes H [C][NS] into rows row0 .. row0+NS-1 of a [*][C] table.
-__global__ void k_transpose_head(const float* __restrict__ H, int C, int NS, int row0, float* __restrict__ out) {
+// divided by the balance of the features.
+__global__ void k_transpose_head(const float* __restrict__ H, const float* __restrict__ bal, int C, int NS, int row0,
+                                 float* __restrict__ out) {
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < C * NS; i += gridDim.x * blockDim.x) {
     const int c = i / NS, s = i % NS;
-    out[(size_t)(row0 + s) * C + c] = H[i];
+    out[(size_t)(row0 + s) * C + c] = H[i] * unbalance(bal[c]);
   }
 }
 
-// Copies H [C][16] into columns col0 .. col0+15 of a [C][32] table.
-__global__ void k_put_cols16(const float* __restrict__ H, int C, int col0, float* __restrict__ out) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < C * 16; i += gridDim.x * blockDim.x)
-    out[(i / 16) * 32 + col0 + (i % 16)] = H[i];
+// A head [C][NS] divided by the balance of the features, into columns col0 .. of
+// a [C][stride] table.
+__global__ void k_unbalance_head(const float* __restrict__ H, const float* __restrict__ bal, int C, int NS, int stride,
+                                 int col0, float* __restrict__ out) {
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < C * NS; i += gridDim.x * blockDim.x)
+    out[(i / NS) * stride + col0 + i % NS] = H[i] * unbalance(bal[i / NS]);
+}
+
+// Rows [n][C] (a bias, an embedding) times a balance.
+__global__ void k_balance_rows(const float* __restrict__ src, const float* __restrict__ bal, int n, int C,
+                               float* __restrict__ dst) {
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n * C; i += gridDim.x * blockDim.x) dst[i] = src[i] * bal[i % C];
 }
 
 // ---------------------------------------------------------------------------
@@ -238,73 +330,6 @@ __global__ void k_put_cols16(const float* __restrict__ H, int C, int col0, float
 // the decoder's stage-2 kernel, so that all produce identical bits.  A lane
 // (r, g) holds C / 4 features of voxel r: x[8 ch + j] = channel 32 ch + 8g + j
 // (C = 16: x[j] = channel 4g + j).
-
-// B operand of the head from a lane's features.
-template <int C>
-struct HeadOp {
-  static constexpr int NCH = C >= 32 ? C / 32 : 1;
-  static constexpr int BLOCK = NCH * weight_planes(C) * 64;  // 16-byte words of one packed 16-symbol block
-  uint4 hi[NCH], lo[C >= 32 ? NCH : 1];
-  float fac;
-  __device__ __forceinline__ void set(const float (&x)[C / 4]) {
-    uint32_t h[C / 8], l[C / 8];
-    fac = row_split<C / 4>(x, h, l);
-    if constexpr (C >= 32) {
-#pragma unroll
-      for (int ch = 0; ch < NCH; ++ch) {
-        hi[ch] = make_uint4(h[4 * ch], h[4 * ch + 1], h[4 * ch + 2], h[4 * ch + 3]);
-        lo[ch] = make_uint4(l[4 * ch], l[4 * ch + 1], l[4 * ch + 2], l[4 * ch + 3]);
-      }
-    } else {
-      hi[0] = make_uint4(h[0], h[1], l[0], l[1]);
-    }
-  }
-};
-
-// H^T x of one 16-symbol block in units of the two factors: lane (r, g) ends
-// with symbols 4g .. 4g + 3 of voxel r.  hp: the block's packed operands.
-template <int C>
-__device__ __forceinline__ f4 head_block(const uint4* hp, int lane, const HeadOp<C>& b) {
-  constexpr int NCH = HeadOp<C>::NCH;
-  f4 p = f4{0.0f, 0.0f, 0.0f, 0.0f};
-  if constexpr (C >= 32) {
-#pragma unroll
-    for (int ch = 0; ch < NCH; ++ch) p = mfma_h(hp[(2 * ch + 1) * 64 + lane], b.hi[ch], p);
-#pragma unroll
-    for (int ch = 0; ch < NCH; ++ch) p = mfma_h(hp[2 * ch * 64 + lane], b.lo[ch], p);
-#pragma unroll
-    for (int ch = 0; ch < NCH; ++ch) p = mfma_h(hp[2 * ch * 64 + lane], b.hi[ch], p);
-  } else {
-#pragma unroll
-    for (int pl = weight_planes(C) - 1; pl >= 0; --pl) p = mfma_h(hp[pl * 64 + lane], b.hi[0], p);
-  }
-  return p;
-}
-
-// 16 logits of one stage of the two-stage head.
-template <int C>
-__device__ __forceinline__ f4 head16(const uint4* hp, float hfac, const float* __restrict__ hb,
-                                     const float (&x)[C / 4], int lane, int g) {
-  HeadOp<C> b;
-  b.set(x);
-  const f4 p = head_block<C>(hp, lane, b);
-  const float f = b.fac * hfac;
-  f4 z = *reinterpret_cast<const f4*>(hb + 4 * g);
-#pragma unroll
-  for (int e = 0; e < 4; ++e) z[e] = fmaf(p[e], f, z[e]);
-  return z;
-}
-
-// Natural-log normaliser of the 16 logits spread over lanes r, r+16, r+32, r+48.
-__device__ __forceinline__ float lse16(const f4& z) {
-  float m = fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3]));
-  m = fmaxf(m, __shfl_xor(m, 16));
-  m = fmaxf(m, __shfl_xor(m, 32));
-  float s = (__expf(z[0] - m) + __expf(z[1] - m)) + (__expf(z[2] - m) + __expf(z[3] - m));
-  s += __shfl_xor(s, 16);
-  s += __shfl_xor(s, 32);
-  return m + __logf(s);
-}
 
 // The lane's C / 4 entries of a row of C floats, in the order above.
 template <int C>
@@ -342,6 +367,83 @@ __device__ __forceinline__ void add_row(const float (&x)[C / 4], const float* __
   for (int i = 0; i < C / 4; ++i) out[i] = x[i] + out[i];
 }
 
+// x times the same entries of a row (a balance); out may be x.
+template <int C>
+__device__ __forceinline__ void mul_row(const float (&x)[C / 4], const float* __restrict__ row, int g,
+                                        float (&out)[C / 4]) {
+  float b[C / 4];
+  load_row<C>(row, g, b);
+#pragma unroll
+  for (int i = 0; i < C / 4; ++i) out[i] = x[i] * b[i];
+}
+
+// B operand of a head from a lane's (balanced) features.
+template <int C>
+struct HeadOp {
+  static constexpr int NCH = C >= 32 ? C / 32 : 1;
+  static constexpr int BLOCK = NCH * weight_planes(C) * 64;  // 16-byte words of one packed 16-symbol block
+  uint4 hi[NCH], lo[C >= 32 ? NCH : 1];
+  float fac;
+  __device__ __forceinline__ void set(const float (&x)[C / 4]) {
+    uint32_t h[C / 8], l[C / 8];
+    fac = row_split<C / 4>(x, h, l);
+    if constexpr (C >= 32) {
+#pragma unroll
+      for (int ch = 0; ch < NCH; ++ch) {
+        hi[ch] = make_uint4(h[4 * ch], h[4 * ch + 1], h[4 * ch + 2], h[4 * ch + 3]);
+        lo[ch] = make_uint4(l[4 * ch], l[4 * ch + 1], l[4 * ch + 2], l[4 * ch + 3]);
+      }
+    } else {
+      hi[0] = make_uint4(h[0], h[1], l[0], l[1]);
+    }
+  }
+};
+
+// H^T x of one 16-symbol block in units of the row's and the symbols' factors: lane (r, g) ends
+// with symbols 4g .. 4g + 3 of voxel r.  hp: the block's packed operands.
+template <int C>
+__device__ __forceinline__ f4 head_block(const uint4* hp, int lane, const HeadOp<C>& b) {
+  constexpr int NCH = HeadOp<C>::NCH;
+  f4 p = f4{0.0f, 0.0f, 0.0f, 0.0f};
+  if constexpr (C >= 32) {
+#pragma unroll
+    for (int ch = 0; ch < NCH; ++ch) p = mfma_h(hp[(2 * ch + 1) * 64 + lane], b.hi[ch], p);
+#pragma unroll
+    for (int ch = 0; ch < NCH; ++ch) p = mfma_h(hp[2 * ch * 64 + lane], b.lo[ch], p);
+#pragma unroll
+    for (int ch = 0; ch < NCH; ++ch) p = mfma_h(hp[2 * ch * 64 + lane], b.hi[ch], p);
+  } else {
+#pragma unroll
+    for (int pl = weight_planes(C) - 1; pl >= 0; --pl) p = mfma_h(hp[pl * 64 + lane], b.hi[0], p);
+  }
+  return p;
+}
+
+// 16 logits of one stage of the two-stage head.
+template <int C>
+__device__ __forceinline__ f4 head16(const uint4* hp, const float* __restrict__ hfac,
+                                     const float* __restrict__ hb, const float (&x)[C / 4], int lane, int g) {
+  HeadOp<C> b;
+  b.set(x);
+  const f4 p = head_block<C>(hp, lane, b);
+  const f4 f = *reinterpret_cast<const f4*>(hfac + 4 * g);
+  f4 z = *reinterpret_cast<const f4*>(hb + 4 * g);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) z[e] = fmaf(p[e] * b.fac, f[e], z[e]);
+  return z;
+}
+
+// Natural-log normaliser of the 16 logits spread over lanes r, r+16, r+32, r+48.
+__device__ __forceinline__ float lse16(const f4& z) {
+  float m = fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3]));
+  m = fmaxf(m, __shfl_xor(m, 16));
+  m = fmaxf(m, __shfl_xor(m, 32));
+  float s = (__expf(z[0] - m) + __expf(z[1] - m)) + (__expf(z[2] - m) + __expf(z[3] - m));
+  s += __shfl_xor(s, 16);
+  s += __shfl_xor(s, 32);
+  return m + __logf(s);
+}
+
 __global__ void k_copy_f32(const float* __restrict__ src, float* __restrict__ dst, int n) {
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
     dst[i] = src[i];
@@ -364,7 +466,8 @@ struct ConvArgs {
   const float* wfac;      // their factors [C]
   const float* bias;      // [C]
   const uint4* hw;        // packed head weights (last layer)
-  const float* hfac;      // their factors: one per head matrix
+  const float* hfac;      // the symbols' factors, as hb; [256]: the one they share, or 0 (one-stage)
+  const float* hrat;      // two-stage head: what takes the features to stage 2's balance [C]
   const float* hb;        // [256]
   float* lse;             // [cap_model]
   float* logits;          // optional [rows][256] (two-stage: [rows][32]), row = packed row - moff[b_lo]
@@ -385,6 +488,7 @@ struct ConvArgs {
   float* xb;              // child rows' input X_B (rows of scale b + 1), or NULL
   uint32_t* xb_s;         // X_B as split rows
   float* xb_r;            // their factors
+  const float* xrat;      // what takes X_B to the balance of the conv that reads them [C]
   const float* emb_d;     // [8][C]
   const uint8_t* code;    // per-scale regions: O_b
   const int32_t* fc;      // per-scale regions: first child row in V_{b+1}
@@ -601,10 +705,11 @@ constexpr float LOG2E_F = 1.4426950408889634f;
 // requested (lo[t], or NULL), and the group's normaliser terms per lane: gm =
 // the max of the lane's 16 logits, part = the sum of exp(z - gm).
 template <int C, int NT>
-__device__ __forceinline__ void head_group(const uint4* s_h, const float* __restrict__ hb, float hfac,
+__device__ __forceinline__ void head_group(const uint4* s_h, const float* __restrict__ hb, const float* __restrict__ hfac,
                                            const HeadOp<C> (&op)[NT], float* const (&lo)[NT], int lane, int g,
                                            int grp, float (&gm)[NT], float (&part)[NT]) {
   f4 zz[NT][4];
+  const float shared = hfac[256];
 #pragma unroll
   for (int q4 = 0; q4 < 4; ++q4) {
     const int sb = grp * 4 + q4;
@@ -613,9 +718,11 @@ __device__ __forceinline__ void head_group(const uint4* s_h, const float* __rest
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       const f4 p = head_block<C>(hp, lane, op[t]);
-      const float f = op[t].fac * hfac;
+      const float f1 = op[t].fac * shared;
+      f4 f = f4{f1, f1, f1, f1};
+      if (shared == 0.0f) f = *reinterpret_cast<const f4*>(hfac + 16 * sb + 4 * g) * op[t].fac;  // uniform
 #pragma unroll
-      for (int e = 0; e < 4; ++e) zz[t][q4][e] = fmaf(p[e], f, bias[e]);
+      for (int e = 0; e < 4; ++e) zz[t][q4][e] = fmaf(p[e], f[e], bias[e]);
     }
   }
 #pragma unroll
@@ -676,7 +783,9 @@ template <int C>
 __device__ __forceinline__ void head_two(const ConvArgs& a, const float (&x)[C / 4], const uint4* s_h, int lane, int g,
                                          const TileRef& tr, int64_t mo_first) {
   constexpr int BLK = HeadOp<C>::BLOCK;
-  const f4 z1 = head16<C>(s_h, a.hfac[0], a.hb, x, lane, g);
+  float rt[C / 4];
+  load_row<C>(a.hrat, g, rt);  // before the stores of stage 1, which it would wait behind
+  const f4 z1 = head16<C>(s_h, a.hfac, a.hb, x, lane, g);
   const float l1 = lse16(z1);
   if (tr.valid && g == 0) a.lse[tr.prow] = l1;
   float* lo = (a.logits && tr.valid) ? a.logits + (tr.prow - mo_first) * 32 + 4 * g : nullptr;
@@ -685,7 +794,9 @@ __device__ __forceinline__ void head_two(const ConvArgs& a, const float (&x)[C /
   const int s1 = a.s1_code[tr.lvb + (tr.prow - tr.mo)] & 15;
   float x2[C / 4];
   add_row<C>(x, a.emb + s1 * C, g, x2);
-  const f4 z2 = head16<C>(s_h + BLK, a.hfac[1], a.hb + 16, x2, lane, g);
+#pragma unroll
+  for (int i = 0; i < C / 4; ++i) x2[i] *= rt[i];
+  const f4 z2 = head16<C>(s_h + BLK, a.hfac + 16, a.hb + 16, x2, lane, g);
   const float l2 = lse16(z2);
   if (tr.valid && g == 0) {
     a.lse2[tr.prow] = l2;
@@ -708,7 +819,6 @@ __device__ __forceinline__ void head_epilogue(const ConvArgs& a, const float (&x
     HeadOp<C> op[NT];
     float* lo[NT];
     float m[NT], ssum[NT];
-    const float hfac = a.hfac[0];
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       op[t].set(x[t]);
@@ -719,7 +829,7 @@ __device__ __forceinline__ void head_epilogue(const ConvArgs& a, const float (&x
 #pragma unroll 1
     for (int grp = 0; grp < 4; ++grp) {
       float gm[NT], part[NT];
-      head_group<C, NT>(s_h, a.hb, hfac, op, lo, lane, g, grp, gm, part);
+      head_group<C, NT>(s_h, a.hb, a.hfac, op, lo, lane, g, grp, gm, part);
 #pragma unroll
       for (int t = 0; t < NT; ++t) lse_merge(m[t], ssum[t], gm[t], part[t]);
     }
@@ -775,20 +885,33 @@ __device__ __forceinline__ void store_split_piece(const float* x, float mul, int
   }
 }
 
-// A piece's work ends here where the registers do not hold that of all pieces.
+// Entries of a row that a lane works on at once: all of its C / 4, at C = 128 a
+// piece, whose work ends at piece_end: the registers do not hold that of all four.
+constexpr int at_once(int C) { return C > 64 ? 8 : C / 4; }
 template <int C>
 __device__ __forceinline__ void piece_end() {
-  if constexpr (C > 32) __builtin_amdgcn_sched_barrier(0);
+  if constexpr (C > 64) __builtin_amdgcn_sched_barrier(0);
 }
 
-// Stores a lane's entries of a split row and, from lane group 0, its factor.
-template <int C, int STEP = 16>
-__device__ __forceinline__ void store_split(const float (&x)[C / 4], int g, uint32_t* row, float* fac) {
-  float mul, f;
-  row_scale<STEP>(abs_max(x), mul, f);
+// Stores a lane's entries of a row as a split row and, from lane group 0, its
+// factor.  part(c0, y) gives entries c0 .. of the row (twice for each piece at C =
+// 128).
+template <int C, int STEP = 16, typename Part>
+__device__ __forceinline__ void store_split(Part part, int g, uint32_t* row, float* fac) {
+  constexpr int N = C / 4, NC = at_once(C);
+  float m = 0.0f, mul, f, y[NC];
 #pragma unroll
-  for (int ch = 0; ch < (C >= 32 ? C / 32 : 1); ++ch) {
-    store_split_piece<C>(x + 8 * ch, mul, ch, g, row);
+  for (int c0 = 0; c0 < N; c0 += NC) {
+    part(c0, y);
+    m = abs_max(y, m);
+    piece_end<C>();
+  }
+  row_scale<STEP>(m, mul, f);
+#pragma unroll
+  for (int c0 = 0; c0 < N; c0 += NC) {
+    if constexpr (N > NC) part(c0, y);
+#pragma unroll
+    for (int q = 0; q < NC; q += 8) store_split_piece<C>(y + q, mul, (c0 + q) / 8, g, row);
     piece_end<C>();
   }
   if (g == 0) *fac = f;
@@ -971,9 +1094,9 @@ __device__ __forceinline__ void conv_sum(const ConvArgs& a, const uint4* s_w, ui
 template <int C, bool XB>
 __device__ __forceinline__ void conv_epilogue(const ConvArgs& a, const f4 (&sum)[C / 16], int g, const TileRef& tr,
                                               float (&x)[C / 4]) {
-  constexpr int N = C / 4, NC = N < 8 ? N : 8;
+  constexpr int N = C / 4, NC = at_once(C);
 #pragma unroll
-  for (int c0 = 0; c0 < N; c0 += NC) {  // one 32-channel piece at a time
+  for (int c0 = 0; c0 < N; c0 += NC) {
     float wf[NC], bs[NC];
     load_row<4 * NC>(a.wfac + 4 * c0, g, wf);
     load_row<4 * NC>(a.bias + 4 * c0, g, bs);
@@ -996,36 +1119,45 @@ __device__ __forceinline__ void conv_epilogue(const ConvArgs& a, const f4 (&sum)
     const uint32_t code = a.code[tr.lvb + (tr.prow - tr.mo)];
     const int64_t first = a.fc[tr.lvb + (tr.prow - tr.mo)];
     if (cmo + cn > a.cap_model) cmo = -1;  // overflow (latched where the size was made): no writes
-    auto child = [&](int c0, int d, float (&y)[NC]) {
-      load_row<4 * NC>(a.emb_d + d * C + 4 * c0, g, y);
-#pragma unroll
-      for (int i = 0; i < NC; ++i) y[i] = x[c0 + i] + y[i];
-    };
+    float rt[NC];
+    if constexpr (N == NC) load_row<4 * NC>(a.xrat, g, rt);
     int rank = 0;
     for (int d = 0; d < 8; ++d) {
       if (cmo >= 0 && ((code >> d) & 1u)) {
         const int64_t row = cmo + first + rank;
-        float m = 0.0f, mul, f, y[NC];
+        auto child = [&](int c0, float (&y)[NC]) {
+          load_row<4 * NC>(a.emb_d + d * C + 4 * c0, g, y);
+#pragma unroll
+          for (int i = 0; i < NC; ++i) y[i] = x[c0 + i] + y[i];
+        };
+        float y[NC];
 #pragma unroll
         for (int c0 = 0; c0 < N; c0 += NC) {
-          child(c0, d, y);
+          child(c0, y);
           store_row<4 * NC>(y, g, a.xb + row * C + 4 * c0);
-          m = abs_max(y, m);
           piece_end<C>();
         }
-        row_scale(m, mul, f);
+        auto split = [&](int c0, float (&z)[NC]) {
+          if constexpr (N > NC) {
+            child(c0, z);
+            mul_row<4 * NC>(z, a.xrat + 4 * c0, g, z);
+          } else {
 #pragma unroll
-        for (int c0 = 0; c0 < N; c0 += NC) {
-          if constexpr (N > NC) child(c0, d, y);  // formed again: all pieces would not fit the registers
-          store_split_piece<C>(y, mul, c0 / NC, g, a.xb_s + row * C);
-          piece_end<C>();
-        }
-        if (g == 0) a.xb_r[row] = f;
+            for (int i = 0; i < NC; ++i) z[i] = y[i] * rt[i];
+          }
+        };
+        store_split<C>(split, g, a.xb_s + row * C, a.xb_r + row);
         ++rank;
       }
     }
   }
-  if (a.s_out) store_split<C>(x, g, a.s_out + tr.prow * C, a.r_out + tr.prow);
+  if (a.s_out) {
+    auto own = [&](int c0, float (&y)[NC]) {
+#pragma unroll
+      for (int i = 0; i < NC; ++i) y[i] = x[c0 + i];
+    };
+    store_split<C>(own, g, a.s_out + tr.prow * C, a.r_out + tr.prow);
+  }
   if (a.h_out) store_row<C>(x, g, a.h_out + tr.prow * C);
 }
 
@@ -1186,7 +1318,7 @@ __global__ void __launch_bounds__(CONV_THREADS) k_conv(ConvArgs a) {
         op[0].set(x);
         float* lo[1] = {(a.logits && tr[0].valid) ? a.logits + (tr[0].prow - mo_first) * 256 + 4 * g : nullptr};
         float gm[1], part[1];
-        head_group<C, 1>(s_h, a.hb, a.hfac[0], op, lo, lane, g, gi, gm, part);
+        head_group<C, 1>(s_h, a.hb, a.hfac, op, lo, lane, g, gi, gm, part);
         s_x2[(q * 4 + gi) * 64 + lane] = make_float2(gm[0], part[0]);
       }
       __syncthreads();
@@ -1359,15 +1491,41 @@ __device__ __forceinline__ void base_cell_rows(uint64_t kf, int b, int g, const 
   for (int j = 0; j < 8; ++j) nb[j] = (ok[j] && keys[at[j]] == want[j]) ? (int32_t)at[j] : -1;
 }
 
-// X_A = Emb_O[code] at a row, in fp32 (the residual) and split (the conv's
-// input); lanes 4r + g.
+// Emb_O [256][C] as split rows with the balance of the conv that reads X_A (emb as
+// given); 64
+// lanes 4r + g per 16 rows.
 template <int C>
-__device__ __forceinline__ void embed_row(const float* __restrict__ emb, int g, int64_t row, float* __restrict__ X,
+__global__ void __launch_bounds__(64) k_split_embed(const float* __restrict__ emb, const float* __restrict__ bal,
+                                                    uint32_t* __restrict__ rows, float* __restrict__ facs) {
+  const int row = blockIdx.x * 16 + (threadIdx.x >> 2), g = threadIdx.x & 3;
+  float x[C / 4], y[C / 4];
+  load_row<C>(emb + row * C, g, x);
+  mul_row<C>(x, bal, g, y);
+  auto own = [&](int c0, auto& p) {
+#pragma unroll
+    for (int i = 0; i < at_once(C); ++i) p[i] = y[c0 + i];
+  };
+  store_split<C, 1>(own, g, rows + row * C, facs + row);
+}
+
+// X_A = Emb_O[code] at a row, in fp32 (the residual) and split (the conv's
+// input, a row of k_split_embed); lanes 4r + g.
+struct EmbedTab {
+  const float* emb;      // [256][C], with the features' balance
+  const uint32_t* rows;  // [256][C]
+  const float* facs;     // [256]
+};
+template <int C>
+__device__ __forceinline__ void embed_row(const EmbedTab& t, int code, int g, int64_t row, float* __restrict__ X,
                                           uint32_t* __restrict__ XS, float* __restrict__ XR) {
   float x[C / 4];
-  load_row<C>(emb, g, x);
+  load_row<C>(t.emb + code * C, g, x);
   store_row<C>(x, g, X + row * C);
-  store_split<C, 1>(x, g, XS + row * C, XR + row);
+  const uint4* src = reinterpret_cast<const uint4*>(t.rows + code * C);
+  uint4* dst = reinterpret_cast<uint4*>(XS + row * C);
+#pragma unroll
+  for (int i = g; i < C / 4; i += 4) dst[i] = src[i];
+  if (g == 0) XR[row] = t.facs[code];
 }
 
 // WIDE: plain map rows, as k_convw reads them; else those of store_map (k_conv).
@@ -1375,7 +1533,7 @@ template <int C, bool WIDE>
 __global__ void __launch_bounds__(256) k_top_prep(int lo, int nsc, int n_embed, int b0, RowMap rm,
                                                   const uint64_t* __restrict__ lv_key,
                                                   const uint8_t* __restrict__ lv_code, int64_t cap_pts,
-                                                  CellArgs cells, const float* __restrict__ emb_o, int32_t* __restrict__ nbr,
+                                                  CellArgs cells, EmbedTab emb_o, int32_t* __restrict__ nbr,
                                                   float* __restrict__ X, uint32_t* __restrict__ XS,
                                                   float* __restrict__ XR) {
   __shared__ uint64_t s_par[4][16][9];  // rows padded: the 16 voxels' cells in different banks
@@ -1421,7 +1579,7 @@ __global__ void __launch_bounds__(256) k_top_prep(int lo, int nsc, int n_embed, 
     } else {
       store_map(nbr, mo + vr, valid, g, nb);
     }
-    if (valid && si < n_embed) embed_row<C>(emb_o + (int)lv_code[lvb + vr] * C, g, mo + vr, X, XS, XR);
+    if (valid && si < n_embed) embed_row<C>(emb_o, lv_code[lvb + vr], g, mo + vr, X, XS, XR);
   }
 }
 
@@ -1510,7 +1668,7 @@ template <int C>
 __global__ void __launch_bounds__(256) k_top_prep5(int lo, int nsc, int n_embed, int b0, RowMap rm,
                                                    const uint64_t* __restrict__ lv_key,
                                                    const uint8_t* __restrict__ lv_code, int64_t cap_pts,
-                                                   CellArgs cells, const float* __restrict__ emb_o, int32_t* __restrict__ nbr,
+                                                   CellArgs cells, EmbedTab emb_o, int32_t* __restrict__ nbr,
                                                    float* __restrict__ X, uint32_t* __restrict__ XS,
                                                    float* __restrict__ XR) {
   __shared__ uint64_t s_par[4][16][27];
@@ -1550,7 +1708,7 @@ __global__ void __launch_bounds__(256) k_top_prep5(int lo, int nsc, int n_embed,
       int4* dst = reinterpret_cast<int4*>(nbr + (mo + vr) * 128 + 32 * g);
 #pragma unroll
       for (int q = 0; q < 8; ++q) dst[q] = make_int4(nb[4 * q], nb[4 * q + 1], nb[4 * q + 2], nb[4 * q + 3]);
-      if (si < n_embed) embed_row<C>(emb_o + (int)lv_code[lvb + vr] * C, g, mo + vr, X, XS, XR);
+      if (si < n_embed) embed_row<C>(emb_o, lv_code[lvb + vr], g, mo + vr, X, XS, XR);
     }
   }
 }
@@ -2144,7 +2302,8 @@ hipError_t run_headw(Ctx& c, bool two, const ConvArgs& a) {
 // voxel's octant (8), which of the 8 cells around it the cell is (8) and the
 // cell's code (256): F[oct][e][code] [C] = the sum over the cell's occupied
 // children that touch the voxel of W[k]^T [delta, code].  The table is formed
-// once per weight set, in double, and the layer is the bias plus 8 rows of it,
+// once per weight set, in double (times the balance obal of the layer's output),
+// and the layer is the bias plus 8 rows of it,
 // in cell order (code 0, an absent cell, has a zero row).
 //
 // Bound by the probe -> row latency chain and L2 reads (8 C-float rows per
@@ -2158,7 +2317,8 @@ hipError_t run_headw(Ctx& c, bool two, const ConvArgs& a) {
 // 128-beam scan 159 -> 127 us.  8 unconditional rows per voxel instead of the
 // occupied cells' only took 42 us at 14 bits.
 template <int C>
-__global__ void __launch_bounds__(256) k_first_table(const float* __restrict__ W, float* __restrict__ F) {
+__global__ void __launch_bounds__(256) k_first_table(const float* __restrict__ W, const float* __restrict__ obal,
+                                                     float* __restrict__ F) {
   const int co = threadIdx.x % C;
   const int row = blockIdx.x * (256 / C) + threadIdx.x / C;  // (oct * 8 + e) * 256 + code
   const uint32_t code = row & 255u, e = (row >> 8) & 7u, oct = (uint32_t)row >> 11;
@@ -2182,7 +2342,7 @@ __global__ void __launch_bounds__(256) k_first_table(const float* __restrict__ W
     for (int i = 0; i < 8; ++i)
       if ((code >> i) & 1u) acc += (double)w[(3 + i) * C];
   }
-  F[(size_t)row * C + co] = (float)acc;
+  F[(size_t)row * C + co] = (float)acc * obal[co];
 }
 
 struct FirstArgs {
@@ -2291,6 +2451,8 @@ CellArgs cell_args(const Ctx& c) {
   return CellArgs{c.d_hash, c.hash_lg, c.hreg(), c.fbits, c.b0(), c.cap_pts, c.lv_code, c.lv_fc};
 }
 
+EmbedTab embed_tab(const Ctx& c) { return EmbedTab{c.w_embo, c.w_embs, c.w_embr}; }
+
 template <int C>
 hipError_t run_first(Ctx& c, const FirstArgs& a) {
   // 8 blocks per CU at most; fewer when the capacity cannot fill them
@@ -2335,7 +2497,8 @@ __global__ void __launch_bounds__(256) k_head2(int b, const int32_t* __restrict_
                                                const int32_t* __restrict__ moff, int64_t cap_model,
                                                const float* __restrict__ hL, const uint8_t* __restrict__ s1,
                                                const uint8_t* __restrict__ code, const uint4* __restrict__ hw2,
-                                               const float* __restrict__ hfac2, const float* __restrict__ hb2,
+                                               const float* __restrict__ hfac2, const float* __restrict__ hrat,
+                                               const float* __restrict__ hb2,
                                                const float* __restrict__ emb, float* __restrict__ lse2,
                                                float* __restrict__ logits2, uint8_t* __restrict__ s1_out,
                                                uint32_t* err) {
@@ -2345,7 +2508,6 @@ __global__ void __launch_bounds__(256) k_head2(int b, const int32_t* __restrict_
   if (mo + n > cap_model) n = 0;  // overflow was latched where the size was made
   const int64_t ntiles = (n + 15) / 16;
   const int wpb = blockDim.x / 64;
-  const float hfac = *hfac2;
   for (int64_t tile = (int64_t)blockIdx.x * wpb + (threadIdx.x >> 6); tile < ntiles;
        tile += (int64_t)gridDim.x * wpb) {
     const int64_t row = tile * 16 + r;
@@ -2360,7 +2522,8 @@ __global__ void __launch_bounds__(256) k_head2(int b, const int32_t* __restrict_
       a1 = 0;
     }
     add_row<C>(x, emb + a1 * C, g, x2);
-    const f4 z2 = head16<C>(hw2, hfac, hb2, x2, lane, g);
+    mul_row<C>(x2, hrat, g, x2);
+    const f4 z2 = head16<C>(hw2, hfac2, hb2, x2, lane, g);
     const float l2 = lse16(z2);
     if (valid && g == 0) {
       lse2[prow] = l2;
@@ -2378,55 +2541,81 @@ static int head_block_words(int C) { return (C >= 32 ? C / 32 : 1) * weight_plan
 hipError_t launch_pack_weights(Ctx& c, const reno_weights& w) {
   ProfScope ps_(c, RENO_K_OTHER);
   const int C = c.p.channels;
-  auto pack_conv = [&](const float* src, int kv, int l) {
-    uint16_t* out = reinterpret_cast<uint16_t*>(c.w_conv[l]);
-    hipLaunchKernelGGL(k_weight_max, dim3(WMAX_BLOCKS), dim3(256), 0, c.stream, src, kv * C, C, c.w_part);
-    const dim3 grid((unsigned)std::min<int64_t>(1024, ((int64_t)kv * C * C + 255) / 256));
-    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(256), 0, c.stream, src, kv, c.w_part, out, c.wfac(l)); };
-    switch (C) {
-      case 128: go(k_pack_conv<128>); break;
-      case 64: go(k_pack_conv<64>); break;
-      case 32: go(k_pack_conv<32>); break;
-      default: go(k_pack_conv<16>);
-    }
-  };
-  if (c.p.model_mode == RENO_MODEL_TOP) {  // four C -> C convs and the two embeddings
-    for (int l = 0; l < 4; ++l) {
-      pack_conv(w.top_w[l], c.kvol(), l);
-      hipLaunchKernelGGL(k_copy_f32, dim3(1), dim3(256), 0, c.stream, w.top_b[l], c.w_bias[l], C);
-    }
-    hipLaunchKernelGGL(k_copy_f32, dim3(32), dim3(256), 0, c.stream, w.emb_o, c.w_embo, 256 * C);
-    hipLaunchKernelGGL(k_copy_f32, dim3(1), dim3(256), 0, c.stream, w.emb_d, c.w_embd, 8 * C);
+  const bool top = c.top(), two = c.p.head_mode == RENO_HEAD_TWO_STAGE;
+  const int L = top ? 4 : c.p.layers, kv = top ? c.kvol() : 27;
+  auto conv_w = [&](int l) { return top ? w.top_w[l] : w.conv_w[l]; };
+  // balance of every matrix's inputs
+  for (int l = top ? 0 : 1; l < L; ++l)
+    hipLaunchKernelGGL(k_balance, dim3(C), dim3(256), 0, c.stream, conv_w(l), kv, C, C, c.wbal(l));
+  if (two) {
+    hipLaunchKernelGGL(k_balance, dim3(C), dim3(256), 0, c.stream, w.head1_w, 1, C, 16, c.w_hbal);
+    hipLaunchKernelGGL(k_balance, dim3(C), dim3(256), 0, c.stream, w.head2_w, 1, C, 16, c.w_hbal + 128);
+  } else {
+    hipLaunchKernelGGL(k_balance, dim3(C), dim3(256), 0, c.stream, w.head_w, 1, C, 256, c.w_hbal);
   }
-  for (int l = 0; l < c.p.layers && c.p.model_mode != RENO_MODEL_TOP; ++l) {
-    if (l == 0) {
+  hipLaunchKernelGGL(k_feature_balance, dim3(1), dim3(128), 0, c.stream, C, c.w_hbal, two ? c.w_hbal + 128 : nullptr,
+                     c.w_hrat, top ? c.wbal(2) : nullptr, c.w_xrat);
+  // and of a layer's output (full predictor, conv A2: X_B, added to B2's output)
+  auto obal = [&](int l) -> const float* { return l == L - 1 || (top && l == 1) ? c.w_hbal : c.wbal(l + 1); };
+  auto rows = [&](const float* src, const float* bal, int n, float* dst) {
+    hipLaunchKernelGGL(k_balance_rows, dim3((unsigned)(n * C + 255) / 256), dim3(256), 0, c.stream, src, bal, n, C, dst);
+  };
+  for (int l = 0; l < L; ++l) {
+    const float* src = conv_w(l);
+    if (!top && l == 0) {
       const dim3 grid(8 * 8 * 256 * C / 256);
-      if (C == 32) hipLaunchKernelGGL(k_first_table<32>, grid, dim3(256), 0, c.stream, w.conv_w[0], c.w_conv[0]);
-      else hipLaunchKernelGGL(k_first_table<16>, grid, dim3(256), 0, c.stream, w.conv_w[0], c.w_conv[0]);
+      if (C == 32) hipLaunchKernelGGL(k_first_table<32>, grid, dim3(256), 0, c.stream, src, obal(0), c.w_conv[0]);
+      else hipLaunchKernelGGL(k_first_table<16>, grid, dim3(256), 0, c.stream, src, obal(0), c.w_conv[0]);
     } else {
-      pack_conv(w.conv_w[l], 27, l);
+      uint16_t* out = reinterpret_cast<uint16_t*>(c.w_conv[l]);
+      hipLaunchKernelGGL(k_weight_max, dim3(WMAX_BLOCKS), dim3(256), 0, c.stream, src, kv * C, C, c.wbal(l), c.w_part);
+      const dim3 grid((unsigned)std::min<int64_t>(1024, ((int64_t)kv * C * C + 255) / 256));
+      auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, grid, dim3(256), 0, c.stream, src, kv, c.w_part, c.wbal(l), obal(l), out, c.wfac(l));
+      };
+      switch (C) {
+        case 128: go(k_pack_conv<128>); break;
+        case 64: go(k_pack_conv<64>); break;
+        case 32: go(k_pack_conv<32>); break;
+        default: go(k_pack_conv<16>);
+      }
     }
-    hipLaunchKernelGGL(k_copy_f32, dim3(1), dim3(256), 0, c.stream, w.conv_b[l], c.w_bias[l], C);
+    rows(top ? w.top_b[l] : w.conv_b[l], obal(l), 1, c.w_bias[l]);
+  }
+  if (top) {
+    rows(w.emb_o, c.w_hbal, 256, c.w_embo);
+    rows(w.emb_d, c.w_hbal, 8, c.w_embd);
+    auto go = [&](auto kern) {
+      hipLaunchKernelGGL(kern, dim3(16), dim3(64), 0, c.stream, w.emb_o, c.wbal(0), c.w_embs, c.w_embr);
+    };
+    switch (C) {
+      case 128: go(k_split_embed<128>); break;
+      case 64: go(k_split_embed<64>); break;
+      case 32: go(k_split_embed<32>); break;
+      default: go(k_split_embed<16>);
+    }
   }
   uint16_t* hw = reinterpret_cast<uint16_t*>(c.w_head);
-  if (c.p.head_mode == RENO_HEAD_TWO_STAGE) {
+  if (two) {
     // packed blocks [stage 1][stage 2], biases [b1 | b2], plain [C][H1 | H2]
-    hipLaunchKernelGGL(k_pack_head, dim3(1), dim3(256), 0, c.stream, w.head1_w, C, 16, hw, c.w_hfac);
-    hipLaunchKernelGGL(k_pack_head, dim3(1), dim3(256), 0, c.stream, w.head2_w, C, 16,
-                       hw + head_block_words(C) * 2, c.w_hfac + 1);
+    hipLaunchKernelGGL(k_head_max, dim3(1), dim3(64), 0, c.stream, w.head1_w, C, 16, c.w_hbal, c.w_part);
+    hipLaunchKernelGGL(k_head_max, dim3(1), dim3(64), 0, c.stream, w.head2_w, C, 16, c.w_hbal + 128, c.w_part + 16);
+    hipLaunchKernelGGL(k_pack_head, dim3(1), dim3(256), 0, c.stream, w.head1_w, C, 16, c.w_hbal, c.w_part, hw, c.w_hfac);
+    hipLaunchKernelGGL(k_pack_head, dim3(1), dim3(256), 0, c.stream, w.head2_w, C, 16, c.w_hbal + 128, c.w_part + 16,
+                       hw + head_block_words(C) * 2, c.w_hfac + 16);
     hipLaunchKernelGGL(k_copy_f32, dim3(1), dim3(64), 0, c.stream, w.head1_b, c.w_hbias, 16);
     hipLaunchKernelGGL(k_copy_f32, dim3(1), dim3(64), 0, c.stream, w.head2_b, c.w_hbias + 16, 16);
-    hipLaunchKernelGGL(k_put_cols16, dim3(2), dim3(256), 0, c.stream, w.head1_w, C, 0, c.w_head_plain);
-    hipLaunchKernelGGL(k_put_cols16, dim3(2), dim3(256), 0, c.stream, w.head2_w, C, 16, c.w_head_plain);
-    hipLaunchKernelGGL(k_copy_f32, dim3(2), dim3(256), 0, c.stream, w.emb_s1, c.w_emb, 16 * C);
-    hipLaunchKernelGGL(k_transpose_head, dim3(2), dim3(256), 0, c.stream, w.head1_w, C, 16, 0, c.w_head_t);
-    hipLaunchKernelGGL(k_transpose_head, dim3(2), dim3(256), 0, c.stream, w.head2_w, C, 16, 16, c.w_head_t);
+    hipLaunchKernelGGL(k_unbalance_head, dim3(2), dim3(256), 0, c.stream, w.head1_w, c.w_hbal, C, 16, 32, 0, c.w_head_plain);
+    hipLaunchKernelGGL(k_unbalance_head, dim3(2), dim3(256), 0, c.stream, w.head2_w, c.w_hbal, C, 16, 32, 16, c.w_head_plain);
+    rows(w.emb_s1, c.w_hbal, 16, c.w_emb);
+    hipLaunchKernelGGL(k_transpose_head, dim3(2), dim3(256), 0, c.stream, w.head1_w, c.w_hbal, C, 16, 0, c.w_head_t);
+    hipLaunchKernelGGL(k_transpose_head, dim3(2), dim3(256), 0, c.stream, w.head2_w, c.w_hbal, C, 16, 16, c.w_head_t);
   } else {
-    hipLaunchKernelGGL(k_pack_head, dim3(16), dim3(256), 0, c.stream, w.head_w, C, 256, hw, c.w_hfac);
+    hipLaunchKernelGGL(k_head_max, dim3(4), dim3(64), 0, c.stream, w.head_w, C, 256, c.w_hbal, c.w_part);
+    hipLaunchKernelGGL(k_pack_head, dim3(16), dim3(256), 0, c.stream, w.head_w, C, 256, c.w_hbal, c.w_part, hw, c.w_hfac);
     hipLaunchKernelGGL(k_copy_f32, dim3(1), dim3(256), 0, c.stream, w.head_b, c.w_hbias, 256);
-    hipLaunchKernelGGL(k_copy_f32, dim3(32), dim3(256), 0, c.stream, w.head_w, c.w_head_plain,
-                       C * 256);
-    hipLaunchKernelGGL(k_transpose_head, dim3(32), dim3(256), 0, c.stream, w.head_w, C, 256, 0, c.w_head_t);
+    hipLaunchKernelGGL(k_unbalance_head, dim3(32), dim3(256), 0, c.stream, w.head_w, c.w_hbal, C, 256, 256, 0, c.w_head_plain);
+    hipLaunchKernelGGL(k_transpose_head, dim3(32), dim3(256), 0, c.stream, w.head_w, c.w_hbal, C, 256, 0, c.w_head_t);
   }
   return hipGetLastError();
 }
@@ -2453,7 +2642,7 @@ hipError_t launch_top(Ctx& c, int b_lo, int b_hi, float* logits, bool second) {
     const int blocks = (int)std::min<int64_t>(2048, (c.cap_rows() + 63) / 64);
 #define RENO_PREP(CC)                                                                                         \
   hipLaunchKernelGGL((k_top_prep<CC, false>), dim3(blocks), dim3(256), 0, c.stream, n_lo, b_hi - n_lo + 1,      \
-                     b_hi - n_lo, b0, rm, c.lv_key, c.lv_code, (int64_t)c.cap_pts, cell_args(c), c.w_embo,    \
+                     b_hi - n_lo, b0, rm, c.lv_key, c.lv_code, (int64_t)c.cap_pts, cell_args(c), embed_tab(c), \
                      c.d_nbr, c.h_c, c.s_c, c.r_c)
     if (C == 32) RENO_PREP(32); else RENO_PREP(16);
 #undef RENO_PREP
@@ -2468,6 +2657,7 @@ hipError_t launch_top(Ctx& c, int b_lo, int b_hi, float* logits, bool second) {
   a.hb = c.w_hbias;
   a.hw = reinterpret_cast<const uint4*>(c.w_head);
   a.hfac = c.w_hfac;
+  a.hrat = c.w_hrat;
   a.lse = c.d_lse;
   a.err = c.d_err;
   a.emb = c.w_emb;
@@ -2498,6 +2688,7 @@ hipError_t launch_top(Ctx& c, int b_lo, int b_hi, float* logits, bool second) {
     a.xb_r = c.r_d;
     a.w = c.w_conv[wi];
     a.wfac = c.wfac(wi);
+    a.xrat = c.w_xrat;
     a.bias = c.w_bias[wi];
     a.logits = last ? logits : nullptr;
     ProfScope ps_(c, last ? RENO_K_CONV_LAST : RENO_K_CONV_MID);
@@ -2523,11 +2714,11 @@ hipError_t launch_top_wide(Ctx& c, int b_lo, int b_hi, float* logits, bool secon
     const int blocks = (int)std::min<int64_t>(2048, (c.cap_rows() + 63) / 64);
     if (KV == 125)
       hipLaunchKernelGGL(k_top_prep5<C>, dim3(blocks), dim3(256), 0, c.stream, n_lo, b_hi - n_lo + 1, b_hi - n_lo,
-                         b0, rm, c.lv_key, c.lv_code, (int64_t)c.cap_pts, cell_args(c), c.w_embo,
+                         b0, rm, c.lv_key, c.lv_code, (int64_t)c.cap_pts, cell_args(c), embed_tab(c),
                          c.d_nbr, c.h_c, c.s_c, c.r_c);
     else
       hipLaunchKernelGGL((k_top_prep<C, true>), dim3(blocks), dim3(256), 0, c.stream, n_lo, b_hi - n_lo + 1,
-                         b_hi - n_lo, b0, rm, c.lv_key, c.lv_code, (int64_t)c.cap_pts, cell_args(c), c.w_embo,
+                         b_hi - n_lo, b0, rm, c.lv_key, c.lv_code, (int64_t)c.cap_pts, cell_args(c), embed_tab(c),
                          c.d_nbr, c.h_c, c.s_c, c.r_c);
   }
   ConvArgs a{};
@@ -2540,6 +2731,7 @@ hipError_t launch_top_wide(Ctx& c, int b_lo, int b_hi, float* logits, bool secon
   a.hb = c.w_hbias;
   a.hw = reinterpret_cast<const uint4*>(c.w_head);
   a.hfac = c.w_hfac;
+  a.hrat = c.w_hrat;
   a.lse = c.d_lse;
   a.err = c.d_err;
   a.emb = c.w_emb;
@@ -2560,6 +2752,7 @@ hipError_t launch_top_wide(Ctx& c, int b_lo, int b_hi, float* logits, bool secon
                        KV == 125 ? 5 : 3, c.d_nbr, c.d_perm, c.d_next);
     a.perm = c.d_perm;
   }
+  const bool two = c.p.head_mode == RENO_HEAD_TWO_STAGE;
   hipError_t e = hipSuccess;
   auto conv = [&](int lo, int hi, int wi, const void* in, const float* r_in, float* out, const float* res, float* xb,
                   bool last) {
@@ -2577,6 +2770,7 @@ hipError_t launch_top_wide(Ctx& c, int b_lo, int b_hi, float* logits, bool secon
     a.xb_r = c.r_d;
     a.w = c.w_conv[wi];
     a.wfac = c.wfac(wi);
+    a.xrat = c.w_xrat;
     a.bias = c.w_bias[wi];
     a.next = c.d_next + 8 * wi;
     ProfScope ps_(c, RENO_K_CONV_MID);
@@ -2597,7 +2791,7 @@ hipError_t launch_top_wide(Ctx& c, int b_lo, int b_hi, float* logits, bool secon
     a.b_hi = b_hi;
     a.h_in = c.h_a;
     a.logits = logits;
-    e = run_headw<C>(c, c.p.head_mode == RENO_HEAD_TWO_STAGE, a);
+    e = run_headw<C>(c, two, a);
   }
   if (e != hipSuccess) return e;
   return hipGetLastError();
@@ -2632,6 +2826,7 @@ hipError_t launch_model(Ctx& c, int b_lo, int b_hi, float* logits, bool second) 
   a.hb = c.w_hbias;
   a.hw = reinterpret_cast<const uint4*>(c.w_head);
   a.hfac = c.w_hfac;
+  a.hrat = c.w_hrat;
   a.lse = c.d_lse;
   a.err = c.d_err;
   a.emb = c.w_emb;
@@ -2684,7 +2879,7 @@ hipError_t launch_head2(Ctx& c, int b, const uint8_t* s1, float* logits2) {
   const int blocks = (int)std::min<int64_t>(1024, (c.cap_pts + 63) / 64);
   auto go = [&](auto kern) {
     hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), 0, c.stream, b, c.d_count, c.d_moff, (int64_t)c.cap_model,
-                       c.hlast(), s1, code, hw2, c.w_hfac + 1, c.w_hbias + 16, c.w_emb, c.d_lse2, logits2, c.d_s1,
+                       c.hlast(), s1, code, hw2, c.w_hfac + 16, c.w_hrat, c.w_hbias + 16, c.w_emb, c.d_lse2, logits2, c.d_s1,
                        c.d_err);
   };
   switch (c.p.channels) {

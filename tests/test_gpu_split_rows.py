@@ -1,11 +1,14 @@
 """Split-fp16 conv layers and heads (fp32 values carried as a factor and two
-fp16 halves) against the oracle: magnitudes far from 1, rows and channels of
-mixed magnitude, all-zero weights, the smallest and ragged tiles, and a context
-whose scales are too large for 32-bit row offsets.
+fp16 halves) against the oracle: magnitudes far from 1, rows, channels and symbols
+of mixed magnitude, NaN, all-zero weights, the smallest and ragged tiles, and a
+context whose scales are too large for 32-bit row offsets.
 
-Bound: a product keeps 2^-22 of the row's largest entry times the channel's
-largest weight, sums add in fp32: 4e-6 of the largest logit is some ten times
-what three layers and a head of such sums show (2e-7 to 4e-7)."""
+Bound: a product keeps 2^-21 of itself, sums add in fp32: 4e-6 of the largest
+logit is some ten times what three layers and a head of such sums show (2e-7 to
+4e-7).  Where weights and features are scaled by powers of two that cancel, the
+bits stay the same."""
+import copy
+
 import numpy as np
 import pytest
 import torch  # noqa: F401  (slow first import on a fresh box: at collection)
@@ -72,6 +75,125 @@ def test_ragged_tiles_and_mixed_channels(n):
     w["conv_b"][1][7] = 0.0
     say("split rows, ragged", n)
     _check(_run(pts, B, b0, R, C, 3, w), pts, B, b0, R, w)
+
+
+@pytest.mark.parametrize("spread", [16, 26, 40])
+@pytest.mark.parametrize("C,two", [(16, False), (32, False), (32, True)])
+def test_channels_of_compensated_magnitude(spread, C, two):
+    """Hidden channels scaled by powers of two up to 2^spread apart, the weights that read them scaled back: in fp32
+    arithmetic the same products, so the same logits bit for bit as without the scaling, and the oracle's."""
+    B, b0, R = 8, 4, 10.0
+    pts = _cloud(3000, B, R, 5)
+    w = gen_weights(C, 3, seed=11, bias_std=0.1, two_stage=two)
+    rs = np.random.RandomState(spread + C)
+    v = copy.deepcopy(w)
+    for l in range(3):
+        f = (2.0 ** rs.randint(-spread // 2, spread // 2 + 1, C)).astype(np.float32)
+        f[:2] = 2.0 ** (spread // 2), 2.0 ** -(spread // 2)
+        v["conv_w"][l] *= f
+        v["conv_b"][l] *= f
+        if l < 2:
+            v["conv_w"][l + 1] /= f[:, None]
+        elif two:
+            v["head1_w"] /= f[:, None]
+            v["head2_w"] /= f[:, None]
+            v["emb_s1"] *= f
+        else:
+            v["head_w"] /= f[:, None]
+    say("split rows, channels 2 ^", spread, "apart, C", C, "two-stage", two)
+    lg = _run(pts, B, b0, R, C, 3, v, two)
+    _check(lg, pts, B, b0, R, w, two)
+    np.testing.assert_array_equal(lg, _run(pts, B, b0, R, C, 3, w, two))
+
+
+@pytest.mark.parametrize("C,ks,two", [(16, 3, True), (32, 3, False), (64, 3, True), (16, 5, False), (128, 3, False)])
+def test_full_predictor_channels_of_compensated_magnitude(C, ks, two):
+    """The same of the full predictor: the channels of X_A, X_B and their blocks' outputs scaled alike (the residuals
+    add them), the hidden ones of each block on their own, up to 2^26 apart; codes and bits of the coder too."""
+    B, b0, R = 7, 4, 10.0
+    pts = _cloud(1500, B, R, 4)
+    w = gen_weights(C, 2, seed=15, bias_std=0.1, two_stage=two, top=True, kernel_size=ks)
+    rs = np.random.RandomState(C + ks)
+    v = copy.deepcopy(w)
+    f = (2.0 ** rs.randint(-13, 14, C)).astype(np.float32)
+    v["emb_o"] *= f
+    v["emb_d"] *= f
+    for l in (0, 2):
+        t = (2.0 ** rs.randint(-13, 14, C)).astype(np.float32)
+        v["top_w"][l] = v["top_w"][l] / f[:, None] * t
+        v["top_b"][l] *= t
+        v["top_w"][l + 1] = v["top_w"][l + 1] / t[:, None] * f
+        v["top_b"][l + 1] *= f
+    for n in ("1", "2") if two else ("",):
+        v[f"head{n}_w"] /= f[:, None]
+    if two:
+        v["emb_s1"] *= f
+    say("split rows, full predictor C", C, "k", ks, "two-stage", two)
+    got = []
+    for u in (v, w):
+        ctx = reno.Context(len(pts), B, b0, R, C, 2, two_stage=two, top=True, kernel_size=ks)
+        ctx.set_weights(reno.weights_to_device(u))
+        words = ctx.encode_frame(to_dev(pts), B)
+        got.append([words.copy(), ctx.predict_probs(reno.RENO_ALL_SCALES, logits=True).cpu().numpy(),
+                    ctx.code_length(reno.RENO_ALL_SCALES)[0].cpu().numpy()])
+        ctx.close()
+    for a, b in zip(*got):
+        np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("C,two", [(16, False), (32, False), (32, True)])
+def test_symbols_of_any_magnitude(C, two):
+    """Columns of the head scaled by 2^0 .. 2^-40, without biases: each logit scaled by its power of two, exactly."""
+    B, b0, R = 8, 4, 10.0
+    pts = _cloud(1000, B, R, 6)
+    w = gen_weights(C, 2, seed=12, bias_std=0.1, two_stage=two)
+    f = (2.0 ** -np.linspace(0, 40, 16 if two else 256).round()).astype(np.float32)
+    v = dict(w)
+    for n in ("1", "2") if two else ("",):
+        w[f"head{n}_b"] = np.zeros_like(w[f"head{n}_b"])
+        v[f"head{n}_b"] = w[f"head{n}_b"]
+        v[f"head{n}_w"] = w[f"head{n}_w"] * f
+    say("split rows, head columns, C", C, "two-stage", two)
+    np.testing.assert_array_equal(_run(pts, B, b0, R, C, 2, v, two),
+                                  _run(pts, B, b0, R, C, 2, w, two) * (np.concatenate([f, f]) if two else f))
+
+
+@pytest.mark.parametrize("e", [-100, 60, 112])
+def test_features_near_the_ends_of_fp32(e):
+    """The features from the second layer on scaled by 2^e, the head's weights scaled back: every product and sum
+    stays inside fp32's range, so the logits are those of the unscaled model."""
+    B, b0, R, C = 8, 4, 10.0, 32
+    pts = _cloud(1500, B, R, 8)
+    w = gen_weights(C, 4, seed=13, bias_std=0.1)
+    v = copy.deepcopy(w)
+    f = np.float32(2.0) ** np.float32(e)
+    v["conv_w"][1] *= f
+    for l in (1, 2, 3):
+        v["conv_b"][l] *= f
+    v["head_w"] /= f
+    say("split rows, features times 2 ^", e)
+    np.testing.assert_array_equal(_run(pts, B, b0, R, C, 4, v), _run(pts, B, b0, R, C, 4, w))
+
+
+def test_nan_embedding_shows():
+    """NaN in one row of Emb(S1): the stage-2 logits of exactly the voxels with that S1 are NaN."""
+    B, b0, R, C = 8, 4, 10.0, 32
+    pts = _cloud(2000, B, R, 9)
+    w = gen_weights(C, 2, seed=14, bias_std=0.1, two_stage=True)
+    s1 = np.concatenate([oracle.Pyramid.from_points(pts, B, b0, R).codes(b) for b in range(b0 + 1, B)]) & 15
+    bad = int(np.bincount(s1).argmax())
+    good = _run(pts, B, b0, R, C, 2, w, True)
+    w["emb_s1"] = w["emb_s1"].copy()
+    w["emb_s1"][bad, 5] = np.nan
+    say("split rows, NaN embedding of S1 =", bad)
+    ctx = reno.Context(len(pts), B, b0, R, C, 2, two_stage=True)
+    ctx.set_weights(reno.weights_to_device(w))
+    ctx.build_pyramid(to_dev(pts), B)
+    lg = ctx.predict_probs(reno.RENO_ALL_SCALES, logits=True).cpu().numpy()
+    ctx.close()
+    assert np.isnan(lg[s1 == bad][:, 16:]).all()
+    np.testing.assert_array_equal(lg[s1 != bad], good[s1 != bad])
+    np.testing.assert_array_equal(lg[:, :16], good[:, :16])
 
 
 def test_all_zero_layer():
