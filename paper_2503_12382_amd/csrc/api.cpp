@@ -52,8 +52,8 @@ void free_all(Ctx* c) {
                   c->d_status, c->d_hash,   c->d_hreg,   c->h_a,      c->h_b,      c->d_nbr,     c->d_lse,
                   c->d_partial, c->d_total, c->w_head,   c->w_hbias,  c->w_head_plain,
                   c->d_lse2,    c->w_emb,   c->d_s1,     c->w_head_t, c->d_perm, c->d_next,
-                  c->h_c,       c->h_d,     c->w_embo,   c->w_embd,   c->s_c,     c->s_d,
-                  c->r_a,       c->r_b,     c->r_c,      c->r_d,      c->w_wfac,  c->w_hfac,
+                  c->h_d,       c->w_embo,  c->w_embd,   c->s_c,      c->r_a,     c->r_b,
+                  c->r_c,       c->w_wfac,  c->w_hfac,
                   c->w_part,    c->w_bal,   c->w_hbal,    c->w_hrat,  c->w_xrat,    c->w_embs,
                   c->w_embr};
   for (void* p : ptrs)
@@ -216,12 +216,7 @@ reno_status reno_create(const reno_params* p, void* hip_stream, reno_ctx** out) 
   A(dalloc(&c->w_part, (size_t)64 * 128, &c->device_bytes));
   if (top) {
     A(dalloc(&c->s_c, rows * C, &c->device_bytes));
-    A(dalloc(&c->s_d, rows * C, &c->device_bytes));
     A(dalloc(&c->r_c, rows, &c->device_bytes));
-    A(dalloc(&c->r_d, rows, &c->device_bytes));
-  }
-  if (top) {
-    A(dalloc(&c->h_c, rows * C, &c->device_bytes));
     A(dalloc(&c->h_d, rows * C, &c->device_bytes));
     A(dalloc(&c->w_embo, (size_t)256 * C, &c->device_bytes));
     A(dalloc(&c->w_embs, (size_t)256 * C, &c->device_bytes));
@@ -231,8 +226,8 @@ reno_status reno_create(const reno_params* p, void* hip_stream, reno_ctx** out) 
   A(dalloc(&c->d_nbr, rows * c->nbr_stride(), &c->device_bytes));
   A(dalloc(&c->d_lse, (size_t)cap_model, &c->device_bytes));
   A(dalloc(&c->d_lse2, (size_t)cap_model, &c->device_bytes));
-  A(dalloc(&c->d_perm, rows, &c->device_bytes));
-  A(dalloc(&c->d_next, 32, &c->device_bytes));
+  if (c->wide()) A(dalloc(&c->d_perm, rows, &c->device_bytes));
+  if (c->wide()) A(dalloc(&c->d_next, 32, &c->device_bytes));
   A(dalloc(&c->d_s1, (size_t)cap_model, &c->device_bytes));
   A(dalloc(&c->d_partial, (size_t)reno::NLEV * ((c->cap_pts + 63) / 64), &c->device_bytes));
   A(dalloc(&c->d_total, reno::NLEV, &c->device_bytes));
@@ -259,21 +254,15 @@ reno_status reno_create(const reno_params* p, void* hip_stream, reno_ctx** out) 
     return fail(nullptr, e == hipErrorOutOfMemory ? RENO_E_NOMEM : RENO_E_HIP, msg);
   }
   // tickets start at zero (every frame clears them again); the reserved zero
-  // row of each feature buffer is never written afterwards
+  // row of each buffer that a conv reads is never written afterwards
   e = hipMemsetAsync(c->d_ticket, 0, sizeof(uint32_t) * reno::TICKETS, c->stream);
   if (e == hipSuccess)
     e = hipMemsetAsync(c->h_a + (size_t)cap_model * C, 0, sizeof(float) * C, c->stream);
   if (e == hipSuccess)
     e = hipMemsetAsync(c->h_b + (size_t)cap_model * C, 0, sizeof(float) * C, c->stream);
   if (e == hipSuccess && top)
-    e = hipMemsetAsync(c->h_c + (size_t)cap_model * C, 0, sizeof(float) * C, c->stream);
-  if (e == hipSuccess && top)
-    e = hipMemsetAsync(c->h_d + (size_t)cap_model * C, 0, sizeof(float) * C, c->stream);
-  if (e == hipSuccess && top)
     e = hipMemsetAsync(c->s_c + (size_t)cap_model * C, 0, sizeof(float) * C, c->stream);
-  if (e == hipSuccess && top)
-    e = hipMemsetAsync(c->s_d + (size_t)cap_model * C, 0, sizeof(float) * C, c->stream);
-  for (float* r : {c->r_a, c->r_b, c->r_c, c->r_d})  // the zero rows' factors
+  for (float* r : {c->r_a, c->r_b, c->r_c})  // the zero rows' factors
     if (e == hipSuccess && r) e = hipMemsetAsync(r + cap_model, 0, sizeof(float), c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess) {

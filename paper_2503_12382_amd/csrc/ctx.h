@@ -82,14 +82,11 @@ struct Ctx {
   // with a factor per row in the r_ array of the same letter
   float* h_a = nullptr;         // [cap_rows][C]
   float* h_b = nullptr;
-  float* h_c = nullptr;         // full predictor: X_A = Emb_O[O] of the parent scales (with a zero row)
-  float* h_d = nullptr;         // full predictor: X_B of the target scales (with a zero row)
-  uint32_t* s_c = nullptr;      // full predictor: X_A and X_B as split rows
-  uint32_t* s_d = nullptr;
+  float* h_d = nullptr;         // full predictor: X_B of the target scales
+  uint32_t* s_c = nullptr;      // full predictor: X_A = Emb_O[O] of the parent scales, then X_B, as split rows
   float* r_a = nullptr;         // [cap_rows] each
   float* r_b = nullptr;
   float* r_c = nullptr;
-  float* r_d = nullptr;
   int32_t* d_nbr = nullptr;     // [cap_rows][nbr_stride()]
   int32_t* d_perm = nullptr;    // [cap_rows] tile order of the streamed-weight conv layers
   uint32_t* d_next = nullptr;   // their work counters [layer][XCD]

@@ -479,7 +479,7 @@ struct ConvArgs {
   uint8_t* s1_out;        // [cap_model] the S1 stage 2 used
   const int32_t* perm;    // k_convw: tile order, tile slot -> packed row
   // full predictor
-  const float* res;       // residual input added before the ReLU (same rows as h_out), or NULL
+  const float* res;       // residual input added before the ReLU (same rows as h_out), or NULL; see emb_o
   int b_ext;              // scale whose rows live past the zero row (the base scale), or -1
   int64_t ext_off;        // first packed row of that scale (cap_model + 1)
   int64_t cap_rows;       // rows of the feature buffers
@@ -490,6 +490,7 @@ struct ConvArgs {
   float* xb_r;            // their factors
   const float* xrat;      // what takes X_B to the balance of the conv that reads them [C]
   const float* emb_d;     // [8][C]
+  const float* emb_o;     // [256][C]: the residual input X_A of that layer
   const uint8_t* code;    // per-scale regions: O_b
   const int32_t* fc;      // per-scale regions: first child row in V_{b+1}
 };
@@ -1095,6 +1096,11 @@ template <int C, bool XB>
 __device__ __forceinline__ void conv_epilogue(const ConvArgs& a, const f4 (&sum)[C / 16], int g, const TileRef& tr,
                                               float (&x)[C / 4]) {
   constexpr int N = C / 4, NC = at_once(C);
+  // residual block: ReLU(x + conv(.)), x read at the voxel's own row; X_A (the
+  // block that feeds the children) is a row of Emb_O
+  uint32_t code = 0;
+  if constexpr (XB) code = a.code[tr.lvb + (tr.prow - tr.mo)];
+  const float* res = XB ? a.emb_o + code * C : a.res ? a.res + tr.prow * C : nullptr;
 #pragma unroll
   for (int c0 = 0; c0 < N; c0 += NC) {
     float wf[NC], bs[NC];
@@ -1102,9 +1108,9 @@ __device__ __forceinline__ void conv_epilogue(const ConvArgs& a, const f4 (&sum)
     load_row<4 * NC>(a.bias + 4 * c0, g, bs);
 #pragma unroll
     for (int i = 0; i < NC; ++i) x[c0 + i] = fmaf(sum[(c0 + i) / 4][i % 4], wf[i], bs[i]);
-    if (a.res) {  // residual block: ReLU(x + conv(.)), x read at the voxel's own row
+    if (res) {
       float rs[NC];
-      load_row<4 * NC>(a.res + tr.prow * C + 4 * c0, g, rs);
+      load_row<4 * NC>(res + 4 * c0, g, rs);
 #pragma unroll
       for (int i = 0; i < NC; ++i) x[c0 + i] += rs[i];
     }
@@ -1116,7 +1122,6 @@ __device__ __forceinline__ void conv_epilogue(const ConvArgs& a, const f4 (&sum)
   if constexpr (XB) {  // children v of this voxel u: X_B[v] = F[u] + Emb_D[delta(v)]
     int64_t cmo = a.moff[tr.b + 1];
     const int64_t cn = a.count[tr.b + 1];
-    const uint32_t code = a.code[tr.lvb + (tr.prow - tr.mo)];
     const int64_t first = a.fc[tr.lvb + (tr.prow - tr.mo)];
     if (cmo + cn > a.cap_model) cmo = -1;  // overflow (latched where the size was made): no writes
     float rt[NC];
@@ -1508,19 +1513,14 @@ __global__ void __launch_bounds__(64) k_split_embed(const float* __restrict__ em
   store_split<C, 1>(own, g, rows + row * C, facs + row);
 }
 
-// X_A = Emb_O[code] at a row, in fp32 (the residual) and split (the conv's
-// input, a row of k_split_embed); lanes 4r + g.
+// X_A = Emb_O[code] at a row, as the split row of k_split_embed; lanes 4r + g.
 struct EmbedTab {
-  const float* emb;      // [256][C], with the features' balance
   const uint32_t* rows;  // [256][C]
   const float* facs;     // [256]
 };
 template <int C>
-__device__ __forceinline__ void embed_row(const EmbedTab& t, int code, int g, int64_t row, float* __restrict__ X,
-                                          uint32_t* __restrict__ XS, float* __restrict__ XR) {
-  float x[C / 4];
-  load_row<C>(t.emb + code * C, g, x);
-  store_row<C>(x, g, X + row * C);
+__device__ __forceinline__ void embed_row(const EmbedTab& t, int code, int g, int64_t row, uint32_t* __restrict__ XS,
+                                          float* __restrict__ XR) {
   const uint4* src = reinterpret_cast<const uint4*>(t.rows + code * C);
   uint4* dst = reinterpret_cast<uint4*>(XS + row * C);
 #pragma unroll
@@ -1534,8 +1534,7 @@ __global__ void __launch_bounds__(256) k_top_prep(int lo, int nsc, int n_embed, 
                                                   const uint64_t* __restrict__ lv_key,
                                                   const uint8_t* __restrict__ lv_code, int64_t cap_pts,
                                                   CellArgs cells, EmbedTab emb_o, int32_t* __restrict__ nbr,
-                                                  float* __restrict__ X, uint32_t* __restrict__ XS,
-                                                  float* __restrict__ XR) {
+                                                  uint32_t* __restrict__ XS, float* __restrict__ XR) {
   __shared__ uint64_t s_par[4][16][9];  // rows padded: the 16 voxels' cells in different banks
   __shared__ int64_t s_n[32], s_mo[32], s_tpre[32];
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
@@ -1579,7 +1578,7 @@ __global__ void __launch_bounds__(256) k_top_prep(int lo, int nsc, int n_embed, 
     } else {
       store_map(nbr, mo + vr, valid, g, nb);
     }
-    if (valid && si < n_embed) embed_row<C>(emb_o, lv_code[lvb + vr], g, mo + vr, X, XS, XR);
+    if (valid && si < n_embed) embed_row<C>(emb_o, lv_code[lvb + vr], g, mo + vr, XS, XR);
   }
 }
 
@@ -1669,8 +1668,7 @@ __global__ void __launch_bounds__(256) k_top_prep5(int lo, int nsc, int n_embed,
                                                    const uint64_t* __restrict__ lv_key,
                                                    const uint8_t* __restrict__ lv_code, int64_t cap_pts,
                                                    CellArgs cells, EmbedTab emb_o, int32_t* __restrict__ nbr,
-                                                   float* __restrict__ X, uint32_t* __restrict__ XS,
-                                                   float* __restrict__ XR) {
+                                                   uint32_t* __restrict__ XS, float* __restrict__ XR) {
   __shared__ uint64_t s_par[4][16][27];
   __shared__ int64_t s_n[32], s_mo[32], s_tpre[32];
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, r = lane >> 2, g = lane & 3;
@@ -1708,7 +1706,7 @@ __global__ void __launch_bounds__(256) k_top_prep5(int lo, int nsc, int n_embed,
       int4* dst = reinterpret_cast<int4*>(nbr + (mo + vr) * 128 + 32 * g);
 #pragma unroll
       for (int q = 0; q < 8; ++q) dst[q] = make_int4(nb[4 * q], nb[4 * q + 1], nb[4 * q + 2], nb[4 * q + 3]);
-      if (si < n_embed) embed_row<C>(emb_o, lv_code[lvb + vr], g, mo + vr, X, XS, XR);
+      if (si < n_embed) embed_row<C>(emb_o, lv_code[lvb + vr], g, mo + vr, XS, XR);
     }
   }
 }
@@ -2451,7 +2449,7 @@ CellArgs cell_args(const Ctx& c) {
   return CellArgs{c.d_hash, c.hash_lg, c.hreg(), c.fbits, c.b0(), c.cap_pts, c.lv_code, c.lv_fc};
 }
 
-EmbedTab embed_tab(const Ctx& c) { return EmbedTab{c.w_embo, c.w_embs, c.w_embr}; }
+EmbedTab embed_tab(const Ctx& c) { return EmbedTab{c.w_embs, c.w_embr}; }
 
 template <int C>
 hipError_t run_first(Ctx& c, const FirstArgs& a) {
@@ -2622,10 +2620,11 @@ hipError_t launch_pack_weights(Ctx& c, const reno_weights& w) {
 
 // Full predictor on the scales b_lo .. b_hi (Sec. 3.2, Eqs. 6-9):
 //   neighbour maps of scales b_lo-1 .. b_hi, X_A = Emb_O[O^{d-1}] on scales
-//   b_lo-1 .. b_hi-1 (h_c, split s_c)                             one prep launch
+//   b_lo-1 .. b_hi-1 (split rows s_c)                             one prep launch
 //   T = ReLU(conv_A1(X_A))                                        (split h_b)
 //   F_A = ReLU(X_A + conv_A2(T)), scattered to the children as
-//   X_B = F_A[parent] + Emb_D[delta] on scales b_lo .. b_hi       (h_d, split s_d; F_A itself is not stored)
+//   X_B = F_A[parent] + Emb_D[delta] on scales b_lo .. b_hi       (h_d, split s_c, X_A being used up; F_A itself
+//   is not stored)
 //   T = ReLU(conv_B1(X_B))                                        (split h_b)
 //   F_B = ReLU(X_B + conv_B2(T)), fused with the head             (h_a)
 // The base scale's rows live past the zero row.  F_B of earlier calls is
@@ -2643,7 +2642,7 @@ hipError_t launch_top(Ctx& c, int b_lo, int b_hi, float* logits, bool second) {
 #define RENO_PREP(CC)                                                                                         \
   hipLaunchKernelGGL((k_top_prep<CC, false>), dim3(blocks), dim3(256), 0, c.stream, n_lo, b_hi - n_lo + 1,      \
                      b_hi - n_lo, b0, rm, c.lv_key, c.lv_code, (int64_t)c.cap_pts, cell_args(c), embed_tab(c), \
-                     c.d_nbr, c.h_c, c.s_c, c.r_c)
+                     c.d_nbr, c.s_c, c.r_c)
     if (C == 32) RENO_PREP(32); else RENO_PREP(16);
 #undef RENO_PREP
   }
@@ -2668,6 +2667,7 @@ hipError_t launch_top(Ctx& c, int b_lo, int b_hi, float* logits, bool second) {
   a.ext_off = ext_off;
   a.cap_rows = c.cap_rows();
   a.emb_d = c.w_embd;
+  a.emb_o = c.w_embo;
   a.code = c.lv_code;
   a.fc = c.lv_fc;
   const bool two = c.p.head_mode == RENO_HEAD_TWO_STAGE;
@@ -2684,8 +2684,8 @@ hipError_t launch_top(Ctx& c, int b_lo, int b_hi, float* logits, bool second) {
     a.r_out = c.r_b;
     a.res = res;
     a.xb = xb;
-    a.xb_s = c.s_d;
-    a.xb_r = c.r_d;
+    a.xb_s = c.s_c;
+    a.xb_r = c.r_c;
     a.w = c.w_conv[wi];
     a.wfac = c.wfac(wi);
     a.xrat = c.w_xrat;
@@ -2695,8 +2695,8 @@ hipError_t launch_top(Ctx& c, int b_lo, int b_hi, float* logits, bool second) {
     e = (C == 32) ? run_layer<32>(c, last, two, a) : run_layer<16>(c, last, two, a);
   };
   conv(n_lo, b_hi - 1, 0, c.s_c, c.r_c, c.h_b, nullptr, nullptr, false);
-  conv(n_lo, b_hi - 1, 1, c.h_b, c.r_b, nullptr, c.h_c, c.h_d, false);
-  conv(b_lo, b_hi, 2, c.s_d, c.r_d, c.h_b, nullptr, nullptr, false);
+  conv(n_lo, b_hi - 1, 1, c.h_b, c.r_b, nullptr, nullptr, c.h_d, false);
+  conv(b_lo, b_hi, 2, c.s_c, c.r_c, c.h_b, nullptr, nullptr, false);
   conv(b_lo, b_hi, 3, c.h_b, c.r_b, c.h_a, c.h_d, nullptr, true);
   return e == hipSuccess ? hipGetLastError() : e;
 }
@@ -2715,11 +2715,11 @@ hipError_t launch_top_wide(Ctx& c, int b_lo, int b_hi, float* logits, bool secon
     if (KV == 125)
       hipLaunchKernelGGL(k_top_prep5<C>, dim3(blocks), dim3(256), 0, c.stream, n_lo, b_hi - n_lo + 1, b_hi - n_lo,
                          b0, rm, c.lv_key, c.lv_code, (int64_t)c.cap_pts, cell_args(c), embed_tab(c),
-                         c.d_nbr, c.h_c, c.s_c, c.r_c);
+                         c.d_nbr, c.s_c, c.r_c);
     else
       hipLaunchKernelGGL((k_top_prep<C, true>), dim3(blocks), dim3(256), 0, c.stream, n_lo, b_hi - n_lo + 1,
                          b_hi - n_lo, b0, rm, c.lv_key, c.lv_code, (int64_t)c.cap_pts, cell_args(c), embed_tab(c),
-                         c.d_nbr, c.h_c, c.s_c, c.r_c);
+                         c.d_nbr, c.s_c, c.r_c);
   }
   ConvArgs a{};
   a.b0 = b0;
@@ -2742,6 +2742,7 @@ hipError_t launch_top_wide(Ctx& c, int b_lo, int b_hi, float* logits, bool secon
   a.ext_off = ext_off;
   a.cap_rows = c.cap_rows();
   a.emb_d = c.w_embd;
+  a.emb_o = c.w_embo;
   a.code = c.lv_code;
   a.fc = c.lv_fc;
   {  // tiles of voxels with similar neighbourhoods: smaller offset unions per tile and group
@@ -2766,8 +2767,8 @@ hipError_t launch_top_wide(Ctx& c, int b_lo, int b_hi, float* logits, bool secon
     a.r_out = c.r_b;
     a.res = res;
     a.xb = xb;
-    a.xb_s = c.s_d;
-    a.xb_r = c.r_d;
+    a.xb_s = c.s_c;
+    a.xb_r = c.r_c;
     a.w = c.w_conv[wi];
     a.wfac = c.wfac(wi);
     a.xrat = c.w_xrat;
@@ -2781,8 +2782,8 @@ hipError_t launch_top_wide(Ctx& c, int b_lo, int b_hi, float* logits, bool secon
     e = hipGetLastError();
   };
   conv(n_lo, b_hi - 1, 0, c.s_c, c.r_c, c.h_b, nullptr, nullptr, false);
-  conv(n_lo, b_hi - 1, 1, c.h_b, c.r_b, nullptr, c.h_c, c.h_d, false);
-  conv(b_lo, b_hi, 2, c.s_d, c.r_d, c.h_b, nullptr, nullptr, false);
+  conv(n_lo, b_hi - 1, 1, c.h_b, c.r_b, nullptr, nullptr, c.h_d, false);
+  conv(b_lo, b_hi, 2, c.s_c, c.r_c, c.h_b, nullptr, nullptr, false);
   conv(b_lo, b_hi, 3, c.h_b, c.r_b, c.h_a, c.h_d, nullptr, true);
   if (e != hipSuccess) return e;
   {

@@ -166,3 +166,17 @@ def test_top_single_scale_encoder_calls(scan_cache):
     assert off == lg.shape[0]
     enc.close()
     ctx.close()
+
+
+@pytest.mark.parametrize("C,ks", [(16, 3), (32, 3), (32, 5), (128, 3)])
+def test_memory_per_model_row(C, ks):
+    """A model row of the full predictor holds four rows of C floats (X_A becomes X_B, Emb_O is read by code), three
+    row factors, its map row and the normalisers; the streamed-weight kernels add a tile slot."""
+    info = []
+    for rows in (40000, 80000):
+        ctx = reno.Context(10000, 12, 4, 10.0, C, 2, top=True, kernel_size=ks, max_model_voxels=rows)
+        m = ctx.memory_info()
+        info.append(m["device_bytes"] - 16 * m["hash_slots"])
+        ctx.close()
+    per = 4 * 4 * C + 3 * 4 + 4 * (128 if ks == 5 else 32) + 4 + 4 + 1 + (4 if C > 32 or ks == 5 else 0)
+    assert abs((info[1] - info[0]) / 40000 - per) < 1.0
