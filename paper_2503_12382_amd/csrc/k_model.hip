@@ -5,13 +5,13 @@
 // normaliser (Eq. 10).  The first layer, whose input is 11 bits, is a sum of
 // table rows (k_first); the others are matrix products (k_conv).
 //
-// Matrix layers: a wavefront owns 16 or 32 consecutive voxels of one scale (in
-// small launches a quad of waves shares 16).  Each layer is computed
+// Matrix layers: a wavefront owns 16 voxels of one scale (in small launches a quad
+// of waves shares them, or a block's waves a few tiles).  Each layer is computed
 // transposed, out^T[c_out][16] = sum_k W_k^T in_k^T, on fp16 MFMA 16x16x32
 // with split operands (below): the A operand is the offset's weights (staged
 // once per block in LDS), the B operand the gathered neighbour rows (lane
-// (r, g) loads a contiguous slice of the row of voxel r's neighbour).  Only
-// offsets with at least one occupied neighbour in the tile are issued.  A
+// (r, g) holds a slice of the row of voxel r's neighbour).  Only offsets with at
+// least one occupied neighbour in the tile are issued.  A
 // lane ends with 8 consecutive channels of its voxel, which is exactly the B
 // operand of the head, so the head (16 x 256 logits per tile) runs from
 // registers, followed by a row max / sum of exp over the 64 logits a lane
@@ -471,7 +471,6 @@ struct ConvArgs {
   const float* hb;        // [256]
   float* lse;             // [cap_model]
   float* logits;          // optional [rows][256] (two-stage: [rows][32]), row = packed row - moff[b_lo]
-  uint32_t* err;
   // two-stage head
   const float* emb;       // [16][C]
   const uint8_t* s1_code; // codes of the per-scale regions (S1 = O & 15), or NULL: stage 1 only
@@ -702,51 +701,44 @@ __device__ __forceinline__ void parent_cell_rows(uint64_t kf, int b, int g, cons
 constexpr float LOG2E_F = 1.4426950408889634f;
 
 // One group of 64 symbols of the 256-way head (symbol blocks 4 grp .. 4 grp
-// + 3, 16 symbols each) for NT tiles: logits z = H^T x + b, stored when
-// requested (lo[t], or NULL), and the group's normaliser terms per lane: gm =
-// the max of the lane's 16 logits, part = the sum of exp(z - gm).
-template <int C, int NT>
+// + 3, 16 symbols each) for a tile: logits z = H^T x + b, stored when requested
+// (lo, or NULL), and the group's normaliser terms per lane: gm = the max of the
+// lane's 16 logits, part = the sum of exp(z - gm).
+template <int C>
 __device__ __forceinline__ void head_group(const uint4* s_h, const float* __restrict__ hb, const float* __restrict__ hfac,
-                                           const HeadOp<C> (&op)[NT], float* const (&lo)[NT], int lane, int g,
-                                           int grp, float (&gm)[NT], float (&part)[NT]) {
-  f4 zz[NT][4];
+                                           const HeadOp<C>& op, float* lo, int lane, int g, int grp, float& gm,
+                                           float& part) {
+  f4 zz[4];
   const float shared = hfac[256];
 #pragma unroll
   for (int q4 = 0; q4 < 4; ++q4) {
     const int sb = grp * 4 + q4;
     const f4 bias = *reinterpret_cast<const f4*>(hb + 16 * sb + 4 * g);
-    const uint4* hp = s_h + (size_t)sb * HeadOp<C>::BLOCK;
+    const f4 p = head_block<C>(s_h + (size_t)sb * HeadOp<C>::BLOCK, lane, op);
+    const float f1 = op.fac * shared;
+    f4 f = f4{f1, f1, f1, f1};
+    if (shared == 0.0f) f = *reinterpret_cast<const f4*>(hfac + 16 * sb + 4 * g) * op.fac;  // uniform
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const f4 p = head_block<C>(hp, lane, op[t]);
-      const float f1 = op[t].fac * shared;
-      f4 f = f4{f1, f1, f1, f1};
-      if (shared == 0.0f) f = *reinterpret_cast<const f4*>(hfac + 16 * sb + 4 * g) * op[t].fac;  // uniform
-#pragma unroll
-      for (int e = 0; e < 4; ++e) zz[t][q4][e] = fmaf(p[e], f[e], bias[e]);
-    }
+    for (int e = 0; e < 4; ++e) zz[q4][e] = fmaf(p[e], f[e], bias[e]);
   }
+  float mx = zz[0][0];
 #pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    float mx = zz[t][0][0];
+  for (int q4 = 0; q4 < 4; ++q4)
 #pragma unroll
-    for (int q4 = 0; q4 < 4; ++q4)
+    for (int e = 0; e < 4; ++e) mx = fmaxf(mx, zz[q4][e]);
+  // exp(z - gm) as 2^(z log2(e) - gm log2(e)): one fused multiply-add per term
+  const float ml = mx * LOG2E_F;
+  float s = __builtin_amdgcn_exp2f(fmaf(zz[0][0], LOG2E_F, -ml));
 #pragma unroll
-      for (int e = 0; e < 4; ++e) mx = fmaxf(mx, zz[t][q4][e]);
-    // exp(z - gm) as 2^(z log2(e) - gm log2(e)): one fused multiply-add per term
-    const float ml = mx * LOG2E_F;
-    float s = __builtin_amdgcn_exp2f(fmaf(zz[t][0][0], LOG2E_F, -ml));
+  for (int q4 = 0; q4 < 4; ++q4)
 #pragma unroll
-    for (int q4 = 0; q4 < 4; ++q4)
+    for (int e = 0; e < 4; ++e)
+      if (q4 || e) s += __builtin_amdgcn_exp2f(fmaf(zz[q4][e], LOG2E_F, -ml));
+  gm = mx;
+  part = s;
+  if (lo) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (q4 || e) s += __builtin_amdgcn_exp2f(fmaf(zz[t][q4][e], LOG2E_F, -ml));
-    gm[t] = mx;
-    part[t] = s;
-    if (lo[t]) {
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) *reinterpret_cast<f4*>(lo[t] + 16 * (grp * 4 + q4)) = zz[t][q4];
-    }
+    for (int q4 = 0; q4 < 4; ++q4) *reinterpret_cast<f4*>(lo + 16 * (grp * 4 + q4)) = zz[q4];
   }
 }
 
@@ -806,36 +798,26 @@ __device__ __forceinline__ void head_two(const ConvArgs& a, const float (&x)[C /
   if (lo) *reinterpret_cast<f4*>(lo + 16) = z2;
 }
 
-// The head on the features of NT tiles in registers: the one-stage 256-way
-// head with its softmax normaliser (Eq. 10), or the two-stage head.  Writes
-// lse (lse2, S1) at the tiles' rows and, when requested, the logits at row
-// prow - mo_first.  The NT tiles share the reads of the head's weights.
-template <int C, bool TWO, int NT>
-__device__ __forceinline__ void head_epilogue(const ConvArgs& a, const float (&x)[NT][C / 4], const uint4* s_h,
-                                              int lane, int g, const TileRef (&tr)[NT], int64_t mo_first) {
+// The head on a tile's features in registers: the one-stage 256-way head with its
+// softmax normaliser (Eq. 10), or the two-stage head.  Writes lse (lse2, S1) at
+// the tile's rows and, when requested, the logits at row prow - mo_first.
+template <int C, bool TWO>
+__device__ __forceinline__ void head_epilogue(const ConvArgs& a, const float (&x)[C / 4], const uint4* s_h, int lane,
+                                              int g, const TileRef& tr, int64_t mo_first) {
   if constexpr (TWO) {
-#pragma unroll
-    for (int t = 0; t < NT; ++t) head_two<C>(a, x[t], s_h, lane, g, tr[t], mo_first);
+    head_two<C>(a, x, s_h, lane, g, tr, mo_first);
   } else {
-    HeadOp<C> op[NT];
-    float* lo[NT];
-    float m[NT], ssum[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      op[t].set(x[t]);
-      lo[t] = (a.logits && tr[t].valid) ? a.logits + (tr[t].prow - mo_first) * 256 + 4 * g : nullptr;
-      m[t] = -INFINITY;
-      ssum[t] = 0.0f;
-    }
+    HeadOp<C> op;
+    op.set(x);
+    float* lo = (a.logits && tr.valid) ? a.logits + (tr.prow - mo_first) * 256 + 4 * g : nullptr;
+    float m = -INFINITY, ssum = 0.0f;
 #pragma unroll 1
     for (int grp = 0; grp < 4; ++grp) {
-      float gm[NT], part[NT];
-      head_group<C, NT>(s_h, a.hb, a.hfac, op, lo, lane, g, grp, gm, part);
-#pragma unroll
-      for (int t = 0; t < NT; ++t) lse_merge(m[t], ssum[t], gm[t], part[t]);
+      float gm, part;
+      head_group<C>(s_h, a.hb, a.hfac, op, lo, lane, g, grp, gm, part);
+      lse_merge(m, ssum, gm, part);
     }
-#pragma unroll
-    for (int t = 0; t < NT; ++t) lse_finish(a, m[t], ssum[t], g, tr[t].valid, tr[t].prow);
+    lse_finish(a, m, ssum, g, tr.valid, tr.prow);
   }
 }
 
@@ -1256,12 +1238,12 @@ __global__ void __launch_bounds__(CONV_THREADS) k_conv(ConvArgs a) {
     for (int64_t slot = w;;) {
       const int64_t u = conv_tile(slot, tch);
       if (u >= total) break;
-      TileRef tr[1];
+      TileRef tr;
       f4 sum[NCB];
-      float x[1][N];
-      open((int)u, -1, tr[0], sum);
-      conv_epilogue<C, KIND == CONV_SCATTER>(a, sum, g, tr[0], x[0]);
-      if constexpr (LAST) head_epilogue<C, TWO, 1>(a, x, s_h, lane, g, tr, mo_first);
+      float x[N];
+      open((int)u, -1, tr, sum);
+      conv_epilogue<C, KIND == CONV_SCATTER>(a, sum, g, tr, x);
+      if constexpr (LAST) head_epilogue<C, TWO>(a, x, s_h, lane, g, tr, mo_first);
       int nxt = 0;
       if (lane == 0) nxt = atomicAdd(&s_next, 1);
       slot = CONV_WAVES + __builtin_amdgcn_readfirstlane(nxt);
@@ -1279,9 +1261,9 @@ __global__ void __launch_bounds__(CONV_THREADS) k_conv(ConvArgs a) {
     const int q = w >> 2, gi = w & 3;
     const int tile = (int)blockIdx.x + (int)gridDim.x * q;
     const bool has = tile < total;  // wave-uniform
-    TileRef tr[1]{};
+    TileRef tr{};
     f4 sum[NCB];
-    if (has) open(tile, gi, tr[0], sum);
+    if (has) open(tile, gi, tr, sum);
     __syncthreads();  // every conv loop of the block is done: the weight area is free
     f4* s_x = reinterpret_cast<f4*>(s_w);                           // [quad][slot 0..3][NCB][64]: group sums 1-3, x
     float2* s_x2 = reinterpret_cast<float2*>(s_x + 16 * NCB * 64);  // [quad][group][64]: (gm, part)
@@ -1300,14 +1282,14 @@ __global__ void __launch_bounds__(CONV_THREADS) k_conv(ConvArgs a) {
         t += *xs(2, cb);
         sum[cb] = t;
       }
-      float x[1][N];
-      conv_epilogue<C, KIND == CONV_SCATTER>(a, sum, g, tr[0], x[0]);
+      float x[N];
+      conv_epilogue<C, KIND == CONV_SCATTER>(a, sum, g, tr, x);
       if constexpr (LAST && !TWO) {
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb)  // the features for the quad's other waves
-          *xs(3, cb) = f4{x[0][4 * cb], x[0][4 * cb + 1], x[0][4 * cb + 2], x[0][4 * cb + 3]};
+          *xs(3, cb) = f4{x[4 * cb], x[4 * cb + 1], x[4 * cb + 2], x[4 * cb + 3]};
       }
-      if constexpr (LAST && TWO) head_epilogue<C, TWO, 1>(a, x, s_h, lane, g, tr, mo_first);
+      if constexpr (LAST && TWO) head_epilogue<C, TWO>(a, x, s_h, lane, g, tr, mo_first);
     }
     if constexpr (LAST && !TWO) {
       __syncthreads();
@@ -1319,12 +1301,12 @@ __global__ void __launch_bounds__(CONV_THREADS) k_conv(ConvArgs a) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) x[4 * cb + e] = t[e];
         }
-        HeadOp<C> op[1];
-        op[0].set(x);
-        float* lo[1] = {(a.logits && tr[0].valid) ? a.logits + (tr[0].prow - mo_first) * 256 + 4 * g : nullptr};
-        float gm[1], part[1];
-        head_group<C, 1>(s_h, a.hb, a.hfac, op, lo, lane, g, gi, gm, part);
-        s_x2[(q * 4 + gi) * 64 + lane] = make_float2(gm[0], part[0]);
+        HeadOp<C> op;
+        op.set(x);
+        float* lo = (a.logits && tr.valid) ? a.logits + (tr.prow - mo_first) * 256 + 4 * g : nullptr;
+        float gm, part;
+        head_group<C>(s_h, a.hb, a.hfac, op, lo, lane, g, gi, gm, part);
+        s_x2[(q * 4 + gi) * 64 + lane] = make_float2(gm, part);
       }
       __syncthreads();
       if (has && gi == 0) {
@@ -1334,7 +1316,7 @@ __global__ void __launch_bounds__(CONV_THREADS) k_conv(ConvArgs a) {
           const float2 v = s_x2[(q * 4 + k) * 64 + lane];
           lse_merge(m, ssum, v.x, v.y);
         }
-        lse_finish(a, m, ssum, g, tr[0].valid, tr[0].prow);
+        lse_finish(a, m, ssum, g, tr.valid, tr.prow);
       }
     }
   }
@@ -1714,10 +1696,6 @@ __global__ void __launch_bounds__(256) k_top_prep5(int lo, int nsc, int n_embed,
 // Offset set of up to 128 offsets (wave-uniform).
 struct OffMask {
   uint64_t lo = 0, hi = 0;
-  __device__ __forceinline__ void set(int o) {
-    if (o < 64) lo |= 1ull << o;
-    else hi |= 1ull << (o - 64);
-  }
   __device__ __forceinline__ bool has(int o) const { return o < 64 ? (lo >> o) & 1ull : (hi >> (o - 64)) & 1ull; }
   // lowest offset, removed from the set (-1 when empty)
   __device__ __forceinline__ int pop() {
@@ -2267,11 +2245,10 @@ __global__ void __launch_bounds__((headw_threads<C, TWO>())) k_headw(ConvArgs a)
     const int64_t nvox = s_nv[si], mo = s_mo[si];
     const int64_t row = (tile - s_tpre[si]) * 16 + r;
     const bool valid = row < nvox;
-    const TileRef tr[1] = {{a.b_lo + si, mo, (int64_t)(a.b_lo + si - a.b0) * a.cap_pts,
-                            mo + (valid ? row : nvox - 1), valid}};
-    float x[1][C / 4];
-    load_row<C>(a.h_in + tr[0].prow * C, g, x[0]);
-    head_epilogue<C, TWO, 1>(a, x, s_h, lane, g, tr, s_mo[0]);
+    const TileRef tr{a.b_lo + si, mo, (int64_t)(a.b_lo + si - a.b0) * a.cap_pts, mo + (valid ? row : nvox - 1), valid};
+    float x[C / 4];
+    load_row<C>(a.h_in + tr.prow * C, g, x);
+    head_epilogue<C, TWO>(a, x, s_h, lane, g, tr, s_mo[0]);
   }
 }
 
@@ -2618,7 +2595,42 @@ hipError_t launch_pack_weights(Ctx& c, const reno_weights& w) {
   return hipGetLastError();
 }
 
-// Full predictor on the scales b_lo .. b_hi (Sec. 3.2, Eqs. 6-9):
+// What every layer and head launch of a context is given.
+static ConvArgs conv_args(const Ctx& c, bool second) {
+  ConvArgs a{};
+  a.b0 = c.b0();
+  a.count = c.d_count;
+  a.moff = c.d_moff;
+  a.cap_pts = c.cap_pts;
+  a.cap_model = c.cap_model;
+  a.nbr = c.d_nbr;
+  a.hb = c.w_hbias;
+  a.hw = reinterpret_cast<const uint4*>(c.w_head);
+  a.hfac = c.w_hfac;
+  a.hrat = c.w_hrat;
+  a.lse = c.d_lse;
+  a.emb = c.w_emb;
+  a.s1_code = second ? c.lv_code : nullptr;
+  a.lse2 = c.d_lse2;
+  a.s1_out = c.d_s1;
+  a.b_ext = -1;
+  a.cap_rows = c.cap_rows();
+  if (c.top()) {  // the base scale's rows live past the zero row
+    a.b_ext = c.b0();
+    a.ext_off = c.cap_model + 1;
+    a.emb_d = c.w_embd;
+    a.emb_o = c.w_embo;
+    a.code = c.lv_code;
+    a.fc = c.lv_fc;
+    a.xb_s = c.s_c;
+    a.xb_r = c.r_c;
+    a.xrat = c.w_xrat;
+    a.r_out = c.r_b;
+  }
+  return a;
+}
+
+// Full predictor on the scales b_lo .. b_hi (Sec. 3.2, Eqs. 6-9), after its inputs:
 //   neighbour maps of scales b_lo-1 .. b_hi, X_A = Emb_O[O^{d-1}] on scales
 //   b_lo-1 .. b_hi-1 (split rows s_c)                             one prep launch
 //   T = ReLU(conv_A1(X_A))                                        (split h_b)
@@ -2626,125 +2638,76 @@ hipError_t launch_pack_weights(Ctx& c, const reno_weights& w) {
 //   X_B = F_A[parent] + Emb_D[delta] on scales b_lo .. b_hi       (h_d, split s_c, X_A being used up; F_A itself
 //   is not stored)
 //   T = ReLU(conv_B1(X_B))                                        (split h_b)
-//   F_B = ReLU(X_B + conv_B2(T)), fused with the head             (h_a)
-// The base scale's rows live past the zero row.  F_B of earlier calls is
-// never overwritten (code lengths of a scale stay valid after the next
-// scale's call).
-hipError_t launch_top(Ctx& c, int b_lo, int b_hi, float* logits, bool second) {
-  const int b0 = c.b0();
-  const int64_t ext_off = c.cap_model + 1;
-  const RowMap rm{c.d_count, c.d_moff, (int64_t)c.cap_model, b0, ext_off, c.cap_rows()};
-  const int C = c.p.channels;
+//   F_B = ReLU(X_B + conv_B2(T)), and the head                    (h_a)
+// F_B of earlier calls is never overwritten (code lengths of a scale stay valid
+// after the next scale's call).  layer(wi, last) launches a.
+template <typename Layer>
+hipError_t top_layers(Ctx& c, ConvArgs& a, int b_lo, int b_hi, Layer layer) {
   const int n_lo = b_lo - 1;  // stage A runs one scale below stage B
-  {
-    ProfScope ps_(c, RENO_K_TOP_INPUT);
-    const int blocks = (int)std::min<int64_t>(2048, (c.cap_rows() + 63) / 64);
-#define RENO_PREP(CC)                                                                                         \
-  hipLaunchKernelGGL((k_top_prep<CC, false>), dim3(blocks), dim3(256), 0, c.stream, n_lo, b_hi - n_lo + 1,      \
-                     b_hi - n_lo, b0, rm, c.lv_key, c.lv_code, (int64_t)c.cap_pts, cell_args(c), embed_tab(c), \
-                     c.d_nbr, c.s_c, c.r_c)
-    if (C == 32) RENO_PREP(32); else RENO_PREP(16);
-#undef RENO_PREP
-  }
-  ConvArgs a{};
-  a.b0 = b0;
-  a.count = c.d_count;
-  a.moff = c.d_moff;
-  a.cap_pts = c.cap_pts;
-  a.cap_model = c.cap_model;
-  a.nbr = c.d_nbr;
-  a.hb = c.w_hbias;
-  a.hw = reinterpret_cast<const uint4*>(c.w_head);
-  a.hfac = c.w_hfac;
-  a.hrat = c.w_hrat;
-  a.lse = c.d_lse;
-  a.err = c.d_err;
-  a.emb = c.w_emb;
-  a.s1_code = second ? c.lv_code : nullptr;
-  a.lse2 = c.d_lse2;
-  a.s1_out = c.d_s1;
-  a.b_ext = b0;
-  a.ext_off = ext_off;
-  a.cap_rows = c.cap_rows();
-  a.emb_d = c.w_embd;
-  a.emb_o = c.w_embo;
-  a.code = c.lv_code;
-  a.fc = c.lv_fc;
-  const bool two = c.p.head_mode == RENO_HEAD_TWO_STAGE;
   hipError_t e = hipSuccess;
-  auto conv = [&](int lo, int hi, int wi, const void* in, const float* r_in, float* out, const float* res, float* xb,
-                  bool last) {
+  auto conv = [&](int lo, int hi, int wi, const void* in, const float* r_in, float* out, float* s_out, const float* res,
+                  float* xb) {
     if (e != hipSuccess) return;
     a.b_lo = lo;
     a.b_hi = hi;
     a.h_in = static_cast<const float*>(in);
     a.r_in = r_in;
-    a.h_out = last ? out : nullptr;
-    a.s_out = last ? nullptr : reinterpret_cast<uint32_t*>(out);
-    a.r_out = c.r_b;
+    a.h_out = out;
+    a.s_out = reinterpret_cast<uint32_t*>(s_out);
     a.res = res;
     a.xb = xb;
-    a.xb_s = c.s_c;
-    a.xb_r = c.r_c;
     a.w = c.w_conv[wi];
     a.wfac = c.wfac(wi);
-    a.xrat = c.w_xrat;
     a.bias = c.w_bias[wi];
-    a.logits = last ? logits : nullptr;
-    ProfScope ps_(c, last ? RENO_K_CONV_LAST : RENO_K_CONV_MID);
-    e = (C == 32) ? run_layer<32>(c, last, two, a) : run_layer<16>(c, last, two, a);
+    e = layer(wi, wi == 3);
   };
-  conv(n_lo, b_hi - 1, 0, c.s_c, c.r_c, c.h_b, nullptr, nullptr, false);
-  conv(n_lo, b_hi - 1, 1, c.h_b, c.r_b, nullptr, nullptr, c.h_d, false);
-  conv(b_lo, b_hi, 2, c.s_c, c.r_c, c.h_b, nullptr, nullptr, false);
-  conv(b_lo, b_hi, 3, c.h_b, c.r_b, c.h_a, c.h_d, nullptr, true);
-  return e == hipSuccess ? hipGetLastError() : e;
+  conv(n_lo, b_hi - 1, 0, c.s_c, c.r_c, nullptr, c.h_b, nullptr, nullptr);
+  conv(n_lo, b_hi - 1, 1, c.h_b, c.r_b, nullptr, nullptr, nullptr, c.h_d);
+  conv(b_lo, b_hi, 2, c.s_c, c.r_c, nullptr, c.h_b, nullptr, nullptr);
+  conv(b_lo, b_hi, 3, c.h_b, c.r_b, c.h_a, nullptr, c.h_d, nullptr);
+  return e;
 }
 
-// Full predictor with streamed weights (5x5x5 kernels or C above 32): the
-// steps of launch_top on k_convw and a separate head launch.
-template <int C, int KV>
-hipError_t launch_top_wide(Ctx& c, int b_lo, int b_hi, float* logits, bool second) {
-  const int b0 = c.b0();
-  const int64_t ext_off = c.cap_model + 1;
-  const RowMap rm{c.d_count, c.d_moff, (int64_t)c.cap_model, b0, ext_off, c.cap_rows()};
-  const int n_lo = b_lo - 1;
+hipError_t launch_top(Ctx& c, int b_lo, int b_hi, float* logits, bool second) {
+  const int b0 = c.b0(), n_lo = b_lo - 1;
+  ConvArgs a = conv_args(c, second);
+  const RowMap rm{a.count, a.moff, a.cap_model, a.b_ext, a.ext_off, a.cap_rows};
+  const bool c32 = c.p.channels == 32, two = c.p.head_mode == RENO_HEAD_TWO_STAGE;
   {
     ProfScope ps_(c, RENO_K_TOP_INPUT);
     const int blocks = (int)std::min<int64_t>(2048, (c.cap_rows() + 63) / 64);
-    if (KV == 125)
-      hipLaunchKernelGGL(k_top_prep5<C>, dim3(blocks), dim3(256), 0, c.stream, n_lo, b_hi - n_lo + 1, b_hi - n_lo,
-                         b0, rm, c.lv_key, c.lv_code, (int64_t)c.cap_pts, cell_args(c), embed_tab(c),
-                         c.d_nbr, c.s_c, c.r_c);
-    else
-      hipLaunchKernelGGL((k_top_prep<C, true>), dim3(blocks), dim3(256), 0, c.stream, n_lo, b_hi - n_lo + 1,
-                         b_hi - n_lo, b0, rm, c.lv_key, c.lv_code, (int64_t)c.cap_pts, cell_args(c), embed_tab(c),
-                         c.d_nbr, c.s_c, c.r_c);
+    auto go = [&](auto kern) {
+      hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), 0, c.stream, n_lo, b_hi - n_lo + 1, b_hi - n_lo, b0, rm,
+                         c.lv_key, c.lv_code, (int64_t)c.cap_pts, cell_args(c), embed_tab(c), c.d_nbr, c.s_c, c.r_c);
+    };
+    if (c32) go(k_top_prep<32, false>);
+    else go(k_top_prep<16, false>);
   }
-  ConvArgs a{};
-  a.b0 = b0;
-  a.count = c.d_count;
-  a.moff = c.d_moff;
-  a.cap_pts = c.cap_pts;
-  a.cap_model = c.cap_model;
-  a.nbr = c.d_nbr;
-  a.hb = c.w_hbias;
-  a.hw = reinterpret_cast<const uint4*>(c.w_head);
-  a.hfac = c.w_hfac;
-  a.hrat = c.w_hrat;
-  a.lse = c.d_lse;
-  a.err = c.d_err;
-  a.emb = c.w_emb;
-  a.s1_code = second ? c.lv_code : nullptr;
-  a.lse2 = c.d_lse2;
-  a.s1_out = c.d_s1;
-  a.b_ext = b0;
-  a.ext_off = ext_off;
-  a.cap_rows = c.cap_rows();
-  a.emb_d = c.w_embd;
-  a.emb_o = c.w_embo;
-  a.code = c.lv_code;
-  a.fc = c.lv_fc;
+  const hipError_t e = top_layers(c, a, b_lo, b_hi, [&](int, bool last) {  // the head fused with the last one
+    a.logits = last ? logits : nullptr;
+    ProfScope ps_(c, last ? RENO_K_CONV_LAST : RENO_K_CONV_MID);
+    return c32 ? run_layer<32>(c, last, two, a) : run_layer<16>(c, last, two, a);
+  });
+  return e == hipSuccess ? hipGetLastError() : e;
+}
+
+// Full predictor with streamed weights (5x5x5 kernels or C above 32): the same
+// layers on k_convw and a separate head launch.
+template <int C, int KV>
+hipError_t launch_top_wide(Ctx& c, int b_lo, int b_hi, float* logits, bool second) {
+  const int b0 = c.b0(), n_lo = b_lo - 1;
+  ConvArgs a = conv_args(c, second);
+  const RowMap rm{a.count, a.moff, a.cap_model, a.b_ext, a.ext_off, a.cap_rows};
+  {
+    ProfScope ps_(c, RENO_K_TOP_INPUT);
+    const int blocks = (int)std::min<int64_t>(2048, (c.cap_rows() + 63) / 64);
+    auto go = [&](auto kern) {
+      hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), 0, c.stream, n_lo, b_hi - n_lo + 1, b_hi - n_lo, b0, rm,
+                         c.lv_key, c.lv_code, (int64_t)c.cap_pts, cell_args(c), embed_tab(c), c.d_nbr, c.s_c, c.r_c);
+    };
+    if constexpr (KV == 125) go(k_top_prep5<C>);
+    else go(k_top_prep<C, true>);
+  }
   {  // tiles of voxels with similar neighbourhoods: smaller offset unions per tile and group
     ProfScope pso_(c, RENO_K_OTHER);
     const int nsc = b_hi - n_lo + 1;
@@ -2753,46 +2716,21 @@ hipError_t launch_top_wide(Ctx& c, int b_lo, int b_hi, float* logits, bool secon
                        KV == 125 ? 5 : 3, c.d_nbr, c.d_perm, c.d_next);
     a.perm = c.d_perm;
   }
-  const bool two = c.p.head_mode == RENO_HEAD_TWO_STAGE;
-  hipError_t e = hipSuccess;
-  auto conv = [&](int lo, int hi, int wi, const void* in, const float* r_in, float* out, const float* res, float* xb,
-                  bool last) {
-    if (e != hipSuccess) return;
-    a.b_lo = lo;
-    a.b_hi = hi;
-    a.h_in = static_cast<const float*>(in);
-    a.r_in = r_in;
-    a.h_out = last ? out : nullptr;
-    a.s_out = last ? nullptr : reinterpret_cast<uint32_t*>(out);
-    a.r_out = c.r_b;
-    a.res = res;
-    a.xb = xb;
-    a.xb_s = c.s_c;
-    a.xb_r = c.r_c;
-    a.w = c.w_conv[wi];
-    a.wfac = c.wfac(wi);
-    a.xrat = c.w_xrat;
-    a.bias = c.w_bias[wi];
+  hipError_t e = top_layers(c, a, b_lo, b_hi, [&](int wi, bool) {
     a.next = c.d_next + 8 * wi;
     ProfScope ps_(c, RENO_K_CONV_MID);
-    if (xb)
+    if (a.xb)
       hipLaunchKernelGGL((k_convw<C, KV, true>), dim3(cw_blocks(C)), dim3(64 * cw_waves(C)), 0, c.stream, a);
     else
       hipLaunchKernelGGL((k_convw<C, KV, false>), dim3(cw_blocks(C)), dim3(64 * cw_waves(C)), 0, c.stream, a);
-    e = hipGetLastError();
-  };
-  conv(n_lo, b_hi - 1, 0, c.s_c, c.r_c, c.h_b, nullptr, nullptr, false);
-  conv(n_lo, b_hi - 1, 1, c.h_b, c.r_b, nullptr, nullptr, c.h_d, false);
-  conv(b_lo, b_hi, 2, c.s_c, c.r_c, c.h_b, nullptr, nullptr, false);
-  conv(b_lo, b_hi, 3, c.h_b, c.r_b, c.h_a, c.h_d, nullptr, true);
+    return hipGetLastError();
+  });
   if (e != hipSuccess) return e;
   {
     ProfScope ps_(c, RENO_K_CONV_LAST);
-    a.b_lo = b_lo;
-    a.b_hi = b_hi;
     a.h_in = c.h_a;
     a.logits = logits;
-    e = run_headw<C>(c, two, a);
+    e = run_headw<C>(c, c.p.head_mode == RENO_HEAD_TWO_STAGE, a);
   }
   if (e != hipSuccess) return e;
   return hipGetLastError();
@@ -2814,30 +2752,12 @@ hipError_t launch_top_wide_any(Ctx& c, int b_lo, int b_hi, float* logits, bool s
 
 hipError_t launch_model(Ctx& c, int b_lo, int b_hi, float* logits, bool second) {
   if (c.wide()) return launch_top_wide_any(c, b_lo, b_hi, logits, second);
-  if (c.p.model_mode == RENO_MODEL_TOP) return launch_top(c, b_lo, b_hi, logits, second);
-  ConvArgs a{};
+  if (c.top()) return launch_top(c, b_lo, b_hi, logits, second);
+  ConvArgs a = conv_args(c, second);
   a.b_lo = b_lo;
   a.b_hi = b_hi;
-  a.b0 = c.b0();
-  a.count = c.d_count;
-  a.moff = c.d_moff;
-  a.cap_pts = c.cap_pts;
-  a.cap_model = c.cap_model;
-  a.nbr = c.d_nbr;
-  a.hb = c.w_hbias;
-  a.hw = reinterpret_cast<const uint4*>(c.w_head);
-  a.hfac = c.w_hfac;
-  a.hrat = c.w_hrat;
-  a.lse = c.d_lse;
-  a.err = c.d_err;
-  a.emb = c.w_emb;
-  a.s1_code = second ? c.lv_code : nullptr;
-  a.lse2 = c.d_lse2;
-  a.s1_out = c.d_s1;
   const bool two = c.p.head_mode == RENO_HEAD_TWO_STAGE;
   const int L = c.p.layers;
-  a.b_ext = -1;
-  a.cap_rows = c.cap_rows();
   const RowMap rm{c.d_count, c.d_moff, (int64_t)c.cap_model, -1, 0, c.cap_rows()};
   const bool c32 = c.p.channels == 32;
   hipError_t e = hipSuccess;
