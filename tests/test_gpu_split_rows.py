@@ -206,16 +206,25 @@ def test_all_zero_layer():
     _check(_run(pts, B, b0, R, C, 3, w), pts, B, b0, R, w)
 
 
-def test_infinite_features_stay_infinite():
-    """A feature overflow (a finite weight times its count beyond fp32) reaches the logits as non-finite values, as
-    in fp32 arithmetic; other voxels are untouched."""
-    B, b0, R, C = 6, 4, 10.0, 32
-    pts = _cloud(40, B, R, 1)
+def test_features_that_overflow_are_infinite():
+    """A finite weight of 3e38 on one bit of the parent's code, doubled by the next layer: every voxel with a neighbour
+    (or itself) of that bit gets infinite logits, as in fp32 arithmetic; the others are untouched, bit for bit."""
+    B, b0, R, C, bit = 6, 4, 10.0, 32, 0
+    pts = _cloud(60, B, R, 1)
     w = gen_weights(C, 2, seed=4, bias_std=0.1)
-    w["conv_b"][0][3] = np.float32(np.inf)
-    say("split rows, infinite feature")
-    lg = _run(pts, B, b0, R, C, 2, w)
-    assert not np.isfinite(lg).any(axis=1).all() and np.isinf(lg).any()
+    w["conv_w"][1][:, 5] = 2.0                              # channel 5 feeds every output through every offset
+    w["head_w"] = np.abs(w["head_w"]) + np.float32(1e-3)    # no sign cancels an infinite feature
+    P = oracle.Pyramid.from_points(pts, B, b0, R)
+    hot = (P.codes(b0)[P.parent(b0 + 1)] >> bit & 1) == 1
+    hit = np.array([any(n >= 0 and hot[n] for n in row) for row in P.neighbors(b0 + 1)])
+    assert 0 < hot.sum() < hit.sum() < len(hit)
+    lg = []
+    for big in (0.0, 3e38):
+        w["conv_w"][0][13, 3 + bit, 5] = big                # the voxel's own cell (centre offset)
+        say("split rows, weight", big)
+        lg.append(_run(pts, B, b0, R, C, 2, w))
+    assert np.isposinf(lg[1][hit]).all() and np.isfinite(lg[0]).all()
+    np.testing.assert_array_equal(lg[1][~hit], lg[0][~hit])
 
 
 @pytest.mark.parametrize("C,two", [(16, False), (32, False), (32, True)])
