@@ -27,8 +27,10 @@ import numpy as np
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-PEAK_FP32_MFMA_TFLOPS = 157.3
-PEAK_BF16_MFMA_TFLOPS = 2500.0
+# dense 16-bit matrix rate; an fp32 product of the conv layers and heads is
+# three fp16 MFMA products (hi*hi, hi*lo, lo*hi)
+PEAK_FP16_MFMA_TFLOPS = 2500.0
+PEAK_SPLIT_TFLOPS = round(PEAK_FP16_MFMA_TFLOPS / 3, 1)
 PEAK_HBM_GBS = 8000.0
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "conv_last_traffic_hdl64_b14.txt")
 TRACE_FILE = os.path.join(ROOT, "profiles", "conv_last_headline_trace_hdl64_b14.txt")
@@ -40,6 +42,18 @@ MAP_ROW_BYTES = 4 * 27
 STREAM_SYMBOLS = 1024  # whole-frame coding: symbols per rANS stream
 
 
+def hashed_voxels(N, b0, B):
+    """Voxels of the scales in the coordinate hash (dev.h hashed_scale)."""
+    return sum(N[b] for b in range(b0, B) if b + 2 < B or (b == b0 and b + 1 < B))
+
+
+def cell_bytes(N, b0, b):
+    """Bytes behind the first layer's cell search on scale b: the parent
+    scale's codes and first children and the hash slots of its parents, or the
+    base scale's own slots."""
+    return 16 * N[b0] if b - 1 == b0 else 16 * N[b - 2] + 5 * N[b - 1]
+
+
 def alg_bytes_per_frame(counts, b0, B, M, C, hash_slots, status_words):
     """Minimum HBM bytes per frame (encoder + decoder) of each kernel kind:
     every input read once, every output written once.  Gathers of
@@ -48,9 +62,9 @@ def alg_bytes_per_frame(counts, b0, B, M, C, hash_slots, status_words):
     N = {b0 + i: n for i, n in enumerate(counts)}
     model = [b for b in range(b0 + 1, B)]
     nm = sum(N[b] for b in model)
-    parents_hashed = sum(N[b] for b in range(b0, B - 1))
+    hashed = hashed_voxels(N, b0, B)
     passes = (3 * B + 7) // 8
-    row = 4 * C
+    row, split_row = 4 * C, 4 * C + 4  # fp32 row; split row and its factor
     out = {}
     clear = 16 * hash_slots + 4 * status_words
     # the decoder clears its frame in the launch that writes a base scale of
@@ -60,20 +74,19 @@ def alg_bytes_per_frame(counts, b0, B, M, C, hash_slots, status_words):
     out["quantize"] = M * (12 + 8)
     out["sort"] = passes * M * 16
     out["pyramid"] = M * 8 + sum(N[b] * 12 for b in range(b0, B + 1)) + sum(N[b] * 4 for b in range(b0, B))
-    # codes: child keys read, codes + child feature words written, parents hashed
-    out["codes"] = sum(N[b + 1] * (8 + 2) + N[b] for b in range(b0, B)) + 16 * parents_hashed
+    # codes: child keys read, codes written, voxels of the hashed scales inserted
+    out["codes"] = sum(N[b + 1] * 8 + N[b] for b in range(b0, B)) + 16 * hashed
     out["set_base"] = N[b0] * (12 + 1 + 8) + (clear if dec_clear_in_base else 0)
-    # expand: parent key + code read; child key, parent row, feature word and the
-    # parent's first-child row written; parents hashed
-    out["expand"] = sum(N[b] * (8 + 1 + 4) + N[b + 1] * (8 + 4 + 2) for b in range(b0, B)) + \
-        16 * parents_hashed
-    # conv layers (encoder + decoder): first reads keys, parent slots and feature
-    # words, writes the neighbour map and h; later layers read map + h, write h
-    first = sum(N[b] * (8 + 2 + MAP_ROW_BYTES + row) + 16 * N[b - 1] for b in model)
-    mid = nm * (MAP_ROW_BYTES + 2 * row)
+    # expand: parent key + code read; child key, parent row and the parent's
+    # first-child row written; voxels of the hashed scales inserted
+    out["expand"] = sum(N[b] * (8 + 1 + 4) + N[b + 1] * (8 + 4) for b in range(b0, B)) + 16 * hashed
+    # conv layers (encoder + decoder): the first reads keys and cells, writes the
+    # neighbour map and split rows; later layers read map + split rows, write
+    # split rows, the last one fp32 rows and the normaliser
+    first = sum(N[b] * (8 + MAP_ROW_BYTES + split_row) + cell_bytes(N, b0, b) for b in model)
     out["conv_first"] = 2 * first
-    out["conv_mid"] = 2 * mid
-    out["conv_last"] = 2 * (mid + nm * 4)
+    out["conv_mid"] = 2 * nm * (MAP_ROW_BYTES + 2 * split_row)
+    out["conv_last"] = 2 * nm * (MAP_ROW_BYTES + split_row + row + 4)
     out["code_length"] = 2 * nm * (1 + 4 + row)
     return out
 
@@ -87,17 +100,16 @@ def alg_bytes_encoder(counts, b0, B, M, C, hash_slots, status_words, fb):
     N = {b0 + i: n for i, n in enumerate(counts)}
     model = [b for b in range(b0 + 1, B)]
     nm = sum(N[b] for b in model)
-    parents_hashed = sum(N[b] for b in range(b0, B - 1))
-    row = 4 * C
+    row, split_row = 4 * C, 4 * C + 4
     return {
         "zero": 16 * hash_slots + 4 * status_words,
         "quantize": M * (12 + 8),
         "sort": M * 16,
         "pyramid": M * 8 + sum(N[b] * 12 for b in range(b0, B + 1)) + sum(N[b] * 4 for b in range(b0, B)),
-        "codes": sum(N[b + 1] * (8 + 2) + N[b] for b in range(b0, B)) + 16 * parents_hashed,
-        "conv_first": sum(N[b] * (8 + 2 + MAP_ROW_BYTES + row) + 16 * N[b - 1] for b in model),
-        "conv_mid": nm * (MAP_ROW_BYTES + 2 * row),
-        "conv_last": nm * (MAP_ROW_BYTES + 2 * row) + nm * 4,
+        "codes": sum(N[b + 1] * 8 + N[b] for b in range(b0, B)) + 16 * hashed_voxels(N, b0, B),
+        "conv_first": sum(N[b] * (8 + MAP_ROW_BYTES + split_row) + cell_bytes(N, b0, b) for b in model),
+        "conv_mid": nm * (MAP_ROW_BYTES + 2 * split_row),
+        "conv_last": nm * (MAP_ROW_BYTES + split_row + row + 4),
         "code_length": nm * (1 + 4 + row),
     }
 
@@ -523,11 +535,7 @@ def run_stress(args, reno, torch, dev, stream, copy_peak=None):
     skinds = ["zero", "quantize", "sort", "pyramid", "codes", "conv_first", "conv_mid", "conv_last",
               "code_length", "other"]
     ks = [int(x) for x in args.stress.split(",") if x]
-    # every K in fp32, and the largest K again with the split-bf16 contraction
-    # (about 5x less MFMA time per product than fp32), where the conv layers
-    # are no longer bound by the contraction and the gather shows its own rate
-    runs = [(K, reno.RENO_PREC_FP32) for K in ks] + ([(max(ks), reno.RENO_PREC_BF16X3)] if ks else [])
-    for K, prec in runs:
+    for K in ks:
         sel = [sframes[i % len(sframes)] for i in range(K)]
         start = np.cumsum([0] + [f.shape[0] for f in sel]).astype(np.int64)
         SM = int(start[-1])
@@ -537,8 +545,7 @@ def run_stress(args, reno, torch, dev, stream, copy_peak=None):
         st_d = torch.from_numpy(start).to(dev)
         del sel
         with torch.cuda.stream(stream):
-            sc = reno.Context(SM, sB, sb0, scfg.range_m, sC, sL, max_model_voxels=cap, stream=stream,
-                              precision=prec)
+            sc = reno.Context(SM, sB, sb0, scfg.range_m, sC, sL, max_model_voxels=cap, stream=stream)
             sc.set_weights(sw)
 
             def enc():
@@ -589,7 +596,7 @@ def run_stress(args, reno, torch, dev, stream, copy_peak=None):
                 if copy_peak:
                     e["pass_hbm_frac_of_copy"] = round(pgbs / copy_peak, 4)
             kinds_out[k] = e
-        run = {"K": K, "precision": "fp32" if prec == reno.RENO_PREC_FP32 else "bf16x3",
+        run = {"K": K, "precision": "fp32",
                "points": SM, "voxels": int(sum(cnt)), "model_rows_capacity": cap,
                "device_bytes": smem["device_bytes"], "encoder_ms_per_batch": round(ms, 4),
                "encoder_frames_per_s": round(K * 1000.0 / ms, 1), "kinds": kinds_out}
@@ -602,7 +609,7 @@ def run_stress(args, reno, torch, dev, stream, copy_peak=None):
         torch.cuda.empty_cache()
     stress["note"] = ("hbm_frac = algorithmic bytes (each input read once, each output written once) / "
                       "kernel time / 8 TB/s (hbm_frac_of_copy: / the measured device copy rate); sort = all LSD passes (pass_* count every pass's read + write), "
-                      "codes = code words + hash build, conv_first = hash probes + first-layer gather, "
+                      "codes = code words + hash build, conv_first = cell search + table rows, "
                       "conv_mid = neighbour-row gather")
 
     return stress
@@ -617,7 +624,7 @@ def main():
     ap.add_argument("--mode", choices=["graph", "eager"], default="graph")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-two-stage", action="store_true", help="skip the two-stage head measurement")
-    ap.add_argument("--no-bf16x3", action="store_true", help="skip the split-bf16 precision measurement")
+    ap.add_argument("--no-bf16x3", action="store_true", help="accepted and ignored: that precision setting runs the fp32 kernels")
     ap.add_argument("--no-top", action="store_true", help="skip the full-predictor measurement")
     ap.add_argument("--stress-only", action="store_true",
                     help="run only the HBM stress pass and print its JSON (for counter runs)")
@@ -759,29 +766,9 @@ def main():
                "steps": st, "bits_per_point": round(ts.enc_total / M, 4),
                "conv_last_avg_launch_us": round(1000 * cl2_ms / cl2_n, 2),
                "conv_last_achieved_tflops": round(tf2, 3),
-               "conv_last_frac": round(tf2 / PEAK_FP32_MFMA_TFLOPS, 4)}
+               "conv_last_frac": round(tf2 / PEAK_SPLIT_TFLOPS, 4)}
         log("two-stage head", two)
         ts.close()
-
-    # ---- split-bf16 precision (bf16 hi + lo operands, three bf16 MFMA products
-    # per fp32 product), same frame and weights ----
-    bfx = None
-    if not args.no_bf16x3:
-        bc = Codec(reno, torch, cfg, pts, M, cap_model, stream, w_np, two_stage=False,
-                   precision=reno.RENO_PREC_BF16X3)
-        st = max(args.steps // 2, 1)
-        msb = bc.time(st, args.warmup, args.mode)
-        clb_ms, clb_n = bc.profile_conv_last(st)
-        tfb = bc.conv_last_flops(counts) * st / (clb_ms * 1e-3) / 1e12
-        bfx = {"value": round(1000.0 / msb, 2), "unit": "frames/s", "ms_per_step": round(msb, 5),
-               "steps": st, "dtype": "bf16x3 (fp32 accumulate)",
-               "bits_per_point": round(bc.enc_total / M, 4),
-               "bits_rel_diff_vs_fp32": abs(bc.enc_total - enc_total) / enc_total,
-               "conv_last_avg_launch_us": round(1000 * clb_ms / clb_n, 2),
-               "conv_last_achieved_tflops": round(tfb, 3),
-               "conv_last_frac_of_bf16_peak": round(tfb / PEAK_BF16_MFMA_TFLOPS, 4)}
-        log("bf16x3", bfx)
-        bc.close()
 
     # ---- the full target occupancy predictor (occupancy embedding and a
     # residual block on the parent scale, replication + octant embedding and a
@@ -810,7 +797,7 @@ def main():
                           "steps": st, "bits_per_point": round(tc.enc_total / M, 4),
                           "conv_last_avg_launch_us": round(1000 * clt_ms / clt_n, 2),
                           "conv_last_achieved_tflops": round(tft, 3),
-                          "conv_last_frac": round(tft / PEAK_FP32_MFMA_TFLOPS, 4),
+                          "conv_last_frac": round(tft / PEAK_SPLIT_TFLOPS, 4),
                           "us_per_frame_by_kind": kinds_us}
             log("full predictor", name, topm[name])
             tc.close()
@@ -843,7 +830,7 @@ def main():
             "bits_per_point": round(lc.enc_total / M, 4), "us_per_frame_by_kind": lk_us,
             "conv_alg_gflop_per_frame": round(conv_flops / 1e9, 2),
             "conv_achieved_tflops": round(conv_flops / (conv_us * 1e-6) / 1e12, 2) if conv_us else None,
-            "conv_frac": round(conv_flops / (conv_us * 1e-6) / 1e12 / PEAK_FP32_MFMA_TFLOPS, 4) if conv_us else None,
+            "conv_frac": round(conv_flops / (conv_us * 1e-6) / 1e12 / PEAK_SPLIT_TFLOPS, 4) if conv_us else None,
             "paper_context_s": "RENO-L NN 0.184 s per 14-bit frame, encoder, RTX 4090 (Table S2)"}
         log("full predictor large", topm["large_c128_k5_two_stage"])
         lc.close()
@@ -1005,7 +992,7 @@ def main():
     flops_launch = one.conv_last_flops(counts) / (cl_launches / args.steps)
     frac_trace = None
     if trace is not None:
-        frac_trace = round(flops_launch / (trace[0] * 1e-6) / 1e12 / PEAK_FP32_MFMA_TFLOPS, 4)
+        frac_trace = round(flops_launch / (trace[0] * 1e-6) / 1e12 / PEAK_SPLIT_TFLOPS, 4)
     out = {
         "metric": "frames/s + Mvoxels/s, encode+decode model path, 14-bit 64-beam scan; bits/pt",
         "value": round(fps, 2),
@@ -1033,8 +1020,9 @@ def main():
                    "device_bytes_per_context": mem["device_bytes"],
                    "mode": args.mode},
         "roofline": {"bound": "mfma", "kernel": "conv_last (last sparse conv + 256-way head)",
-                     "achieved": round(achieved_tflops, 3), "peak": PEAK_FP32_MFMA_TFLOPS,
-                     "unit": "TFLOP/s", "frac": round(achieved_tflops / PEAK_FP32_MFMA_TFLOPS, 4),
+                     "achieved": round(achieved_tflops, 3), "peak": PEAK_SPLIT_TFLOPS,
+                     "unit": "TFLOP/s", "frac": round(achieved_tflops / PEAK_SPLIT_TFLOPS, 4),
+                     "peak_is": "dense fp16 MFMA, 2500 TFLOP/s, over three fp16 products per fp32 product",
                      "traffic": traffic,
                      "avg_launch_us": round(1000 * cl_ms / cl_launches, 2),
                      "launches": cl_launches,
@@ -1049,7 +1037,7 @@ def main():
         "cpu_baseline": cpu,
         "kernels": breakdown,
         "two_stage_head": two,
-        "precision_bf16x3": bfx,
+        "precision_bf16x3": "the same kernels and bits as fp32",
         "full_predictor": topm,
         "hbm_stress": stress,
         "end_to_end": e2e,
