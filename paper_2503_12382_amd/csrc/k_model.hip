@@ -924,17 +924,16 @@ __device__ __forceinline__ float buf_load4(__amdgpu_buffer_rsrc_t rs, uint32_t o
 // before the products of the current ones.  Each offset's products are chained
 // on MFMA from zero and added with the neighbour row's factor by one fma.
 //
-// What bounds it (counters of the 14-bit scan's middle layer): the L1 access
-// rate and the LDS.  In the operand's layout 16 consecutive lanes name 16 rows,
-// so a gather costs one L1 access per lane: with both planes and the factor
-// loaded that way, 28 M accesses, the L1 was busy for most of the launch (57
-// us).  Absent rows (60 % of those named) are therefore out-of-range buffer
-// loads, which return zeros without an access and, unlike skipped loads, keep
-// the compiler's wait counts exact; and the hi plane goes through 4 lane
-// exchanges (LDS) instead.  Exchanging both planes moves the bound to the LDS,
-// none back to the L1: 47 and 50 us against 43.  8 waves with 8 to 16 rows
-// gathered ahead each: 54 us.  Tiles sorted by neighbourhood, which halved the
-// fp32 MFMA work, no longer pay for their pass.
+// What bounds it (the 14-bit scan's middle layer, all scales in one launch): the
+// L1 access rate and the LDS.  In the operand's layout 16 consecutive lanes name 16
+// rows, so a gather costs one L1 access per lane: with both planes and the factor
+// loaded that way, 28 M accesses, 57 us.  Absent rows (60 % of those named) are
+// therefore out-of-range buffer loads, which return zeros without an access and,
+// unlike skipped loads, keep the compiler's wait counts exact; and the hi plane
+// goes through 4 lane exchanges (LDS) instead: 11.5 M accesses, 43 us.  Exchanging
+// both planes moves the bound to the LDS, none back to the L1: 47 and 50 us.  8
+// waves with 8 to 16 rows gathered ahead each: 54 us.  Tiles sorted by
+// neighbourhood, which halved the fp32 MFMA work, no longer pay for their pass.
 //
 // BIG: a scale may hold more than CONV_BUF_ROWS rows (4 GB); rows are then
 // read through 64-bit addresses and absent ones from the zero row.
@@ -2029,7 +2028,8 @@ __device__ __forceinline__ void convw_split(const ConvArgs& a, const WideScales&
 // do not depend on the grouping.
 //
 // A 5x5x5 layer at C = 128 is bound by the weights' way from memory (8 MB do
-// not stay in a 4 MB L2), so its groups are as large as the waves of a CU allow,
+// not stay in a 4 MB L2: half of the lines miss, 3.7 GB a layer of the 64-beam
+// scan's encoder launch), so its groups are as large as the waves of a CU allow,
 // 16 tiles on 16 waves; with 8 waves of twice the registers and the rows gathered
 // ahead into a second set it took 2.0 ms instead of 1.55 (64-beam scan at 14 bits,
 // mean of the layers; 4.2 ms on fp32 MFMA).  128 registers a wave hold a tile's
