@@ -263,8 +263,9 @@ __global__ void __launch_bounds__(64) k_head_max(const float* __restrict__ H, in
 // 256 symbols whose largest weights lie within 2^8 of each other share the factor
 // of the largest: a symbol's entries down to 2^-9 of its own largest keep their 22
 // bits, and a logit's smaller terms an absolute 2^-32 of the largest one.  Where
-// they do, fac_out[256] is that factor, else 0: one factor instead of a load and
-// four products per block takes the 256-way head's launch from 65 to 62 us.
+// they do, fac_out[256] is that factor, else 0.  With the factors read per symbol
+// always (and rows balanced as they are split) the logits of the 14-bit scan took
+// 180 us, with one factor (and balance folded into the weights) 170.
 __global__ void __launch_bounds__(256) k_pack_head(const float* __restrict__ H, int C, int NS,
                                                    const float* __restrict__ bal, const float* __restrict__ smax,
                                                    uint16_t* __restrict__ out, float* __restrict__ fac_out) {
@@ -2034,7 +2035,8 @@ __device__ __forceinline__ void convw_split(const ConvArgs& a, const WideScales&
 // ahead into a second set it took 2.0 ms instead of 1.55 (64-beam scan at 14 bits,
 // mean of the layers; 4.2 ms on fp32 MFMA).  128 registers a wave hold a tile's
 // sums and rows at C = 128 with little to spare: a few values of the opening and
-// the epilogue go through scratch (52 to 80 bytes a lane; none at C <= 64).
+// the epilogue go through scratch (52 to 104 bytes a lane; at C = 64 up to 20 in
+// the layer that feeds the children).
 // Groups differ in their offsets (27 to 125), so blocks take them first come,
 // first served, their own XCD's share before the others' (2.33 -> 2.0 ms in the
 // 8-wave form).
