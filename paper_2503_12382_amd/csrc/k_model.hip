@@ -1841,6 +1841,14 @@ __device__ __forceinline__ int opaque(int v) {
   return v;
 }
 
+// The lane, formed anew: in the staged walk over the offsets, whose registers are
+// full at C = 128, a lane index kept across an offset went through scratch.
+__device__ __forceinline__ int lane_now() {
+  int l;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+  return l;
+}
+
 __device__ __forceinline__ uint64_t uniform64(uint64_t v) {
   const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
   const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
@@ -2035,8 +2043,9 @@ __device__ __forceinline__ void convw_split(const ConvArgs& a, const WideScales&
 // ahead into a second set it took 2.0 ms instead of 1.55 (64-beam scan at 14 bits,
 // mean of the layers; 4.2 ms on fp32 MFMA).  128 registers a wave hold a tile's
 // sums and rows at C = 128 with little to spare: a few values of the opening and
-// the epilogue go through scratch (52 to 104 bytes a lane; at C = 64 up to 20 in
-// the layer that feeds the children).
+// the epilogue go through scratch (52 to 104 bytes a lane; at C = 64 up to 12 in
+// the layer that feeds the children), none of the walk: one lane index reloaded for
+// each gather cost 8 % of the encoder's launch, for it waits for all loads in flight.
 // Groups differ in their offsets (27 to 125), so blocks take them first come,
 // first served, their own XCD's share before the others' (2.33 -> 2.0 ms in the
 // 8-wave form).
@@ -2124,7 +2133,7 @@ __global__ void __launch_bounds__(64 * cw_waves(C), 4) k_convw(ConvArgs a) {
     // before into the same registers
     const int32_t* maprow = a.nbr + tr.prow * S::NBS;
     auto entry = [&](int k) -> int32_t { return (k >= 0 && have) ? maprow[k] : -1; };
-    auto gather = [&](int32_t nn) { xa.load(a, tr.valid && nn >= 0 ? tr.mo + nn : -1, g); };
+    auto gather = [&](int32_t nn) { xa.load(a, tr.valid && nn >= 0 ? tr.mo + nn : -1, lane_now() >> 4); };
     f4 acc[NCB];
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) acc[cb] = f4{0.0f, 0.0f, 0.0f, 0.0f};
