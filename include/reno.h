@@ -77,7 +77,9 @@ typedef enum {
                                    multiplied by it.  A product x_c w_co is kept to
                                    2^-21 of itself, or to about 2^-39 of the row's
                                    largest |x_c| b_c times the output's largest
-                                   |w_co| / b_c where that is more; beside the rounding
+                                   |w_co| / b_c where that is more (a 256-way head whose
+                                   symbols' largest lie within 2^8: the matrix's); beside
+                                   the rounding
                                    of the sums, fp32 accuracy unless the products of a
                                    row differ by more than 2^15.  Weights must be finite
                                    (an infinite one gives NaN) */
